@@ -817,19 +817,23 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
         img_dev = (const float *)ws->img_tmp;
     }
     // carve the float scratch: two key buffers (sort), the record regions
-    // (keys then changes; after the records are compacted, the change-point
-    // output's chi), the region counts and offsets, the digit table and its
+    // (after the records are compacted, the change-point output's chi), the region counts and offsets, the digit table and its
     // scan sums, the curve's tile sums, the counts
-    int64_t slots = 0;
-    const int64_t regions = float_regions(dims, &slots);
-    if (regions < 0) return ECC_E_UNSUPPORTED;
+    ChangeJob job{};
+    rc = float_job(img_dev, dims, 0, INT64_MAX, &job);
+    if (rc) return rc;
+    int64_t regions = 0, region_slots = 0;
+    rc = change_regions(job, &regions, &region_slots);
+    if (rc) return rc;
+    // (the change points' chi goes to the regions once the records are compacted)
+    const int64_t slots = std::max(regions * region_slots, steps_only ? n : 0);
     const int64_t digit_entries = std::max(radix_count_entries(n, 4), radix_count_entries(n, 8));
     const int64_t ft = float_tiles(n);
     enum { kKey0, kKey1, kNz, kNzCnt, kNzOff, kCounts, kSums, kTileA, kTileB, kBound, kCnt, kSteps, kNbuf };
     size_t off[kNbuf], total = 0;
-    const int64_t scan_entries = std::max(std::max(digit_entries, regions), steps_only ? n : 0);
+    const int64_t scan_entries = std::max(std::max(digit_entries, regions + 1), steps_only ? n : 0);
     const size_t sz[kNbuf] = {(size_t)n * 4, (size_t)n * 4, (size_t)slots * 8, (size_t)regions * 4,
-                              (size_t)regions * 4, (size_t)digit_entries * 4,
+                              (size_t)(regions + 1) * 4, (size_t)digit_entries * 4,
                               (size_t)radix_scan_tiles(scan_entries) * 4, (size_t)ft * 8, (size_t)ft * 8,
                               (size_t)(ft + 1) * 8, 64,
                               steps_only ? (size_t)n * 4 : 0};
@@ -847,8 +851,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     if (rc) return rc;
     uint8_t *b = (uint8_t *)ws->fbuf;
     uint32_t *key[2] = {(uint32_t *)(b + off[kKey0]), (uint32_t *)(b + off[kKey1])};
-    uint32_t *nz_key = (uint32_t *)(b + off[kNz]);
-    int32_t *nz_chg = (int32_t *)(nz_key + slots);
+    uint64_t *nz = (uint64_t *)(b + off[kNz]);
     uint32_t *nz_cnt = (uint32_t *)(b + off[kNzCnt]);
     uint32_t *nz_off = (uint32_t *)(b + off[kNzOff]);
     uint32_t *counts = (uint32_t *)(b + off[kCounts]);
@@ -856,7 +859,6 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     int64_t *tile_a = (int64_t *)(b + off[kTileA]);
     int64_t *tile_b = (int64_t *)(b + off[kTileB]);
     int64_t *bound = (int64_t *)(b + off[kBound]);
-    int64_t *nnz_dev = (int64_t *)(b + off[kCnt]);
     int64_t *count_dev = (int64_t *)(b + off[kCnt] + 8);
     int64_t *count2_dev = (int64_t *)(b + off[kCnt] + 16);
     uint32_t *mask_dev = (uint32_t *)(b + off[kCnt] + 32);  // the key sort's top-byte mask (8 words)
@@ -868,15 +870,16 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     int64_t *nnz_host_dev = (int64_t *)(ws->host_status_dev + 2);
     *nnz_host = -1;
 
-    rc = launch_float_change(img_dev, dims, key[0], nz_key, nz_chg, nz_cnt, nz_off, ws->status, s);
+    rc = launch_change_records(job, nz, nz_cnt, s);
     if (rc) return rc;
-    rc = launch_nz_total(nz_cnt, nz_off, regions, sums, nnz_dev, nnz_host_dev, s);
+    rc = launch_nz_total(nz_cnt, nz_off, regions, sums, nnz_host_dev, s);
     if (rc) return rc;
     hipEvent_t counted = nullptr;
     ECC_HIP(hipEventCreateWithFlags(&counted, hipEventDisableTiming));
     hipError_t e = hipEventRecord(counted, s);
     if (e == hipSuccess) {
-        rc = radix_sort_keys(key, n, counts, sums, mask_dev, ws->host_status + 4, ws->host_status_dev + 4, s);
+        rc = radix_sort_keys(img_dev, key, n, counts, sums, mask_dev, ws->host_status + 4, ws->host_status_dev + 4,
+                             ws->status, s);
         e = hipEventSynchronize(counted);
     }
     (void)hipEventDestroy(counted);
@@ -894,7 +897,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     uint64_t *rec[2] = {(uint64_t *)ws->frec, (uint64_t *)((uint8_t *)ws->frec + rb)};
     int64_t *prefix = (int64_t *)((uint8_t *)ws->frec + 2 * rb);
     if (nnz > 0) {
-        rc = launch_nz_compact(nz_key, nz_chg, nz_cnt, nz_off, regions, slots / regions, rec[0], s);
+        rc = launch_nz_compact(nz, nz_cnt, nz_off, regions, region_slots, rec[0], s);
         if (rc) return rc;
         rc = radix_sort_records(rec, nnz, counts, sums, s);
         if (rc) return rc;
@@ -920,7 +923,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     }
     if (steps_only) {  // compact into buffers free after the curve: the second key buffer, the regions
         float *step_keys = (float *)key[1];
-        int64_t *step_chi = (int64_t *)nz_key;
+        int64_t *step_chi = (int64_t *)nz;
         rc = launch_change_points(out_keys, out_chi, kcount, (uint32_t *)(b + off[kSteps]), sums, step_keys,
                                   step_chi, count2_dev, s);
         if (rc) return rc;

@@ -1,0 +1,503 @@
+// Per-voxel changes of images that are not counted value by value in the
+// integer kernel's histograms: float images (every voxel whose change is not
+// zero leaves a record) and integer images with four axes longer than 1.
+//
+// The change of the curve at a voxel's value is the signed count of the cells
+// whose value the voxel gives (Sec. 3, Algorithm 1; Sec. 2, "Sublevel Set
+// Filtration": a cell's value is the minimum over the voxels that contain
+// it).  Any choice among equal minima gives the same curve, since the cell's
+// value is what is counted.
+//
+// Algorithm 1 inspects the 3^d - 1 neighbours of a voxel.  Here each cell is
+// looked at once instead: of the 2^d cell types per voxel (an axis of a cell
+// is an interval, the voxel's own, or a vertex between two voxels), the
+// minimum of a type with one more vertex axis is the smaller of two minima
+// of the type without it, so one comparison per cell tells which of the two
+// gave it (2^d - 1 comparisons and minima per voxel: 15 in place of 80 for
+// d = 4), and the cell's sign is passed along these comparisons, axis by
+// axis, to the voxel that gave the minimum:
+//  1. axis 0 (walked): for every set S of the other axes, the field F_S is
+//     the 2-window minimum of the image along the axes of S.  Edge i of a
+//     line of F_S along axis 0 keeps r_S = c_{i-1} - c_i, c_i = [F_S at i+1 <
+//     F_S at i] (a vertex goes to the smaller of its two edges and cancels
+//     it); c = 1 before the first and 0 after the last plane;
+//  2. the last axis x: r_{S+x} goes to the position x-1 if F_{S+x} < F_S
+//     there (the left value is strictly smaller), else to x, and is
+//     subtracted from r_S;
+//  3. the other in-plane axes y, then z, in the same way.
+// What is left at a voxel, times (-1)^(in-plane axes), is its change.  On the
+// far edge of an in-plane axis, the field with and the field without it have
+// equal lines and cancel, so the field without it is skipped there and the
+// field with it never reaches past the edge (as in the integer kernel).
+//
+// Layout.  A lane holds A x B voxels: rows y0 .. y0+A-1 of the planes z0 ..
+// z0+B-1, at one x, and walks axis 0.  It loads those rows and one row on
+// either side per axis ((A+2)(B+2) values per plane, clamped into the image:
+// equal values never pass anything outwards).  The lanes of a wave are 64
+// consecutive positions of the flattened (row group, x) index, so that lines
+// of any length fill the waves; the first and the last lane serve their
+// neighbours only (62 of 64 emit, all of them at the ends of the index).  A
+// value at x-1 comes from the lane before (wave shift), and what goes to x-1
+// goes to the lane before.
+// The r of up to four types (without and with y, z) of one position are the
+// bytes of one word: the comparison masks are pushed into the low bits
+// of a word, spread to bytes by one 24-bit product, and steps 1 and 2 work
+// on whole words.
+#include <algorithm>
+
+#include "ecc_internal.h"
+
+namespace ecc {
+
+namespace {
+
+constexpr uint32_t kBufWord3 = 0x00020000;
+constexpr int kShr1 = 0x138;  // lane i reads lane i-1
+constexpr int kShl1 = 0x130;  // lane i reads lane i+1
+
+struct ChangeParams {
+    PlaneSrc src;
+    int32_t nx, ny, nz;      // in-plane extents (1 where the axis is absent)
+    int32_t lanes;           // flattened length: row groups * nx
+    int32_t wu;              // waves over it
+    int32_t nzt;             // groups of B planes along z
+    int32_t e0, e1;          // emitted planes of axis 0, buffer coordinates
+    int32_t lo_inf, hi_inf;  // planes e0-1 and e1 lie outside the image
+    int32_t zc;              // planes of axis 0 per walk
+    int64_t items;           // waves of work
+    uint32_t invert;         // integers: values read as v ^ invert
+    // records (float): item i's region is rec[i * region ..], its count cnt[i]
+    uint64_t *rec;
+    uint32_t *cnt;
+    uint32_t region;
+    // integers: count rows (one per workgroup) or the changes vector
+    int32_t *partial;
+    int64_t *vcec;
+    uint32_t *status;
+    uint32_t limit;  // integers: values >= limit are an error
+};
+
+template <typename T>
+struct Val {
+    using type = uint32_t;
+};
+template <>
+struct Val<float> {
+    using type = float;
+};
+
+__device__ __forceinline__ uint32_t vmin(uint32_t a, uint32_t b) { return a < b ? a : b; }
+// (as written, without the quieting of its inputs that fminf adds: a NaN
+// input only occurs in an image that is rejected, or as the absent left
+// value below, where the other input is returned)
+__device__ __forceinline__ float vmin(float a, float b) {
+    float r;
+    asm("v_min_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint32_t bits_of(uint32_t v) { return v; }
+__device__ __forceinline__ uint32_t bits_of(float v) { return __float_as_uint(v); }
+__device__ __forceinline__ void from_bits(uint32_t b, uint32_t &v) { v = b; }
+__device__ __forceinline__ void from_bits(uint32_t b, float &v) { v = __uint_as_float(b); }
+
+// m = 2 m + (lane bit of the comparison)
+__device__ __forceinline__ void push(uint32_t &m, bool c) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(c);
+    uint64_t co;
+    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(m), "=&s"(co) : "s"(mask));
+}
+
+// Cell types of a position: bit 0: y is a vertex axis, bit 1: z is one; type
+// t's byte of a word is byte t.  At row position a == A (the row past the
+// lane's own) only the types with y are needed, at b == B only those with z.
+template <int NL, int A, int B>
+struct Types {
+    static constexpr bool has(int a, int b, int t) {
+        if ((t & 1) && NL < 1) return false;
+        if ((t & 2) && NL < 2) return false;
+        if (a == A && !(t & 1)) return false;
+        if (b == B && !(t & 2)) return false;
+        return true;
+    }
+    // The packed bits (present types, ascending from bit 0) to the low bits of
+    // their bytes: one product, whose terms do not meet (other bits of the
+    // bytes may be set); a single type's bit is shifted, since a factor of
+    // 2^24 is beyond the 24-bit product.
+    static __device__ __forceinline__ uint32_t spread(uint32_t m, int a, int b) {
+        uint32_t f = 0;
+        int j = 0, last = 0;
+        for (int t = 0; t < 4; ++t)
+            if (has(a, b, t)) f += 1u << (8 * t - j), ++j, last = t;
+        return j == 1 ? m << (8 * last) : __umul24(m, f);
+    }
+};
+
+enum { kRecords = 0, kHistogram = 1, kAtomic = 2 };
+
+// EMIT: kRecords (float), kHistogram (integers, m = M bins in LDS, one count
+// row per workgroup), kAtomic (integers, int64 adds to the changes vector).
+template <typename T, int NL, int EMIT, int M, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
+    using V = typename Val<T>::type;
+    constexpr int A = NL == 0 ? 1 : NL == 1 ? 4 : 2;
+    constexpr int B = NL == 2 ? 2 : 1;
+    constexpr int HY = NL >= 1, HZ = NL == 2;
+    constexpr int RA = A + 2 * HY, RB = B + 2 * HZ;  // loaded rows
+    constexpr int PA = A + HY, PB = B + HZ;          // positions
+    using Ty = Types<NL, A, B>;
+    constexpr uint32_t kBias = 0x08080808u;
+    __shared__ int32_t hist[EMIT == kHistogram ? M : 1];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if constexpr (EMIT == kHistogram) {
+        for (int i = threadIdx.x; i < M; i += 64 * WAVES) hist[i] = 0;
+        __syncthreads();
+    }
+    uint32_t orv = 0;
+    const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
+    for (int64_t item = (int64_t)blk * WAVES + wave; item < P.items; item += (int64_t)gridDim.x * WAVES) {
+        const int32_t k = (int32_t)(item % P.wu);
+        const int32_t rest = (int32_t)(item / P.wu);
+        const int32_t zt = rest % P.nzt;
+        const int32_t zs = P.e0 + (rest / P.nzt) * P.zc;
+        const int32_t ze = min(zs + P.zc, P.e1);
+        const int32_t z0 = zt * B;
+
+        const int32_t u = 62 * k + lane;
+        const bool in = u < P.lanes;
+        const int32_t uc = min(u, P.lanes - 1);
+        const int32_t yt = uc / P.nx, x = uc - yt * P.nx;
+        const int32_t y0 = yt * A;
+        // lanes that emit: all but the first (unless it starts the index)
+        // and the last (unless it ends it)
+        const uint64_t emit = __builtin_amdgcn_ballot_w64(in && (lane > 0 || k == 0) && (lane < 63 || u == P.lanes - 1));
+
+        // loaded rows: per lane the row's byte offset with x, per wave the
+        // plane's offset along z
+        uint32_t vo[RA], zo[RB];
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+            vo[a] = ((uint32_t)min(max(y0 + a - HY, 0), P.ny - 1) * (uint32_t)P.nx + (uint32_t)x) * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+            zo[b] = (uint32_t)min(max(z0 + b - HZ, 0), P.nz - 1) * (uint32_t)P.ny * (uint32_t)P.nx * (uint32_t)sizeof(T);
+        const uint32_t x0m = x == 0 ? 0xFFFFFFFFu : 0u;  // no left value
+        // validity of the types per row and plane position (low bits of the
+        // bytes): a type without an axis stops before its last index
+        uint32_t my[PA], myx[PA], mz[PB];
+#pragma unroll
+        for (int a = 0; a < PA; ++a) {
+            const int32_t y = y0 + a;
+            my[a] = 0;
+            if (in) my[a] = (HY == 0 || y <= P.ny - 2 ? 0x00010001u : 0u) | (HY && y <= P.ny - 1 ? 0x01000100u : 0u);
+            myx[a] = x <= P.nx - 2 ? my[a] : 0u;
+        }
+#pragma unroll
+        for (int b = 0; b < PB; ++b) {
+            const int32_t z = z0 + b;
+            mz[b] = (HZ == 0 || z <= P.nz - 2 ? 0x00000101u : 0u) | (HZ && z <= P.nz - 1 ? 0x01010000u : 0u);
+        }
+
+        auto plane_ptr = [&](int32_t p) { return (p < 0 ? P.src.lo_base : P.src.base) + (int64_t)p * P.src.plane_bytes; };
+        auto load = [&](int32_t p, V (&f)[RA][RB]) {
+            __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)plane_ptr(p), (short)0,
+                                                                          (int)(uint32_t)P.src.plane_bytes, kBufWord3);
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+                for (int a = 0; a < RA; ++a) {
+                    if constexpr (sizeof(T) == 4) from_bits(__builtin_amdgcn_raw_buffer_load_b32(rs, vo[a], zo[b], 0), f[a][b]);
+                    else if constexpr (sizeof(T) == 2) from_bits(__builtin_amdgcn_raw_buffer_load_b16(rs, vo[a], zo[b], 0), f[a][b]);
+                    else from_bits(__builtin_amdgcn_raw_buffer_load_b8(rs, vo[a], zo[b], 0), f[a][b]);
+                }
+        };
+        // fields of a plane: g[a][b][t][0] without x, [1] with x
+        auto fields = [&](const V (&f0)[RA][RB], V (&g)[PA][PB][4][2]) {
+            V f[RA][RB][2];
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int b = 0; b < RB; ++b) {
+                    V v = f0[a][b];
+                    if constexpr (sizeof(T) < 4) v ^= P.invert;
+                    f[a][b][0] = v;
+                    // the left value: all ones at x = 0 (a NaN, or the
+                    // largest integer), which the minimum passes over
+                    const uint32_t l = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)bits_of(v), kShr1, 0xF, 0xF, true) | x0m;
+                    V left;
+                    from_bits(l, left);
+                    f[a][b][1] = vmin(v, left);
+                }
+#pragma unroll
+            for (int xi = 0; xi < 2; ++xi) {
+                V fy[PA][RB];
+                if constexpr (HY) {
+#pragma unroll
+                    for (int a = 0; a < PA; ++a)
+#pragma unroll
+                        for (int b = 0; b < RB; ++b) fy[a][b] = vmin(f[a][b][xi], f[a + 1][b][xi]);
+                }
+#pragma unroll
+                for (int a = 0; a < PA; ++a)
+#pragma unroll
+                    for (int b = 0; b < PB; ++b) {
+                        g[a][b][0][xi] = f[a + HY][b + HZ][xi];
+                        if constexpr (HY) g[a][b][1][xi] = fy[a][b + HZ];
+                        if constexpr (HZ) {
+                            g[a][b][2][xi] = vmin(f[a + HY][b][xi], f[a + HY][b + 1][xi]);
+                            g[a][b][3][xi] = vmin(fy[a][b], fy[a][b + 1]);
+                        }
+                    }
+            }
+        };
+        // c of plane i from the fields of planes i and i+1: words without x
+        // and with x
+        // bits of the types at a position, spread to their bytes
+        auto gather = [&](int a, int b, auto &&bit) -> uint32_t {
+            uint32_t m = 0;
+            bool first = true;
+#pragma unroll
+            for (int t = 3; t >= 0; --t)
+                if (Ty::has(a, b, t)) {
+                    if (first) m = bit(t) ? 1u : 0u;
+                    else push(m, bit(t));
+                    first = false;
+                }
+            return Ty::spread(m, a, b);
+        };
+        auto compare = [&](const V (&gn)[PA][PB][4][2], const V (&gc)[PA][PB][4][2], int a, int b, uint32_t &ca,
+                           uint32_t &cb) {
+            ca = gather(a, b, [&](int t) { return gn[a][b][t][0] < gc[a][b][t][0]; }) & myx[a] & mz[b];
+            cb = gather(a, b, [&](int t) { return gn[a][b][t][1] < gc[a][b][t][1]; }) & my[a] & mz[b];
+        };
+        const bool lo_real = !(zs == P.e0 && P.lo_inf);
+        const bool hi_real = !(ze == P.e1 && P.hi_inf);
+
+        V gc[PA][PB][4][2];
+        uint32_t xw[PA][PB], cw[PA][PB];  // c(without x) - c(with x); c(with x), of the plane before
+        V nx[RA][RB];
+        load(zs, nx);
+        fields(nx, gc);
+        if (lo_real) {
+            V gl[PA][PB][4][2];
+            load(zs - 1, nx);
+            fields(nx, gl);
+#pragma unroll
+            for (int a = 0; a < PA; ++a)
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    uint32_t ca, cb;
+                    compare(gc, gl, a, b, ca, cb);
+                    xw[a][b] = ca - cb;
+                    cw[a][b] = cb;
+                }
+        } else {  // (c = 1 before the first plane)
+#pragma unroll
+            for (int a = 0; a < PA; ++a)
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    uint32_t tm = 0;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (Ty::has(a, b, t)) tm |= 1u << (8 * t);
+                    cw[a][b] = my[a] & mz[b] & tm;
+                    xw[a][b] = (myx[a] & mz[b] & tm) - cw[a][b];
+                }
+        }
+        uint32_t count = 0;  // records of this item
+        auto load_next = [&](int32_t p) {
+            if (p < ze || (p == ze && hi_real)) {
+                load(p, nx);
+            } else {
+                // above every value: c = 0 after the last plane
+#pragma unroll
+                for (int a = 0; a < RA; ++a)
+#pragma unroll
+                    for (int b = 0; b < RB; ++b) from_bits(sizeof(T) == 4 ? 0x7F800000u : (0xFFFFFFFFu ^ P.invert), nx[a][b]);
+            }
+        };
+        load_next(zs + 1);
+        // one plane: fields gc; those of the next plane are left in gn
+        auto step = [&](const V (&gc)[PA][PB][4][2], V (&gn)[PA][PB][4][2], int32_t z) {
+            fields(nx, gn);
+            if (z + 1 < ze) load_next(z + 2);
+            // steps 1 and 2 at every position: the r of its types, biased by
+            // 8 per byte
+            uint32_t r[PA][PB];
+#pragma unroll
+            for (int a = 0; a < PA; ++a)
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    uint32_t ca, cb;
+                    compare(gn, gc, a, b, ca, cb);
+                    // types whose left value is strictly smaller
+                    const uint32_t m = gather(a, b, [&](int t) { return gc[a][b][t][1] < gc[a][b][t][0]; });
+                    const uint32_t xn = ca - cb;
+                    // (what goes to the left, negated, and the rest kept
+                    // opaque: the shifted value is then only ever added.  A
+                    // subtraction with a shifted operand may be compiled to
+                    // v_subrev_u32 with the shift on its first source, and
+                    // that form shifted the second source on the card.)
+                    const uint32_t left = (cb & m) - (cw[a][b] & m);
+                    uint32_t rest = (xw[a][b] + kBias) - xn - left;
+                    asm("" : "+v"(rest));
+                    r[a][b] = rest + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)left, kShl1, 0xF, 0xF, true);
+                    xw[a][b] = xn;
+                    cw[a][b] = cb;
+                }
+            auto byte = [&](uint32_t w, int t) -> int32_t { return (int32_t)((w >> (8 * t)) & 0xFFu); };
+            // steps y and z.  u: per position b, what is left at row a of the
+            // types without y; biases cancel where y exists (8 - 8), else 8
+            constexpr int kOff = NL == 0 ? 8 : 0;
+            int32_t fin[A][B];
+            V val[A][B];
+#pragma unroll
+            for (int a = 0; a < A; ++a) {
+                int32_t uz[PB];  // the type z at this row
+#pragma unroll
+                for (int b = 0; b < PB; ++b) {
+                    auto pass_y = [&](int t0, int t1) -> int32_t {  // type t0 less what comes back of type t1 = t0 + y
+                        int32_t s = byte(r[a][b], t0);
+                        if constexpr (HY) {
+                            const int32_t own = byte(r[a][b], t1);
+                            s -= own - (gc[a][b][t1][0] < gc[a][b][t0][0] ? own : 8);
+                            s -= gc[a + 1][b][t1][0] < gc[a + 1][b][t0][0] ? byte(r[a + 1][b], t1) : 8;
+                        }
+                        return s;
+                    };
+                    if (b < B) {
+                        fin[a][b] = pass_y(0, 1);
+                        val[a][b] = gc[a][b][0][0];
+                    }
+                    if constexpr (HZ) uz[b] = pass_y(2, 3);
+                }
+                if constexpr (HZ) {
+#pragma unroll
+                    for (int b = 0; b < B; ++b) {
+                        const int32_t lz = gc[a][b][2][0] < gc[a][b][0][0] ? uz[b] : 0;
+                        const int32_t lz1 = gc[a][b + 1][2][0] < gc[a][b + 1][0][0] ? uz[b + 1] : 0;
+                        fin[a][b] -= uz[b] - lz + lz1;
+                    }
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < A; ++a)
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const uint64_t nz = __builtin_amdgcn_ballot_w64(fin[a][b] != kOff) & emit;
+                    const int32_t chg = NL == 1 ? fin[a][b] - kOff : kOff - fin[a][b];
+                    if constexpr (EMIT == kRecords) {
+                        if (nz != 0) {
+                            const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(nz >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)nz, 0u));
+                            if (__builtin_amdgcn_inverse_ballot_w64(nz)) {
+                                const uint32_t key = f32_key(bits_of(val[a][b]));
+                                (P.rec + item * P.region + count)[at] = ((uint64_t)key << 32) | (uint32_t)chg;
+                            }
+                            count += (uint32_t)__builtin_popcountll(nz);
+                        }
+                    } else {
+                        if (__builtin_amdgcn_inverse_ballot_w64(emit) && y0 + a < P.ny && z0 + b < P.nz) orv |= bits_of(val[a][b]);
+                        if (__builtin_amdgcn_inverse_ballot_w64(nz)) {
+                            const uint32_t v = bits_of(val[a][b]);
+                            if constexpr (EMIT == kHistogram) {
+                                if (v < (uint32_t)M) atomicAdd(&hist[v], chg);
+                            } else {
+                                if (v < P.limit) atomicAdd((unsigned long long *)&P.vcec[v], (unsigned long long)(int64_t)chg);
+                            }
+                        }
+                    }
+                }
+        };
+        V gd[PA][PB][4][2];
+        int32_t z = zs;
+        for (; z + 1 < ze; z += 2) {
+            step(gc, gd, z);
+            step(gd, gc, z + 1);
+        }
+        if (z < ze) step(gc, gd, z);
+        if constexpr (EMIT == kRecords) {
+            if (lane == 0) P.cnt[item] = count;
+        }
+    }
+    if constexpr (EMIT != kRecords) {
+        if (__builtin_amdgcn_ballot_w64(orv >= P.limit) != 0 && lane == 0) atomicOr(P.status, kStatusRange);
+    }
+    if constexpr (EMIT == kHistogram) {
+        __syncthreads();
+        int32_t *dst = P.partial + (size_t)blockIdx.x * M;
+        for (int i = threadIdx.x; i < M; i += 64 * WAVES) dst[i] = hist[i];
+    }
+}
+
+}  // namespace
+
+// Geometry of a launch.
+static int change_params(const ChangeJob &job, int per_lane_a, int per_lane_b, ChangeParams *p) {
+    p->src = job.src;
+    p->nx = job.nx;
+    p->ny = job.ny;
+    p->nz = job.nz;
+    const int64_t lanes = (int64_t)((job.ny + per_lane_a - 1) / per_lane_a) * job.nx;
+    if (lanes > INT32_MAX || job.src.plane_bytes > (int64_t)UINT32_MAX) {
+        set_error("change kernel: plane too large");
+        return ECC_E_UNSUPPORTED;
+    }
+    p->lanes = (int32_t)lanes;
+    p->wu = lanes <= 64 ? 1 : (int32_t)((lanes - 2 + 61) / 62);
+    p->nzt = (job.nz + per_lane_b - 1) / per_lane_b;
+    p->e0 = job.e0;
+    p->e1 = job.e1;
+    p->lo_inf = job.lo_inf;
+    p->hi_inf = job.hi_inf;
+    const int64_t planes = job.e1 - job.e0, per_plane = (int64_t)p->wu * p->nzt;
+    const int64_t target = (int64_t)device_cu_count() * 48;
+    int64_t chunks = (target + per_plane - 1) / per_plane;
+    int64_t zc = chunks >= planes ? 1 : (planes + chunks - 1) / chunks;
+    if (zc < 8) zc = 8;
+    if (zc > planes) zc = planes;
+    p->zc = (int32_t)zc;
+    p->items = per_plane * ((planes + zc - 1) / zc);
+    if (p->items / p->wu > INT32_MAX) {
+        set_error("change kernel: too many lines");
+        return ECC_E_UNSUPPORTED;
+    }
+    p->invert = 0;
+    return ECC_OK;
+}
+
+static int lane_rows(int nl) { return nl == 0 ? 1 : nl == 1 ? 4 : 2; }
+static int lane_planes(int nl) { return nl == 2 ? 2 : 1; }
+
+int change_regions(const ChangeJob &job, int64_t *regions, int64_t *region_slots) {
+    ChangeParams p{};
+    const int a = lane_rows(job.nl), b = lane_planes(job.nl);
+    int rc = change_params(job, a, b, &p);
+    if (rc) return rc;
+    *regions = p.items;
+    *region_slots = (int64_t)64 * a * b * p.zc;
+    return ECC_OK;
+}
+
+int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hipStream_t stream) {
+    ChangeParams p{};
+    const int a = lane_rows(job.nl), b = lane_planes(job.nl);
+    int rc = change_params(job, a, b, &p);
+    if (rc) return rc;
+    p.rec = rec;
+    p.cnt = cnt;
+    p.region = (uint32_t)(64 * a * b * p.zc);
+    void *tok = nullptr;
+    rc = profile_begin(stream, &tok);
+    if (rc) return rc;
+    const dim3 grid((unsigned)((p.items + 3) / 4)), block(256);
+    switch (job.nl) {
+    case 0: hipLaunchKernelGGL((change_kernel<float, 0, kRecords, 1, 4>), grid, block, 0, stream, p); break;
+    case 1: hipLaunchKernelGGL((change_kernel<float, 1, kRecords, 1, 4>), grid, block, 0, stream, p); break;
+    default: hipLaunchKernelGGL((change_kernel<float, 2, kRecords, 1, 4>), grid, block, 0, stream, p); break;
+    }
+    ECC_HIP(hipGetLastError());
+    return profile_end(stream, tok);
+}
+
+}  // namespace ecc

@@ -1,450 +1,98 @@
 // Float32 images (Sec. 3, "Other Ranges of Gray Values"): the values are not known
-// in advance, so every voxel's key is written and the keys are sorted to
-// find the distinct values; the voxels whose change is not zero (a few in a
-// hundred) are also written, as (key, change) records, and each change is
-// added at its key's rank among the distinct values; a prefix sum over the
-// distinct values gives the curve.
-//
-// The change of a voxel v is the signed count of the cells of the cubical
-// complex that v introduces (Sec. 3, Algorithm 1: a cell enters with the
-// first of its incident voxels in the order "smaller value first, ties broken
-// by position").  A cell of the closed voxel v is named by a direction
-// s in {-1,0,1}^D (s_i = 0: the cell spans v along axis i; s_i = +-1: it is
-// the face on that side); it has dimension #{i : s_i = 0}.  Its other
-// incident voxels are v + delta with delta_i in {0, s_i}, delta != 0, so v
-// introduces it iff none of those precedes v.  With U_s = OR of "precedes"
-// over that box, U_s = prec(s) | OR_{i : s_i != 0} U_{s with s_i = 0}, and
-//     change(v) = sum_s (-1)^dim(s) [U_s = 0] = 1 - sum_{s != 0} (-1)^dim(s) U_s
-// (the first sum over all s is prod_i (2 - 1) = 1).
-//
-// On the GPU a wave holds 64 consecutive voxels of one line of the last axis
-// (their neighbourhoods staged in LDS by the workgroup);
-// "precedes" for each of the 3^D - 1 neighbour directions is one ballot, the
-// recursion for U_s runs on those wave-wide masks in scalar registers, and
-// each U_s is accumulated per lane with one add-with-carry.
+// in advance, so every voxel's key is sorted to find the distinct values; the
+// voxels whose change is not zero (a few in a hundred) leave (key, change)
+// records (ecc_change.hip), and each change is added at its key's rank among
+// the distinct values; a prefix sum over the distinct values gives the curve.
 //
 // Keys: the canonical float (-0 folded into +0) mapped to an unsigned integer
-// with the same order (sign bit set: all bits flipped; else the sign bit set).
+// with the same order (f32_key).
 
 #include "ecc_internal.h"
 
 namespace ecc {
-
-__device__ __forceinline__ uint32_t f32_key(uint32_t u) {
-    if ((u & 0x7FFFFFFFu) == 0u) u = 0u;  // -0 -> +0
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 __device__ __forceinline__ float key_to_f32(uint32_t k) {
     const uint32_t u = (k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k;
     return __uint_as_float(u);
 }
 
-constexpr int pow3(int d) { return d == 0 ? 1 : 3 * pow3(d - 1); }
-// base-3 digit k of a direction code: 0 -> -1, 1 -> 0, 2 -> +1
-constexpr int digit3(int t, int k) { return (t / pow3(k)) % 3; }
-template <int D>
-constexpr int nonzeros(int t) {
-    int c = 0;
-    for (int k = 0; k < D; ++k) c += digit3(t, k) != 1;
-    return c;
-}
-// delta earlier than v in C order: its first non-zero component (axis 0 is
-// the most significant, digit D-1-k holds axis k) is negative
-template <int D>
-constexpr bool earlier(int t) {
-    for (int a = 0; a < D; ++a) {
-        const int dg = digit3(t, D - 1 - a);
-        if (dg != 1) return dg == 0;
-    }
-    return false;
-}
-
-__device__ __forceinline__ uint64_t ballot64(bool b) { return __builtin_amdgcn_ballot_w64(b); }
-
-// m = 2 m + (lane bit of mask): one VALU op, the mask is the carry-in (the
-// carry-out goes to a scratch scalar pair).
-__device__ __forceinline__ void push_bit(uint32_t &m, uint64_t mask) {
-    uint64_t co;
-    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(m), "=&s"(co) : "s"(mask));
-}
-
-// Bit layout of the direction masks: word w, bit b holds direction
-// t = w * BW + b (BW = 3^min(D, 3) directions per word, NW words).
-template <int D>
-constexpr int kBW = D >= 3 ? 27 : pow3(D);
-template <int D>
-constexpr int kNW = D == 4 ? 3 : 1;
-// bits of a 27-bit word whose digit k is 1 (no offset along that axis)
-constexpr uint32_t mid_mask(int k) {
-    uint32_t m = 0;
-    for (int b = 0; b < 27; ++b)
-        if (digit3(b, k) == 1) m |= 1u << b;
-    return m;
-}
-constexpr uint32_t kMid[3] = {mid_mask(0), mid_mask(1), mid_mask(2)};
-// directions whose box enters the sum with sign +1 (PLUS) or -1, zero
-// direction excluded
-template <int D, bool PLUS>
-struct SignMasks {
-    uint32_t m[3];
-    constexpr SignMasks() : m{} {
-        for (int t = 0; t < pow3(D); ++t) {
-            if (t == (pow3(D) - 1) / 2) continue;
-            const bool even = ((D - nonzeros<D>(t)) & 1) == 0;
-            if (even == PLUS) m[t / kBW<D>] |= 1u << (t % kBW<D>);
-        }
-    }
-};
-template <int D>
-constexpr SignMasks<D, true> kPlus{};
-template <int D>
-constexpr SignMasks<D, false> kMinus{};
-
-struct FloatView {
-    int32_t n[4];       // extents, axis 0 slowest, padded in front with 1
-    uint32_t stride[4]; // element strides
-    int32_t bpr;        // blocks per line of the last axis
-    int32_t run;        // lines along axis 2 walked by one workgroup
-    int32_t nruns;      // runs per axis-2 extent
-    int32_t e0, e1;     // axis-0 indices whose voxels are emitted (the others are neighbours only)
-};
-
-// One thread per voxel.  D = number of axes after dropping axes of extent 1
-// (the complex of the others times unit intervals has the same curve).
-//
-// A workgroup of T threads takes T consecutive voxels (x in [xs, xs+T)) of a
-// run of consecutive lines along axis 2 of the padded view and walks the run
-// line by line.  The values of the 3^D neighbourhood come from LDS: a ring of
-// four slots, one per line position along axis 2, each holding the
-// S = 3^(D-2) lines at offsets -1, 0, +1 along the axes before it, over
-// x in [xs-1, xs+T], x-major (the S values of one x are adjacent: a thread's
-// 3 S neighbours in a slot lie within 12 S bytes of one address, so one
-// address per slot serves all its reads).  While line y is compared, the loads for line y+2 are in
-// flight; each line is loaded once per workgroup (one coalesced load per
-// thread and line, plus one load for the two ends of all S lines), instead of
-// 3^D - 1 scattered loads per voxel.  Absent neighbours (outside the image)
-// are stored as NaN, which compares false and so never precedes.
-// Outputs: keys[i] for every voxel i; for every voxel whose change is not
-// zero, one (key, change) record in the workgroup's own region of the record
-// arrays (region b = records [b * T * run, (b+1) * T * run), as many slots as
-// the workgroup has voxels), at a slot taken from an LDS counter (one LDS
-// add per wave and line); nz_cnt[b] and nz_off[b] receive the region's
-// record count.
-template <int D, int T>
-__global__ void __launch_bounds__(T) float_change_kernel(const float *__restrict__ img, uint32_t img_bytes,
-                                                         FloatView v, uint32_t *__restrict__ keys,
-                                                         uint32_t *__restrict__ nz_key, int32_t *__restrict__ nz_chg,
-                                                         uint32_t *__restrict__ nz_cnt, uint32_t *__restrict__ nz_off,
-                                                         uint32_t *status) {
-    constexpr int P = pow3(D);
-    constexpr int C = (P - 1) / 2;             // code of the zero direction
-    constexpr int S = D >= 2 ? pow3(D - 2) : 1;  // lines per slot
-    constexpr int PITCH = T + 2;
-    constexpr int BW = kBW<D>, NW = kNW<D>;
-    __shared__ float ring[4 * S * PITCH];
-    __shared__ uint32_t region_count;
-    const int32_t nx = v.n[3], n2 = v.n[2];
-    const int tid = (int)threadIdx.x;
-    if (tid == 0) region_count = 0;  // (the first barrier below orders it)
-    // block -> (outer line over axes 0..1, run along axis 2, x block); uniform
-    const uint32_t blk = blockIdx.x;
-    const uint32_t region = blk * (uint32_t)(T * v.run);
-    int32_t r = __builtin_amdgcn_readfirstlane((int32_t)blk);
-    const int32_t xs = (r % v.bpr) * T;
-    r /= v.bpr;
-    const int32_t y0 = (r % v.nruns) * v.run;
-    const int32_t y1 = min(y0 + v.run, n2);
-    r /= v.nruns;
-    const int32_t c1 = r % v.n[1];
-    const int32_t c0 = r / v.n[1];
-    if (c0 < v.e0 || c0 >= v.e1) {  // (uniform) a collar plane of a streamed chunk: nothing to emit
-        if (tid == 0) {
-            nz_cnt[blk] = 0;
-            nz_off[blk] = 0;
-        }
-        return;
-    }
-    const int32_t x = xs + tid;
-    const bool act = x < nx;
-    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)img, (short)0, (int)img_bytes, 0x00020000);
-    const float nan = __uint_as_float(0x7FC00000u);
-
-    // slot line j: offsets (digit 0 of j -> axis 1, digit 1 -> axis 0).  Per
-    // workgroup: its element offset at axis-2 position 0 (32-bit: images
-    // hold fewer than 2^30 elements) and whether it exists (bit j of lmask).
-    uint32_t lb0[S];
-    uint32_t lmask = 0;
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-        const int32_t a1 = c1 + (D >= 3 ? (j % 3) - 1 : 0);
-        const int32_t a0 = c0 + (D >= 4 ? (j / 3) % 3 - 1 : 0);
-        lb0[j] = (uint32_t)a0 * v.stride[0] + (uint32_t)a1 * v.stride[1];
-        if (a1 >= 0 && a1 < v.n[1] && a0 >= 0 && a0 < v.n[0]) lmask |= 1u << j;
-    }
-    // the end values x = xs-1 (even lanes) and xs+T (odd lanes) of line
-    // (tid >> 1), lanes 0 .. 2S-1
-    const int ej = tid >> 1;
-    const int32_t xe = (tid & 1) ? xs + T : xs - 1;
-    uint32_t elb0 = 0;
-#pragma unroll
-    for (int j = 0; j < S; ++j)
-        if (j == ej) elb0 = lb0[j];
-    const bool eok = tid < 2 * S && ((lmask >> (ej < S ? ej : 0)) & 1u) && xe >= 0 && xe < nx;
-    // Every load is issued, branch-free: offsets of absent lines or of lanes
-    // past the line's end may point anywhere (wrapped 32-bit arithmetic), but a
-    // raw buffer load is bounds-checked against the image (past the end it
-    // returns 0 and touches nothing), and such values are replaced by NaN.
-    auto fetch = [&](int32_t y, float (&val)[S], float &end) {
-        const bool yok = y >= 0 && y < n2;
-        const uint32_t ys = (uint32_t)y * v.stride[2];
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            const float w = __uint_as_float(
-                __builtin_amdgcn_raw_buffer_load_b32(rs, (lb0[j] + ys + (uint32_t)x) * 4u, 0, 0));
-            val[j] = (yok && ((lmask >> j) & 1u) && act) ? w : nan;
-        }
-        const float we = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (elb0 + ys + (uint32_t)xe) * 4u, 0, 0));
-        end = (yok && eok) ? we : nan;
-    };
-    // element index of this thread's voxel in line (S / 2) at position y
-    auto own_index = [&](int32_t y) -> uint32_t { return lb0[S / 2] + (uint32_t)y * v.stride[2] + (uint32_t)x; };
-    auto store = [&](int32_t y, const float (&val)[S], float end) {
-        float *slot = ring + (y & 3) * (S * PITCH);
-#pragma unroll
-        for (int j = 0; j < S; ++j) slot[(1 + tid) * S + j] = val[j];
-        if (tid < 2 * S) slot[((tid & 1) ? T + 1 : 0) * S + ej] = end;
-    };
-
-    float val[S], end;
-    for (int32_t y = y0 - 1; y <= y0 + 1; ++y) {
-        fetch(y, val, end);
-        store(y, val, end);
-    }
-    for (int32_t y = y0; y < y1; ++y) {
-        __syncthreads();  // slots y-1 .. y+1 written; slot y+2 (= y-2) no longer read
-        const bool next = y + 1 < y1;
-        if (next) fetch(y + 2, val, end);
-        // this voxel's column in the three slots around y
-        const float *col[3];
-#pragma unroll
-        for (int dy = 0; dy < 3; ++dy) col[dy] = ring + ((y - 1 + dy) & 3) * (S * PITCH) + (1 + tid) * S;
-        const float f0 = col[1][S / 2];
-        const uint32_t own_bits = __float_as_uint(f0);
-        const uint32_t k0 = f32_key(own_bits);
-
-        // Per lane, bit b of word w says whether neighbour t = w * BW + b
-        // precedes v (IEEE comparisons: -0 == +0, infinities are ordinary
-        // values, NaN (an absent neighbour) never precedes; a NaN in the image
-        // fails the call).  The zero direction's bit is 0.
-        uint32_t M[NW];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            uint32_t m = 0;
-#pragma unroll
-            for (int b = BW - 1; b >= 0; --b) {
-                const int t = w * BW + b;
-                if (t == C) {
-                    m <<= 1;
-                    continue;
-                }
-                const int dx = digit3(t, 0) - 1;
-                const int dyi = D >= 2 ? digit3(t, 1) : 1;
-                const int j = D >= 3 ? t / 9 : 0;
-                const float fn = col[dyi][dx * S + j];
-                push_bit(m, ballot64(earlier<D>(t) ? (fn <= f0) : (fn < f0)));
-            }
-            M[w] = m;
-        }
-        // U_t (some vertex of the box spanned by v and v + t, other than v,
-        // precedes v): the OR of the bits over the box's directions, taken
-        // axis by axis (the box is a product): every digit 0 or 2 receives
-        // the bit of the same direction with that digit set to 1 (no offset).
-#pragma unroll
-        for (int k = 0; k < (D < 3 ? D : 3); ++k) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const uint32_t mid = M[w] & kMid[k];
-                M[w] |= (mid << pow3(k)) | (mid >> pow3(k));
-            }
-        }
-        if constexpr (D == 4) {
-            M[0] |= M[1];
-            M[2] |= M[1];
-        }
-        // the signed sum of the boxes that v completes, (-1)^dim each,
-        // dim = D - (non-zero components)
-        int32_t acc = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w)
-            acc += (int32_t)__builtin_popcount(M[w] & kPlus<D>.m[w]) - (int32_t)__builtin_popcount(M[w] & kMinus<D>.m[w]);
-        if (ballot64(act && (own_bits & 0x7FFFFFFFu) > 0x7F800000u) != 0 && (threadIdx.x & (kWave - 1)) == 0)
-            atomicOr(status, kStatusNaN);
-        const int32_t chg = 1 - acc;
-        if (act && keys) keys[own_index(y)] = k0;
-        const uint64_t nzm = ballot64(act && chg != 0);
-        if (nzm != 0) {
-            const int lane = (int)(threadIdx.x & (kWave - 1));
-            const int leader = __builtin_ctzll(nzm);
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(&region_count, (uint32_t)__builtin_popcountll(nzm));
-            base = (uint32_t)__builtin_amdgcn_readlane((int)base, leader);
-            if (act && chg != 0) {
-                const uint64_t below = lane == 0 ? 0ull : (nzm & (~0ull >> (64 - lane)));
-                const uint32_t slot = region + base + (uint32_t)__builtin_popcountll(below);
-                nz_key[slot] = k0;
-                nz_chg[slot] = chg;
-            }
-        }
-        if (next) store(y + 2, val, end);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        nz_cnt[blk] = region_count;
-        nz_off[blk] = region_count;
-    }
-}
-
-// Geometry of the change kernel's launch for an image (workgroups, threads,
-// lines per run), shared by the launch and by the record layout.
-struct FloatGrid {
-    FloatView v;
-    int D, threads;
-    int64_t grid;
-};
-
-static int float_grid(const ecc_dims *dims, FloatGrid *g) {
-    // drop axes of extent 1, pad in front to four axes
-    int32_t ext[4];
+// The walk of a float image (or of a window of its planes) in the change
+// kernel: axes of extent 1 are dropped (the complex of the others times unit
+// intervals has the same curve), the first of the rest is walked.
+int float_job(const float *img_dev, const ecc_dims *dims, int64_t e0, int64_t e1, ChangeJob *job) {
+    int64_t ext[4];
     int d = 0;
     int64_t total = 1;
     for (int i = 0; i < dims->ndim; ++i) {
         total *= dims->n[i];
-        if (dims->n[i] > 1) ext[d++] = (int32_t)dims->n[i];
+        if (dims->n[i] > 1) ext[d++] = dims->n[i];
     }
     if (total * 4 > (int64_t)UINT32_MAX) {
         set_error("float images are limited to 2^30 elements");
         return ECC_E_UNSUPPORTED;
     }
-    FloatView &v = g->v;
-    v = FloatView{};
-    const int D = d == 0 ? 1 : d;
+    *job = ChangeJob{};
     if (d == 0) ext[d++] = 1;
-    for (int k = 0; k < 4; ++k) v.n[k] = 1;
-    for (int i = 0; i < D; ++i) v.n[4 - D + i] = ext[i];
-    uint32_t s = 1;
-    for (int k = 3; k >= 0; --k) {
-        v.stride[k] = s;
-        s *= (uint32_t)v.n[k];
-    }
-    const int nx = v.n[3];
-    const int threads = nx >= 256 ? 256 : ((nx + 63) / 64) * 64;
-    v.bpr = (nx + threads - 1) / threads;
-    v.run = v.n[2] < 32 ? v.n[2] : 32;
-    v.nruns = (v.n[2] + v.run - 1) / v.run;
-    const int64_t grid = (int64_t)v.n[0] * v.n[1] * v.nruns * v.bpr;
-    if (grid > INT32_MAX || grid * threads * v.run > (int64_t)UINT32_MAX) {
-        set_error("float image: too many lines");
-        return ECC_E_UNSUPPORTED;
-    }
-    v.e0 = 0;
-    v.e1 = INT32_MAX;
-    g->D = D;
-    g->threads = threads;
-    g->grid = grid;
+    const int64_t n0 = d == 1 ? 1 : ext[0];
+    job->nl = d <= 2 ? 0 : d - 2;
+    job->nx = (int32_t)ext[d - 1];
+    job->ny = d >= 3 ? (int32_t)ext[d - 2] : 1;
+    job->nz = d >= 4 ? (int32_t)ext[d - 3] : 1;
+    job->src.base = job->src.lo_base = (const uint8_t *)img_dev;
+    job->src.plane_bytes = (int64_t)job->nx * job->ny * job->nz * 4;
+    job->e0 = (int32_t)e0;
+    job->e1 = (int32_t)(e1 < n0 ? e1 : n0);
+    job->lo_inf = e0 == 0;
+    job->hi_inf = e1 >= n0;
     return ECC_OK;
-}
-
-int64_t float_regions(const ecc_dims *dims, int64_t *slots) {
-    FloatGrid g;
-    if (float_grid(dims, &g)) return -1;
-    *slots = g.grid * g.threads * g.v.run;
-    return g.grid;
-}
-
-int launch_float_change(const float *img_dev, const ecc_dims *dims, uint32_t *keys, uint32_t *nz_key,
-                        int32_t *nz_chg, uint32_t *nz_cnt, uint32_t *nz_off, uint32_t *status, hipStream_t stream,
-                        int32_t e0, int32_t e1) {
-    FloatGrid fg;
-    int rc = float_grid(dims, &fg);
-    if (rc) return rc;
-    if ((e0 != 0 || e1 != INT32_MAX) && (fg.D != 4 || dims->ndim != 4)) {
-        set_error("internal error: an emit range needs four axes longer than 1");
-        return ECC_E_ARG;
-    }
-    FloatView v = fg.v;
-    v.e0 = e0;
-    v.e1 = e1;
-    const int D = fg.D, threads = fg.threads;
-    const int64_t grid = fg.grid;
-    int64_t total = 1;
-    for (int i = 0; i < dims->ndim; ++i) total *= dims->n[i];
-    const uint32_t bytes = (uint32_t)(total * 4);
-    void *tok = nullptr;
-    rc = profile_begin(stream, &tok);
-    if (rc) return rc;
-    const dim3 g((unsigned)grid), b(threads);
-#define ECC_FCK(DD)                                                                                              \
-    switch (threads) {                                                                                           \
-    case 64: hipLaunchKernelGGL((float_change_kernel<DD, 64>), g, b, 0, stream, img_dev, bytes, v, keys, nz_key, nz_chg, nz_cnt, nz_off, status); break;   \
-    case 128: hipLaunchKernelGGL((float_change_kernel<DD, 128>), g, b, 0, stream, img_dev, bytes, v, keys, nz_key, nz_chg, nz_cnt, nz_off, status); break; \
-    case 192: hipLaunchKernelGGL((float_change_kernel<DD, 192>), g, b, 0, stream, img_dev, bytes, v, keys, nz_key, nz_chg, nz_cnt, nz_off, status); break; \
-    default: hipLaunchKernelGGL((float_change_kernel<DD, 256>), g, b, 0, stream, img_dev, bytes, v, keys, nz_key, nz_chg, nz_cnt, nz_off, status); break;  \
-    }
-    switch (D) {
-    case 1: ECC_FCK(1); break;
-    case 2: ECC_FCK(2); break;
-    case 3: ECC_FCK(3); break;
-    default: ECC_FCK(4); break;
-    }
-#undef ECC_FCK
-    ECC_HIP(hipGetLastError());
-    return profile_end(stream, tok);
 }
 
 // ----------------------------------------------------------------------------
 // The non-zero change records, from the workgroups' regions to one dense
 // array of 64-bit words (key << 32 | change as uint32), sorted by key.
 
-// After the exclusive scan of nz_off (region offsets): the record count.
-// Written to device memory and to host-mapped memory (read by the host
-// after an event, to size the record sort).
-__global__ void nz_total_kernel(const uint32_t *nz_cnt, const uint32_t *nz_off, int64_t regions, int64_t *total_dev,
-                                int64_t *total_host) {
-    const int64_t t = (int64_t)nz_off[regions - 1] + nz_cnt[regions - 1];
-    *total_dev = t;
-    *total_host = t;
+// After the exclusive scan of nz_off (region offsets; in place, from a copy
+// of the counts with one entry more): the record count, written to
+// host-mapped memory (read by the host after an event, to size the record
+// sort).
+__global__ void nz_total_kernel(const uint32_t *nz_off, int64_t regions, int64_t *total_host) {
+    *total_host = (int64_t)nz_off[regions];
+}
+__global__ void __launch_bounds__(256) nz_copy_kernel(const uint32_t *__restrict__ nz_cnt, int64_t regions,
+                                                      uint32_t *__restrict__ nz_off) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i <= regions) nz_off[i] = i < regions ? nz_cnt[i] : 0u;
 }
 
-int launch_nz_total(const uint32_t *nz_cnt, uint32_t *nz_off, int64_t regions, uint32_t *sums, int64_t *total_dev,
-                    int64_t *total_host, hipStream_t stream) {
-    int rc = exclusive_scan_u32(nz_off, regions, sums, stream);
+int launch_nz_total(const uint32_t *nz_cnt, uint32_t *nz_off, int64_t regions, uint32_t *sums, int64_t *total_host,
+                    hipStream_t stream) {
+    hipLaunchKernelGGL(nz_copy_kernel, dim3((unsigned)((regions + 256) / 256)), dim3(256), 0, stream, nz_cnt, regions,
+                       nz_off);
+    ECC_HIP(hipGetLastError());
+    int rc = exclusive_scan_u32(nz_off, regions + 1, sums, stream);
     if (rc) return rc;
-    hipLaunchKernelGGL(nz_total_kernel, dim3(1), dim3(1), 0, stream, nz_cnt, (const uint32_t *)nz_off, regions,
-                       total_dev, total_host);
+    hipLaunchKernelGGL(nz_total_kernel, dim3(1), dim3(1), 0, stream, (const uint32_t *)nz_off, regions, total_host);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }
 
-__global__ void __launch_bounds__(256) nz_compact_kernel(const uint32_t *__restrict__ nz_key,
-                                                         const int32_t *__restrict__ nz_chg,
+// (a wave per region: a region is one wave's work in the change kernel, a
+// few hundred records)
+__global__ void __launch_bounds__(256) nz_compact_kernel(const uint64_t *__restrict__ nz,
                                                          const uint32_t *__restrict__ nz_cnt,
-                                                         const uint32_t *__restrict__ nz_off, int64_t region_slots,
-                                                         uint64_t *__restrict__ rec) {
-    const uint32_t c = nz_cnt[blockIdx.x];
-    const int64_t src = (int64_t)blockIdx.x * region_slots, dst = nz_off[blockIdx.x];
-    for (uint32_t i = threadIdx.x; i < c; i += blockDim.x)
-        rec[dst + i] = ((uint64_t)nz_key[src + i] << 32) | (uint32_t)nz_chg[src + i];
+                                                         const uint32_t *__restrict__ nz_off, int64_t regions,
+                                                         int64_t region_slots, uint64_t *__restrict__ rec) {
+    const int64_t reg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (reg >= regions) return;
+    const uint32_t c = nz_cnt[reg];
+    const int64_t src = reg * region_slots, dst = nz_off[reg];
+    for (uint32_t i = threadIdx.x & 63; i < c; i += 64) rec[dst + i] = nz[src + i];
 }
 
-int launch_nz_compact(const uint32_t *nz_key, const int32_t *nz_chg, const uint32_t *nz_cnt, const uint32_t *nz_off,
-                      int64_t regions, int64_t region_slots, uint64_t *rec, hipStream_t stream) {
-    if (regions > INT32_MAX) {
-        set_error("float image: too many regions");
-        return ECC_E_UNSUPPORTED;
-    }
-    hipLaunchKernelGGL(nz_compact_kernel, dim3((unsigned)regions), dim3(256), 0, stream, nz_key, nz_chg, nz_cnt, nz_off,
-                       region_slots, rec);
+int launch_nz_compact(const uint64_t *nz, const uint32_t *nz_cnt, const uint32_t *nz_off, int64_t regions,
+                      int64_t region_slots, uint64_t *rec, hipStream_t stream) {
+    hipLaunchKernelGGL(nz_compact_kernel, dim3((unsigned)((regions + 3) / 4)), dim3(256), 0, stream, nz, nz_cnt, nz_off,
+                       regions, region_slots, rec);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }
@@ -453,27 +101,24 @@ int launch_nz_compact(const uint32_t *nz_key, const int32_t *nz_chg, const uint3
 // below 2^24): every region's records added to the changes vector at the
 // record's value (int64 atomics: exact in any order).  Values >= m were
 // flagged by the conversion and are skipped here.
-__global__ void __launch_bounds__(256) records_to_vcec_kernel(const uint32_t *__restrict__ nz_key,
-                                                              const int32_t *__restrict__ nz_chg,
-                                                              const uint32_t *__restrict__ nz_cnt,
+__global__ void __launch_bounds__(256) records_to_vcec_kernel(const uint64_t *__restrict__ nz,
+                                                              const uint32_t *__restrict__ nz_cnt, int64_t regions,
                                                               int64_t region_slots, int m,
                                                               int64_t *__restrict__ vcec) {
-    const uint32_t c = nz_cnt[blockIdx.x];
-    const int64_t src = (int64_t)blockIdx.x * region_slots;
-    for (uint32_t i = threadIdx.x; i < c; i += blockDim.x) {
-        const uint32_t v = (uint32_t)key_to_f32(nz_key[src + i]);
-        if (v < (uint32_t)m) atomicAdd((unsigned long long *)&vcec[v], (unsigned long long)(int64_t)nz_chg[src + i]);
+    const int64_t reg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (reg >= regions) return;
+    const uint32_t c = nz_cnt[reg];
+    const int64_t src = reg * region_slots;
+    for (uint32_t i = threadIdx.x & 63; i < c; i += 64) {
+        const uint32_t v = (uint32_t)key_to_f32((uint32_t)(nz[src + i] >> 32));
+        if (v < (uint32_t)m) atomicAdd((unsigned long long *)&vcec[v], (unsigned long long)(int64_t)(int32_t)nz[src + i]);
     }
 }
 
-int launch_records_to_vcec(const uint32_t *nz_key, const int32_t *nz_chg, const uint32_t *nz_cnt, int64_t regions,
-                           int64_t region_slots, int m, int64_t *vcec, hipStream_t stream) {
-    if (regions > INT32_MAX) {
-        set_error("float image: too many regions");
-        return ECC_E_UNSUPPORTED;
-    }
-    hipLaunchKernelGGL(records_to_vcec_kernel, dim3((unsigned)regions), dim3(256), 0, stream, nz_key, nz_chg, nz_cnt,
-                       region_slots, m, vcec);
+int launch_records_to_vcec(const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions, int64_t region_slots, int m,
+                           int64_t *vcec, hipStream_t stream) {
+    hipLaunchKernelGGL(records_to_vcec_kernel, dim3((unsigned)((regions + 3) / 4)), dim3(256), 0, stream, nz, nz_cnt,
+                       regions, region_slots, m, vcec);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }

@@ -241,43 +241,57 @@ struct MergeJob {
 // then each image's scan into its curve (fixed grids, loops over the work).
 int launch_batch_merge(const void *table_dev, int colsum_grid, int scan_grid, hipStream_t stream);
 
+// Order-preserving 32-bit key of a float's bits: -0 is folded into +0; sign
+// bit set: all bits flipped, else the sign bit set.
+__device__ __forceinline__ uint32_t f32_key(uint32_t u) {
+    if ((u & 0x7FFFFFFFu) == 0u) u = 0u;
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// Change kernel (ecc_change.hip): planes [e0, e1) of axis 0 of an image with
+// one to three in-plane axes.
+struct ChangeJob {
+    PlaneSrc src;
+    int nl;               // in-plane axes besides the last: 0, 1 (y) or 2 (y and z)
+    int32_t nx, ny, nz;   // in-plane extents (1 where the axis is absent), the last axis nx
+    int32_t e0, e1;       // planes to emit, buffer coordinates
+    int32_t lo_inf, hi_inf;  // planes e0-1 and e1 lie outside the image
+};
+// The float image's records (key << 32 | change as uint32, for the voxels
+// whose change is not zero): region i holds its cnt[i] records from
+// rec[i * region_slots] on.
+int change_regions(const ChangeJob &job, int64_t *regions, int64_t *region_slots);
+int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hipStream_t stream);
+
 // Float path (ecc_float.hip, ecc_sort.hip).
-// The change kernel writes every voxel's order-preserving 32-bit key and,
-// for the voxels whose change is not zero, (key, change) records into its
-// workgroup's region: region b holds slots [b * R, (b+1) * R) of nz_key and
-// nz_chg, R = slots / regions (float_regions); nz_cnt[b] and nz_off[b]
-// receive the region's record count.
-int64_t float_regions(const ecc_dims *dims, int64_t *slots);  // regions, or -1 with the error set
-// keys may be null (not written).  [e0, e1): the axis-0 planes whose voxels
-// are emitted, for an image with four axes longer than 1 (the default: all);
-// the other planes are neighbours only and their regions stay empty.
-int launch_float_change(const float *img_dev, const ecc_dims *dims, uint32_t *keys, uint32_t *nz_key,
-                        int32_t *nz_chg, uint32_t *nz_cnt, uint32_t *nz_off, uint32_t *status, hipStream_t stream,
-                        int32_t e0 = 0, int32_t e1 = INT32_MAX);
+// The change kernel's job for planes [e0, e1) of a float image (e1 may lie
+// past the end).
+int float_job(const float *img_dev, const ecc_dims *dims, int64_t e0, int64_t e1, ChangeJob *job);
 // Integer images through the change kernel: the regions' records added to
 // vcec (m int64) at the records' values.
-int launch_records_to_vcec(const uint32_t *nz_key, const int32_t *nz_chg, const uint32_t *nz_cnt, int64_t regions,
-                           int64_t region_slots, int m, int64_t *vcec, hipStream_t stream);
-// Exclusive scan of nz_off (regions entries; sums: radix_scan_tiles(regions)),
-// then the record count into *total_dev and *total_host (host-mapped).
-int launch_nz_total(const uint32_t *nz_cnt, uint32_t *nz_off, int64_t regions, uint32_t *sums, int64_t *total_dev,
-                    int64_t *total_host, hipStream_t stream);
-// The regions' records, densely, as key << 32 | (uint32) change.
-int launch_nz_compact(const uint32_t *nz_key, const int32_t *nz_chg, const uint32_t *nz_cnt, const uint32_t *nz_off,
-                      int64_t regions, int64_t region_slots, uint64_t *rec, hipStream_t stream);
+int launch_records_to_vcec(const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions, int64_t region_slots, int m,
+                           int64_t *vcec, hipStream_t stream);
+// nz_off (regions + 1 entries): the regions' offsets, an exclusive scan of
+// nz_cnt (sums: radix_scan_tiles(regions + 1)), and the record count into
+// *total_host (host-mapped).
+int launch_nz_total(const uint32_t *nz_cnt, uint32_t *nz_off, int64_t regions, uint32_t *sums, int64_t *total_host,
+                    hipStream_t stream);
+// The regions' records, densely.
+int launch_nz_compact(const uint64_t *nz, const uint32_t *nz_cnt, const uint32_t *nz_off, int64_t regions,
+                      int64_t region_slots, uint64_t *rec, hipStream_t stream);
 // Tiles of the radix sort for n words of elem (4 or 8) bytes.
 int64_t radix_tiles(int64_t n, int elem);
 int64_t radix_scan_tiles(int64_t entries);
 // Digit-table entries of a sort of n words of elem bytes (digits of up to
 // 10 bits for keys, 8 for records); sums: radix_scan_tiles of that.
 int64_t radix_count_entries(int64_t n, int elem);
-// Sorts key[0]; on return key[0] is the sorted buffer and key[1] the other
-// (the two may be swapped).  mask_dev: 8 device words; mask_host /
+// Sorts the keys of the n floats of img; on return key[0] is the sorted buffer
+// and key[1] the other (the two may be swapped).  A NaN sets kStatusNaN.  mask_dev: 8 device words; mask_host /
 // mask_host_dev: 8 words of host-mapped memory, host and device views.
 // Synchronizes on an event recorded early in the sort (the host reads which
 // top bytes occur to choose the last passes).
-int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
-                    volatile uint32_t *mask_host, uint32_t *mask_host_dev, hipStream_t stream);
+int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
+                    volatile uint32_t *mask_host, uint32_t *mask_host_dev, uint32_t *status, hipStream_t stream);
 // Sorts rec[0] in place (an even number of passes).
 int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
 int64_t float_tiles(int64_t n);

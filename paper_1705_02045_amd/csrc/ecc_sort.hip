@@ -79,13 +79,14 @@ __device__ __forceinline__ void build_rank(const uint32_t *__restrict__ mask, ui
 // small sorts take fewer tiles per workgroup to keep the chip busy.
 constexpr int kCountTiles = 16;
 
-// MASK (the first pass over 32-bit keys): also ORs the presence of each
-// key's top byte into mask (8 words, zero before the launch).
+// MASK (the first pass over 32-bit keys): the words are the image's floats,
+// mapped to keys as they are loaded; also ORs the presence of each key's top
+// byte into mask (8 words, zero before the launch) and reports a NaN.
 template <typename T, int BITS, bool AGG, bool REMAP, bool MASK>
 __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__restrict__ rec, int64_t n,
                                                                    int shift, int64_t tiles, int tpw,
                                                                    uint32_t *__restrict__ counts,
-                                                                   uint32_t *__restrict__ mask) {
+                                                                   uint32_t *__restrict__ mask, uint32_t *status) {
     constexpr int kItems = SortTile<T>::kItems;
     constexpr int64_t kTile = SortTile<T>::kTile;
     constexpr int kDig = 1 << BITS;
@@ -101,6 +102,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
     const int lane = tid & (kWave - 1);
     const int64_t tb = (int64_t)blockIdx.x * tpw;
     uint32_t last = 256u;  // MASK: the top byte this thread noted last
+    bool nan = false;
     for (int k = 0; k < tpw && tb + k < tiles; ++k) {
         const int64_t t0 = (tb + k) * kTile;
         T r[kItems];
@@ -108,6 +110,10 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = t0 + (int64_t)j * kSortThreads + tid;
             r[j] = i < n ? rec[i] : T(0);
+            if constexpr (MASK) {
+                nan |= (r[j] & 0x7FFFFFFFu) > 0x7F800000u;
+                r[j] = f32_key(r[j]);
+            }
         }
         // AGG (a top digit: sign and exponent, a handful of values): same-digit
         // lanes would serialize on one LDS address, so up to four rounds take the
@@ -143,6 +149,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
             if ((rem >> lane) & 1ull) atomicAdd(&cnt[k][d], 1u);
         }
     }
+    if (MASK && __builtin_amdgcn_ballot_w64(nan) != 0 && lane == 0) atomicOr(status, kStatusNaN);
     __syncthreads();
     if (MASK && tid < 256) {  // wave w: bytes 64 w .. 64 w + 63, mask words 2 w and 2 w + 1
         const uint64_t b = __builtin_amdgcn_ballot_w64(present[tid] != 0);
@@ -161,7 +168,8 @@ __global__ void mask_publish_kernel(const uint32_t *__restrict__ mask, uint32_t 
     if (threadIdx.x < 8) host[threadIdx.x] = mask[threadIdx.x];
 }
 
-template <typename T, int BITS, bool REMAP>
+// FIRST: the words are the image's floats, mapped to keys as they are loaded.
+template <typename T, int BITS, bool REMAP, bool FIRST = false>
 __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8))) radix_scatter_kernel(const T *__restrict__ in, int64_t n,
                                                                      int shift, int64_t tiles,
                                                                      const uint32_t *__restrict__ offsets,
@@ -204,12 +212,16 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
     const bool full = t0 + kTile <= n;
     if (full) {
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) r[j] = in[wb + j * kWave + lane];
+        for (int j = 0; j < kItems; ++j) {
+            r[j] = in[wb + j * kWave + lane];
+            if constexpr (FIRST) r[j] = f32_key(r[j]);
+        }
     } else {
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = wb + (int64_t)j * kWave + lane;
             r[j] = i < n ? in[i] : ~T(0);
+            if constexpr (FIRST) r[j] = i < n ? f32_key(r[j]) : ~T(0);
         }
     }
     auto digit = [&](int j) -> uint32_t { return digit_of<T, BITS, REMAP>(r[j], shift, rank_t); };
@@ -441,14 +453,14 @@ int64_t radix_scan_tiles(int64_t entries) { return (entries + kScanTile - 1) / k
 int64_t radix_count_entries(int64_t n, int elem) { return (elem == 4 ? 1024 : 256) * radix_tiles(n, elem); }
 
 // One pass: counts, their scan, the scatter from v[*cur] to the other buffer.
-template <typename T, int BITS, bool AGG, bool REMAP, bool MASK>
+template <typename T, int BITS, bool AGG, bool REMAP>
 static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts, uint32_t *sums, uint32_t *mask,
                       hipStream_t stream) {
     const int64_t tiles = radix_tiles(n, (int)sizeof(T));
     const int tpw = (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
     const unsigned cgrid = (unsigned)((tiles + tpw - 1) / tpw);
-    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG, REMAP, MASK>), dim3(cgrid), dim3(kSortThreads), 0, stream,
-                       (const T *)v[*cur], n, shift, tiles, tpw, counts, mask);
+    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG, REMAP, false>), dim3(cgrid), dim3(kSortThreads), 0, stream,
+                       (const T *)v[*cur], n, shift, tiles, tpw, counts, mask, (uint32_t *)nullptr);
     ECC_HIP(hipGetLastError());
     int rc = exclusive_scan_u32(counts, ((int64_t)1 << BITS) * tiles, sums, stream);
     if (rc) return rc;
@@ -468,9 +480,9 @@ static int check_count(int64_t n) {
     return ECC_OK;
 }
 
-int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
-                    volatile uint32_t *mask_host, uint32_t *mask_host_dev, hipStream_t stream) {
-    if (n <= 1) return ECC_OK;
+int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums,
+                    uint32_t *mask_dev, volatile uint32_t *mask_host, uint32_t *mask_host_dev, uint32_t *status,
+                    hipStream_t stream) {
     int rc = check_count(n);
     if (rc) return rc;
     int cur = 0;
@@ -480,7 +492,7 @@ int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sum
     const int64_t tiles = radix_tiles(n, 4);
     const int tpw = (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
     hipLaunchKernelGGL((radix_count_kernel<uint32_t, 9, false, false, true>), dim3((unsigned)((tiles + tpw - 1) / tpw)),
-                       dim3(kSortThreads), 0, stream, (const uint32_t *)key[0], n, 0, tiles, tpw, counts, mask_dev);
+                       dim3(kSortThreads), 0, stream, (const uint32_t *)img, n, 0, tiles, tpw, counts, mask_dev, status);
     ECC_HIP(hipGetLastError());
     hipLaunchKernelGGL(mask_publish_kernel, dim3(1), dim3(64), 0, stream, (const uint32_t *)mask_dev, mask_host_dev);
     ECC_HIP(hipGetLastError());
@@ -490,13 +502,13 @@ int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sum
     if (e == hipSuccess) {
         rc = exclusive_scan_u32(counts, 512 * tiles, sums, stream);
         if (!rc) {
-            hipLaunchKernelGGL((radix_scatter_kernel<uint32_t, 9, false>), dim3((unsigned)tiles), dim3(kSortThreads), 0,
-                               stream, (const uint32_t *)key[0], n, 0, tiles, (const uint32_t *)counts,
+            hipLaunchKernelGGL((radix_scatter_kernel<uint32_t, 9, false, true>), dim3((unsigned)tiles), dim3(kSortThreads), 0,
+                               stream, (const uint32_t *)img, n, 0, tiles, (const uint32_t *)counts,
                                (const uint32_t *)mask_dev, key[1]);
             e = hipGetLastError();
             cur = 1;
         }
-        if (!rc && e == hipSuccess) rc = radix_pass<uint32_t, 9, false, false, false>(key, &cur, n, 9, counts, sums, mask_dev, stream);
+        if (!rc && e == hipSuccess) rc = radix_pass<uint32_t, 9, false, false>(key, &cur, n, 9, counts, sums, mask_dev, stream);
         const hipError_t w = hipEventSynchronize(noted);
         if (e == hipSuccess) e = w;
     }
@@ -506,12 +518,12 @@ int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sum
     int present = 0;
     for (int w = 0; w < 8; ++w) present += __builtin_popcount(mask_host[w]);
     if (present <= 8) {  // ranks in 3 bits: a 9-bit digit
-        rc = radix_pass<uint32_t, 9, false, true, false>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
+        rc = radix_pass<uint32_t, 9, false, true>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
     } else if (present <= 16) {  // ranks in 4 bits: a 10-bit digit
-        rc = radix_pass<uint32_t, 10, false, true, false>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
+        rc = radix_pass<uint32_t, 10, false, true>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
     } else {  // bits 18-24 and 25-31 (sign and high exponent bits: a handful of values)
-        rc = radix_pass<uint32_t, 7, false, false, false>(key, &cur, n, 18, counts, sums, mask_dev, stream);
-        if (!rc) rc = radix_pass<uint32_t, 7, true, false, false>(key, &cur, n, 25, counts, sums, mask_dev, stream);
+        rc = radix_pass<uint32_t, 7, false, false>(key, &cur, n, 18, counts, sums, mask_dev, stream);
+        if (!rc) rc = radix_pass<uint32_t, 7, true, false>(key, &cur, n, 25, counts, sums, mask_dev, stream);
     }
     if (rc) return rc;
     if (cur == 1) std::swap(key[0], key[1]);
@@ -525,9 +537,9 @@ int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *
     int cur = 0;
     for (int pass = 0; pass < 4 && !rc; ++pass) {
         if (pass == 3)
-            rc = radix_pass<uint64_t, 8, true, false, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
+            rc = radix_pass<uint64_t, 8, true, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
         else
-            rc = radix_pass<uint64_t, 8, false, false, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
+            rc = radix_pass<uint64_t, 8, false, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
     }
     return rc;
 }

@@ -124,11 +124,12 @@ int run_chunk_4d(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t lo, in
         w.ndim = 4;
         w.n[0] = min64(step, hi - lo) + 2;
         for (int k = 1; k < 4; ++k) w.n[k] = st->n4[k];
-        int64_t slots = 0;
-        const int64_t regions = float_regions(&w, &slots);
-        if (regions < 0) return ECC_E_UNSUPPORTED;
+        ChangeJob job{};
+        int64_t regions = 0, region_slots = 0;
         int rc = ensure_bytes((void **)&st->wbuf, &st->wbuf_bytes, (size_t)(w.n[0] * pe) * 4);
-        if (!rc) rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, (size_t)slots * 8 + (size_t)regions * 8);
+        if (!rc) rc = float_job(st->wbuf, &w, 0, INT64_MAX, &job);
+        if (!rc) rc = change_regions(job, &regions, &region_slots);
+        if (!rc) rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, (size_t)(regions * region_slots) * 8 + (size_t)regions * 4);
         if (rc) return rc;
     }
     for (int64_t b0 = lo; b0 < hi; b0 += step) {
@@ -155,20 +156,20 @@ int run_chunk_4d(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t lo, in
         w.ndim = 4;
         w.n[0] = p;
         for (int k = 1; k < 4; ++k) w.n[k] = st->n4[k];
-        int64_t slots = 0;
-        const int64_t regions = float_regions(&w, &slots);
-        if (regions < 0) return ECC_E_UNSUPPORTED;
-        const size_t off_cnt = (size_t)slots * 8, off_off = off_cnt + (size_t)regions * 4;
-        rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, off_off + (size_t)regions * 4);
+        // (a one-plane window: its plane is emitted, and the kernel sees three axes)
+        ChangeJob job{};
+        int64_t regions = 0, region_slots = 0;
+        rc = float_job(st->wbuf, &w, p > 1 ? b0 - wlo : 0, p > 1 ? b1 - wlo : INT64_MAX, &job);
+        if (!rc) rc = change_regions(job, &regions, &region_slots);
         if (rc) return rc;
-        uint32_t *nz_key = (uint32_t *)st->nzbuf;
-        int32_t *nz_chg = (int32_t *)(nz_key + slots);
-        uint32_t *nz_cnt = (uint32_t *)(st->nzbuf + off_cnt), *nz_off = (uint32_t *)(st->nzbuf + off_off);
-        // (a one-plane image: its plane is emitted, and the kernel sees three axes)
-        rc = launch_float_change(st->wbuf, &w, nullptr, nz_key, nz_chg, nz_cnt, nz_off, st->status, st->compute,
-                                 p > 1 ? (int32_t)(b0 - wlo) : 0, p > 1 ? (int32_t)(b1 - wlo) : INT32_MAX);
+        const size_t off_cnt = (size_t)(regions * region_slots) * 8;
+        rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, off_cnt + (size_t)regions * 4);
         if (rc) return rc;
-        rc = launch_records_to_vcec(nz_key, nz_chg, nz_cnt, regions, slots / regions, st->m, st->vcec, st->compute);
+        uint64_t *nz = (uint64_t *)st->nzbuf;
+        uint32_t *nz_cnt = (uint32_t *)(st->nzbuf + off_cnt);
+        rc = launch_change_records(job, nz, nz_cnt, st->compute);
+        if (rc) return rc;
+        rc = launch_records_to_vcec(nz, nz_cnt, regions, region_slots, st->m, st->vcec, st->compute);
         if (rc) return rc;
     }
     return ECC_OK;
