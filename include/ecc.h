@@ -86,8 +86,8 @@ int ecc_threshold_count(ecc_dtype dtype, int64_t *m_out);
  *          ECC_F32).  chi/keys may be host or device pointers.
  *   stream: work is enqueued on it; the call returns after the curve is
  *          written (it synchronizes that stream).
- * Integer images with four axes longer than 1 are computed exactly through
- * the float path (their curve read at every integer threshold).
+ * Integer images with four axes longer than 1 (at most 2^30 voxels) take the
+ * float path's change kernel, with their changes counted per value.
  * Errors: ECC_E_ARG, ECC_E_RANGE (U14), ECC_E_NAN (F32),
  *         ECC_E_BUFFER_TOO_SMALL, ECC_E_NOMEM, ECC_E_HIP, ECC_E_UNSUPPORTED. */
 int ecc_compute(const void *image, const ecc_dims *dims, ecc_dtype dtype, ecc_curve *curve, void *stream);
@@ -100,8 +100,7 @@ int ecc_compute(const void *image, const ecc_dims *dims, ecc_dtype dtype, ecc_cu
  * can enter after the cell it bounds); chi[m-1] = 1 (the whole box).
  * Computed as the change vector of m-1-v read back reversed: the cells whose
  * maximum is t are those whose minimum of m-1-v is m-1-t.  Images with four
- * axes longer than 1 go through the float path on m-1-v: chi[t] = 1 minus
- * that image's curve at m-2-t.
+ * axes longer than 1 count their changes at m-1-v in the same way.
  * Integer dtypes u8 and u14; arguments, synchronisation and errors as
  * ecc_compute (ECC_E_UNSUPPORTED for ECC_F32 and ECC_U16). */
 int ecc_compute_max_entry(const void *image, const ecc_dims *dims, ecc_dtype dtype, ecc_curve *curve,
@@ -143,7 +142,7 @@ int ecc_compute_quantized(const float *image, const ecc_dims *dims, float lo, fl
  * t = 0..m-1.  Axes of length 1 are dropped (one to four may remain).
  * Computed from the largest-value convention of the image and of every face
  * of its box (inclusion-exclusion over the faces, (-1)^codim; the full box
- * of a 4-D image through the float path, as ecc_compute_max_entry).
+ * of a 4-D image through the change kernel, as ecc_compute_max_entry).
  * Integer dtypes u8 and u14; arguments, synchronisation and errors as
  * ecc_compute (ECC_E_UNSUPPORTED for ECC_F32 and ECC_U16). */
 int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, ecc_curve *curve, void *stream);
@@ -251,9 +250,8 @@ int ecc_release_workspaces(void);
  * passes of 32768 bins (Sec. 3, "Range of Values"), each adding the values
  * of its half of 0..65535 to that half of the changes vector.  Planes with
  * three axes longer than 1 (4-D images, planes of at most 2^28 voxels) go
- * through the float path's change kernel: a launch's planes and their
- * collars as float32 in one window buffer, the non-zero changes of the
- * launch's planes added at their voxels' values. */
+ * through the change kernel that float images take, their changes counted
+ * per value. */
 typedef struct ecc_stream ecc_stream;
 
 /* Starts a stream for an image of full_dims (ndim 1..4).  The handle owns

@@ -635,80 +635,69 @@ static bool is_device_ptr(const void *p) {
 
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Float images: records -> sort -> per-key running sums (ecc_float.hip,
-// ecc_sort.hip).  Synchronous: the number of distinct values is only known
-// at the end.
-static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc_curve *curve, hipStream_t s,
-                         bool steps_only);
-
-// Integer images the integer kernel does not take (four axes longer than 1):
-// exact through the float path, whose curve is a step function over the
-// image's distinct values; chi(T_t) is its value at the largest distinct
-// value <= t.  max_entry: the float path runs on the inverted image (values
-// m - 1 - v) and the result is reflected (launch_reflect_curve).  out_dev
-// receives m int64: the curve, or with changes (max_entry only) the changes
-// vector.  img_dev is device memory.
-static int int_via_float_dev(const void *img_dev, const ecc_dims *dims, int64_t total, ecc_dtype dtype,
-                             bool max_entry, bool changes, int64_t *out_dev, hipStream_t s, Workspace *ws) {
-    const int64_t m = threshold_count(dtype);
-    if (total > (int64_t)UINT32_MAX) {
-        set_error("integer path: image too large for the float path");
+// Integer images with four axes longer than 1 (the integer kernel takes at
+// most two in-plane axes): every voxel's change from the change kernel
+// (ecc_change.hip).  The image's planes along its first longer axis.
+static int four_d_job(const void *img_dev, const ecc_dims *dims, int64_t total, int dtype, bool max_entry,
+                      ChangeJob *job) {
+    if (total * 4 > (int64_t)UINT32_MAX) {
+        set_error("integer images with four axes longer than 1 are limited to 2^30 elements");
         return ECC_E_UNSUPPORTED;
     }
-    const size_t eb = elem_bytes(dtype);
-    // i2f_buf: the float image, the float curve (keys, chi), the expanded curve
-    const size_t o_keys = align256((size_t)total * 4), o_chi = o_keys + align256((size_t)total * 4);
-    const size_t o_out = o_chi + align256((size_t)total * 8);
-    int rc = ensure_bytes(&ws->i2f_buf, &ws->i2f_buf_bytes, o_out + (size_t)m * 8);
-    if (rc) return rc;
-    uint8_t *buf = (uint8_t *)ws->i2f_buf;
-    uint32_t *flag = ws->status + kStatusMinMaxOffset / 4 + 3;
-    rc = launch_zero(flag, 4, s);
-    if (rc) return rc;
-    rc = launch_int_to_f32(img_dev, (int)eb, total, (uint32_t)m, max_entry ? 1 : 0, (float *)buf, flag, s);
-    if (rc) return rc;
-    uint32_t bad = 0;
-    ECC_HIP(hipMemcpyAsync(&bad, flag, 4, hipMemcpyDeviceToHost, s));
-    ECC_HIP(hipStreamSynchronize(s));
-    if (bad) {
-        set_error("a 14-bit image holds a value >= 16384");
-        return ECC_E_RANGE;
+    int64_t n[4];
+    int d = 0;
+    for (int i = 0; i < dims->ndim; ++i)
+        if (dims->n[i] > 1) n[d++] = dims->n[i];
+    if (d != 4) {
+        set_error("integer path: shape not supported (an extent beyond 2^31)");
+        return ECC_E_UNSUPPORTED;
     }
-    ecc_curve fc{};
-    fc.capacity = total;
-    fc.keys = (float *)(buf + o_keys);
-    fc.chi = (int64_t *)(buf + o_chi);
-    rc = compute_float(buf, dims, total, &fc, s, false);
-    if (rc) return rc;
-    int64_t *g = max_entry ? (int64_t *)(buf + o_out) : out_dev;
-    rc = launch_expand_steps(fc.keys, fc.chi, fc.count, (int)m, g, s);
-    if (rc) return rc;
-    if (max_entry) return launch_reflect_curve(g, (int)m, changes ? 1 : 0, out_dev, s);
+    *job = ChangeJob{};
+    job->dtype = dtype;
+    job->nl = 2;
+    job->nx = (int32_t)n[3];
+    job->ny = (int32_t)n[2];
+    job->nz = (int32_t)n[1];
+    job->src.base = job->src.lo_base = (const uint8_t *)img_dev;
+    job->src.plane_bytes = n[1] * n[2] * n[3] * (int64_t)elem_bytes(dtype);
+    job->e1 = (int32_t)n[0];
+    job->lo_inf = job->hi_inf = 1;
+    job->invert = max_entry ? 1 : 0;
     return ECC_OK;
 }
 
-static int compute_int_via_float(const void *image, const ecc_dims *dims, int64_t total, ecc_dtype dtype,
-                                 ecc_curve *curve, hipStream_t s, bool max_entry) {
-    const int64_t m = threshold_count(dtype);
-    Workspace *ws = nullptr;
-    int rc = get_workspace(s, &ws);
-    if (rc) return rc;
-    const size_t eb = elem_bytes(dtype);
-    const void *img_dev = image;
-    if (!is_device_ptr(image)) {
-        rc = ensure_bytes(&ws->img_tmp, &ws->img_tmp_bytes, (size_t)total * eb);
+// The curve of such an image into chi_dev, or, with changes_out, only its
+// changes vector there (a range error then stays set in ws->status for a
+// later scan to report).  max_entry: counted at m-1-v and merged reversed, as
+// in three dimensions.
+static int enqueue_four_d(const ChangeJob &job, bool max_entry, int64_t *chi_dev, int64_t *changes_out,
+                          uint32_t *status_out, hipStream_t s, Workspace *ws) {
+    const int m = (int)threshold_count(job.dtype);
+    if (job.dtype == ECC_U16) {
+        int rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)m * sizeof(int64_t));
         if (rc) return rc;
-        ECC_HIP(hipMemcpyAsync(ws->img_tmp, image, (size_t)total * eb, hipMemcpyHostToDevice, s));
-        img_dev = ws->img_tmp;
+        rc = launch_zero(ws->vcec16, (size_t)m * sizeof(int64_t), s);
+        if (rc) return rc;
+        rc = launch_change_counts(job, nullptr, ws->vcec16, ws->status, s);
+        if (rc) return rc;
+        return launch_merge(nullptr, 0, m, nullptr, ws->vcec16, true, true, chi_dev, ws->status, status_out, s);
     }
-    rc = ensure_bytes((void **)&ws->chi_tmp, &ws->chi_tmp_bytes, (size_t)m * 8);
+    int rows = 0;
+    int rc = change_count_rows(job, &rows);
     if (rc) return rc;
-    rc = int_via_float_dev(img_dev, dims, total, dtype, max_entry, false, ws->chi_tmp, s, ws);
+    rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)rows * m * sizeof(int32_t));
     if (rc) return rc;
-    ECC_HIP(hipMemcpyAsync(curve->chi, ws->chi_tmp, (size_t)m * 8, hipMemcpyDefault, s));
-    ECC_HIP(hipStreamSynchronize(s));
-    curve->count = m;
-    return ECC_OK;
+    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes, (size_t)merge_stage_rows(rows) * m * sizeof(int64_t));
+    if (rc) return rc;
+    rc = ensure_bytes((void **)&ws->vcec, &ws->vcec_bytes, (size_t)m * sizeof(int64_t));
+    if (rc) return rc;
+    rc = launch_change_counts(job, ws->partial, nullptr, ws->status, s);
+    if (rc) return rc;
+    if (changes_out)
+        return launch_merge(ws->partial, rows, m, ws->stage, changes_out, false, false, nullptr, ws->status, nullptr, s,
+                            max_entry);
+    return launch_merge(ws->partial, rows, m, ws->stage, ws->vcec, false, true, chi_dev, ws->status, status_out, s,
+                        max_entry);
 }
 
 // Synchronous integer curve: host or device image and curve.  max_entry:
@@ -731,11 +720,12 @@ static int compute_int(const void *image, const ecc_dims *dims, int64_t total, e
         return ECC_E_BUFFER_TOO_SMALL;
     }
     IntView v{};
+    ChangeJob four{};
     int unsup = 0;
-    if (!normalize_int_view(dims, &v, &unsup)) {
-        if (total <= (int64_t)UINT32_MAX) return compute_int_via_float(image, dims, total, dtype, curve, s, max_entry);
-        set_error("integer path: shape not supported (4 axes longer than 1, or an extent beyond 2^31)");
-        return ECC_E_UNSUPPORTED;
+    const bool four_d = !normalize_int_view(dims, &v, &unsup);
+    if (four_d) {
+        int rc = four_d_job(nullptr, dims, total, dtype, max_entry, &four);
+        if (rc) return rc;
     }
     Workspace *ws = nullptr;
     int rc = get_workspace(s, &ws);
@@ -755,7 +745,11 @@ static int compute_int(const void *image, const ecc_dims *dims, int64_t total, e
         if (rc) return rc;
         chi_target = ws->chi_tmp;
     }
-    if (dtype == ECC_U16 && !ws->fixed && env_int("ECC_U16_WINDOWS", 0) == 0) {
+    if (four_d) {
+        four.src.base = four.src.lo_base = (const uint8_t *)img_dev;
+        *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
+        rc = enqueue_four_d(four, max_entry, chi_target, nullptr, ws->host_status_dev, s, ws);
+    } else if (dtype == ECC_U16 && !ws->fixed && env_int("ECC_U16_WINDOWS", 0) == 0) {
         *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
         rc = enqueue_u16_adaptive(img_dev, v, chi_target, ws->host_status_dev, s, ws);
     } else if (dtype == ECC_U16) {  // only the windows between the image's minimum and maximum
@@ -820,7 +814,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     // (after the records are compacted, the change-point output's chi), the region counts and offsets, the digit table and its
     // scan sums, the curve's tile sums, the counts
     ChangeJob job{};
-    rc = float_job(img_dev, dims, 0, INT64_MAX, &job);
+    rc = float_job(img_dev, dims, &job);
     if (rc) return rc;
     int64_t regions = 0, region_slots = 0;
     rc = change_regions(job, &regions, &region_slots);
@@ -1299,8 +1293,6 @@ int ecc_release_workspaces(void) {
         w->frec = nullptr;
         drop(w->dual_buf, &w->dual_buf_bytes);
         w->dual_buf = nullptr;
-        drop(w->i2f_buf, &w->i2f_buf_bytes);
-        w->i2f_buf = nullptr;
         drop(w->vcec16, &w->vcec16_bytes);
         w->vcec16 = nullptr;
     }
@@ -1423,7 +1415,7 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
     int d = 0;
     for (int k = 0; k < dims->ndim; ++k)
         if (dims->n[k] > 1) n[d++] = dims->n[k];
-    // (d <= 4: the full box of a 4-D image goes through the float path, its
+    // (d <= 4: the full box of a 4-D image goes through the change kernel, its
     // faces of at most three dimensions through the integer kernel)
     hipStream_t s = (hipStream_t)stream;
     Workspace *ws = nullptr;
@@ -1511,7 +1503,9 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
             ecc_dims bd{};
             bd.ndim = 4;
             for (int k = 0; k < 4; ++k) bd.n[k] = n[k];
-            rc = int_via_float_dev(img_dev, &bd, total, dtype, true, true, curves + (size_t)f * m, s, ws);
+            ChangeJob box{};
+            rc = four_d_job(img_dev, &bd, total, dtype, true, &box);
+            if (!rc) rc = enqueue_four_d(box, true, nullptr, curves + (size_t)f * m, nullptr, s, ws);
             if (rc) {
                 sync_sides();
                 return rc;

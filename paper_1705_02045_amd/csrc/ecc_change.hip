@@ -500,4 +500,56 @@ int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hi
     return profile_end(stream, tok);
 }
 
+// Integer images: 4-D only (nl = 2).  Eight waves per workgroup share a
+// 16384-bin histogram (64 KiB of LDS), one workgroup per CU (two waves per
+// SIMD at the kernel's registers); the 256-bin form has four per workgroup.
+// The workgroups take items in turn, so there is one count row per workgroup
+// of a grid of at most one (16384 bins) or four (256 bins) per CU.
+static int int_geometry(const ChangeJob &job, ChangeParams *p, int *waves, int64_t *grid) {
+    if (job.nl != 2) {
+        set_error("internal error: integer change kernel on %d line axes", job.nl);
+        return ECC_E_ARG;
+    }
+    int rc = change_params(job, lane_rows(2), lane_planes(2), p);
+    if (rc) return rc;
+    const bool wide = job.dtype == ECC_U14;
+    *waves = wide ? 8 : 4;
+    *grid = std::min<int64_t>((p->items + *waves - 1) / *waves, (int64_t)device_cu_count() * (wide ? 1 : 4));
+    p->invert = job.invert ? (uint32_t)threshold_count(job.dtype) - 1u : 0u;
+    p->limit = (uint32_t)threshold_count(job.dtype);
+    return ECC_OK;
+}
+
+int change_count_rows(const ChangeJob &job, int *rows) {
+    ChangeParams p{};
+    int waves = 0;
+    int64_t grid = 0;
+    int rc = int_geometry(job, &p, &waves, &grid);
+    if (rc) return rc;
+    *rows = (int)grid;
+    return ECC_OK;
+}
+
+int launch_change_counts(const ChangeJob &job, int32_t *partial, int64_t *vcec, uint32_t *status, hipStream_t stream) {
+    ChangeParams p{};
+    int waves = 0;
+    int64_t grid = 0;
+    int rc = int_geometry(job, &p, &waves, &grid);
+    if (rc) return rc;
+    p.partial = partial;
+    p.vcec = vcec;
+    p.status = status;
+    void *tok = nullptr;
+    rc = profile_begin(stream, &tok);
+    if (rc) return rc;
+    const dim3 g((unsigned)grid);
+    switch (job.dtype) {
+    case ECC_U8: hipLaunchKernelGGL((change_kernel<uint8_t, 2, kHistogram, 256, 4>), g, dim3(256), 0, stream, p); break;
+    case ECC_U14: hipLaunchKernelGGL((change_kernel<uint16_t, 2, kHistogram, 16384, 8>), g, dim3(512), 0, stream, p); break;
+    default: hipLaunchKernelGGL((change_kernel<uint16_t, 2, kAtomic, 1, 4>), g, dim3(256), 0, stream, p); break;
+    }
+    ECC_HIP(hipGetLastError());
+    return profile_end(stream, tok);
+}
+
 }  // namespace ecc

@@ -16,10 +16,9 @@ __device__ __forceinline__ float key_to_f32(uint32_t k) {
     return __uint_as_float(u);
 }
 
-// The walk of a float image (or of a window of its planes) in the change
-// kernel: axes of extent 1 are dropped (the complex of the others times unit
+// Axes of extent 1 are dropped (the complex of the others times unit
 // intervals has the same curve), the first of the rest is walked.
-int float_job(const float *img_dev, const ecc_dims *dims, int64_t e0, int64_t e1, ChangeJob *job) {
+int float_job(const float *img_dev, const ecc_dims *dims, ChangeJob *job) {
     int64_t ext[4];
     int d = 0;
     int64_t total = 1;
@@ -33,17 +32,16 @@ int float_job(const float *img_dev, const ecc_dims *dims, int64_t e0, int64_t e1
     }
     *job = ChangeJob{};
     if (d == 0) ext[d++] = 1;
-    const int64_t n0 = d == 1 ? 1 : ext[0];
+    job->dtype = ECC_F32;
     job->nl = d <= 2 ? 0 : d - 2;
     job->nx = (int32_t)ext[d - 1];
     job->ny = d >= 3 ? (int32_t)ext[d - 2] : 1;
     job->nz = d >= 4 ? (int32_t)ext[d - 3] : 1;
     job->src.base = job->src.lo_base = (const uint8_t *)img_dev;
     job->src.plane_bytes = (int64_t)job->nx * job->ny * job->nz * 4;
-    job->e0 = (int32_t)e0;
-    job->e1 = (int32_t)(e1 < n0 ? e1 : n0);
-    job->lo_inf = e0 == 0;
-    job->hi_inf = e1 >= n0;
+    job->e0 = 0;
+    job->e1 = d == 1 ? 1 : (int32_t)ext[0];
+    job->lo_inf = job->hi_inf = 1;
     return ECC_OK;
 }
 
@@ -93,32 +91,6 @@ int launch_nz_compact(const uint64_t *nz, const uint32_t *nz_cnt, const uint32_t
                       int64_t region_slots, uint64_t *rec, hipStream_t stream) {
     hipLaunchKernelGGL(nz_compact_kernel, dim3((unsigned)((regions + 3) / 4)), dim3(256), 0, stream, nz, nz_cnt, nz_off,
                        regions, region_slots, rec);
-    ECC_HIP(hipGetLastError());
-    return ECC_OK;
-}
-
-// Integer images through the change kernel (their values as floats, exact
-// below 2^24): every region's records added to the changes vector at the
-// record's value (int64 atomics: exact in any order).  Values >= m were
-// flagged by the conversion and are skipped here.
-__global__ void __launch_bounds__(256) records_to_vcec_kernel(const uint64_t *__restrict__ nz,
-                                                              const uint32_t *__restrict__ nz_cnt, int64_t regions,
-                                                              int64_t region_slots, int m,
-                                                              int64_t *__restrict__ vcec) {
-    const int64_t reg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (reg >= regions) return;
-    const uint32_t c = nz_cnt[reg];
-    const int64_t src = reg * region_slots;
-    for (uint32_t i = threadIdx.x & 63; i < c; i += 64) {
-        const uint32_t v = (uint32_t)key_to_f32((uint32_t)(nz[src + i] >> 32));
-        if (v < (uint32_t)m) atomicAdd((unsigned long long *)&vcec[v], (unsigned long long)(int64_t)(int32_t)nz[src + i]);
-    }
-}
-
-int launch_records_to_vcec(const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions, int64_t region_slots, int m,
-                           int64_t *vcec, hipStream_t stream) {
-    hipLaunchKernelGGL(records_to_vcec_kernel, dim3((unsigned)((regions + 3) / 4)), dim3(256), 0, stream, nz, nz_cnt,
-                       regions, region_slots, m, vcec);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }
@@ -550,86 +522,6 @@ int launch_change_points(const float *keys, const int64_t *chi, int64_t K, uint3
     if (rc) return rc;
     hipLaunchKernelGGL(step_scatter_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, keys, chi,
                        (const uint32_t *)pos, K, out_keys, out_chi, count);
-    ECC_HIP(hipGetLastError());
-    return ECC_OK;
-}
-
-// ----------------------------------------------------------------------------
-// Integer images through the float path (images the integer kernel does not
-// take: four axes longer than 1).  Values convert exactly to float32; the
-// float curve lists chi after each distinct value, and chi(T_t) for integer
-// t is its value at the largest distinct value <= t (0 below the first).
-
-// invert: writes limit - 1 - v (the image whose smallest-value curve gives
-// the largest-value curve, see launch_reflect_curve); values >= limit set
-// the status bit either way.
-template <typename T>
-__global__ void __launch_bounds__(256) int_to_f32_kernel(const T *__restrict__ img, int64_t n, uint32_t limit,
-                                                         int invert, float *__restrict__ out, uint32_t *status) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    bool bad = false;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const uint32_t v = img[i];
-        bad |= v >= limit;
-        out[i] = invert ? (float)((int32_t)limit - 1 - (int32_t)v) : (float)v;
-    }
-    if (__builtin_amdgcn_ballot_w64(bad) != 0 && (threadIdx.x & 63) == 0) atomicOr(status, kStatusRange);
-}
-
-int launch_int_to_f32(const void *img, int elem, int64_t n, uint32_t limit, int invert, float *out,
-                      uint32_t *status, hipStream_t stream) {
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    if (elem == 1)
-        hipLaunchKernelGGL(int_to_f32_kernel<uint8_t>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           (const uint8_t *)img, n, limit, invert, out, status);
-    else
-        hipLaunchKernelGGL(int_to_f32_kernel<uint16_t>, dim3((unsigned)blocks), dim3(256), 0, stream,
-                           (const uint16_t *)img, n, limit, invert, out, status);
-    ECC_HIP(hipGetLastError());
-    return ECC_OK;
-}
-
-__global__ void __launch_bounds__(256) expand_steps_kernel(const float *__restrict__ keys,
-                                                           const int64_t *__restrict__ chi, int64_t K, int m,
-                                                           int64_t *__restrict__ out) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= m) return;
-    const float ft = (float)t;
-    int64_t lo = 0, hi = K;  // first index with keys[idx] > t
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if (keys[mid] <= ft) lo = mid + 1;
-        else hi = mid;
-    }
-    out[t] = lo > 0 ? chi[lo - 1] : 0;
-}
-
-int launch_expand_steps(const float *keys, const int64_t *chi, int64_t K, int m, int64_t *out,
-                        hipStream_t stream) {
-    hipLaunchKernelGGL(expand_steps_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, keys, chi, K, m, out);
-    ECC_HIP(hipGetLastError());
-    return ECC_OK;
-}
-
-// Largest-value convention from the smallest-value curve g of the inverted
-// image (values m - 1 - v): a cell's largest value is <= t exactly when its
-// smallest inverted value is >= m - 1 - t, so the cells counted at t are all
-// cells (the whole box, chi = 1) less those counted in g at m - 2 - t:
-//   curve:   out[t] = 1 - g[m - 2 - t]
-//   changes: out[t] = g[m - 1 - t] - g[m - 2 - t]
-// (g[-1] = 0).
-__global__ void __launch_bounds__(256) reflect_curve_kernel(const int64_t *__restrict__ g, int m, int changes,
-                                                            int64_t *__restrict__ out) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= m) return;
-    const int64_t below = t <= m - 2 ? g[m - 2 - t] : 0;
-    out[t] = changes ? g[m - 1 - t] - below : 1 - below;
-}
-
-int launch_reflect_curve(const int64_t *g, int m, int changes, int64_t *out, hipStream_t stream) {
-    hipLaunchKernelGGL(reflect_curve_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, g, m, changes, out);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }

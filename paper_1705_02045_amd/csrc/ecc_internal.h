@@ -118,8 +118,6 @@ struct Workspace {
     size_t frec_bytes = 0;
     void *dual_buf = nullptr;    // dual complex: gathered faces of the box, per-face curves
     size_t dual_buf_bytes = 0;
-    void *i2f_buf = nullptr;     // integer images through the float path: float copy, float curve, expanded curve
-    size_t i2f_buf_bytes = 0;
     int64_t *vcec16 = nullptr;   // [65536] changes vector of a 16-bit image (window passes)
     size_t vcec16_bytes = 0;
     // Fixed scratch (the entry point that allocates nothing): the buffers
@@ -256,21 +254,24 @@ struct ChangeJob {
     int32_t nx, ny, nz;   // in-plane extents (1 where the axis is absent), the last axis nx
     int32_t e0, e1;       // planes to emit, buffer coordinates
     int32_t lo_inf, hi_inf;  // planes e0-1 and e1 lie outside the image
+    int dtype;            // ECC_F32 or, with nl = 2, an integer type
+    int invert;           // u8, u14: values read as m-1-v
 };
 // The float image's records (key << 32 | change as uint32, for the voxels
 // whose change is not zero): region i holds its cnt[i] records from
 // rec[i * region_slots] on.
 int change_regions(const ChangeJob &job, int64_t *regions, int64_t *region_slots);
 int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hipStream_t stream);
+// Integer images with four axes longer than 1.  u8 and u14: count rows, one
+// per workgroup (change_count_rows of them, m int32 each), merged as the
+// integer kernel's; u16 (m = 65536, more than a workgroup's histogram
+// holds): int64 adds straight into vcec.  A value >= m sets kStatusRange.
+int change_count_rows(const ChangeJob &job, int *rows);
+int launch_change_counts(const ChangeJob &job, int32_t *partial, int64_t *vcec, uint32_t *status, hipStream_t stream);
 
 // Float path (ecc_float.hip, ecc_sort.hip).
-// The change kernel's job for planes [e0, e1) of a float image (e1 may lie
-// past the end).
-int float_job(const float *img_dev, const ecc_dims *dims, int64_t e0, int64_t e1, ChangeJob *job);
-// Integer images through the change kernel: the regions' records added to
-// vcec (m int64) at the records' values.
-int launch_records_to_vcec(const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions, int64_t region_slots, int m,
-                           int64_t *vcec, hipStream_t stream);
+// The change kernel's job for a float image.
+int float_job(const float *img_dev, const ecc_dims *dims, ChangeJob *job);
 // nz_off (regions + 1 entries): the regions' offsets, an exclusive scan of
 // nz_cnt (sums: radix_scan_tiles(regions + 1)), and the record count into
 // *total_host (host-mapped).
@@ -308,16 +309,6 @@ int exclusive_scan_u32(uint32_t *a, int64_t n, uint32_t *sums, hipStream_t strea
 // Keys where chi changes, compacted (count written on the device).
 int launch_change_points(const float *keys, const int64_t *chi, int64_t K, uint32_t *pos, uint32_t *sums,
                          float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream);
-// Integer image (elem = 1 or 2 bytes) to float32 (invert: limit - 1 - v);
-// values >= limit set kStatusRange.
-int launch_int_to_f32(const void *img, int elem, int64_t n, uint32_t limit, int invert, float *out,
-                      uint32_t *status, hipStream_t stream);
-// Largest-value curve (changes = 0) or changes vector (changes = 1) from the
-// smallest-value curve g of the inverted image, m entries.
-int launch_reflect_curve(const int64_t *g, int m, int changes, int64_t *out, hipStream_t stream);
-// out[t] = chi at the largest key <= t (0 below keys[0]), t < m.
-int launch_expand_steps(const float *keys, const int64_t *chi, int64_t K, int m, int64_t *out,
-                        hipStream_t stream);
 // Float image to integer bins (elem = 1 or 2 bytes), NaN -> kStatusNaN.
 int launch_quantize(const float *img, int64_t n, float lo, float scale, int m, int elem, void *out,
                     uint32_t *status, hipStream_t stream);

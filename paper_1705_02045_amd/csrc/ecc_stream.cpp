@@ -12,12 +12,9 @@
 // know its values in advance; each pass adds the values of its half of
 // 0..65535 to that half of the changes vector.
 //
-// Planes with three axes longer than 1 (4-D images) go through the float
-// path's change kernel instead (Sec. 3, "Other Ranges of Gray Values": the
-// same owner rule on any ordered values): a launch's planes and its collars
-// are converted to float32 into one window buffer, the kernel emits the
-// changes of the launch's planes only (the collars are neighbours), and the
-// non-zero changes are added to the changes vector at their voxels' values.
+// Planes with three axes longer than 1 (4-D images) go through the change
+// kernel (ecc_change.hip) instead, which reads the launch's planes and its
+// collars in place in the same way.
 //
 // Host chunks go through two device staging buffers filled on a copy stream
 // (hipMemcpyAsync), so the copy of chunk k+1 overlaps the kernels of chunk k.
@@ -56,13 +53,9 @@ struct ecc_stream {
     size_t mstage_bytes = 0;
     int64_t *vcec = nullptr;
     uint32_t *status = nullptr;
-    // 4-D images: extents, the float window of a launch and its change records
+    // 4-D images: extents
     bool four_d = false;
     int64_t n4[4] = {0, 0, 0, 0};
-    float *wbuf = nullptr;
-    size_t wbuf_bytes = 0;
-    uint8_t *nzbuf = nullptr;
-    size_t nzbuf_bytes = 0;
 };
 
 namespace {
@@ -85,8 +78,6 @@ void destroy(ecc_stream *st) {
     if (st->partial) (void)hipFree(st->partial);
     if (st->mstage) (void)hipFree(st->mstage);
     if (st->vcec) (void)hipFree(st->vcec);
-    if (st->wbuf) (void)hipFree(st->wbuf);
-    if (st->nzbuf) (void)hipFree(st->nzbuf);
     if (st->status) (void)hipFree(st->status);
     if (st->copy) (void)hipStreamDestroy(st->copy);
     if (prev >= 0) (void)hipSetDevice(prev);
@@ -107,72 +98,31 @@ bool is_device_ptr(const void *p) {
 int64_t min64(int64_t a, int64_t b) { return a < b ? a : b; }
 
 // 4-D images: the changes of image planes [lo, hi) of a push whose chunk
-// holds image planes [f, f + n), the carry holding planes [f - a, f).  A
-// launch covers planes [b0, b1) with the window [b0 - 1, b1 + 1) within the
-// image, as many planes at a time as the float kernel takes (below 2^30
-// values).
-int run_chunk_4d(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t lo, int64_t hi) {
-    const int64_t n0 = st->view.n0;
-    const int64_t pe = st->n4[1] * st->n4[2] * st->n4[3];  // elements per plane
-    const int eb = st->dtype == ECC_U8 ? 1 : 2;
-    const int64_t step = (((int64_t)1 << 30) - 1) / pe - 2;  // (>= 1: planes hold at most 2^28 values)
-    const uint8_t *carry = st->carry_buf[st->cur];
-    // every buffer at its largest size first: a push that fails to allocate
-    // has added nothing, so it can be pushed again
-    {
-        ecc_dims w{};
-        w.ndim = 4;
-        w.n[0] = min64(step, hi - lo) + 2;
-        for (int k = 1; k < 4; ++k) w.n[k] = st->n4[k];
-        ChangeJob job{};
-        int64_t regions = 0, region_slots = 0;
-        int rc = ensure_bytes((void **)&st->wbuf, &st->wbuf_bytes, (size_t)(w.n[0] * pe) * 4);
-        if (!rc) rc = float_job(st->wbuf, &w, 0, INT64_MAX, &job);
-        if (!rc) rc = change_regions(job, &regions, &region_slots);
-        if (!rc) rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, (size_t)(regions * region_slots) * 8 + (size_t)regions * 4);
-        if (rc) return rc;
-    }
-    for (int64_t b0 = lo; b0 < hi; b0 += step) {
-        const int64_t b1 = min64(b0 + step, hi);
-        const int64_t wlo = b0 > 0 ? b0 - 1 : 0, whi = b1 < n0 ? b1 + 1 : n0;
-        const int64_t p = whi - wlo;
-        const int64_t ncar = wlo < f ? f - wlo : 0;  // window planes from the carry (0..2)
-        if (ncar > st->ncarry) {
-            set_error("internal error: 4-D stream window");
-            return ECC_E_STATE;
-        }
-        int rc = ensure_bytes((void **)&st->wbuf, &st->wbuf_bytes, (size_t)(p * pe) * 4);
-        if (rc) return rc;
-        if (ncar > 0) {
-            rc = launch_int_to_f32(carry + (st->ncarry - ncar) * st->plane_bytes, eb, ncar * pe, (uint32_t)st->m, 0,
-                                   st->wbuf, st->status, st->compute);
-            if (rc) return rc;
-        }
-        const int64_t c0 = wlo + ncar;  // first window plane from the chunk
-        rc = launch_int_to_f32(chunk + (c0 - f) * st->plane_bytes, eb, (whi - c0) * pe, (uint32_t)st->m, 0,
-                               st->wbuf + ncar * pe, st->status, st->compute);
-        if (rc) return rc;
-        ecc_dims w{};
-        w.ndim = 4;
-        w.n[0] = p;
-        for (int k = 1; k < 4; ++k) w.n[k] = st->n4[k];
-        // (a one-plane window: its plane is emitted, and the kernel sees three axes)
-        ChangeJob job{};
-        int64_t regions = 0, region_slots = 0;
-        rc = float_job(st->wbuf, &w, p > 1 ? b0 - wlo : 0, p > 1 ? b1 - wlo : INT64_MAX, &job);
-        if (!rc) rc = change_regions(job, &regions, &region_slots);
-        if (rc) return rc;
-        const size_t off_cnt = (size_t)(regions * region_slots) * 8;
-        rc = ensure_bytes((void **)&st->nzbuf, &st->nzbuf_bytes, off_cnt + (size_t)regions * 4);
-        if (rc) return rc;
-        uint64_t *nz = (uint64_t *)st->nzbuf;
-        uint32_t *nz_cnt = (uint32_t *)(st->nzbuf + off_cnt);
-        rc = launch_change_records(job, nz, nz_cnt, st->compute);
-        if (rc) return rc;
-        rc = launch_records_to_vcec(nz, nz_cnt, regions, region_slots, st->m, st->vcec, st->compute);
-        if (rc) return rc;
-    }
-    return ECC_OK;
+// holds image planes from f on, the carry holding the planes before it.
+int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int64_t hi) {
+    ChangeJob j{};
+    j.dtype = st->dtype;
+    j.nl = 2;
+    j.nx = (int32_t)st->n4[3];
+    j.ny = (int32_t)st->n4[2];
+    j.nz = (int32_t)st->n4[1];
+    j.src = src;
+    j.e0 = (int32_t)(lo - f);
+    j.e1 = (int32_t)(hi - f);
+    j.lo_inf = lo == 0;
+    j.hi_inf = hi == st->view.n0;
+    if (st->dtype == ECC_U16) return launch_change_counts(j, nullptr, st->vcec, st->status, st->compute);
+    int rows = 0;
+    int rc = change_count_rows(j, &rows);
+    if (rc) return rc;
+    rc = ensure_bytes((void **)&st->partial, &st->partial_bytes, (size_t)rows * st->m * sizeof(int32_t));
+    if (rc) return rc;
+    rc = ensure_bytes((void **)&st->mstage, &st->mstage_bytes, (size_t)merge_stage_rows(rows) * st->m * sizeof(int64_t));
+    if (rc) return rc;
+    rc = launch_change_counts(j, st->partial, nullptr, st->status, st->compute);
+    if (rc) return rc;
+    return launch_merge(st->partial, rows, st->m, st->mstage, st->vcec, true, false, nullptr, st->status, nullptr,
+                        st->compute);
 }
 
 // Adds the changes of image planes [emitted, hi) of a push whose chunk holds
@@ -187,7 +137,7 @@ int run_chunk(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t n, int64_
     uint8_t *carry = st->carry_buf[st->cur];
     const int64_t lo = st->emitted;  // f - 1, or 0 on the first push
     if (lo < hi && st->four_d) {
-        int rc = run_chunk_4d(st, chunk, f, lo, hi);
+        int rc = run_chunk_4d(st, PlaneSrc{chunk, carry + a * pb, pb}, f, lo, hi);
         if (rc) return rc;
     } else if (lo < hi) {
         IntJob j{};
@@ -303,7 +253,7 @@ int ecc_stream_begin(const ecc_dims *full_dims, ecc_dtype dtype, void *stream, e
     } else if (k == 2 && ins[0] * ins[1] <= INT32_MAX) {
         v.nin = 2; v.n1 = (int32_t)ins[0]; v.n2 = (int32_t)ins[1];
     } else if (k == 3 && ins[0] * ins[1] * ins[2] <= ((int64_t)1 << 28)) {
-        v.nin = 3;  // 4-D: the float change kernel on a window of planes
+        v.nin = 3;  // 4-D: the change kernel
         v.n1 = 1;
         v.n2 = 1;
     } else {

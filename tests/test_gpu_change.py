@@ -47,6 +47,33 @@ def test_change_tile_edges(shape, kind):
     check(img)
 
 
+# 4-D integer images: shapes at the tiles' edges, every dtype and convention
+EDGES_4D = [(2, 2, 2, 2), (3, 4, 5, 31), (8, 2, 3, 62), (9, 5, 4, 13), (17, 3, 2, 21), (4, 7, 6, 64), (10, 9, 11, 12)]
+CONVENTIONS = [("u8", "min"), ("u8", "max"), ("u8", "dual"), ("u14", "min"), ("u14", "max"), ("u14", "dual"),
+               ("u16", "min")]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", EDGES_4D, ids=str)
+@pytest.mark.parametrize("dtype,convention", CONVENTIONS, ids=str)
+def test_change_4d_integers(shape, dtype, convention):
+    import paper_1705_02045_amd as ecc
+    m = ecc.THRESHOLDS[dtype]
+    rng = np.random.default_rng(sum(shape) + m)
+    # the lowest and highest values among others, with ties
+    img = rng.choice(np.array([0, 1, m // 2, m - 2, m - 1]), size=shape)
+    img = np.where(rng.random(shape) < 0.6, img, rng.integers(0, m, size=shape))
+    img = img.astype(np.uint8 if dtype == "u8" else np.uint16)
+    t = torch.from_numpy(img if dtype == "u8" else img.view(np.int16)).cuda()
+    if convention == "min":
+        got, want = ecc.compute(t, dtype), oracle.curve(img, m=m)
+    elif convention == "max":
+        got, want = ecc.compute_max_entry(t, dtype), oracle.curve_max_entry(img, m=m)
+    else:
+        got, want = ecc.compute_dual(t, dtype), oracle.curve_dual(img, m=m)
+    assert np.array_equal(got.cpu().numpy(), want)
+
+
 def test_no_subtraction_with_a_lane_shift():
     """v_subrev_u32 with a lane shift on its first source shifted the second
     on the card: the change kernel's build holds no such subtraction."""
