@@ -11,8 +11,7 @@ CSRC = HERE / "csrc"
 LIB = HERE / "libecc.so"
 
 SOURCES = ["ecc_api.cpp", "ecc_stream.cpp", "ecc_batch.cpp", "ecc_profile.cpp", "ecc_noalloc.cpp", "ecc_int.hip",
-           "ecc_scan.hip", "ecc_change.hip",
-           "ecc_float.hip", "ecc_sort.hip"]
+           "ecc_scan.hip", "ecc_change.hip", "ecc_distinct.hip", "ecc_float.hip", "ecc_sort.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -858,47 +858,58 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     uint32_t *mask_dev = (uint32_t *)(b + off[kCnt] + 32);  // the key sort's top-byte mask (8 words)
     float *out_keys = direct ? curve->keys : (float *)(b + out_k);
     int64_t *out_chi = direct ? curve->chi : (int64_t *)(b + out_c);
-    // the record count, read on the host while the keys are sorted: a word of
-    // the host-mapped status block
-    volatile int64_t *nnz_host = (volatile int64_t *)(ws->host_status + 2);
-    int64_t *nnz_host_dev = (int64_t *)(ws->host_status_dev + 2);
-    *nnz_host = -1;
-
-    rc = launch_change_records(job, nz, nz_cnt, s);
-    if (rc) return rc;
-    rc = launch_nz_total(nz_cnt, nz_off, regions, sums, nnz_host_dev, s);
-    if (rc) return rc;
-    hipEvent_t counted = nullptr;
-    ECC_HIP(hipEventCreateWithFlags(&counted, hipEventDisableTiming));
-    hipError_t e = hipEventRecord(counted, s);
-    if (e == hipSuccess) {
-        rc = radix_sort_keys(img_dev, key, n, counts, sums, mask_dev, ws->host_status + 4, ws->host_status_dev + 4,
-                             ws->status, s);
-        e = hipEventSynchronize(counted);
-    }
-    (void)hipEventDestroy(counted);
-    ECC_HIP(e);
-    if (rc) return rc;
-    const int64_t nnz = *nnz_host;
-    if (nnz < 0 || nnz > n) {
-        set_error("internal error: %lld change records for %lld voxels", (long long)nnz, (long long)n);
-        return ECC_E_HIP;
-    }
-    // the dense records (two sort buffers) and their prefix
-    const size_t rb = align256((size_t)nnz * 8);
-    rc = ensure_bytes(&ws->frec, &ws->frec_bytes, 3 * rb + 256);
-    if (rc) return rc;
-    uint64_t *rec[2] = {(uint64_t *)ws->frec, (uint64_t *)((uint8_t *)ws->frec + rb)};
-    int64_t *prefix = (int64_t *)((uint8_t *)ws->frec + 2 * rb);
-    if (nnz > 0) {
-        rc = launch_nz_compact(nz, nz_cnt, nz_off, regions, region_slots, rec[0], s);
+    // the host reads which top bytes occur while the change kernel runs
+    hipEvent_t ev = nullptr;
+    ECC_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    rc = radix_key_counts(img_dev, n, counts, sums, mask_dev, ws->host_status_dev + 4, ws->status, ev, s);
+    if (!rc) rc = launch_change_records(job, nz, nz_cnt, s);
+    hipError_t e = hipEventSynchronize(ev);
+    int present = 0;
+    for (int w = 0; w < 8; ++w) present += __builtin_popcount((ws->host_status + 4)[w]);
+    if (!rc && e == hipSuccess && present <= kMaxDistinctBytes) {
+        (void)hipEventDestroy(ev);
+        rc = ensure_bytes(&ws->fbits, &ws->fbits_bytes, distinct_scratch_bytes(present, n));
         if (rc) return rc;
-        rc = radix_sort_records(rec, nnz, counts, sums, s);
+        rc = launch_distinct_curve(img_dev, n, present, counts, mask_dev, key[0], ws->fbits, nz, nz_cnt, regions,
+                                   region_slots, out_keys, out_chi, count_dev, s);
+        if (rc) return rc;
+    } else {
+        // the record count, read on the host while the keys are sorted: a
+        // word of the host-mapped status block
+        volatile int64_t *nnz_host = (volatile int64_t *)(ws->host_status + 2);
+        *nnz_host = -1;
+        if (!rc && e == hipSuccess) {
+            rc = launch_nz_total(nz_cnt, nz_off, regions, sums, (int64_t *)(ws->host_status_dev + 2), s);
+            if (!rc) e = hipEventRecord(ev, s);
+            if (!rc && e == hipSuccess) {
+                rc = radix_sort_keys(img_dev, key, n, counts, sums, s);
+                e = hipEventSynchronize(ev);
+            }
+        }
+        (void)hipEventDestroy(ev);
+        ECC_HIP(e);
+        if (rc) return rc;
+        const int64_t nnz = *nnz_host;
+        if (nnz < 0 || nnz > n) {
+            set_error("internal error: %lld change records for %lld voxels", (long long)nnz, (long long)n);
+            return ECC_E_HIP;
+        }
+        // the dense records (two sort buffers) and their prefix
+        const size_t rb = align256((size_t)nnz * 8);
+        rc = ensure_bytes(&ws->frec, &ws->frec_bytes, 3 * rb + 256);
+        if (rc) return rc;
+        uint64_t *rec[2] = {(uint64_t *)ws->frec, (uint64_t *)((uint8_t *)ws->frec + rb)};
+        int64_t *prefix = (int64_t *)((uint8_t *)ws->frec + 2 * rb);
+        if (nnz > 0) {
+            rc = launch_nz_compact(nz, nz_cnt, nz_off, regions, region_slots, rec[0], s);
+            if (rc) return rc;
+            rc = radix_sort_records(rec, nnz, counts, sums, s);
+            if (rc) return rc;
+        }
+        rc = launch_float_curve(key[0], n, rec[0], nnz, prefix, (uint32_t *)tile_b, sums, tile_a, bound, count_dev,
+                                out_keys, out_chi, s);
         if (rc) return rc;
     }
-    rc = launch_float_curve(key[0], n, rec[0], nnz, prefix, (uint32_t *)tile_b, sums, tile_a, bound, count_dev, out_keys,
-                            out_chi, s);
-    if (rc) return rc;
     uint32_t st = 0;
     int64_t kcount = 0;
     ECC_HIP(hipMemcpyAsync(&st, ws->status, 4, hipMemcpyDeviceToHost, s));
@@ -1291,6 +1302,8 @@ int ecc_release_workspaces(void) {
         w->fbuf = nullptr;
         drop(w->frec, &w->frec_bytes);
         w->frec = nullptr;
+        drop(w->fbits, &w->fbits_bytes);
+        w->fbits = nullptr;
         drop(w->dual_buf, &w->dual_buf_bytes);
         w->dual_buf = nullptr;
         drop(w->vcec16, &w->vcec16_bytes);

@@ -1,0 +1,614 @@
+// The distinct values of a float image and the curve at them (Sec. 3, "Other
+// Ranges of Gray Values"), without sorting the keys: the keys (f32_key) that
+// can occur are few enough for one bit each.  An image whose keys hold P
+// different top bytes (sign and high exponent bits; at most 32) has its keys
+// among P * 2^24 values: the byte's rank among those present and the low 24
+// bits, in the keys' own order, give a key's position p.
+//
+// A bit per position in memory, set by every voxel, would be bound by atomics
+// (27 G/s at random places on MI355X: 10 ms for 2^28 voxels).  So the keys
+// are first split by their lowest 9 bits, which are spread evenly in any
+// image of many values, into 512 buckets (one pass: digit counts, their scan,
+// a scatter that need not keep an order), and a bucket's bits, one per
+// remaining value (P * 2^15), are set in LDS:
+//  1. bucket_scatter_kernel: the keys by bucket, as idx = p >> 9;
+//  2. bucket_bits_kernel: a workgroup per bucket (large ones are shared) sets
+//     the bucket's bits in LDS, P * 4 KiB, and adds them to bits[bucket][idx];
+//  3. order_bits_kernel: bits[bucket][idx] to the order of p (idx first, then
+//     the bucket), with the count of set bits before each block of 256;
+//  4. expand_kernel: the k-th set bit is the k-th distinct value; its chi is
+//     cleared;
+//  5. add_records_kernel: each record's change is added to chi at its key's
+//     rank (the set bits before it);
+//  6. chi_sums_kernel, chi_scan_kernel, chi_prefix_kernel: the running sum.
+#include <algorithm>
+
+#include "ecc_internal.h"
+
+namespace ecc {
+
+namespace {
+
+constexpr int kBucketBits = 9;
+constexpr int kBuckets = 1 << kBucketBits;
+constexpr int kIdxPerByte = 1 << (24 - kBucketBits);  // idx values per top byte
+constexpr int kWordsPerByte = kIdxPerByte / 32;       // words of a bucket's bits per top byte
+
+// rank[t]: present top bytes below t; called by every thread of a workgroup
+// of at least 256, ends with a barrier
+__device__ __forceinline__ void rank_table(const uint32_t *__restrict__ mask, uint8_t *rank) {
+    const int t = threadIdx.x;
+    if (t < 256) {
+        uint32_t c = 0;
+        for (int w = 0; w < (t >> 5); ++w) c += (uint32_t)__builtin_popcount(mask[w]);
+        c += (uint32_t)__builtin_popcount(mask[t >> 5] & ((1u << (t & 31)) - 1u));
+        rank[t] = (uint8_t)c;
+    }
+    __syncthreads();
+}
+
+// ---- 1. a tile of kTile keys, the same tiles as the digit counts
+constexpr int kThreads = 1024;
+constexpr int kItems = 8;
+constexpr int kTile = kThreads * kItems;
+
+__global__ void __launch_bounds__(kThreads) bucket_scatter_kernel(const float *__restrict__ img, int64_t n, int64_t tiles,
+                                                                  const uint32_t *__restrict__ offsets,
+                                                                  const uint32_t *__restrict__ mask,
+                                                                  uint32_t *__restrict__ out) {
+    __shared__ uint32_t buf[kTile];       // the tile's keys by bucket
+    __shared__ uint32_t cnt[kBuckets];    // keys per bucket, then the bucket's first slot
+    __shared__ uint32_t dest[kBuckets];   // output position minus slot
+    __shared__ uint32_t ws[kBuckets / 64];
+    __shared__ uint8_t rank[256];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t tile = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t t0 = (int64_t)tile * kTile;
+    const int valid = (int)std::min<int64_t>(kTile, n - t0);
+    const uint32_t gpos = tid < kBuckets ? offsets[(int64_t)tid * tiles + tile] : 0u;
+    if (tid < kBuckets) cnt[tid] = 0;
+    rank_table(mask, rank);
+    uint32_t key[kItems], at[kItems];
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(img) + t0;
+    const bool vec = valid == kTile && (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
+    if (vec) {
+#pragma unroll
+        for (int q = 0; q < kItems / 4; ++q) {
+            const uint4 w = reinterpret_cast<const uint4 *>(src)[q * kThreads + tid];
+            key[4 * q] = w.x;
+            key[4 * q + 1] = w.y;
+            key[4 * q + 2] = w.z;
+            key[4 * q + 3] = w.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) key[j] = j * kThreads + tid < valid ? src[j * kThreads + tid] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        key[j] = f32_key(key[j]);
+        if (vec || j * kThreads + tid < valid) at[j] = atomicAdd(&cnt[key[j] & (kBuckets - 1)], 1u);
+    }
+    __syncthreads();
+    // first slot of each bucket
+    uint32_t c = 0, x = 0;
+    if (tid < kBuckets) {
+        c = x = cnt[tid];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        if (lane == 63) ws[tid >> 6] = x;
+    }
+    __syncthreads();
+    if (tid < kBuckets) {
+        uint32_t s = x - c;
+        for (int w = 0; w < (tid >> 6); ++w) s += ws[w];
+        cnt[tid] = s;
+        dest[tid] = gpos - s;  // (mod 2^32: positions are below 2^30)
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+        if (vec || j * kThreads + tid < valid) buf[cnt[key[j] & (kBuckets - 1)] + at[j]] = key[j];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        const int s = j * kThreads + tid;
+        if (s < valid) {
+            const uint32_t k = buf[s];
+            out[dest[k & (kBuckets - 1)] + (uint32_t)s] = ((uint32_t)rank[k >> 24] << (24 - kBucketBits)) | ((k & 0xFFFFFFu) >> kBucketBits);
+        }
+    }
+}
+
+// ---- 2. Buckets are cut into shares of at most `share` keys; a workgroup
+// takes one share (at most kBuckets + n / share of them).  A bucket of one
+// share is stored, the others are OR-ed (bits is zero before the launch).
+__global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *__restrict__ idx, int64_t n, int64_t tiles,
+                                                               const uint32_t *__restrict__ offsets, uint32_t share,
+                                                               int words, uint32_t *__restrict__ bits) {
+    extern __shared__ uint32_t lds[];
+    __shared__ uint32_t ws[kBuckets / 64];
+    __shared__ uint32_t my[4];  // bucket, its first key, keys of this share, shares of the bucket
+    const int tid = threadIdx.x, lane = tid & 63;
+    if (tid == 0) my[2] = 0;
+    uint32_t beg = 0, len = 0, ns = 0, x = 0;
+    if (tid < kBuckets) {
+        beg = offsets[(int64_t)tid * tiles];
+        len = (tid + 1 < kBuckets ? offsets[(int64_t)(tid + 1) * tiles] : (uint32_t)n) - beg;
+        ns = x = (len + share - 1) / share;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        if (lane == 63) ws[tid >> 6] = x;
+    }
+    for (int i = tid; i < words; i += kThreads) lds[i] = 0;
+    __syncthreads();
+    if (tid < kBuckets) {
+        uint32_t s = x - ns;  // this bucket's first workgroup
+        for (int w = 0; w < (tid >> 6); ++w) s += ws[w];
+        if (blockIdx.x >= s && blockIdx.x < s + ns) {
+            const uint32_t b = (blockIdx.x - s) * share;
+            my[0] = (uint32_t)tid;
+            my[1] = beg + b;
+            my[2] = len - b < share ? len - b : share;
+            my[3] = ns;
+        }
+    }
+    __syncthreads();
+    const uint32_t m = my[2];
+    if (m == 0) return;  // (uniform) past the last share
+    const uint32_t *src = idx + my[1];
+    auto set = [&](uint32_t v) { atomicOr(&lds[v >> 5], 1u << (v & 31u)); };
+    uint32_t head = (uint32_t)((16u - (uint32_t)(reinterpret_cast<uintptr_t>(src) & 15u)) & 15u) / 4u;
+    if (head > m) head = m;
+    if ((uint32_t)tid < head) set(src[tid]);
+    const uint32_t quads = (m - head) / 4u;
+    const uint4 *q4 = reinterpret_cast<const uint4 *>(src + head);
+    uint32_t i = tid;
+    for (; i + 3 * kThreads < quads; i += 4 * kThreads) {
+        uint4 w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = q4[i + u * kThreads];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            set(w[u].x);
+            set(w[u].y);
+            set(w[u].z);
+            set(w[u].w);
+        }
+    }
+    for (; i < quads; i += kThreads) {
+        const uint4 w = q4[i];
+        set(w.x);
+        set(w.y);
+        set(w.z);
+        set(w.w);
+    }
+    for (uint32_t t = head + 4u * quads + tid; t < m; t += kThreads) set(src[t]);
+    __syncthreads();
+    uint32_t *dst = bits + (size_t)my[0] * words;
+    const bool whole = my[3] == 1;
+    for (int w = tid; w < words; w += kThreads) {
+        const uint32_t v = lds[w];
+        if (v == 0) continue;
+        if (whole) dst[w] = v;
+        else atomicOr(&dst[w], v);
+    }
+}
+
+// ---- 3. A tile: 16 words of every bucket, i.e. 512 idx by 512 buckets, 2^18
+// positions.  A thread transposes 32 x 32 bits in registers: the words w of
+// the buckets 32 g .. 32 g + 31 become, for the 32 idx of word w, word g of
+// the idx's row of 16.
+constexpr int kTileWords = 16;
+constexpr int kOrdWords = kTileWords * kBuckets;  // 8192 words in p order
+constexpr int kBlockWords = 8;                    // words per counted block
+constexpr int kTileBlocks = kOrdWords / kBlockWords;
+
+template <int S, uint32_t LOW>
+__device__ __forceinline__ void transpose_step(uint32_t (&a)[32]) {
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        if (i & S) continue;
+        const uint32_t t = ((a[i] >> S) ^ a[i + S]) & LOW;
+        a[i] ^= t << S;
+        a[i + S] ^= t;
+    }
+}
+// afterwards bit i of a[j] is the former bit j of a[i]
+__device__ __forceinline__ void transpose32(uint32_t (&a)[32]) {
+    transpose_step<16, 0x0000FFFFu>(a);
+    transpose_step<8, 0x00FF00FFu>(a);
+    transpose_step<4, 0x0F0F0F0Fu>(a);
+    transpose_step<2, 0x33333333u>(a);
+    transpose_step<1, 0x55555555u>(a);
+}
+
+__global__ void __launch_bounds__(256) order_bits_kernel(const uint32_t *__restrict__ bits, int words,
+                                                         uint32_t *__restrict__ ord, uint32_t *__restrict__ blk,
+                                                         uint32_t *__restrict__ total) {
+    __shared__ __attribute__((aligned(16))) uint32_t t[kOrdWords + kOrdWords / 8];
+    __shared__ uint32_t ws[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int w0 = blockIdx.x * kTileWords;
+    uint32_t any = 0;
+    // 4 threads load a bucket's 16 words; word w of bucket d is kept at
+    // d * 16 + (w + d / 32) % 16 (the threads of one w and 16 g then read
+    // 16 banks)
+    for (int i = tid; i < kBuckets * 4; i += 256) {
+        const int d = i >> 2, q = i & 3;
+        const uint4 v = *reinterpret_cast<const uint4 *>(bits + (size_t)d * words + w0 + 4 * q);
+        const int r = d >> 5;
+        t[d * 16 + ((4 * q + 0 + r) & 15)] = v.x;
+        t[d * 16 + ((4 * q + 1 + r) & 15)] = v.y;
+        t[d * 16 + ((4 * q + 2 + r) & 15)] = v.z;
+        t[d * 16 + ((4 * q + 3 + r) & 15)] = v.w;
+        any |= v.x | v.y | v.z | v.w;
+    }
+    const bool empty = __syncthreads_or((int)(any != 0)) == 0;
+    uint32_t *dst = ord + (size_t)blockIdx.x * kOrdWords;
+    uint32_t *db = blk + (size_t)blockIdx.x * kTileBlocks;
+    if (empty) {  // (uniform) nothing reads the words or the blocks of an empty tile
+        if (tid == 0) total[blockIdx.x] = 0;
+        return;
+    }
+    const int g = tid & 15, w = tid >> 4;
+    uint32_t a[32];
+#pragma unroll
+    for (int i = 0; i < 32; ++i) a[i] = t[(32 * g + i) * 16 + ((w + g) & 15)];
+    transpose32(a);
+    __syncthreads();
+    // in p order, with 4 words of padding per 32: idx w * 32 + j, word g
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        const int o = (w * 32 + j) * 16 + g;
+        t[o + (o >> 5) * 4] = a[j];
+    }
+    __syncthreads();
+    // a thread counts 32 consecutive words: four blocks
+    uint32_t c[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        c[b] = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(&t[tid * 36 + b * 8 + q * 4]);
+            c[b] += __builtin_popcount(v.x) + __builtin_popcount(v.y) + __builtin_popcount(v.z) + __builtin_popcount(v.w);
+        }
+    }
+    const uint32_t s = c[0] + c[1] + c[2] + c[3];
+    uint32_t x = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t u = __shfl_up(x, off, 64);
+        if (lane >= off) x += u;
+    }
+    if (lane == 63) ws[wave] = x;
+    __syncthreads();
+    uint32_t p = x - s;
+    for (int v = 0; v < wave; ++v) p += ws[v];
+    *reinterpret_cast<uint4 *>(db + tid * 4) = make_uint4(p, p + c[0], p + c[0] + c[1], p + c[0] + c[1] + c[2]);
+    if (tid == 255) total[blockIdx.x] = p + s;
+    for (int i = tid; i < kOrdWords / 4; i += 256) {
+        const int o = 4 * i;
+        *reinterpret_cast<uint4 *>(dst + o) = *reinterpret_cast<const uint4 *>(&t[o + (o >> 5) * 4]);
+    }
+}
+
+// The exclusive scan of the tiles' totals (base[tiles] = their sum, also to
+// *count): one workgroup.
+__global__ void __launch_bounds__(1024) tile_base_kernel(const uint32_t *__restrict__ total, int tiles,
+                                                         uint32_t *__restrict__ base, int64_t *count) {
+    __shared__ uint32_t ws[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t carry = 0;
+    for (int c0 = 0; c0 < tiles; c0 += 1024) {
+        const int i = c0 + tid;
+        const uint32_t v = i < tiles ? total[i] : 0u;
+        uint32_t x = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        if (lane == 63) ws[wave] = x;
+        __syncthreads();
+        uint32_t p = carry;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) p += ws[w];
+            carry += ws[w];
+        }
+        if (i < tiles) base[i] = p + x - v;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        base[tiles] = carry;
+        *count = (int64_t)carry;
+    }
+}
+
+// ---- 4. A wave takes 64 words (eight blocks) at a time: each lane's set
+// bits are put, in order, into LDS, and leave as one run.
+constexpr int kExpandWaves = 4;
+constexpr int kExpandWords = 64;
+
+__global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_t *__restrict__ ord,
+                                                                   const uint32_t *__restrict__ blk,
+                                                                   const uint32_t *__restrict__ base,
+                                                                   const uint32_t *__restrict__ mask, int parts,
+                                                                   float *__restrict__ out_keys,
+                                                                   int64_t *__restrict__ out_chi) {
+    __shared__ uint32_t st[kExpandWaves][kExpandWords * 33];
+    __shared__ uint8_t byte_of[256];  // top byte of a rank
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tile = blockIdx.x / parts, part = blockIdx.x % parts;
+    if (base[tile] == base[tile + 1]) return;  // (uniform) an empty tile
+    {
+        uint32_t c = 0;
+        for (int w = 0; w < (tid >> 5); ++w) c += (uint32_t)__builtin_popcount(mask[w]);
+        const uint32_t m = mask[tid >> 5];
+        c += (uint32_t)__builtin_popcount(m & ((1u << (tid & 31)) - 1u));
+        if ((m >> (tid & 31)) & 1u) byte_of[c] = (uint8_t)tid;
+    }
+    __syncthreads();
+    const int chunks = kOrdWords / kExpandWords / parts;  // chunks of this workgroup
+    for (int ch = wave; ch < chunks; ch += kExpandWaves) {
+        const uint32_t w0 = (uint32_t)tile * kOrdWords + (uint32_t)(part * chunks + ch) * kExpandWords;
+        uint32_t v = ord[w0 + lane];
+        const uint32_t first = base[tile] + blk[w0 / kBlockWords];
+        const uint32_t c = (uint32_t)__builtin_popcount(v);
+        uint32_t x = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        if (cnt == 0) continue;
+        const uint32_t p0 = (w0 + lane) * 32u;
+        const uint32_t top = (uint32_t)byte_of[p0 >> 24] << 24;
+        uint32_t q = x - c;
+        while (v != 0) {
+            const uint32_t bit = (uint32_t)__builtin_ctz(v);
+            v &= v - 1;
+            st[wave][q + (q >> 5)] = top | ((p0 + bit) & 0xFFFFFFu);
+            ++q;
+        }
+        // (one wave's own LDS operations take effect in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        for (uint32_t i = lane; i < cnt; i += 64) {
+            const uint32_t k = st[wave][i + (i >> 5)];
+            out_keys[first + i] = __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+            out_chi[first + i] = 0;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+}
+
+// ---- 5. A wave per region of records.
+__global__ void __launch_bounds__(256) add_records_kernel(const uint64_t *__restrict__ nz,
+                                                          const uint32_t *__restrict__ nz_cnt, int64_t regions,
+                                                          int64_t region_slots, const uint32_t *__restrict__ ord,
+                                                          const uint32_t *__restrict__ blk,
+                                                          const uint32_t *__restrict__ base,
+                                                          const uint32_t *__restrict__ mask,
+                                                          int64_t *__restrict__ chi) {
+    __shared__ uint8_t rank[256];
+    rank_table(mask, rank);
+    const int lane = threadIdx.x & 63;
+    for (int64_t reg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); reg < regions; reg += (int64_t)gridDim.x * 4) {
+        const uint32_t c = nz_cnt[reg];
+        const uint64_t *src = nz + reg * region_slots;
+        for (uint32_t i = lane; i < c; i += 64) {
+            const uint64_t r = src[i];
+            const uint32_t k = (uint32_t)(r >> 32);
+            const uint32_t p = ((uint32_t)rank[k >> 24] << 24) | (k & 0xFFFFFFu);
+            const uint32_t b = p >> 8;
+            uint32_t at = base[p >> 18] + blk[b];
+            const uint4 *w4 = reinterpret_cast<const uint4 *>(ord + (size_t)b * kBlockWords);
+            const uint4 a0 = w4[0], a1 = w4[1];
+            const uint32_t w[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+            const uint32_t wi = (p >> 5) & 7u, below = (1u << (p & 31u)) - 1u;
+#pragma unroll
+            for (uint32_t j = 0; j < 8; ++j)
+                at += (uint32_t)__builtin_popcount(w[j] & (j < wi ? 0xFFFFFFFFu : j == wi ? below : 0u));
+            atomicAdd((unsigned long long *)&chi[at], (unsigned long long)(int64_t)(int32_t)(uint32_t)r);
+        }
+    }
+}
+
+// ---- 6. Tiles of kChiTile entries, K of them known on the device only.
+constexpr int kChiThreads = 256;
+constexpr int kChiItems = 16;
+constexpr int kChiTile = kChiThreads * kChiItems;
+
+__global__ void __launch_bounds__(kChiThreads) chi_sums_kernel(const int64_t *__restrict__ chi,
+                                                               const int64_t *__restrict__ count,
+                                                               int64_t *__restrict__ sums) {
+    __shared__ int64_t sh[kChiThreads / 64];
+    const int64_t K = *count, nt = (K + kChiTile - 1) / kChiTile;
+    const int tid = threadIdx.x;
+    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        int64_t s = 0;
+#pragma unroll
+        for (int j = 0; j < kChiItems; ++j) {
+            const int64_t i = t * kChiTile + (int64_t)j * kChiThreads + tid;
+            if (i < K) s += chi[i];
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if ((tid & 63) == 0) sh[tid >> 6] = s;
+        __syncthreads();
+        if (tid == 0) sums[t] = sh[0] + sh[1] + sh[2] + sh[3];
+        __syncthreads();
+    }
+}
+
+__global__ void __launch_bounds__(1024) chi_scan_kernel(const int64_t *__restrict__ count, int64_t *__restrict__ sums) {
+    __shared__ int64_t ws[16];
+    const int64_t nt = (*count + kChiTile - 1) / kChiTile;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int64_t carry = 0;
+    // four entries per thread and round
+    for (int64_t c0 = 0; c0 < nt; c0 += 4096) {
+        const int64_t i0 = c0 + 4 * (int64_t)tid;
+        int64_t v[4], s = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v[j] = i0 + j < nt ? sums[i0 + j] : 0;
+            s += v[j];
+        }
+        int64_t x = s;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        if (lane == 63) ws[wave] = x;
+        __syncthreads();
+        int64_t p = carry + x - s;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) p += ws[w];
+            carry += ws[w];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (i0 + j < nt) sums[i0 + j] = p;
+            p += v[j];
+        }
+        __syncthreads();
+    }
+}
+
+__global__ void __launch_bounds__(kChiThreads) chi_prefix_kernel(int64_t *__restrict__ chi,
+                                                                 const int64_t *__restrict__ count,
+                                                                 const int64_t *__restrict__ sums) {
+    // LDS slot of entry i: one pad word per 16, so that a thread's run of 16
+    // spreads over the banks
+    __shared__ int64_t st[kChiTile + kChiTile / 16];
+    __shared__ int64_t ws[kChiThreads / 64];
+    const int64_t K = *count, nt = (K + kChiTile - 1) / kChiTile;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int64_t t = blockIdx.x; t < nt; t += gridDim.x) {
+        const int64_t t0 = t * kChiTile;
+#pragma unroll
+        for (int j = 0; j < kChiItems; ++j) {
+            const int i = j * kChiThreads + tid;
+            st[i + (i >> 4)] = t0 + i < K ? chi[t0 + i] : 0;
+        }
+        __syncthreads();
+        int64_t v[kChiItems], s = 0;
+#pragma unroll
+        for (int j = 0; j < kChiItems; ++j) {
+            v[j] = st[tid * 17 + j];
+            s += v[j];
+        }
+        int64_t x = s;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int64_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        if (lane == 63) ws[wave] = x;
+        __syncthreads();
+        int64_t p = sums[t] + x - s;
+        for (int w = 0; w < wave; ++w) p += ws[w];
+#pragma unroll
+        for (int j = 0; j < kChiItems; ++j) {
+            p += v[j];
+            st[tid * 17 + j] = p;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kChiItems; ++j) {
+            const int i = j * kChiThreads + tid;
+            if (t0 + i < K) chi[t0 + i] = st[i + (i >> 4)];
+        }
+        __syncthreads();
+    }
+}
+
+size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// scratch of P top bytes and up to n values
+struct Layout {
+    size_t bits, ord, blk, total, base, sums, bytes;
+    int words, tiles;
+};
+Layout layout(int present, int64_t n) {
+    Layout L{};
+    L.words = present * kWordsPerByte;
+    L.tiles = L.words / kTileWords;
+    const size_t all = up256((size_t)L.words * kBuckets * 4);
+    L.bits = 0;
+    L.ord = all;
+    L.blk = 2 * all;
+    L.total = L.blk + up256((size_t)L.tiles * kTileBlocks * 4);
+    L.base = L.total + up256((size_t)L.tiles * 4);
+    L.sums = L.base + up256((size_t)(L.tiles + 1) * 4);
+    L.bytes = L.sums + up256((size_t)((n + kChiTile - 1) / kChiTile) * 8);
+    return L;
+}
+
+}  // namespace
+
+size_t distinct_scratch_bytes(int present, int64_t n) { return layout(present, n).bytes; }
+
+int launch_distinct_curve(const float *img, int64_t n, int present, const uint32_t *offsets, const uint32_t *mask,
+                          uint32_t *idx, void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
+                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream) {
+    static_assert(kTile == kKeyTile && kBuckets == kKeyDigits, "the tiles and digits of the counts");
+    if (present < 1 || present > kMaxDistinctBytes || n < 1 || n >= ((int64_t)1 << 30)) {
+        set_error("internal error: %d top bytes, %lld values", present, (long long)n);
+        return ECC_E_ARG;
+    }
+    const Layout L = layout(present, n);
+    uint8_t *b = (uint8_t *)scratch;
+    uint32_t *bits = (uint32_t *)(b + L.bits), *ord = (uint32_t *)(b + L.ord), *blk = (uint32_t *)(b + L.blk);
+    uint32_t *total = (uint32_t *)(b + L.total), *base = (uint32_t *)(b + L.base);
+    int64_t *sums = (int64_t *)(b + L.sums);
+    const int64_t tiles = (n + kTile - 1) / kTile;
+    hipLaunchKernelGGL(bucket_scatter_kernel, dim3((unsigned)tiles), dim3(kThreads), 0, stream, img, n, tiles, offsets,
+                       mask, idx);
+    ECC_HIP(hipGetLastError());
+    int rc = launch_zero(bits, (size_t)L.words * kBuckets * 4, stream);
+    if (rc) return rc;
+    // evenly filled buckets are one share each (a fifth above the mean)
+    const int64_t share = std::max<int64_t>(4096, n / kBuckets + n / kBuckets / 5);
+    const int64_t grid = kBuckets + n / share;
+    hipLaunchKernelGGL(bucket_bits_kernel, dim3((unsigned)grid), dim3(kThreads), (size_t)L.words * 4, stream,
+                       (const uint32_t *)idx, n, tiles, offsets, (uint32_t)share, L.words, bits);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(order_bits_kernel, dim3((unsigned)L.tiles), dim3(256), 0, stream, (const uint32_t *)bits, L.words,
+                       ord, blk, total);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(tile_base_kernel, dim3(1), dim3(1024), 0, stream, (const uint32_t *)total, L.tiles, base, count);
+    ECC_HIP(hipGetLastError());
+    constexpr int parts = 4;
+    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)(L.tiles * parts)), dim3(64 * kExpandWaves), 0, stream,
+                       (const uint32_t *)ord, (const uint32_t *)blk, (const uint32_t *)base, mask, parts, out_keys,
+                       out_chi);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(add_records_kernel, dim3((unsigned)std::min<int64_t>((regions + 3) / 4, 8192)), dim3(256), 0, stream,
+                       nz, nz_cnt, regions, region_slots, (const uint32_t *)ord, (const uint32_t *)blk,
+                       (const uint32_t *)base, mask, out_chi);
+    ECC_HIP(hipGetLastError());
+    // (K is at most n)
+    const unsigned cg = (unsigned)std::min<int64_t>((n + kChiTile - 1) / kChiTile, 4096);
+    hipLaunchKernelGGL(chi_sums_kernel, dim3(cg), dim3(kChiThreads), 0, stream, (const int64_t *)out_chi,
+                       (const int64_t *)count, sums);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(chi_scan_kernel, dim3(1), dim3(1024), 0, stream, (const int64_t *)count, sums);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(chi_prefix_kernel, dim3(cg), dim3(kChiThreads), 0, stream, out_chi, (const int64_t *)count,
+                       (const int64_t *)sums);
+    ECC_HIP(hipGetLastError());
+    return ECC_OK;
+}
+
+}  // namespace ecc

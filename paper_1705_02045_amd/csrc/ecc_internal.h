@@ -116,6 +116,8 @@ struct Workspace {
     size_t fbuf_bytes = 0;
     void *frec = nullptr;        // float path: the dense records (two buffers) and their prefix
     size_t frec_bytes = 0;
+    void *fbits = nullptr;       // float path: the bits of the distinct values
+    size_t fbits_bytes = 0;
     void *dual_buf = nullptr;    // dual complex: gathered faces of the box, per-face curves
     size_t dual_buf_bytes = 0;
     int64_t *vcec16 = nullptr;   // [65536] changes vector of a 16-bit image (window passes)
@@ -284,15 +286,28 @@ int launch_nz_compact(const uint64_t *nz, const uint32_t *nz_cnt, const uint32_t
 int64_t radix_tiles(int64_t n, int elem);
 int64_t radix_scan_tiles(int64_t entries);
 // Digit-table entries of a sort of n words of elem bytes (digits of up to
-// 10 bits for keys, 8 for records); sums: radix_scan_tiles of that.
+// 9 bits for keys, 8 for records); sums: radix_scan_tiles of that.
 int64_t radix_count_entries(int64_t n, int elem);
-// Sorts the keys of the n floats of img; on return key[0] is the sorted buffer
-// and key[1] the other (the two may be swapped).  A NaN sets kStatusNaN.  mask_dev: 8 device words; mask_host /
-// mask_host_dev: 8 words of host-mapped memory, host and device views.
-// Synchronizes on an event recorded early in the sort (the host reads which
-// top bytes occur to choose the last passes).
-int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
-                    volatile uint32_t *mask_host, uint32_t *mask_host_dev, uint32_t *status, hipStream_t stream);
+// The first pass over the keys of the n floats of img: their digit counts
+// (bits 0-8) per tile of kKeyTile, scanned to output positions in counts
+// (digit-major), and the mask of the top bytes that occur: mask_dev (8 device
+// words) and, complete at the event `noted`, mask_host_dev (the device's view
+// of 8 words of host memory).  A NaN sets kStatusNaN.
+constexpr int64_t kKeyTile = 8192;
+constexpr int kKeyDigits = 512;
+int radix_key_counts(const float *img, int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
+                     uint32_t *mask_host_dev, uint32_t *status, hipEvent_t noted, hipStream_t stream);
+// The rest of the sort into key[0], after radix_key_counts.
+int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
+// The distinct values and the curve at them (ecc_distinct.hip), for images
+// whose keys hold at most kMaxDistinctBytes top bytes; offsets and mask from
+// radix_key_counts, idx: n words, scratch: distinct_scratch_bytes.  Their
+// number goes to *count (device memory).
+constexpr int kMaxDistinctBytes = 32;
+size_t distinct_scratch_bytes(int present, int64_t n);
+int launch_distinct_curve(const float *img, int64_t n, int present, const uint32_t *offsets, const uint32_t *mask,
+                          uint32_t *idx, void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
+                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream);
 // Sorts rec[0] in place (an even number of passes).
 int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
 int64_t float_tiles(int64_t n);

@@ -3,14 +3,11 @@
 // float image, and of the voxels' non-zero (key, change) records, 64-bit
 // words with the key in the high half, sorted on that half.
 //
-// The records take four passes of 8-bit digits.  The keys take 9-bit
-// digits on bits 0-8 and 9-17, then, when the keys hold at most 16 distinct
-// top bytes (sign and high exponent bits: a float image whose values span a
-// few dozen binades), one pass on bits 18-23 joined to the rank of the key's
-// top byte among those present (3 or 4 bits; the rank is monotone in the
-// byte, so the order is the keys' own), else two 7-bit passes on bits 18-24
-// and 25-31.  The first count pass notes which top bytes occur; the host
-// reads that note while the first two passes run and chooses the rest.
+// The records take four passes of 8-bit digits, the keys two of 9 bits and
+// two of 7.  The keys are only sorted when they hold more than
+// kMaxDistinctBytes top bytes (sign and high exponent bits): the first count
+// pass notes which occur, and with fewer the distinct values are found from
+// its counts without sorting (ecc_distinct.hip).
 //
 // A workgroup owns a tile of kTile consecutive keys.  A pass:
 //  1. radix_count_kernel: digit counts per (digit, tile), digit-major;
@@ -39,38 +36,9 @@ struct SortTile {
     static constexpr int64_t kTile = (int64_t)kSortThreads * kItems;
 };
 
-// The digit of a key: BITS bits from `shift`, or (REMAP, 32-bit keys only)
-// bits 18-23 below the rank of the top byte (rank: a 256-entry LDS table;
-// the host takes REMAP passes only when every rank fits in BITS - 6 bits).
-constexpr int kRemapShift = 18;
-constexpr int kRemapLow = 6;
-
-template <typename T, int BITS, bool REMAP>
-__device__ __forceinline__ uint32_t digit_of(T r, int shift, const uint8_t *rank) {
-    if constexpr (REMAP) {
-        static_assert(sizeof(T) == 4 && BITS > kRemapLow, "32-bit keys; the rank takes the digit's high bits");
-        return (((uint32_t)r >> kRemapShift) & ((1u << kRemapLow) - 1u)) | ((uint32_t)rank[(uint32_t)r >> 24] << kRemapLow);
-    } else {
-        return (uint32_t)(r >> shift) & ((1u << BITS) - 1u);
-    }
-}
-
-// The rank table of REMAP passes from the top-byte presence mask (8 words,
-// bit b of word w: byte 32 w + b occurs): rank[t] = present bytes below t.
-// Byte 255, when absent, takes the largest rank of a BITS-bit digit, so that
-// the all-ones keys that pad the last tile take the largest digit.  Called
-// by every thread; ends with a barrier.
-template <int BITS>
-__device__ __forceinline__ void build_rank(const uint32_t *__restrict__ mask, uint8_t *rank) {
-    const int t = threadIdx.x;
-    if (t < 256) {
-        uint32_t c = 0;
-        for (int w = 0; w < (t >> 5); ++w) c += (uint32_t)__builtin_popcount(mask[w]);
-        c += (uint32_t)__builtin_popcount(mask[t >> 5] & ((1u << (t & 31)) - 1u));
-        if (t == 255 && (mask[7] >> 31) == 0u) c = (1u << (BITS - kRemapLow)) - 1u;
-        rank[t] = (uint8_t)c;
-    }
-    __syncthreads();
+template <typename T, int BITS>
+__device__ __forceinline__ uint32_t digit_of(T r, int shift) {
+    return (uint32_t)(r >> shift) & ((1u << BITS) - 1u);
 }
 
 // A count workgroup takes tpw <= kCountTiles consecutive tiles, so that its
@@ -82,7 +50,7 @@ constexpr int kCountTiles = 16;
 // MASK (the first pass over 32-bit keys): the words are the image's floats,
 // mapped to keys as they are loaded; also ORs the presence of each key's top
 // byte into mask (8 words, zero before the launch) and reports a NaN.
-template <typename T, int BITS, bool AGG, bool REMAP, bool MASK>
+template <typename T, int BITS, bool AGG, bool MASK>
 __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__restrict__ rec, int64_t n,
                                                                    int shift, int64_t tiles, int tpw,
                                                                    uint32_t *__restrict__ counts,
@@ -92,13 +60,11 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
     constexpr int kDig = 1 << BITS;
     static_assert(!MASK || sizeof(T) == 4, "top bytes of 32-bit keys");
     __shared__ uint32_t cnt[kCountTiles][kDig + 1];  // (padded: the final transpose reads a column)
-    __shared__ uint8_t rank[REMAP ? 256 : 1];
     __shared__ uint8_t present[MASK ? 256 : 1];  // MASK: top bytes seen
     const int tid = threadIdx.x;
     for (int i = tid; i < kCountTiles * (kDig + 1); i += kSortThreads) (&cnt[0][0])[i] = 0;
     if (MASK && tid < 256) present[tid] = 0;
-    if constexpr (REMAP) build_rank<BITS>(mask, rank);  // (its barrier also orders the clearing)
-    else __syncthreads();
+    __syncthreads();
     const int lane = tid & (kWave - 1);
     const int64_t tb = (int64_t)blockIdx.x * tpw;
     uint32_t last = 256u;  // MASK: the top byte this thread noted last
@@ -126,7 +92,7 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = t0 + (int64_t)j * kSortThreads + tid;
             const bool ok = i < n;
-            const uint32_t d = digit_of<T, BITS, REMAP>(r[j], shift, rank);
+            const uint32_t d = digit_of<T, BITS>(r[j], shift);
             if constexpr (MASK) {
                 const uint32_t top = (uint32_t)r[j] >> 24;
                 if (ok && top != last) {
@@ -163,24 +129,23 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
 }
 
 // The presence mask, copied to host-mapped memory (read by the host after an
-// event, to choose the remaining passes).
+// event, to choose between the bits of the values and the sort).
 __global__ void mask_publish_kernel(const uint32_t *__restrict__ mask, uint32_t *host) {
     if (threadIdx.x < 8) host[threadIdx.x] = mask[threadIdx.x];
 }
 
 // FIRST: the words are the image's floats, mapped to keys as they are loaded.
-template <typename T, int BITS, bool REMAP, bool FIRST = false>
+template <typename T, int BITS, bool FIRST = false>
 __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8))) radix_scatter_kernel(const T *__restrict__ in, int64_t n,
                                                                      int shift, int64_t tiles,
                                                                      const uint32_t *__restrict__ offsets,
-                                                                     const uint32_t *__restrict__ mask,
                                                                      T *__restrict__ out) {
     constexpr int kItems = SortTile<T>::kItems;
     constexpr int64_t kTile = SortTile<T>::kTile;
     constexpr int kChunk = kItems * kWave;       // keys of one wave, consecutive
     constexpr int kDig = 1 << BITS;
     constexpr int kPer = kDig / kWave;           // digits per lane in the scan of the totals
-    static_assert(BITS >= 1 && BITS <= 10, "digits of at most 10 bits (LDS rows of 1024 counts per wave)");
+    static_assert(BITS >= 1 && BITS <= 9, "digits of at most 9 bits (LDS rows of 512 counts per wave)");
     static_assert(kDig <= kSortThreads, "one thread per digit");
     __shared__ T buf[kTile];                     // the tile reordered by digit
     // per wave: digit counts, then the wave's offset per digit (16-bit: a
@@ -188,7 +153,6 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
     __shared__ __attribute__((aligned(16))) uint16_t wcnt[kSortWaves][kDig];
     __shared__ uint32_t start[kDig];             // digit totals, then the first slot of each digit
     __shared__ uint32_t dest[kDig];              // per digit: output position minus first slot
-    __shared__ uint8_t rank_t[REMAP ? 256 : 1];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     // neighbouring tiles on one XCD: they read neighbouring words of the
     // offset table and write neighbouring ends of each digit's runs
@@ -198,7 +162,6 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
     const uint32_t gpos = tid < kDig ? offsets[(int64_t)tid * tiles + tile] : 0u;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) wcnt[wave][lane * kPer + q] = 0;  // the wave's own row
-    if constexpr (REMAP) build_rank<BITS>(mask, rank_t);
 
     // wave w ranks keys t0 + w*kChunk + j*64 + lane (j = 0..kItems-1), in
     // that order: tile order, so the ranking is stable
@@ -207,8 +170,8 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
     const int64_t wb = t0 + (int64_t)wave * kChunk;
     // (a full tile, every tile but the last: loads and stores without bounds
     // checks; in the last tile the keys past the end are all ones, whose
-    // digit is the largest (for REMAP through the rank of byte 255), so that
-    // they rank last in the tile and are never written)
+    // digit is the largest, so that they rank last in the tile and are never
+    // written)
     const bool full = t0 + kTile <= n;
     if (full) {
 #pragma unroll
@@ -224,7 +187,7 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
             if constexpr (FIRST) r[j] = i < n ? f32_key(r[j]) : ~T(0);
         }
     }
-    auto digit = [&](int j) -> uint32_t { return digit_of<T, BITS, REMAP>(r[j], shift, rank_t); };
+    auto digit = [&](int j) -> uint32_t { return digit_of<T, BITS>(r[j], shift); };
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
         const uint32_t d = digit(j);
@@ -306,7 +269,7 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
         for (int j = 0; j < kItems; ++j) {
             const int s = j * kSortThreads + tid;
             const T v = buf[s];
-            out[dest[digit_of<T, BITS, REMAP>(v, shift, rank_t)] + (uint32_t)s] = v;
+            out[dest[digit_of<T, BITS>(v, shift)] + (uint32_t)s] = v;
         }
         return;
     }
@@ -316,7 +279,7 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
         const int s = j * kSortThreads + tid;
         if (s < valid) {
             const T v = buf[s];
-            const uint32_t d = digit_of<T, BITS, REMAP>(v, shift, rank_t);
+            const uint32_t d = digit_of<T, BITS>(v, shift);
             out[dest[d] + (uint32_t)s] = v;
         }
     }
@@ -450,23 +413,25 @@ int64_t radix_tiles(int64_t n, int elem) {
     return (n + t - 1) / t;
 }
 int64_t radix_scan_tiles(int64_t entries) { return (entries + kScanTile - 1) / kScanTile; }
-int64_t radix_count_entries(int64_t n, int elem) { return (elem == 4 ? 1024 : 256) * radix_tiles(n, elem); }
+int64_t radix_count_entries(int64_t n, int elem) { return (elem == 4 ? kKeyDigits : 256) * radix_tiles(n, elem); }
+
+static int count_tiles_per_wg(int64_t tiles) {
+    return (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
+}
 
 // One pass: counts, their scan, the scatter from v[*cur] to the other buffer.
-template <typename T, int BITS, bool AGG, bool REMAP>
-static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts, uint32_t *sums, uint32_t *mask,
-                      hipStream_t stream) {
+template <typename T, int BITS, bool AGG>
+static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
     const int64_t tiles = radix_tiles(n, (int)sizeof(T));
-    const int tpw = (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
+    const int tpw = count_tiles_per_wg(tiles);
     const unsigned cgrid = (unsigned)((tiles + tpw - 1) / tpw);
-    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG, REMAP, false>), dim3(cgrid), dim3(kSortThreads), 0, stream,
-                       (const T *)v[*cur], n, shift, tiles, tpw, counts, mask, (uint32_t *)nullptr);
+    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG, false>), dim3(cgrid), dim3(kSortThreads), 0, stream,
+                       (const T *)v[*cur], n, shift, tiles, tpw, counts, (uint32_t *)nullptr, (uint32_t *)nullptr);
     ECC_HIP(hipGetLastError());
     int rc = exclusive_scan_u32(counts, ((int64_t)1 << BITS) * tiles, sums, stream);
     if (rc) return rc;
-    hipLaunchKernelGGL((radix_scatter_kernel<T, BITS, REMAP>), dim3((unsigned)tiles), dim3(kSortThreads), 0, stream,
-                       (const T *)v[*cur], n, shift, tiles, (const uint32_t *)counts, (const uint32_t *)mask,
-                       v[*cur ^ 1]);
+    hipLaunchKernelGGL((radix_scatter_kernel<T, BITS>), dim3((unsigned)tiles), dim3(kSortThreads), 0, stream,
+                       (const T *)v[*cur], n, shift, tiles, (const uint32_t *)counts, v[*cur ^ 1]);
     ECC_HIP(hipGetLastError());
     *cur ^= 1;
     return ECC_OK;
@@ -480,54 +445,35 @@ static int check_count(int64_t n) {
     return ECC_OK;
 }
 
-int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums,
-                    uint32_t *mask_dev, volatile uint32_t *mask_host, uint32_t *mask_host_dev, uint32_t *status,
-                    hipStream_t stream) {
+int radix_key_counts(const float *img, int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
+                     uint32_t *mask_host_dev, uint32_t *status, hipEvent_t noted, hipStream_t stream) {
+    static_assert(SortTile<uint32_t>::kTile == kKeyTile && kKeyDigits == 512, "9-bit digits of the keys' tiles");
     int rc = check_count(n);
     if (rc) return rc;
-    int cur = 0;
-    // pass 1 notes the top bytes; the host reads them while passes 1 and 2 run
     rc = launch_zero(mask_dev, 32, stream);
     if (rc) return rc;
     const int64_t tiles = radix_tiles(n, 4);
-    const int tpw = (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
-    hipLaunchKernelGGL((radix_count_kernel<uint32_t, 9, false, false, true>), dim3((unsigned)((tiles + tpw - 1) / tpw)),
+    const int tpw = count_tiles_per_wg(tiles);
+    hipLaunchKernelGGL((radix_count_kernel<uint32_t, 9, false, true>), dim3((unsigned)((tiles + tpw - 1) / tpw)),
                        dim3(kSortThreads), 0, stream, (const uint32_t *)img, n, 0, tiles, tpw, counts, mask_dev, status);
     ECC_HIP(hipGetLastError());
     hipLaunchKernelGGL(mask_publish_kernel, dim3(1), dim3(64), 0, stream, (const uint32_t *)mask_dev, mask_host_dev);
     ECC_HIP(hipGetLastError());
-    hipEvent_t noted = nullptr;
-    ECC_HIP(hipEventCreateWithFlags(&noted, hipEventDisableTiming));
-    hipError_t e = hipEventRecord(noted, stream);
-    if (e == hipSuccess) {
-        rc = exclusive_scan_u32(counts, 512 * tiles, sums, stream);
-        if (!rc) {
-            hipLaunchKernelGGL((radix_scatter_kernel<uint32_t, 9, false, true>), dim3((unsigned)tiles), dim3(kSortThreads), 0,
-                               stream, (const uint32_t *)img, n, 0, tiles, (const uint32_t *)counts,
-                               (const uint32_t *)mask_dev, key[1]);
-            e = hipGetLastError();
-            cur = 1;
-        }
-        if (!rc && e == hipSuccess) rc = radix_pass<uint32_t, 9, false, false>(key, &cur, n, 9, counts, sums, mask_dev, stream);
-        const hipError_t w = hipEventSynchronize(noted);
-        if (e == hipSuccess) e = w;
-    }
-    (void)hipEventDestroy(noted);
-    ECC_HIP(e);
-    if (rc) return rc;
-    int present = 0;
-    for (int w = 0; w < 8; ++w) present += __builtin_popcount(mask_host[w]);
-    if (present <= 8) {  // ranks in 3 bits: a 9-bit digit
-        rc = radix_pass<uint32_t, 9, false, true>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
-    } else if (present <= 16) {  // ranks in 4 bits: a 10-bit digit
-        rc = radix_pass<uint32_t, 10, false, true>(key, &cur, n, kRemapShift, counts, sums, mask_dev, stream);
-    } else {  // bits 18-24 and 25-31 (sign and high exponent bits: a handful of values)
-        rc = radix_pass<uint32_t, 7, false, false>(key, &cur, n, 18, counts, sums, mask_dev, stream);
-        if (!rc) rc = radix_pass<uint32_t, 7, true, false>(key, &cur, n, 25, counts, sums, mask_dev, stream);
-    }
-    if (rc) return rc;
-    if (cur == 1) std::swap(key[0], key[1]);
-    return ECC_OK;
+    ECC_HIP(hipEventRecord(noted, stream));
+    return exclusive_scan_u32(counts, (int64_t)kKeyDigits * tiles, sums, stream);
+}
+
+int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
+    const int64_t tiles = radix_tiles(n, 4);
+    hipLaunchKernelGGL((radix_scatter_kernel<uint32_t, 9, true>), dim3((unsigned)tiles), dim3(kSortThreads), 0, stream,
+                       (const uint32_t *)img, n, 0, tiles, (const uint32_t *)counts, key[1]);
+    ECC_HIP(hipGetLastError());
+    int cur = 1;
+    int rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 9, counts, sums, stream);
+    if (!rc) rc = radix_pass<uint32_t, 7, false>(key, &cur, n, 18, counts, sums, stream);
+    // (bits 25-31: sign and high exponent bits, a handful of values)
+    if (!rc) rc = radix_pass<uint32_t, 7, true>(key, &cur, n, 25, counts, sums, stream);
+    return rc;
 }
 
 // Four passes of 8-bit digits on the key half.
@@ -536,10 +482,8 @@ int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *
     int rc = check_count(n);
     int cur = 0;
     for (int pass = 0; pass < 4 && !rc; ++pass) {
-        if (pass == 3)
-            rc = radix_pass<uint64_t, 8, true, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
-        else
-            rc = radix_pass<uint64_t, 8, false, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, nullptr, stream);
+        if (pass == 3) rc = radix_pass<uint64_t, 8, true>(rec, &cur, n, 32 + 8 * pass, counts, sums, stream);
+        else rc = radix_pass<uint64_t, 8, false>(rec, &cur, n, 32 + 8 * pass, counts, sums, stream);
     }
     return rc;
 }
