@@ -168,7 +168,7 @@ int ecc_compute_async(const void *image_dev, const ecc_dims *dims, ecc_dtype dty
 /* For callers that cannot allocate (work under HIP graph capture, serving
  * loops or harnesses that forbid hipMalloc): ecc_compute_async with every
  * scratch buffer in one statically sized device array of the library
- * (68.6 MiB per GPU, held by each GPU the library runs on until the process
+ * (64.6 MiB per GPU, held by each GPU the library runs on until the process
  * ends) instead of a workspace.  Arguments, results and errors as
  * ecc_compute_async; it allocates no memory, host or device.  A launch uses
  * at most 1024 workgroups (larger images give each workgroup more tiles), so

@@ -389,11 +389,9 @@ static int enqueue_int(const void *image_dev, const IntView &v, int dtype, int64
     job.hi_inf = 1;
     job.dtype = dtype;
     job.invert = max_entry ? 1 : 0;
-    rc = ws_ensure(ws, (void **)&ws->stage, &ws->stage_bytes, (size_t)merge_stage_rows(tl.grid) * m * sizeof(int64_t));
-    if (rc) return rc;
     rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
     if (rc) return rc;
-    return launch_merge(ws->partial, tl.grid, m, ws->stage, ws->vcec, false, true, chi_dev, ws->status, status_out,
+    return launch_merge(ws->partial, tl.grid, m, ws->vcec, false, true, chi_dev, ws->status, status_out,
                         stream, max_entry);
 }
 
@@ -450,9 +448,6 @@ static int enqueue_u16_passes(const void *image_dev, const IntView &v, int64_t *
     const IntTiling tl = range_pass_tiling(v, v.n0);
     int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * mpass * sizeof(int32_t));
     if (rc) return rc;
-    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes,
-                      (size_t)merge_stage_rows(tl.grid) * mpass * sizeof(int64_t));
-    if (rc) return rc;
     rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)mtot * sizeof(int64_t));
     if (rc) return rc;
     if (npass == 1) {  // the bins outside the pass stay zero
@@ -474,11 +469,11 @@ static int enqueue_u16_passes(const void *image_dev, const IntView &v, int64_t *
         job.win_shift = lo[i];
         rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
         if (rc) return rc;
-        rc = launch_merge(ws->partial, tl.grid, mpass, ws->stage, ws->vcec16 + lo[i], false, false, nullptr,
+        rc = launch_merge(ws->partial, tl.grid, mpass, ws->vcec16 + lo[i], false, false, nullptr,
                           ws->status, nullptr, stream);
         if (rc) return rc;
     }
-    return launch_merge(nullptr, 0, mtot, nullptr, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
+    return launch_merge(nullptr, 0, mtot, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
 }
 
 // The synchronous call's 16-bit path: the pass over [0, 32768) first, which
@@ -493,9 +488,6 @@ static int enqueue_u16_adaptive(const void *image_dev, const IntView &v, int64_t
     constexpr int mpass = 32768, mtot = 65536;
     const IntTiling tl = range_pass_tiling(v, v.n0);
     int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * mpass * sizeof(int32_t));
-    if (rc) return rc;
-    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes,
-                      (size_t)merge_stage_rows(tl.grid) * mpass * sizeof(int64_t));
     if (rc) return rc;
     rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)mtot * sizeof(int64_t));
     if (rc) return rc;
@@ -519,7 +511,7 @@ static int enqueue_u16_adaptive(const void *image_dev, const IntView &v, int64_t
         job.high_flag = i == 0 ? ws->host_status_dev + 1 : nullptr;
         rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
         if (rc) return rc;
-        rc = launch_merge(ws->partial, tl.grid, mpass, ws->stage, ws->vcec16 + i * mpass, false, false, nullptr,
+        rc = launch_merge(ws->partial, tl.grid, mpass, ws->vcec16 + i * mpass, false, false, nullptr,
                           ws->status, nullptr, stream);
         if (rc) return rc;
         if (i == 0) {
@@ -527,7 +519,7 @@ static int enqueue_u16_adaptive(const void *image_dev, const IntView &v, int64_t
             if (*high == 0u) break;
         }
     }
-    return launch_merge(nullptr, 0, mtot, nullptr, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
+    return launch_merge(nullptr, 0, mtot, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
 }
 
 // Planned from a known range (the entry point that allocates nothing, whose
@@ -548,9 +540,6 @@ static int enqueue_u16(const void *image_dev, const IntView &v, int64_t *chi_dev
     if (rc) return rc;
     rc = ws_ensure(ws, (void **)&ws->vcec, &ws->vcec_bytes, (size_t)mloc * sizeof(int64_t));
     if (rc) return rc;
-    rc = ws_ensure(ws, (void **)&ws->stage, &ws->stage_bytes,
-                   (size_t)merge_stage_rows(tl.grid) * mloc * sizeof(int64_t));
-    if (rc) return rc;
     rc = ws_ensure(ws, (void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)mtot * sizeof(int64_t));
     if (rc) return rc;
     rc = launch_zero(ws->vcec16, (size_t)mtot * sizeof(int64_t), stream);
@@ -569,14 +558,14 @@ static int enqueue_u16(const void *image_dev, const IntView &v, int64_t *chi_dev
         job.win_shift = win[i].shift;
         rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
         if (rc) return rc;
-        rc = launch_merge(ws->partial, tl.grid, mloc, ws->stage, ws->vcec, false, false, nullptr, ws->status,
+        rc = launch_merge(ws->partial, tl.grid, mloc, ws->vcec, false, false, nullptr, ws->status,
                           nullptr, stream);
         if (rc) return rc;
         ECC_HIP(hipMemcpyAsync(ws->vcec16 + win[i].shift + win[i].klo, ws->vcec + win[i].klo,
                                (size_t)(win[i].khi - win[i].klo + 1) * sizeof(int64_t), hipMemcpyDeviceToDevice,
                                stream));
     }
-    return launch_merge(nullptr, 0, mtot, nullptr, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
+    return launch_merge(nullptr, 0, mtot, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
 }
 
 int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, uint32_t *status_out,
@@ -602,9 +591,6 @@ static int enqueue_int_changes(const void *image_dev, const IntView &v, int dtyp
     IntTiling tl = choose_int_tiling(v, dtype, v.n0);
     int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * m * sizeof(int32_t));
     if (rc) return rc;
-    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes,
-                      (size_t)merge_stage_rows(tl.grid) * m * sizeof(int64_t));
-    if (rc) return rc;
     IntJob job{};
     job.src.base = (const uint8_t *)image_dev;
     job.src.lo_base = job.src.base;
@@ -618,7 +604,7 @@ static int enqueue_int_changes(const void *image_dev, const IntView &v, int dtyp
     job.invert = max_entry ? 1 : 0;
     rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
     if (rc) return rc;
-    return launch_merge(ws->partial, tl.grid, m, ws->stage, vcec_out, false, false, nullptr, ws->status, nullptr,
+    return launch_merge(ws->partial, tl.grid, m, vcec_out, false, false, nullptr, ws->status, nullptr,
                         stream, max_entry);
 }
 
@@ -680,23 +666,21 @@ static int enqueue_four_d(const ChangeJob &job, bool max_entry, int64_t *chi_dev
         if (rc) return rc;
         rc = launch_change_counts(job, nullptr, ws->vcec16, ws->status, s);
         if (rc) return rc;
-        return launch_merge(nullptr, 0, m, nullptr, ws->vcec16, true, true, chi_dev, ws->status, status_out, s);
+        return launch_merge(nullptr, 0, m, ws->vcec16, true, true, chi_dev, ws->status, status_out, s);
     }
     int rows = 0;
     int rc = change_count_rows(job, &rows);
     if (rc) return rc;
     rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)rows * m * sizeof(int32_t));
     if (rc) return rc;
-    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes, (size_t)merge_stage_rows(rows) * m * sizeof(int64_t));
-    if (rc) return rc;
     rc = ensure_bytes((void **)&ws->vcec, &ws->vcec_bytes, (size_t)m * sizeof(int64_t));
     if (rc) return rc;
     rc = launch_change_counts(job, ws->partial, nullptr, ws->status, s);
     if (rc) return rc;
     if (changes_out)
-        return launch_merge(ws->partial, rows, m, ws->stage, changes_out, false, false, nullptr, ws->status, nullptr, s,
+        return launch_merge(ws->partial, rows, m, changes_out, false, false, nullptr, ws->status, nullptr, s,
                             max_entry);
-    return launch_merge(ws->partial, rows, m, ws->stage, ws->vcec, false, true, chi_dev, ws->status, status_out, s,
+    return launch_merge(ws->partial, rows, m, ws->vcec, false, true, chi_dev, ws->status, status_out, s,
                         max_entry);
 }
 
@@ -1185,16 +1169,13 @@ int ecc_autotune(const void *image_dev, const ecc_dims *dims, ecc_dtype dtype, v
                 cands.push_back(x);
                 if (!rc) rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes,
                                            (size_t)x.tl.grid * m * sizeof(int32_t));
-                if (!rc)
-                    rc = ensure_bytes((void **)&ws->stage, &ws->stage_bytes,
-                                      (size_t)merge_stage_rows(x.tl.grid) * m * sizeof(int64_t));
             }
     for (int round = 0; round < 4 && !rc; ++round)
         for (Cand &x : cands) {
             if ((e = hipEventRecord(ev[0], s)) != hipSuccess) rc = hip_fail(e, "ecc_autotune: event");
             if (!rc) rc = launch_int_partial(job, x.tl, ws->partial, ws->status, nullptr, s);
             if (!rc)
-                rc = launch_merge(ws->partial, x.tl.grid, m, ws->stage, ws->vcec, false, false, nullptr, ws->status,
+                rc = launch_merge(ws->partial, x.tl.grid, m, ws->vcec, false, false, nullptr, ws->status,
                                   nullptr, s);
             if (!rc && (e = hipEventRecord(ev[1], s)) != hipSuccess) rc = hip_fail(e, "ecc_autotune: event");
             if (!rc && (e = hipEventSynchronize(ev[1])) != hipSuccess) rc = hip_fail(e, "ecc_autotune: sync");
@@ -1292,8 +1273,6 @@ int ecc_release_workspaces(void) {
         w->partial = nullptr;
         drop(w->vcec, &w->vcec_bytes);
         w->vcec = nullptr;
-        drop(w->stage, &w->stage_bytes);
-        w->stage = nullptr;
         drop(w->chi_tmp, &w->chi_tmp_bytes);
         w->chi_tmp = nullptr;
         drop(w->img_tmp, &w->img_tmp_bytes);
@@ -1625,7 +1604,7 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
     // face launch (all read the image's values) is reported and cleared here
     int64_t *chi_dev = curves;
     *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
-    rc = launch_merge(nullptr, 0, (int)m, nullptr, result, true, true, chi_dev, ws->status, ws->host_status_dev, s);
+    rc = launch_merge(nullptr, 0, (int)m, result, true, true, chi_dev, ws->status, ws->host_status_dev, s);
     if (rc) {
         (void)hipStreamSynchronize(s);
         return rc;

@@ -14,12 +14,13 @@ namespace ecc {
 constexpr int kWave = 64;
 constexpr uint32_t kStatusRange = ECC_STATUS_RANGE_BIT;
 constexpr uint32_t kStatusNaN = 2u;  // a float image holds a NaN
-// Device status block (1024 bytes per workspace or stream): word 0 status,
-// word 1 its copy taken by the scan, word 2 the copy handed to the host,
-// words 8-9 a value range, bytes [kStatusTotalsOffset, +512) the scan's
-// group totals.
-constexpr size_t kStatusBytes = 1024;
+// Device status block (one per workspace or stream): word 0 status, word 1
+// its copy taken for the scan, word 2 the copy handed to the host, word 4 the
+// scan's count of workgroups (zero between launches), words 8-9 a value
+// range, from byte kStatusTotalsOffset on the totals of up to 1024 blocks of
+// 64 columns.
 constexpr size_t kStatusTotalsOffset = 128;
+constexpr size_t kStatusBytes = kStatusTotalsOffset + 1024 * 8 + 128;
 constexpr size_t kStatusMinMaxOffset = 32;  // two words: minimum and maximum of a 16-bit image
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
@@ -106,8 +107,6 @@ struct Workspace {
     // top-byte mask.  With its device-side address.
     volatile uint32_t *host_status = nullptr;
     uint32_t *host_status_dev = nullptr;
-    int64_t *stage = nullptr;    // merge stage rows
-    size_t stage_bytes = 0;
     int64_t *chi_tmp = nullptr;  // [m] curve staging for host outputs
     size_t chi_tmp_bytes = 0;
     void *img_tmp = nullptr;     // device copy of a host image
@@ -172,14 +171,11 @@ int plan_u16_windows(uint32_t vmin, uint32_t vmax, U16Window *w);
 // the whole value range), the status copied to status_out (may be null).
 int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, uint32_t *status_out,
                     hipStream_t stream);
-// Column sums of the per-workgroup rows into vcec through int64 stage rows
-// ([merge_stage_rows(rows)][m]) and, with do_scan, the prefix sum of vcec into
-// chi (ecc_scan.hip).  The scan copies the status word to status_out (when
-// not null) and clears it.
-int merge_stage_rows(int rows);
-int launch_merge(const int32_t *partial, int rows, int m, int64_t *stage, int64_t *vcec, bool accumulate,
-                 bool do_scan, int64_t *chi, uint32_t *status, uint32_t *status_out, hipStream_t stream,
-                 bool reverse = false);
+// Column sums of the per-workgroup rows into vcec and, with do_scan, the
+// prefix sum of vcec into chi (ecc_scan.hip).  The scan copies the status
+// word to status_out (when not null) and clears it.
+int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
+                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse = false);
 
 // Copies the n0 x n1 x n2 sub-array of src starting at element `base` with
 // element strides s0, s1, s2 into dst (contiguous, C order).

@@ -1,8 +1,8 @@
 // The stream-ordered integer curve without any allocation, for callers that
 // cannot allocate device memory (code under HIP graph capture, serving loops
 // that forbid it).  Its scratch is one statically sized device array per GPU:
-// the status block, the 16-bit changes vector, the changes vector, the merge
-// stage rows and the per-workgroup count rows, in that order.  The launch's
+// the status block, the 16-bit changes vector, the changes vector and the
+// per-workgroup count rows, in that order.  The launch's
 // workgroups are capped at kMaxRows so that its count rows always fit (a
 // larger image gives each workgroup more tiles), so no image the integer
 // path takes needs more than the array holds.
@@ -20,10 +20,8 @@ constexpr size_t up(size_t b) { return (b + kAlign - 1) / kAlign * kAlign; }
 constexpr size_t kOffStatus = 0;
 constexpr size_t kOffVcec16 = kOffStatus + up(kStatusBytes);
 constexpr size_t kOffVcec = kOffVcec16 + up(65536 * sizeof(int64_t));
-constexpr size_t kOffStage = kOffVcec + up(kMaxBins * sizeof(int64_t));
-constexpr size_t kStageRows = 32;        // merge_stage_rows(kMaxRows)
-constexpr size_t kOffPartial = kOffStage + up(kStageRows * kMaxBins * sizeof(int64_t));
-constexpr size_t kScratchBytes = kOffPartial + up((size_t)kMaxRows * kMaxBins * sizeof(int32_t));  // 68.6 MiB
+constexpr size_t kOffPartial = kOffVcec + up(kMaxBins * sizeof(int64_t));
+constexpr size_t kScratchBytes = kOffPartial + up((size_t)kMaxRows * kMaxBins * sizeof(int32_t));  // 64.6 MiB
 
 // Each GPU holds its own copy until the process ends.  Host code never uses
 // this name as an address: the device address comes from
@@ -60,7 +58,6 @@ using namespace ecc;
 extern "C" int ecc_compute_async_noalloc(const void *image_dev, const ecc_dims *dims, ecc_dtype dtype,
                                          int64_t *chi_dev, uint32_t *status_dev, void *stream) {
     g_err_clear();
-    static_assert(kStageRows >= 32, "stage rows of the merge for kMaxRows rows");
     uint8_t *base = nullptr;
     int rc = scratch_for_current_device(&base);
     if (rc) return rc;
@@ -72,16 +69,14 @@ extern "C" int ecc_compute_async_noalloc(const void *image_dev, const ecc_dims *
     ws.vcec16_bytes = 65536 * sizeof(int64_t);
     ws.vcec = (int64_t *)(base + kOffVcec);
     ws.vcec_bytes = kMaxBins * sizeof(int64_t);
-    ws.stage = (int64_t *)(base + kOffStage);
-    ws.stage_bytes = kStageRows * kMaxBins * sizeof(int64_t);
     ws.partial = (int32_t *)(base + kOffPartial);
     ws.partial_bytes = (size_t)kMaxRows * kMaxBins * sizeof(int32_t);
     // The array keeps the last call's contents: the status words start at
     // zero here (a fill kernel; the kernels set bits in them).  Every other
     // region is overwritten before it is read (the count rows by their
-    // workgroups, the stage rows and changes vector by the merge, the 16-bit
+    // workgroups, the changes vector and the totals by the merge, the 16-bit
     // changes vector cleared by its own pass).
-    rc = launch_zero(ws.status, 16, (hipStream_t)stream);
+    rc = launch_zero(ws.status, 32, (hipStream_t)stream);
     if (rc) return rc;
     return compute_async_ws(image_dev, dims, dtype, chi_dev, status_dev, (hipStream_t)stream, &ws);
 }

@@ -26,156 +26,134 @@ int launch_zero(void *p, size_t bytes, hipStream_t stream) {
 }
 
 // Merge of the per-workgroup rows [rows][m] (int32) into the int64 change
-// vector, in kernels that follow each other on the stream (the kernel
-// boundary orders their memory; no fences or counters):
-//  1. colsum_kernel, block (bx, by): rows by, by+BY, ... of columns
-//     bx*1024 .. +1023 (256 threads x 4 columns, 16-byte loads), written to
-//     stage[by][column], or, with BY == 1, straight into vcec;
-//  2. fold_scan_kernel: the BY stage rows of each column into vcec (BY > 1)
-//     and, with do_scan, the prefix sums of column groups of 1024;
-//  3. scan_offsets_kernel (do_scan): adds the totals of the preceding groups;
-//     the curve is written only if the status word is clear, and the status
-//     is copied out and cleared.
-// With `reverse`, colsum_kernel writes column c of the rows at m-1-c (the
-// largest-value convention: the kernel counted at m-1-value).
-// vcec is overwritten, or added to with `accumulate`.
-__global__ void __launch_bounds__(256) colsum_kernel(const int32_t *__restrict__ partial, int rows, int m,
-                                                     int64_t *__restrict__ dst, int accumulate, int reverse) {
-    const int BY = gridDim.y;
-    const int c0 = blockIdx.x * 1024 + threadIdx.x * 4;
-    if (c0 >= m) return;
-    int64_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-    const int4 *p = reinterpret_cast<const int4 *>(partial);
+// vector and its prefix sum, in kernels that follow each other on the stream
+// (the kernel boundary orders their memory):
+//  1. colsum_kernel: a workgroup of 1024 threads sums all rows of 64 columns
+//     (64 rows at a time, 16 threads of 4 columns each: 256-byte runs) into
+//     vcec and, for a scan, their total into totals; it also hands the status
+//     word over to the scan (status[1]) and clears it;
+//  2. scan_kernel: a workgroup scans 1024 columns, from the sum of the totals
+//     before them.
+// Two launches where the sums of some rows at a time, their fold with the
+// scan of 1024 columns and the offsets of those took three of 4 to 5 us each
+// at least (117 rows of 16384 columns: 10.8 -> 8.5 us, a 97 x 130 x 75 call
+// 39.7 -> 38.3 us; 1024 rows: 12.8 + 6.2 + 5.6 -> 13.9 + 5.3 us).
+// With `reverse`, column c of the rows lands at m-1-c (the largest-value
+// convention: the kernel counted at m-1-value).  vcec is overwritten, or added
+// to with `accumulate`.
+constexpr int kColBlock = 64;
+__global__ void __launch_bounds__(1024) colsum_kernel(const int32_t *__restrict__ partial, int rows, int m,
+                                                      int64_t *__restrict__ vcec, int accumulate, int reverse,
+                                                      int64_t *__restrict__ totals, uint32_t *status) {
+    __shared__ int64_t part[16][kColBlock];  // per wave
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (totals != nullptr && blockIdx.x == 0 && tid == 0) {
+        status[1] = status[0];
+        status[0] = 0u;
+    }
+    const int c4 = tid & 15;
     const size_t stride4 = (size_t)m / 4;
-    int r = blockIdx.y;
-    for (; r + 3 * BY < rows; r += 4 * BY) {
+    const int4 *p = reinterpret_cast<const int4 *>(partial) + (size_t)blockIdx.x * (kColBlock / 4) + c4;
+    int64_t v[4] = {0, 0, 0, 0};
+    int r = tid >> 4;
+    for (; r + 3 * 64 < rows; r += 4 * 64) {
         int4 a[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) a[j] = p[(size_t)(r + j * BY) * stride4 + c0 / 4];
+        for (int u = 0; u < 4; ++u) a[u] = p[(size_t)(r + u * 64) * stride4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            s0 += a[j].x;
-            s1 += a[j].y;
-            s2 += a[j].z;
-            s3 += a[j].w;
+        for (int u = 0; u < 4; ++u) {
+            v[0] += a[u].x;
+            v[1] += a[u].y;
+            v[2] += a[u].z;
+            v[3] += a[u].w;
         }
     }
-    for (; r < rows; r += BY) {
-        const int4 a = p[(size_t)r * stride4 + c0 / 4];
-        s0 += a.x;
-        s1 += a.y;
-        s2 += a.z;
-        s3 += a.w;
+    for (; r < rows; r += 64) {
+        const int4 a = p[(size_t)r * stride4];
+        v[0] += a.x;
+        v[1] += a.y;
+        v[2] += a.z;
+        v[3] += a.w;
     }
-    int64_t *row = dst + (size_t)blockIdx.y * m;
-    if (reverse) {  // column c lands at m-1-c
-        int64_t *d = row + (m - 1 - c0);
-        if (accumulate) {
-            s0 += d[0];
-            s1 += d[-1];
-            s2 += d[-2];
-            s3 += d[-3];
-        }
-        d[0] = s0;
-        d[-1] = s1;
-        d[-2] = s2;
-        d[-3] = s3;
-        return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        v[j] += __shfl_xor(v[j], 16, 64);
+        v[j] += __shfl_xor(v[j], 32, 64);
+        if (lane < 16) part[wave][c4 * 4 + j] = v[j];
     }
-    int64_t *d = row + c0;
-    if (accumulate) {
-        s0 += d[0];
-        s1 += d[1];
-        s2 += d[2];
-        s3 += d[3];
-    }
-    d[0] = s0;
-    d[1] = s1;
-    d[2] = s2;
-    d[3] = s3;
+    __syncthreads();
+    if (tid >= kColBlock) return;
+    int64_t s = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += part[w][tid];
+    const int c = blockIdx.x * kColBlock + tid;
+    const int at = reverse ? m - 1 - c : c;
+    if (accumulate) s += vcec[at];
+    vcec[at] = s;
+    if (totals == nullptr) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (tid == 0) totals[reverse ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x] = s;
 }
 
-// Column group bx (1024 columns, 4 per thread): the BY stage rows are folded
-// into vcec (when stage is not null) and, with do_scan and a clear status
-// word, the group's inclusive prefix sum is written to chi and its total to
-// totals[bx].  Block 0 copies the status word to status[1] for the offsets
-// kernel.
-__global__ void __launch_bounds__(256) fold_scan_kernel(const int64_t *__restrict__ stage, int by, int m,
-                                                        int64_t *__restrict__ vcec, int accumulate, int do_scan,
-                                                        int64_t *__restrict__ chi, uint32_t *status,
-                                                        int64_t *__restrict__ totals) {
-    __shared__ int64_t wsum[4];
+// Sum over the workgroup's 1024 threads, in every thread.
+__device__ __forceinline__ int64_t block_sum_1024(int64_t v, int64_t *sh) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int64_t t = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += sh[w];
+    __syncthreads();
+    return t;
+}
+
+// Columns [1024 b, 1024 b + 1024) of the curve.  With totals (at most 1024 of
+// them) the columns before come from those and the status from status[1];
+// without (a changes vector that is complete already), from vcec itself, and
+// the last workgroup to have read the status word clears it (status[4]
+// counts them).  The curve is written only with a clear status.
+__global__ void __launch_bounds__(1024) scan_kernel(const int64_t *__restrict__ vcec, int m,
+                                                    const int64_t *__restrict__ totals, int64_t *__restrict__ chi,
+                                                    uint32_t *status, uint32_t *status_out) {
+    __shared__ int64_t sh[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c0 = blockIdx.x * 1024 + tid * 4;
-    int64_t v[4] = {0, 0, 0, 0};
-    if (c0 < m) {
+    const int c0 = blockIdx.x * 1024;
+    const int64_t v = c0 + tid < m ? vcec[c0 + tid] : 0;
+    const uint32_t stv = totals != nullptr ? status[1] : *(volatile uint32_t *)status;
+    int64_t before = 0;
+    if (totals != nullptr) {
+        if (tid < c0 / kColBlock) before = totals[tid];
+    } else {
+        int c = tid;
+        for (; c + 3 * 1024 < c0; c += 4 * 1024) {
+            int64_t a[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (stage == nullptr || accumulate) ? vcec[c0 + j] : 0;
-        if (stage != nullptr) {
-            // eight rows of loads in flight (by is a power of two, 2..32)
-            int y = 0;
-            for (; y + 8 <= by; y += 8) {
-                int64_t a[8][4];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) a[u][j] = stage[(size_t)(y + u) * m + c0 + j];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] += a[u][j];
-            }
-            for (; y < by; ++y) {
-                const int64_t *st = stage + (size_t)y * m + c0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] += st[j];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) vcec[c0 + j] = v[j];
+            for (int u = 0; u < 4; ++u) a[u] = vcec[c + u * 1024];
+            before += a[0] + a[1] + a[2] + a[3];
         }
+        for (; c < c0; c += 1024) before += vcec[c];
     }
-    if (!do_scan) return;
-    const uint32_t stv = *status;
-    if (blockIdx.x == 0 && tid == 0) status[1] = stv;
-    if (stv != 0) return;
-    // inclusive scan: within the thread, across the wave, across the 4 waves
-    v[1] += v[0];
-    v[2] += v[1];
-    v[3] += v[2];
-    int64_t x = v[3];
+    before = block_sum_1024(before, sh);
+    int64_t x = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int64_t u = __shfl_up(x, off, 64);
         if (lane >= off) x += u;
     }
-    if (lane == 63) wsum[wave] = x;
+    if (lane == 63) sh[wave] = x;
     __syncthreads();
-    int64_t base = x - v[3];
-    for (int w = 0; w < wave; ++w) base += wsum[w];
-    if (c0 < m) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) chi[c0 + j] = base + v[j];
-    }
-    if (tid == 0) totals[blockIdx.x] = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-}
-
-// Adds the totals of the preceding column groups to chi (when the status
-// copied by fold_scan_kernel is clear); block 0 copies the status out and
-// clears the status word.
-__global__ void __launch_bounds__(256) scan_offsets_kernel(int m, int64_t *__restrict__ chi, uint32_t *status,
-                                                           uint32_t *status_out, const int64_t *__restrict__ totals) {
-    const uint32_t stv = status[1];
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (status_out) *status_out = stv;
-        status[0] = 0u;
-    }
-    if (stv != 0 || blockIdx.x == 0) return;
-    int64_t off = 0;
-    for (int j = 0; j < (int)blockIdx.x; ++j) off += totals[j];
-    const int c0 = blockIdx.x * 1024 + threadIdx.x * 4;
-    if (c0 < m) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) chi[c0 + j] += off;
+    for (int w = 0; w < wave; ++w) before += sh[w];
+    if (stv == 0 && c0 + tid < m) chi[c0 + tid] = before + x;
+    if (blockIdx.x == 0 && tid == 0 && status_out) *status_out = stv;
+    if (totals == nullptr && tid == 0) {
+        // (every thread of this workgroup has read the status word: the
+        // barriers above follow the reads)
+        if (atomicAdd(&status[4], 1u) == gridDim.x - 1) {
+            status[4] = 0u;
+            status[0] = 0u;
+        }
     }
 }
 
@@ -474,93 +452,73 @@ int launch_minmax_u16(const uint16_t *img, int64_t n, uint32_t *out, hipStream_t
     return ECC_OK;
 }
 
-// Curves of at most 1024 thresholds from at most kSmallMergeRows rows: the
-// three merge kernels above in one workgroup (256 threads x 4 columns), for
-// the latency of small images.  The column sums are placed through LDS
-// (with `reverse`, column c lands at m-1-c, in another thread's columns);
-// then vcec, the scan into chi (only with a clear status word), and the
-// status copy and clear, as in the three-kernel form.
-constexpr int kSmallMergeRows = 64;
-__global__ void __launch_bounds__(256) merge_scan_small_kernel(const int32_t *__restrict__ partial, int rows, int m,
-                                                               int64_t *__restrict__ vcec, int accumulate, int reverse,
-                                                               int64_t *__restrict__ chi, uint32_t *status,
-                                                               uint32_t *status_out) {
-    __shared__ int64_t col[1024];
-    __shared__ int64_t wsum[4];
+// Curves of at most 1024 thresholds from at most kSmallMergeRows rows: both
+// steps in one workgroup, for the latency of small images (m / 4 threads per
+// row, 4096 / m rows at a time).  The column sums are placed through LDS (with
+// `reverse`, column c lands at m-1-c); then vcec, the scan into chi (only
+// with a clear status word), and the status copy and clear.  One workgroup
+// reads few bytes per second: 5.6 us for 256 rows of 256 columns, 12.4 us for
+// 1024, where the two launches take 8.5 us and the wait between them.
+constexpr int kSmallMergeRows = 256;
+__global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *__restrict__ partial, int rows, int m,
+                                                                int64_t *__restrict__ vcec, int accumulate, int reverse,
+                                                                int64_t *__restrict__ chi, uint32_t *status,
+                                                                uint32_t *status_out) {
+    __shared__ unsigned long long col[1024];
+    __shared__ int64_t sh[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c0 = tid * 4;
-    const bool own = c0 < m;
-    const uint32_t stv = *status;  // cleared below, after a barrier
+    const uint32_t stv = *(volatile uint32_t *)status;  // cleared below, after a barrier
+    col[tid] = 0;
+    __syncthreads();
     if (rows > 0) {
-        if (own) {
-            int64_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+        const int per = m / 4, step = 1024 / per;
+        const int c0 = (tid % per) * 4;
+        int r = tid / per;
+        if (r < step) {
+            int64_t v[4] = {0, 0, 0, 0};
             const int4 *p = reinterpret_cast<const int4 *>(partial) + c0 / 4;
-            const size_t stride4 = (size_t)m / 4;
-            int r = 0;
-            for (; r + 8 <= rows; r += 8) {
+            const size_t stride4 = (size_t)per;
+            for (; r + 7 * step < rows; r += 8 * step) {
                 int4 a[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) a[j] = p[(size_t)(r + j) * stride4];
+                for (int u = 0; u < 8; ++u) a[u] = p[(size_t)(r + u * step) * stride4];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    s0 += a[j].x;
-                    s1 += a[j].y;
-                    s2 += a[j].z;
-                    s3 += a[j].w;
+                for (int u = 0; u < 8; ++u) {
+                    v[0] += a[u].x;
+                    v[1] += a[u].y;
+                    v[2] += a[u].z;
+                    v[3] += a[u].w;
                 }
             }
-            for (; r < rows; ++r) {
+            for (; r < rows; r += step) {
                 const int4 a = p[(size_t)r * stride4];
-                s0 += a.x;
-                s1 += a.y;
-                s2 += a.z;
-                s3 += a.w;
+                v[0] += a.x;
+                v[1] += a.y;
+                v[2] += a.z;
+                v[3] += a.w;
             }
-            if (reverse) {
-                col[m - 1 - c0] = s0;
-                col[m - 2 - c0] = s1;
-                col[m - 3 - c0] = s2;
-                col[m - 4 - c0] = s3;
-            } else {
-                col[c0] = s0;
-                col[c0 + 1] = s1;
-                col[c0 + 2] = s2;
-                col[c0 + 3] = s3;
-            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) atomicAdd(&col[reverse ? m - 1 - (c0 + j) : c0 + j], (unsigned long long)v[j]);
         }
         __syncthreads();
     }
-    int64_t v[4] = {0, 0, 0, 0};
+    const bool own = tid < m;
+    int64_t v = 0;
     if (own) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int64_t x = (rows == 0 || accumulate) ? vcec[c0 + j] : 0;
-            if (rows > 0) x += col[c0 + j];
-            v[j] = x;
-        }
-        if (rows > 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) vcec[c0 + j] = v[j];
-        }
+        if (rows == 0 || accumulate) v = vcec[tid];
+        v += (int64_t)col[tid];
+        if (rows > 0) vcec[tid] = v;
     }
-    // inclusive scan: within the thread, across the wave, across the 4 waves
-    v[1] += v[0];
-    v[2] += v[1];
-    v[3] += v[2];
-    int64_t x = v[3];
+    int64_t x = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int64_t u = __shfl_up(x, off, 64);
         if (lane >= off) x += u;
     }
-    if (lane == 63) wsum[wave] = x;
+    if (lane == 63) sh[wave] = x;
     __syncthreads();
-    int64_t base = x - v[3];
-    for (int w = 0; w < wave; ++w) base += wsum[w];
-    if (own && stv == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) chi[c0 + j] = base + v[j];
-    }
+    for (int w = 0; w < wave; ++w) x += sh[w];
+    if (own && stv == 0) chi[tid] = x;
     if (tid == 0) {
         status[1] = stv;
         if (status_out) *status_out = stv;
@@ -568,43 +526,28 @@ __global__ void __launch_bounds__(256) merge_scan_small_kernel(const int32_t *__
     }
 }
 
-int merge_stage_rows(int rows) {
-    int by = 1;
-    while (by < 32 && by * 8 <= rows) by *= 2;
-    return by;
-}
-
-int launch_merge(const int32_t *partial, int rows, int m, int64_t *stage, int64_t *vcec, bool accumulate,
-                 bool do_scan, int64_t *chi, uint32_t *status, uint32_t *status_out, hipStream_t stream,
-                 bool reverse) {
-    if (m % 4 != 0 || m > 65536) {
+int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
+                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse) {
+    if (m % 256 != 0 || m > 65536 || (m < 1024 && 1024 % m != 0)) {
         set_error("launch_merge: m = %d not supported", m);
         return ECC_E_ARG;
     }
-    const int groups = (m + 1023) / 1024;
-    if (do_scan && groups == 1 && rows <= kSmallMergeRows) {
-        hipLaunchKernelGGL(merge_scan_small_kernel, dim3(1), dim3(256), 0, stream, partial, rows, m, vcec,
+    if (do_scan && m <= 1024 && rows <= kSmallMergeRows) {
+        hipLaunchKernelGGL(merge_scan_small_kernel, dim3(1), dim3(1024), 0, stream, partial, rows, m, vcec,
                            accumulate ? 1 : 0, reverse ? 1 : 0, chi, status, status_out);
         ECC_HIP(hipGetLastError());
         return ECC_OK;
     }
-    int by = 0;
+    int64_t *totals = do_scan && rows > 0 ? reinterpret_cast<int64_t *>(status) + kStatusTotalsOffset / 8 : nullptr;
     if (rows > 0) {
-        by = merge_stage_rows(rows);
-        hipLaunchKernelGGL(colsum_kernel, dim3(groups, by), dim3(256), 0, stream, partial, rows, m,
-                           by == 1 ? vcec : stage, (by == 1 && accumulate) ? 1 : 0, reverse ? 1 : 0);
+        hipLaunchKernelGGL(colsum_kernel, dim3(m / kColBlock), dim3(1024), 0, stream, partial, rows, m, vcec,
+                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, status);
         ECC_HIP(hipGetLastError());
     }
-    if (by > 1 || do_scan) {
-        int64_t *totals = reinterpret_cast<int64_t *>(status) + kStatusTotalsOffset / 8;
-        hipLaunchKernelGGL(fold_scan_kernel, dim3(groups), dim3(256), 0, stream, by > 1 ? (const int64_t *)stage : nullptr,
-                           by, m, vcec, accumulate ? 1 : 0, do_scan ? 1 : 0, chi, status, totals);
+    if (do_scan) {
+        hipLaunchKernelGGL(scan_kernel, dim3((m + 1023) / 1024), dim3(1024), 0, stream, (const int64_t *)vcec, m,
+                           (const int64_t *)totals, chi, status, status_out);
         ECC_HIP(hipGetLastError());
-        if (do_scan) {
-            hipLaunchKernelGGL(scan_offsets_kernel, dim3(groups), dim3(256), 0, stream, m, chi, status, status_out,
-                               (const int64_t *)totals);
-            ECC_HIP(hipGetLastError());
-        }
     }
     return ECC_OK;
 }

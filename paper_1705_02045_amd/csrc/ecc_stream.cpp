@@ -49,8 +49,6 @@ struct ecc_stream {
     // device change vector and per-workgroup rows
     int32_t *partial = nullptr;
     size_t partial_bytes = 0;
-    int64_t *mstage = nullptr;  // merge stage rows
-    size_t mstage_bytes = 0;
     int64_t *vcec = nullptr;
     uint32_t *status = nullptr;
     // 4-D images: extents
@@ -76,7 +74,6 @@ void destroy(ecc_stream *st) {
         if (st->released[i]) (void)hipEventDestroy(st->released[i]);
     }
     if (st->partial) (void)hipFree(st->partial);
-    if (st->mstage) (void)hipFree(st->mstage);
     if (st->vcec) (void)hipFree(st->vcec);
     if (st->status) (void)hipFree(st->status);
     if (st->copy) (void)hipStreamDestroy(st->copy);
@@ -117,11 +114,9 @@ int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int
     if (rc) return rc;
     rc = ensure_bytes((void **)&st->partial, &st->partial_bytes, (size_t)rows * st->m * sizeof(int32_t));
     if (rc) return rc;
-    rc = ensure_bytes((void **)&st->mstage, &st->mstage_bytes, (size_t)merge_stage_rows(rows) * st->m * sizeof(int64_t));
-    if (rc) return rc;
     rc = launch_change_counts(j, st->partial, nullptr, st->status, st->compute);
     if (rc) return rc;
-    return launch_merge(st->partial, rows, st->m, st->mstage, st->vcec, true, false, nullptr, st->status, nullptr,
+    return launch_merge(st->partial, rows, st->m, st->vcec, true, false, nullptr, st->status, nullptr,
                         st->compute);
 }
 
@@ -155,9 +150,6 @@ int run_chunk(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t n, int64_
         const int mloc = u16 ? 32768 : st->m;  // bins of one launch
         int rc = ensure_bytes((void **)&st->partial, &st->partial_bytes, (size_t)tl.grid * mloc * sizeof(int32_t));
         if (rc) return rc;
-        rc = ensure_bytes((void **)&st->mstage, &st->mstage_bytes,
-                          (size_t)merge_stage_rows(tl.grid) * mloc * sizeof(int64_t));
-        if (rc) return rc;
         if (u16) {
             // two 32768-bin passes, each adding the values of its half of
             // 0..65535 into that half of the changes vector
@@ -166,14 +158,14 @@ int run_chunk(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t n, int64_
                 j.win_shift = i * 32768;
                 rc = launch_int_partial(j, tl, st->partial, st->status, nullptr, st->compute);
                 if (rc) return rc;
-                rc = launch_merge(st->partial, tl.grid, mloc, st->mstage, st->vcec + i * 32768, true, false, nullptr,
+                rc = launch_merge(st->partial, tl.grid, mloc, st->vcec + i * 32768, true, false, nullptr,
                                   st->status, nullptr, st->compute);
                 if (rc) return rc;
             }
         } else {
             rc = launch_int_partial(j, tl, st->partial, st->status, nullptr, st->compute);
             if (rc) return rc;
-            rc = launch_merge(st->partial, tl.grid, st->m, st->mstage, st->vcec, true, false, nullptr, st->status,
+            rc = launch_merge(st->partial, tl.grid, st->m, st->vcec, true, false, nullptr, st->status,
                               nullptr, st->compute);
             if (rc) return rc;
         }
@@ -402,7 +394,7 @@ int ecc_stream_finish(ecc_stream *st, ecc_curve *curve) {
             rc = hip_fail(e, "hipMalloc(curve)");
             break;
         }
-        rc = launch_merge(nullptr, 0, st->m, nullptr, st->vcec, true, true, tmp, st->status, st->status + 2,
+        rc = launch_merge(nullptr, 0, st->m, st->vcec, true, true, tmp, st->status, st->status + 2,
                           st->compute);
         uint32_t stv = 0;
         if (!rc) {
@@ -549,7 +541,7 @@ int stream_finish_async(ecc_stream *st, int64_t *chi_dev, uint32_t *status_dev) 
         set_error("stream_finish_async: %lld of %lld planes pushed", (long long)st->pushed, (long long)st->view.n0);
         return ECC_E_STATE;
     }
-    return launch_merge(nullptr, 0, st->m, nullptr, st->vcec, true, true, chi_dev, st->status, status_dev,
+    return launch_merge(nullptr, 0, st->m, st->vcec, true, true, chi_dev, st->status, status_dev,
                         st->compute);
 }
 
