@@ -419,10 +419,11 @@ int plan_u16_windows(uint32_t vmin, uint32_t vmax, U16Window *w) {
 }
 
 // Tiling of a 32768-bin pass: two rows per wave, two planes of look-ahead,
-// about two workgroups per CU (one resident at a time: 1024^3, 2.21 ms for
-// the full range; one per CU 2.21, four 2.28, eight 2.43).
+// one workgroup per CU (the 128 KiB histogram admits one at a time, and each
+// further one writes another row of 128 KiB to be summed: 463 x 512^2, two
+// passes: 278 us in all, 305 with two per CU, 357 with four).
 IntTiling range_pass_tiling(const IntView &v, int64_t planes) {
-    IntTiling tl = make_int_tiling(v, planes, 2, env_int("ECC_U16_TILES_PER_CU", 2), 16);
+    IntTiling tl = make_int_tiling(v, planes, 2, env_int("ECC_U16_TILES_PER_CU", 1), 16);
     tl.pd = 2;
     tl.mode = 0;
     return tl;
@@ -431,70 +432,26 @@ IntTiling range_pass_tiling(const IntView &v, int64_t planes) {
 // 16-bit images in 32768-bin passes (a 128 KiB workgroup histogram, one
 // workgroup per CU): the fields and comparisons take the raw values and each
 // pass adds the changes at values [lo, lo + 32768) exactly, with no guard
-// bins: one pass from min(vmin, 32768) when the image's values span fewer
-// than 32768, else the passes [0, 32768) and [32768, 65536), each skipping
-// the adds of values outside its range.  Each pass's column sums go to their
-// place in the 65536-bin changes vector, scanned once.
+// bins: [0, 32768), then [32768, 65536), each skipping the adds of values
+// outside its half.  Each pass's column sums go to their half of the
+// 65536-bin changes vector, scanned once.
+// The synchronous call (adaptive) lets the first pass note whether any value
+// lies above its half (a word of host memory, read after the pass), and runs
+// the second only then.  No separate read for the image's range: images
+// below 32768 take one pass (1024^3 14-bit and 15-bit data: 0.92 ms, against
+// 1.15 and 2.54 ms for the range read and one or two windows), full ranges
+// two (1.80 ms, against 3.94 ms in five windows); an image whose values all
+// lie above 32768 reads it once in vain.  The other calls run both.
 static int enqueue_u16_passes(const void *image_dev, const IntView &v, int64_t *chi_dev, uint32_t *status_out,
-                              hipStream_t stream, Workspace *ws, uint32_t vmin, uint32_t vmax) {
-    constexpr int mpass = 32768, mtot = 65536;
-    int32_t lo[2] = {0, mpass};
-    int npass = 2, mode = 2;
-    if (vmax - vmin < (uint32_t)mpass) {
-        npass = 1;
-        mode = 1;
-        lo[0] = (int32_t)(vmin < (uint32_t)mpass ? vmin : (uint32_t)mpass);
-    }
-    const IntTiling tl = range_pass_tiling(v, v.n0);
-    int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * mpass * sizeof(int32_t));
-    if (rc) return rc;
-    rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)mtot * sizeof(int64_t));
-    if (rc) return rc;
-    if (npass == 1) {  // the bins outside the pass stay zero
-        rc = launch_zero(ws->vcec16, (size_t)mtot * sizeof(int64_t), stream);
-        if (rc) return rc;
-    }
-    IntJob job{};
-    job.src.base = (const uint8_t *)image_dev;
-    job.src.lo_base = job.src.base;
-    job.src.plane_bytes = (int64_t)v.n1 * v.n2 * 2;
-    job.view = v;
-    job.e0 = 0;
-    job.e1 = (int32_t)v.n0;
-    job.lo_inf = 1;
-    job.hi_inf = 1;
-    job.dtype = ECC_U16;
-    job.range_pass = mode;
-    for (int i = 0; i < npass; ++i) {
-        job.win_shift = lo[i];
-        rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
-        if (rc) return rc;
-        rc = launch_merge(ws->partial, tl.grid, mpass, ws->vcec16 + lo[i], false, false, nullptr,
-                          ws->status, nullptr, stream);
-        if (rc) return rc;
-    }
-    return launch_merge(nullptr, 0, mtot, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
-}
-
-// The synchronous call's 16-bit path: the pass over [0, 32768) first, which
-// notes whether any value lies above it (a word of host memory, read after
-// the pass), and the pass over [32768, 65536) only then.  No separate read
-// for the image's range: images below 32768 take one pass (1024^3 14-bit
-// and 15-bit data: 0.92 ms, against 1.15 and 2.54 ms for the range read and
-// one or two windows), full ranges two (1.80 ms, against 3.94 ms in five
-// windows); an image whose values all lie above 32768 reads it once in vain.
-static int enqueue_u16_adaptive(const void *image_dev, const IntView &v, int64_t *chi_dev, uint32_t *status_out,
-                                hipStream_t stream, Workspace *ws) {
+                              hipStream_t stream, Workspace *ws, bool adaptive) {
     constexpr int mpass = 32768, mtot = 65536;
     const IntTiling tl = range_pass_tiling(v, v.n0);
     int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * mpass * sizeof(int32_t));
     if (rc) return rc;
     rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)mtot * sizeof(int64_t));
-    if (rc) return rc;
-    rc = launch_zero(ws->vcec16 + mpass, (size_t)mpass * sizeof(int64_t), stream);  // if the second pass is skipped
     if (rc) return rc;
     volatile uint32_t *high = ws->host_status + 1;
-    *high = 0u;
+    if (adaptive) *high = 0u;
     IntJob job{};
     job.src.base = (const uint8_t *)image_dev;
     job.src.lo_base = job.src.base;
@@ -508,18 +465,17 @@ static int enqueue_u16_adaptive(const void *image_dev, const IntView &v, int64_t
     job.range_pass = 2;
     for (int i = 0; i < 2; ++i) {
         job.win_shift = i * mpass;
-        job.high_flag = i == 0 ? ws->host_status_dev + 1 : nullptr;
+        job.high_flag = adaptive && i == 0 ? ws->host_status_dev + 1 : nullptr;
         rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
         if (rc) return rc;
-        rc = launch_merge(ws->partial, tl.grid, mpass, ws->vcec16 + i * mpass, false, false, nullptr,
-                          ws->status, nullptr, stream);
+        rc = launch_merge_half(ws->partial, tl.grid, ws->vcec16, i, adaptive && i == 0, ws->status, stream);
         if (rc) return rc;
-        if (i == 0) {
+        if (adaptive && i == 0) {
             ECC_HIP(hipStreamSynchronize(stream));
             if (*high == 0u) break;
         }
     }
-    return launch_merge(nullptr, 0, mtot, ws->vcec16, true, true, chi_dev, ws->status, status_out, stream);
+    return launch_scan_halves(ws->vcec16, chi_dev, ws->status, status_out, stream);
 }
 
 // Planned from a known range (the entry point that allocates nothing, whose
@@ -534,7 +490,7 @@ static int enqueue_u16(const void *image_dev, const IntView &v, int64_t *chi_dev
     U16Window win[kU16MaxWindows + 1];
     const int nwin = plan_u16_windows(vmin, vmax, win);
     if (nwin > 1 && !ws->fixed && env_int("ECC_U16_WINDOWS", 0) == 0)
-        return enqueue_u16_passes(image_dev, v, chi_dev, status_out, stream, ws, vmin, vmax);
+        return enqueue_u16_passes(image_dev, v, chi_dev, status_out, stream, ws, false);
     IntTiling tl = choose_int_tiling(v, ECC_U16, v.n0, ws->max_grid);
     int rc = ws_ensure(ws, (void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * mloc * sizeof(int32_t));
     if (rc) return rc;
@@ -735,7 +691,7 @@ static int compute_int(const void *image, const ecc_dims *dims, int64_t total, e
         rc = enqueue_four_d(four, max_entry, chi_target, nullptr, ws->host_status_dev, s, ws);
     } else if (dtype == ECC_U16 && !ws->fixed && env_int("ECC_U16_WINDOWS", 0) == 0) {
         *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
-        rc = enqueue_u16_adaptive(img_dev, v, chi_target, ws->host_status_dev, s, ws);
+        rc = enqueue_u16_passes(img_dev, v, chi_target, ws->host_status_dev, s, ws, true);
     } else if (dtype == ECC_U16) {  // only the windows between the image's minimum and maximum
         uint32_t *mm = ws->status + kStatusMinMaxOffset / 4;
         rc = launch_minmax_u16((const uint16_t *)img_dev, total, mm, s);

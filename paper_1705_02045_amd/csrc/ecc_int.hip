@@ -62,11 +62,10 @@ constexpr int kXfInvert = 1;
 constexpr int kXfWindow = 2;
 // 16-bit values in 32768-bin passes: the fields are the raw values (32-bit,
 // kInfRaw above all of them) and each update's LDS address is
-// 4 * (value - win_shift); kXfRange: every value of the image lies in the
-// pass's range; kXfRangeMasked: the adds of values outside it are masked off.
-constexpr int kXfRange = 3;
-constexpr int kXfRangeMasked = 4;
-constexpr bool raw_fields(int xf) { return xf == kXfRange || xf == kXfRangeMasked; }
+// 4 * (value - win_shift); the adds of values outside the pass's range are
+// masked off.
+constexpr int kXfRangeMasked = 3;
+constexpr bool raw_fields(int xf) { return xf == kXfRangeMasked; }
 constexpr uint32_t kInfRaw = 0x10000u;
 
 // Field values are LDS byte offsets of their bins (value * 4), computed with
@@ -143,6 +142,22 @@ __device__ __forceinline__ void pair_values(uint32_t d, uint32_t sh, uint32_t &f
     const uint32_t pv = (uint32_t)__builtin_amdgcn_update_dpp((int)d, (int)f0, kDppWaveShr1, 0xF, 0xF, false);
     asm("v_pk_min_u16 %0, %1, %2" : "=v"(m) : "v"(pv), "v"(f0));
     fx = m;
+}
+// 8-bit images with a histogram copy per lane (REP = 6: bin v of lane l is the
+// word 64 v + l).  Offsets are v << 8 | 4 l: the lane bits are equal in all
+// values that a lane compares, so they change no comparison.
+__device__ __forceinline__ uint32_t lane_off(uint32_t v, uint32_t lane4) {
+    uint32_t r;
+    asm("v_lshl_or_b32 %0, %1, 8, %2" : "=v"(r) : "v"(v), "v"(lane4));
+    return r;
+}
+// The two bytes at x-1 (low) and x of one load: the offset at x, and that of
+// the smaller of the two.
+__device__ __forceinline__ void byte_pair_offsets(uint32_t d, uint32_t lane4, uint32_t &f0, uint32_t &fx) {
+    uint32_t m;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(f0) : "v"(d), "s"(0xFF00u), "v"(lane4));
+    asm("v_min_u32_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_0 src1_sel:BYTE_1" : "=v"(m) : "v"(d));
+    fx = lane_off(m, lane4);
 }
 // clamp(v - s, 0, 16383) on both halves; s2 = s | s << 16 (0 <= s < 65536)
 __device__ __forceinline__ uint32_t pair_window(uint32_t q, uint32_t s2) {
@@ -341,6 +356,37 @@ struct Walker {
         }
     }
 
+    // Offsets with a histogram copy per lane: from the loaded byte pairs
+    // (PAIR), or from the values at x and x-1; inv: 0, or 255 in every byte
+    // for values read as 255 - v.
+    template <bool PAIR>
+    static __device__ __forceinline__ void fields_rep(const uint32_t (&a)[NR], const uint32_t (&b)[NR], uint32_t lane4,
+                                                      uint32_t inv, uint32_t (&g)[NI]) {
+        uint32_t f0[NR], fx[NR];
+#pragma unroll
+        for (int rr = 0; rr < NR; ++rr) {
+            if constexpr (PAIR) {
+                byte_pair_offsets(inv ? a[rr] ^ 0xFFFFu : a[rr], lane4, f0[rr], fx[rr]);
+            } else {
+                const uint32_t va = inv ? a[rr] ^ 0xFFu : a[rr], vb = inv ? b[rr] ^ 0xFFu : b[rr];
+                f0[rr] = lane_off(va, lane4);
+                fx[rr] = lane_off(min_raw(va, vb), lane4);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (NIN == 1) {
+                g[2 * r] = f0[r];
+                g[2 * r + 1] = fx[r];
+            } else {
+                g[4 * r + 0] = f0[r + 1];
+                g[4 * r + 1] = fx[r + 1];
+                g[4 * r + 2] = min_off(f0[r], f0[r + 1]);
+                g[4 * r + 3] = min_off(fx[r], fx[r + 1]);
+            }
+        }
+    }
+
     static __device__ __forceinline__ void set_inf(uint32_t (&g)[NI], uint32_t inf) {
 #pragma unroll
         for (int i = 0; i < NI; ++i) g[i] = inf;
@@ -395,16 +441,20 @@ constexpr int lcm(int a, int b) {
 // wave lies on a far edge, so the comparison masks need no validity mask.
 // PAIR (FULL waves of the row-pair layout): one aligned dword load per row at
 // byte offset vx[rr], and psel, the lane's half of it (16 for odd x, 0 for
-// even x); vxl is unused.
+// even x); vxl is unused.  8-bit values with REP: one 16-bit load per row at
+// the byte offset vx[rr] of x-1.
 // PD: planes of raw loads kept in flight ahead of the plane being compared.
 // The plane loop is unrolled by lcm(2, PD+1) so that every register buffer is
 // addressed with a compile-time index (plane p of the tile uses raw buffer
 // (p - zs) mod (PD+1) and field buffer (p - zs) mod 2).
-template <typename T, int NIN, int R, int MODE, bool FULL, int PD, int XF, bool PAIR = false>
+template <typename T, int NIN, int R, int MODE, bool FULL, int PD, int XF, bool PAIR = false, int REP = 0>
 __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uint32_t (&vx)[R + 1],
                                      const uint32_t (&vxl)[R + 1], const uint32_t (&soff)[R + 1], const EdgeMasks &em,
                                      uint32_t &orv, uint32_t psel = 0) {
-    static_assert(!PAIR || (FULL && NIN == 2 && sizeof(T) == 2), "row pairs: interior 16-bit waves, 2 axes");
+    static_assert(!PAIR || (FULL && NIN == 2 && sizeof(T) == 2) || (FULL && REP != 0),
+                  "row pairs: interior 16-bit waves, 2 axes; byte pairs: interior waves with lane copies");
+    static_assert(REP == 0 || (REP == 6 && sizeof(T) == 1), "a histogram copy per lane: 8-bit values");
+    const uint32_t lane4 = REP ? (threadIdx.x & (kWave - 1)) * 4u : 0u;
     using W = Walker<NIN, R>;
     constexpr int NR = W::NR;
     constexpr int NI = W::NI;
@@ -425,8 +475,10 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
         __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)pp, (short)0, pbytes, kBufferWord3);
 #pragma unroll
         for (int rr = 0; rr < NR; ++rr) {
-            if constexpr (PAIR) {
+            if constexpr (PAIR && ESZ == 2) {
                 a[rr] = __builtin_amdgcn_raw_buffer_load_b32(rs, vx[rr], soff[rr], 0);
+            } else if constexpr (PAIR) {
+                a[rr] = __builtin_amdgcn_raw_buffer_load_b16(rs, vx[rr], soff[rr], 0);
             } else {
                 a[rr] = load_elem(rs, vx[rr], soff[rr], ESZ);
                 b[rr] = load_elem(rs, vxl[rr], soff[rr], ESZ);
@@ -454,7 +506,10 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
             else W::fields_raw(a, b, g);
             return;
         }
-        if constexpr (PAIR) {
+        if constexpr (REP != 0) {
+            W::template fields_rep<PAIR>(a, b, lane4, XF == kXfInvert ? 1u : 0u, g);
+            return;
+        } else if constexpr (PAIR) {
             W::fields_pair(a, psel, g, [&](uint32_t q) -> uint32_t {
                 if constexpr (XF == kXfInvert) return q ^ (kInvMask * 0x10001u);
                 else if constexpr (XF == kXfWindow) return pair_window(q, (uint32_t)wshift * 0x10001u);
@@ -494,16 +549,11 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
                 uint32_t a[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) a[j] = (gc[i + j] << 2) + abase;
-                if constexpr (XF == kXfRangeMasked) {
-                    uint64_t r[4];
+                uint64_t r[4];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) r[j] = ballot(a[j] < kAddrEnd);
-                    update4_masked(a[0], a[1], a[2], a[3], c0, c1, c2, c3, cp[i], cp[i + 1], cp[i + 2], cp[i + 3],
-                                   r[0], r[1], r[2], r[3], e[0], e[1], e[2], e[3]);
-                } else {
-                    update4<W::kGroupSigns, DM>(a[0], a[1], a[2], a[3], c0, c1, c2, c3, cp[i], cp[i + 1], cp[i + 2],
-                                                cp[i + 3], e[0], e[1], e[2], e[3], one, mone);
-                }
+                for (int j = 0; j < 4; ++j) r[j] = ballot(a[j] < kAddrEnd);
+                update4_masked(a[0], a[1], a[2], a[3], c0, c1, c2, c3, cp[i], cp[i + 1], cp[i + 2], cp[i + 3], r[0], r[1],
+                               r[2], r[3], e[0], e[1], e[2], e[3]);
             } else {
                 update4<W::kGroupSigns, DM>(gc[i], gc[i + 1], gc[i + 2], gc[i + 3], c0, c1, c2, c3, cp[i], cp[i + 1],
                                             cp[i + 2], cp[i + 3], e[0], e[1], e[2], e[3], one, mone);
@@ -587,7 +637,14 @@ constexpr int kWavesPerEU() {
 // The tiles of one workgroup of one image: b = the workgroup's index among
 // the image's G workgroups (G <= tiles).  Writes the counts of its tiles to
 // row b of P.partial.
-template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone>
+// REP: 0, or 6 (8-bit values): 64 copies of every bin, one per lane.  Lanes that
+// add to the same bin or bank in one instruction wait for each other: on
+// independent values half the lanes add per field and plane, 64 lanes over
+// 256 words of 32 banks, and the adds set the kernel's time.  With the copies
+// no two lanes of a half-wave share a bank (512^3 independent values: 151 ->
+// 122 us per curve).  The batch kernel keeps one copy (its tiles are short:
+// 287 us against 350 for 96 images).
+template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone, int REP = 0>
 __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const int b, const int G) {
     using W = Walker<NIN, R>;
     constexpr int NR = W::NR;
@@ -602,8 +659,8 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     }
     // (loops with a uniform trip count: a thread-dependent one makes the
     // compiler treat later lane masks as divergent)
-    for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
-        if (i0 + tid < M) hist[i0 + tid] = 0;
+    for (int i0 = 0; i0 < (M << REP); i0 += (int)blockDim.x)
+        if (i0 + tid < (M << REP)) hist[i0 + tid] = 0;
     if (P.zero_vcec && b == 0)
         for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
             if (i0 + tid < M) P.zero_vcec[i0 + tid] = 0;
@@ -639,7 +696,7 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     // x-segment seg0 + r of the single in-plane axis.
     uint32_t vx[R + 1] = {}, vxl[R + 1] = {}, soff[R + 1] = {};
     EdgeMasks em{};
-    bool full = false, any = false;
+    bool full = false, any = false, bytes2 = false;
     uint32_t psel = 0;
     if constexpr (NIN == 1) {
         const int32_t seg0 = (tx * P.wx + wxi) * R;
@@ -651,6 +708,7 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
             vx[r] = (uint32_t)xcl * ESZ;
             vxl[r] = (uint32_t)(xcl > 0 ? xcl - 1 : 0) * ESZ;
         }
+        bytes2 = REP != 0 && full && seg0 > 0;
     } else {
         // Row-pair layout: waves start at odd columns (x0 = 64 k + 1) and
         // column 0 is taken by the lane of column n2 (n2 is even there, so
@@ -664,6 +722,7 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
         psel = (x & 1) ? 16u : 0u;
         const int32_t xcl = min(x, n2 - 1);
         const uint32_t ox = (uint32_t)xcl * ESZ, oxl = (uint32_t)(xcl > 0 ? xcl - 1 : 0) * ESZ;
+        bytes2 = REP != 0 && full && x0 > 0;
 #pragma unroll
         for (int rr = 0; rr < NR; ++rr) {
             // row pairs: the aligned dword holding column x
@@ -684,7 +743,13 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     }
     if (any && zs < ze) {
         if (full) {
-            if constexpr (NIN == 2 && ESZ == 2) {
+            if constexpr (REP != 0) {
+                // (waves at x = 0 have no byte before their first)
+                if (bytes2)
+                    walk<T, NIN, R, MODE, true, PD, XF, true, REP>(P, zs, ze, vxl, vxl, soff, em, orv);
+                else
+                    walk<T, NIN, R, MODE, true, PD, XF, false, REP>(P, zs, ze, vx, vxl, soff, em, orv);
+            } else if constexpr (NIN == 2 && ESZ == 2) {
                 if (pair)
                     walk<T, NIN, R, MODE, true, PD, XF, true>(P, zs, ze, vx, vxl, soff, em, orv, psel);
                 else
@@ -708,10 +773,10 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
                 e2.lx_any2 = ballot(xb < n2);
                 const uint32_t v2[3] = {vx[r], vx[r + 1], 0u}, vl2[3] = {vxl[r], vxl[r + 1], 0u};
                 const uint32_t s2[3] = {0u, 0u, 0u};
-                walk<T, 1, 2, MODE, false, 1, XF>(P, zs, ze, v2, vl2, s2, e2, orv);
+                walk<T, 1, 2, MODE, false, 1, XF, false, REP>(P, zs, ze, v2, vl2, s2, e2, orv);
             }
         } else {
-            walk<T, NIN, R, MODE, false, PD, XF>(P, zs, ze, vx, vxl, soff, em, orv);
+            walk<T, NIN, R, MODE, false, PD, XF, false, REP>(P, zs, ze, vx, vxl, soff, em, orv);
         }
     }
     }  // tiles
@@ -728,8 +793,25 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
     int32_t *dst = P.partial + (size_t)b * M;
-    for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
-        if (i0 + tid < M) dst[i0 + tid] = hist[i0 + tid];
+    if constexpr (REP != 0) {
+        // four threads sum a bin's 64 copies, 16 each, from staggered words
+        // (the bins of a wave then read 32 different banks)
+        static_assert(REP == 6, "four threads of 16 copies");
+        for (int i0 = 0; i0 < M * 4; i0 += (int)blockDim.x) {
+            const int i = i0 + tid, bin = i >> 2, q = i & 3;
+            int32_t c = 0;
+            if (i < M * 4) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) c += hist[bin * 64 + q * 16 + ((j + bin) & 15)];
+            }
+            c += __shfl_xor(c, 1, 64);
+            c += __shfl_xor(c, 2, 64);
+            if (i < M * 4 && q == 0) dst[bin] = c;
+        }
+    } else {
+        for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
+            if (i0 + tid < M) dst[i0 + tid] = hist[i0 + tid];
+    }
 }
 
 // XF, a transform of every loaded value v:
@@ -742,12 +824,12 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
 //    monotone clamp keeps every comparison that decides a kept bin, since
 //    each involves the counted value itself.
 // (32768 bins: a 128 KiB histogram, one workgroup per CU, four waves per SIMD)
-template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone>
+template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone, int REP = 0>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M > 16384 ? 4 : kWavesPerEU<NIN, R, PD>())))
 int_vcec_kernel(KParams P) {
     static_assert(raw_fields(XF) == (M == 32768), "32768 bins: raw-value passes, and only those");
-    __shared__ int32_t hist[M];
-    tile_body<T, M, NIN, R, MODE, PD, XF>(P, hist, blockIdx.x, gridDim.x);
+    __shared__ int32_t hist[M << REP];
+    tile_body<T, M, NIN, R, MODE, PD, XF, REP>(P, hist, blockIdx.x, gridDim.x);
 }
 
 // Batched form: the tiles of every image of a batch in one persistent
@@ -789,13 +871,13 @@ int_vcec_persistent_kernel(uint8_t *__restrict__ table) {
     }
 }
 
-template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone>
+template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone, int REP = 0>
 static int launch_one(const KParams &p, const IntTiling &tl, hipStream_t stream) {
     const int threads = kWave * tl.wx * tl.wy;
     void *tok = nullptr;
     int rc = profile_begin(stream, &tok);
     if (rc) return rc;
-    hipLaunchKernelGGL((int_vcec_kernel<T, M, NIN, R, MODE, PD, XF>), dim3(tl.grid), dim3(threads), 0, stream, p);
+    hipLaunchKernelGGL((int_vcec_kernel<T, M, NIN, R, MODE, PD, XF, REP>), dim3(tl.grid), dim3(threads), 0, stream, p);
     ECC_HIP(hipGetLastError());
     return profile_end(stream, tok);
 }
@@ -827,6 +909,24 @@ static int launch_rows(const KParams &p, const IntTiling &tl, hipStream_t stream
     case 4: return launch_mode<T, M, NIN, 4>(p, tl, stream);
     default: break;
     }
+    set_error("integer kernel: %d rows per wave not built", tl.rows);
+    return ECC_E_UNSUPPORTED;
+}
+
+// 8-bit launches with a histogram copy per lane: workgroups that fill a CU in
+// pairs anyway (more than 12 waves: the 64 KiB then cost no occupancy) and
+// walk at least 16 planes (clearing the copies and summing them takes as
+// long as about one plane).
+static bool lane_copies(const IntTiling &tl) {
+    return tl.mode == 0 && tl.wx * tl.wy > 12 && (int64_t)tl.zc * tl.per_wg >= 16;
+}
+template <int NIN, int XF>
+static int launch_u8_copies(const KParams &p, const IntTiling &tl, hipStream_t stream) {
+    const bool pd2 = tl.pd == 2;
+    if (tl.rows == 2)
+        return pd2 ? launch_one<uint8_t, 256, NIN, 2, 0, 2, XF, 6>(p, tl, stream) : launch_one<uint8_t, 256, NIN, 2, 0, 1, XF, 6>(p, tl, stream);
+    if (tl.rows == 4)
+        return pd2 ? launch_one<uint8_t, 256, NIN, 4, 0, 2, XF, 6>(p, tl, stream) : launch_one<uint8_t, 256, NIN, 4, 0, 1, XF, 6>(p, tl, stream);
     set_error("integer kernel: %d rows per wave not built", tl.rows);
     return ECC_E_UNSUPPORTED;
 }
@@ -892,14 +992,17 @@ int launch_int_partial(const IntJob &job, const IntTiling &tl, int32_t *partial,
                        int64_t *zero_vcec, hipStream_t stream) {
     const KParams p = make_params(job, tl, partial, status, zero_vcec);
     const int nin = job.view.nin;
-    if (job.dtype == ECC_U16 && job.range_pass == 1)  // 32768 values from win_shift on: all of the image's
-        return nin == 1 ? launch_range<1, kXfRange>(p, tl, stream) : launch_range<2, kXfRange>(p, tl, stream);
-    if (job.dtype == ECC_U16 && job.range_pass == 2)  // the same, values outside masked off
+    if (job.dtype == ECC_U16 && job.range_pass == 2)  // 32768 values from win_shift on, the others masked off
         return nin == 1 ? launch_range<1, kXfRangeMasked>(p, tl, stream)
                         : launch_range<2, kXfRangeMasked>(p, tl, stream);
     if (job.dtype == ECC_U16)  // one window of 16382 values per launch
         return nin == 1 ? launch_transformed<uint16_t, 16384, 1, kXfWindow>(p, tl, stream)
                         : launch_transformed<uint16_t, 16384, 2, kXfWindow>(p, tl, stream);
+    if (job.dtype == ECC_U8 && lane_copies(tl)) {
+        if (job.invert)
+            return nin == 1 ? launch_u8_copies<1, kXfInvert>(p, tl, stream) : launch_u8_copies<2, kXfInvert>(p, tl, stream);
+        return nin == 1 ? launch_u8_copies<1, kXfNone>(p, tl, stream) : launch_u8_copies<2, kXfNone>(p, tl, stream);
+    }
     if (job.invert) {
         if (job.dtype == ECC_U8)
             return nin == 1 ? launch_transformed<uint8_t, 256, 1, kXfInvert>(p, tl, stream)

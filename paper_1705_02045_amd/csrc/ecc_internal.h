@@ -70,10 +70,9 @@ struct IntJob {
     int dtype;            // ECC_U8 or ECC_U14
     int invert;           // values read as M-1-v (largest-value convention)
     int32_t win_shift;    // ECC_U16: the launch counts bin = clamp(v - win_shift, 0, 16383)
-    // ECC_U16 in 32768-bin passes: 1 = every value lies in [win_shift,
-    // win_shift + 32768) and the launch counts bin = v - win_shift; 2 = the
-    // same for the values in that range, the others skipped; 0 = a window
-    // as above
+    // ECC_U16 in 32768-bin passes: 2 = the values in [win_shift, win_shift +
+    // 32768) are counted at bin = v - win_shift, the others skipped; 0 = a
+    // window as above
     int range_pass;
     uint32_t *high_flag;  // range passes: set to 1 when a value >= 32768 is loaded (may be null)
 };
@@ -176,6 +175,12 @@ int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, u
 // word to status_out (when not null) and clears it.
 int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
                  uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse = false);
+// The same in parts for 16-bit images in 32768-bin passes: the column sums of
+// a pass over the lower (0) or upper (1) half of 0..65535 into that half of
+// vcec16 (clear, lower half only: the upper half is zeroed), then the scan.
+int launch_merge_half(const int32_t *partial, int rows, int64_t *vcec16, int half, bool clear, uint32_t *status,
+                      hipStream_t stream);
+int launch_scan_halves(const int64_t *vcec16, int64_t *chi, uint32_t *status, uint32_t *status_out, hipStream_t stream);
 
 // Copies the n0 x n1 x n2 sub-array of src starting at element `base` with
 // element strides s0, s1, s2 into dst (contiguous, C order).

@@ -28,10 +28,11 @@ int launch_zero(void *p, size_t bytes, hipStream_t stream) {
 // Merge of the per-workgroup rows [rows][m] (int32) into the int64 change
 // vector and its prefix sum, in kernels that follow each other on the stream
 // (the kernel boundary orders their memory):
-//  1. colsum_kernel: a workgroup of 1024 threads sums all rows of 64 columns
-//     (64 rows at a time, 16 threads of 4 columns each: 256-byte runs) into
-//     vcec and, for a scan, their total into totals; it also hands the status
-//     word over to the scan (status[1]) and clears it;
+//  1. colsum_kernel: a workgroup sums all rows of 64 columns (64 rows at a
+//     time, 16 threads of 4 columns each: 256-byte runs; 16 rows at a time
+//     where there are at most 64, with a quarter of the threads to start) into
+//     vcec and, for a scan, their total into totals; before a scan it also
+//     hands the status word over (status[1]) and clears it;
 //  2. scan_kernel: a workgroup scans 1024 columns, from the sum of the totals
 //     before them.
 // Two launches where the sums of some rows at a time, their fold with the
@@ -41,13 +42,17 @@ int launch_zero(void *p, size_t bytes, hipStream_t stream) {
 // With `reverse`, column c of the rows lands at m-1-c (the largest-value
 // convention: the kernel counted at m-1-value).  vcec is overwritten, or added
 // to with `accumulate`.
+// clear (may be null): m further entries to set to zero, with their totals.
 constexpr int kColBlock = 64;
-__global__ void __launch_bounds__(1024) colsum_kernel(const int32_t *__restrict__ partial, int rows, int m,
-                                                      int64_t *__restrict__ vcec, int accumulate, int reverse,
-                                                      int64_t *__restrict__ totals, uint32_t *status) {
-    __shared__ int64_t part[16][kColBlock];  // per wave
+template <int RG>
+__global__ void __launch_bounds__(16 * RG) colsum_kernel(const int32_t *__restrict__ partial, int rows, int m,
+                                                         int64_t *__restrict__ vcec, int accumulate, int reverse,
+                                                         int64_t *__restrict__ totals, int64_t *__restrict__ clear,
+                                                         int hand, uint32_t *status) {
+    constexpr int kWaves = RG / 4;
+    __shared__ int64_t part[kWaves][kColBlock];  // per wave
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (totals != nullptr && blockIdx.x == 0 && tid == 0) {
+    if (hand && blockIdx.x == 0 && tid == 0) {
         status[1] = status[0];
         status[0] = 0u;
     }
@@ -56,10 +61,10 @@ __global__ void __launch_bounds__(1024) colsum_kernel(const int32_t *__restrict_
     const int4 *p = reinterpret_cast<const int4 *>(partial) + (size_t)blockIdx.x * (kColBlock / 4) + c4;
     int64_t v[4] = {0, 0, 0, 0};
     int r = tid >> 4;
-    for (; r + 3 * 64 < rows; r += 4 * 64) {
+    for (; r + 3 * RG < rows; r += 4 * RG) {
         int4 a[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = p[(size_t)(r + u * 64) * stride4];
+        for (int u = 0; u < 4; ++u) a[u] = p[(size_t)(r + u * RG) * stride4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             v[0] += a[u].x;
@@ -68,7 +73,7 @@ __global__ void __launch_bounds__(1024) colsum_kernel(const int32_t *__restrict_
             v[3] += a[u].w;
         }
     }
-    for (; r < rows; r += 64) {
+    for (; r < rows; r += RG) {
         const int4 a = p[(size_t)r * stride4];
         v[0] += a.x;
         v[1] += a.y;
@@ -85,11 +90,15 @@ __global__ void __launch_bounds__(1024) colsum_kernel(const int32_t *__restrict_
     if (tid >= kColBlock) return;
     int64_t s = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) s += part[w][tid];
+    for (int w = 0; w < kWaves; ++w) s += part[w][tid];
     const int c = blockIdx.x * kColBlock + tid;
     const int at = reverse ? m - 1 - c : c;
     if (accumulate) s += vcec[at];
     vcec[at] = s;
+    if (clear != nullptr) {
+        clear[c] = 0;
+        if (tid == 0) totals[gridDim.x + blockIdx.x] = 0;
+    }
     if (totals == nullptr) return;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
@@ -110,18 +119,18 @@ __device__ __forceinline__ int64_t block_sum_1024(int64_t v, int64_t *sh) {
 }
 
 // Columns [1024 b, 1024 b + 1024) of the curve.  With totals (at most 1024 of
-// them) the columns before come from those and the status from status[1];
-// without (a changes vector that is complete already), from vcec itself, and
-// the last workgroup to have read the status word clears it (status[4]
-// counts them).  The curve is written only with a clear status.
+// them) the columns before come from those, without from vcec itself.  The
+// status comes from status[1] where the column sums have handed it over, else
+// from the status word, which the last workgroup to have read it clears
+// (status[4] counts them).  The curve is written only with a clear status.
 __global__ void __launch_bounds__(1024) scan_kernel(const int64_t *__restrict__ vcec, int m,
-                                                    const int64_t *__restrict__ totals, int64_t *__restrict__ chi,
-                                                    uint32_t *status, uint32_t *status_out) {
+                                                    const int64_t *__restrict__ totals, int handed,
+                                                    int64_t *__restrict__ chi, uint32_t *status, uint32_t *status_out) {
     __shared__ int64_t sh[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c0 = blockIdx.x * 1024;
     const int64_t v = c0 + tid < m ? vcec[c0 + tid] : 0;
-    const uint32_t stv = totals != nullptr ? status[1] : *(volatile uint32_t *)status;
+    const uint32_t stv = handed ? status[1] : *(volatile uint32_t *)status;
     int64_t before = 0;
     if (totals != nullptr) {
         if (tid < c0 / kColBlock) before = totals[tid];
@@ -147,7 +156,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(const int64_t *__restrict__ 
     for (int w = 0; w < wave; ++w) before += sh[w];
     if (stv == 0 && c0 + tid < m) chi[c0 + tid] = before + x;
     if (blockIdx.x == 0 && tid == 0 && status_out) *status_out = stv;
-    if (totals == nullptr && tid == 0) {
+    if (!handed && tid == 0) {
         // (every thread of this workgroup has read the status word: the
         // barriers above follow the reads)
         if (atomicAdd(&status[4], 1u) == gridDim.x - 1) {
@@ -526,6 +535,20 @@ __global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *_
     }
 }
 
+static int64_t *merge_totals(uint32_t *status) { return reinterpret_cast<int64_t *>(status) + kStatusTotalsOffset / 8; }
+
+static int launch_colsum(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, int64_t *totals,
+                         int64_t *clear, bool hand, uint32_t *status, hipStream_t stream, bool reverse) {
+    if (rows <= 64)
+        hipLaunchKernelGGL(colsum_kernel<16>, dim3(m / kColBlock), dim3(256), 0, stream, partial, rows, m, vcec,
+                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, clear, hand ? 1 : 0, status);
+    else
+        hipLaunchKernelGGL(colsum_kernel<64>, dim3(m / kColBlock), dim3(1024), 0, stream, partial, rows, m, vcec,
+                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, clear, hand ? 1 : 0, status);
+    ECC_HIP(hipGetLastError());
+    return ECC_OK;
+}
+
 int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
                  uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse) {
     if (m % 256 != 0 || m > 65536 || (m < 1024 && 1024 % m != 0)) {
@@ -538,17 +561,34 @@ int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool ac
         ECC_HIP(hipGetLastError());
         return ECC_OK;
     }
-    int64_t *totals = do_scan && rows > 0 ? reinterpret_cast<int64_t *>(status) + kStatusTotalsOffset / 8 : nullptr;
+    int64_t *totals = merge_totals(status);
     if (rows > 0) {
-        hipLaunchKernelGGL(colsum_kernel, dim3(m / kColBlock), dim3(1024), 0, stream, partial, rows, m, vcec,
-                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, status);
-        ECC_HIP(hipGetLastError());
+        int rc = launch_colsum(partial, rows, m, vcec, accumulate, do_scan ? totals : nullptr, nullptr, do_scan, status,
+                               stream, reverse);
+        if (rc) return rc;
     }
     if (do_scan) {
         hipLaunchKernelGGL(scan_kernel, dim3((m + 1023) / 1024), dim3(1024), 0, stream, (const int64_t *)vcec, m,
-                           (const int64_t *)totals, chi, status, status_out);
+                           rows > 0 ? (const int64_t *)totals : (const int64_t *)nullptr, rows > 0 ? 1 : 0, chi, status,
+                           status_out);
         ECC_HIP(hipGetLastError());
     }
+    return ECC_OK;
+}
+
+// A 16-bit image's pass over one half of 0..65535: its column sums and totals
+// into that half; clear: the other half (the upper) is set to zero.
+int launch_merge_half(const int32_t *partial, int rows, int64_t *vcec16, int half, bool clear, uint32_t *status,
+                      hipStream_t stream) {
+    constexpr int m = 32768;
+    return launch_colsum(partial, rows, m, vcec16 + half * m, false, merge_totals(status) + half * (m / kColBlock),
+                         clear ? vcec16 + m : nullptr, false, status, stream, false);
+}
+
+int launch_scan_halves(const int64_t *vcec16, int64_t *chi, uint32_t *status, uint32_t *status_out, hipStream_t stream) {
+    hipLaunchKernelGGL(scan_kernel, dim3(64), dim3(1024), 0, stream, vcec16, 65536,
+                       (const int64_t *)merge_totals(status), 0, chi, status, status_out);
+    ECC_HIP(hipGetLastError());
     return ECC_OK;
 }
 
