@@ -184,8 +184,8 @@ int ecc_compute_async_noalloc(const void *image_dev, const ecc_dims *dims, ecc_d
  * Tile shapes.  The integer kernel's tiling of a launch has three
  * parameters: rows per wave (2 or 4), waves along x (up to 16 of a
  * workgroup's 16) and workgroups per CU (the image is split along axis 0
- * until about that many tiles per CU exist; planes with more tiles give a
- * workgroup several).  By default a rule of the launch's size picks them
+ * into at most about that many tiles per CU, as many as fill whole rounds of
+ * the CUs best; planes with more tiles give a workgroup several).  By default a rule of the launch's size picks them
  * (measured on MI355X); ecc_autotune times the candidates on an image and
  * keeps the fastest for its shape in a process-wide table consulted by every
  * later launch of that shape (dtype, plane shape and number of planes; the

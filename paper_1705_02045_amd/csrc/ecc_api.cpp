@@ -258,11 +258,38 @@ static int env_int(const char *name, int dflt) {
 
 // Tuning overrides (measurement only): ECC_INT_ROWS, ECC_INT_MODE, ECC_INT_PD, ECC_INT_WX, ECC_U16_TILES_PER_CU,
 // ECC_U16_WINDOWS (1: 16-bit images in the window form),
-// ECC_INT_WAVES, ECC_INT_TILES_PER_CU, ECC_INT_TILE_STRIDE, ECC_INT_PAIR (0: no row pairs).
+// ECC_INT_WAVES, ECC_INT_TILES_PER_CU, ECC_INT_TILE_STRIDE, ECC_INT_PAIR (0: no row pairs),
+// ECC_INT_PLAN (0: exactly the tiles per CU asked for).
+// Waves along x of a plane of xs 64-column segments, at most cap: the fewest
+// idle wave slots of 16 (whole tiles cover xs, whole waves fill a workgroup),
+// from 4 on (narrower tiles touch more pages per byte); the widest of equals.
+static int choose_wx(int64_t xs, int cap, int max_waves) {
+    int best = (int)std::min<int64_t>(xs, cap);
+    double best_use = 0;
+    for (int w = best; w >= std::min<int64_t>(xs, 4); --w) {
+        const int64_t tx = (xs + w - 1) / w;
+        const double use = (double)xs / (double)(tx * w) * (double)(max_waves / w * w) / max_waves;
+        if (use > best_use + 1e-9) {
+            best_use = use;
+            best = w;
+        }
+    }
+    return best;
+}
+
 // The tiling for given parameters: R rows per wave, up to wx_cap waves
 // along x (16-wave workgroups), about tiles_per_cu workgroups per CU.
+// planned: at most that many.  The number of workgroups is then the one with
+// the least estimated time, over 1 .. tiles_per_cu per CU: the planes that the
+// fullest CU walks, each walk 4 planes longer than its tile (its prologue); a
+// sixth more for a workgroup that has its CU to itself; and the count rows,
+// each worth row_cost planes of one workgroup (its 64 KiB are cleared, written
+// and read again).  The 4 and row_cost are fitted to 248 launches of 0.5 to
+// 600 million voxels (9 % off on average).  512^3 at 14 bits in 512 workgroups,
+// two per CU, takes 104 us where 1024 took 149; 400 x 413 x 390 82 us where
+// 1040 workgroups, most CUs idle in their last round, took 91.
 IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_per_cu, int wx_cap,
-                          int max_grid = 0) {
+                          int max_grid = 0, bool planned = false, double row_cost = 0) {
     IntTiling t{};
     t.rows = rows;
     t.mode = env_int("ECC_INT_MODE", 0);
@@ -276,7 +303,8 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
         tiles_xy = (segs + t.wx - 1) / t.wx;
     } else {
         const int64_t xs = (v.n2 + kWave - 1) / kWave;
-        t.wx = (int)(xs < wx_cap ? xs : wx_cap);
+        if (planned) t.wx = choose_wx(xs, std::min(xs <= 16 ? 16 : 8, wx_cap), max_waves);
+        else t.wx = (int)(xs < wx_cap ? xs : wx_cap);
         const int64_t ys = (v.n1 + t.rows - 1) / t.rows;
         const int64_t wy = max_waves / t.wx;
         t.wy = (int)(ys < wy ? ys : wy);
@@ -285,27 +313,57 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
     // split axis 0 until there are about tiles_per_cu tiles per CU; planes
     // with more tiles than that get several tiles per workgroup, so the
     // per-workgroup rows stay about tiles_per_cu per CU
-    const int64_t target = (int64_t)cus * tiles_per_cu;
-    int64_t tz = (target + tiles_xy - 1) / tiles_xy;
-    if (tz < 1) tz = 1;
-    if (tz > planes) tz = planes;
-    int64_t zc = (planes + tz - 1) / tz;
-    if (zc < 8 && planes >= 8) zc = 8;
+    auto walk_for = [&](int64_t tz) {
+        if (tz < 1) tz = 1;
+        if (tz > planes) tz = planes;
+        int64_t zc = (planes + tz - 1) / tz;
+        if (zc < 8 && planes >= 8) zc = 8;
+        return zc;
+    };
+    int64_t zc = 0, per = 0;
+    auto fit = [&](int64_t target, int64_t tz) {
+        const int64_t z = walk_for(tz);
+        const int64_t tiles = tiles_xy * ((planes + z - 1) / z);
+        int64_t p = tiles > target ? (tiles + target - 1) / target : 1;
+        // a cap on the workgroups (fixed scratch): more tiles per workgroup
+        if (max_grid > 0 && (tiles + p - 1) / p > max_grid) p = (tiles + max_grid - 1) / max_grid;
+        const int64_t grid = (tiles + p - 1) / p;
+        zc = z;
+        per = p;
+        t.grid = (int)grid;
+        const int64_t rounds = (grid + cus - 1) / cus;
+        return ((double)rounds + (rounds % 2 ? 1.0 / 6 : 0.0)) * (double)(p * (z + 4)) + row_cost * (double)grid;
+    };
+    if (planned) {
+        double best = 0;
+        int64_t best_target = 0, best_tz = 0;
+        for (int k = 1; k <= tiles_per_cu; ++k) {
+            const int64_t target = (int64_t)cus * k;
+            for (int64_t tz = target / tiles_xy; tz <= target / tiles_xy + 1; ++tz) {
+                const double c = fit(target, tz);
+                if (best_target == 0 || c < best) {
+                    best = c;
+                    best_target = target;
+                    best_tz = tz;
+                }
+            }
+        }
+        (void)fit(best_target, best_tz);
+    } else {
+        const int64_t target = (int64_t)cus * tiles_per_cu;
+        (void)fit(target, (target + tiles_xy - 1) / tiles_xy);
+    }
     t.zc = (int)zc;
     // planes of loads in flight: two on walks of 128 planes and more (1024^3:
     // 2 % faster, 512 x 4096^2: 7 %), one on shorter walks, where the longer
     // prologue costs more than it hides (14 x 8192^2: 20 % slower with two);
     // two with four rows per wave, whose register budget (one workgroup per
     // CU) holds them without spills (64-plane slabs of 14450^2: 2 % faster)
-    t.pd = env_int("ECC_INT_PD", (zc >= 128 || rows >= 4) ? 2 : 1);
-    const int64_t tiles = tiles_xy * ((planes + zc - 1) / zc);
-    int64_t per = tiles > target ? (tiles + target - 1) / target : 1;
-    // a cap on the workgroups (fixed scratch): more tiles per workgroup
-    if (max_grid > 0 && (tiles + per - 1) / per > max_grid) per = (tiles + max_grid - 1) / max_grid;
+    // with one in-plane axis one (16384^2 at 14 bits: 148 us against 160)
+    t.pd = env_int("ECC_INT_PD", ((zc >= 128 && v.nin == 2) || rows >= 4) ? 2 : 1);
     t.per_wg = (int)per;
     t.tile_stride = env_int("ECC_INT_TILE_STRIDE", 0);
     t.pair = env_int("ECC_INT_PAIR", 1);
-    t.grid = (int)((tiles + per - 1) / per);
     return t;
 }
 
@@ -363,9 +421,20 @@ static ecc_tiling tiling_params(const IntView &v, int dtype, int64_t planes) {
     return c;
 }
 
+// Whether a launch's workgroups are planned (make_int_tiling): 14-bit
+// launches below 2^30 voxels, 8-bit ones below 2^27.  Above that, finer splits
+// than the plan's were as fast or faster (1024^3 at 14 bits: 649 us in 1024
+// workgroups, 658 in 512; 128 x 1024^2 at 8 bits: 102 us against 104).
+static bool planned_tiling(const IntView &v, int dtype, int64_t planes) {
+    return planes * (int64_t)v.n1 * v.n2 < (int64_t)1 << (dtype == ECC_U8 ? 27 : 30) && env_int("ECC_INT_PLAN", 1) != 0;
+}
+static IntTiling tiling_from(const IntView &v, int dtype, int64_t planes, const ecc_tiling &c, int max_grid) {
+    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned_tiling(v, dtype, planes),
+                           dtype == ECC_U8 ? 0.0075 : 0.045);
+}
+
 IntTiling choose_int_tiling(const IntView &v, int dtype, int64_t planes, int max_grid) {
-    const ecc_tiling c = tiling_params(v, dtype, planes);
-    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid);
+    return tiling_from(v, dtype, planes, tiling_params(v, dtype, planes), max_grid);
 }
 
 // Enqueue the whole integer computation for a device-resident image.
@@ -423,7 +492,7 @@ int plan_u16_windows(uint32_t vmin, uint32_t vmax, U16Window *w) {
 // further one writes another row of 128 KiB to be summed: 463 x 512^2, two
 // passes: 278 us in all, 305 with two per CU, 357 with four).
 IntTiling range_pass_tiling(const IntView &v, int64_t planes) {
-    IntTiling tl = make_int_tiling(v, planes, 2, env_int("ECC_U16_TILES_PER_CU", 1), 16);
+    IntTiling tl = make_int_tiling(v, planes, 2, env_int("ECC_U16_TILES_PER_CU", 1), 16, 0, true);
     tl.pd = 2;
     tl.mode = 0;
     return tl;
@@ -1120,7 +1189,7 @@ int ecc_autotune(const void *image_dev, const ecc_dims *dims, ecc_dtype dtype, v
                 x.p.rows = rows_c[a];
                 x.p.tiles_per_cu = tpc_c[b];
                 x.p.waves_x = wx_c[c + (v.nin == 2 ? 0 : 1)];
-                x.tl = make_int_tiling(v, v.n0, x.p.rows, x.p.tiles_per_cu, x.p.waves_x);
+                x.tl = tiling_from(v, dtype, v.n0, x.p, 0);
                 x.best = 1e30f;
                 cands.push_back(x);
                 if (!rc) rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes,
