@@ -154,9 +154,9 @@ int get_workspace(void *stream, Workspace **out) {
     return ECC_OK;
 }
 
-// Side streams of a caller's stream: the box faces of the dual complex run
-// on them, concurrently with the full box on the caller's stream (a fork at
-// the call's start, a join before the faces' changes are summed).  Created
+// Side streams of a caller's stream: the faces of a 4-D image's dual complex
+// run on them, concurrently with the full box on the caller's stream (a fork
+// at the call's start, a join before the faces' changes are summed).  Created
 // on first use per (device, caller's stream) with the default priority,
 // non-blocking, and kept for the process; each has its own workspace.
 struct SideStreams {
@@ -601,36 +601,30 @@ int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, u
     return enqueue_u16(image_dev, v, chi_dev, status_out, stream, ws, 0, 65535);
 }
 
-// Changes vector only (no scan) of a device image into vcec_out; a range
-// error stays set in ws->status for a later scan to report.
-// plane_stride: elements between consecutive planes of a view with one
-// in-plane axis (0: the planes are contiguous rows); the kernel reads only
-// the first n2 elements of each plane.
-static int enqueue_int_changes(const void *image_dev, const IntView &v, int dtype, int64_t *vcec_out,
-                               hipStream_t stream, Workspace *ws, bool max_entry, int64_t plane_stride = 0) {
+// Count rows only (no merge) of a device image in the largest-value convention
+// (entries at m-1-v) into ws->partial, with room for extra_rows more behind
+// the *rows written; a range error stays set in ws->status for a later scan to
+// report.
+static int enqueue_max_entry_rows(const void *image_dev, const IntView &v, int dtype, int extra_rows, int *rows,
+                                  hipStream_t stream, Workspace *ws) {
     const int m = (int)threshold_count(dtype);
-    if (plane_stride != 0 && (v.nin != 1 || plane_stride < v.n2 || plane_stride * (int64_t)elem_bytes(dtype) > INT32_MAX)) {
-        set_error("internal error: plane stride %lld for a view of %d in-plane axes", (long long)plane_stride, v.nin);
-        return ECC_E_ARG;
-    }
     IntTiling tl = choose_int_tiling(v, dtype, v.n0);
-    int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes, (size_t)tl.grid * m * sizeof(int32_t));
+    int rc = ensure_bytes((void **)&ws->partial, &ws->partial_bytes,
+                          (size_t)(tl.grid + extra_rows) * m * sizeof(int32_t));
     if (rc) return rc;
+    *rows = tl.grid;
     IntJob job{};
     job.src.base = (const uint8_t *)image_dev;
     job.src.lo_base = job.src.base;
-    job.src.plane_bytes = (plane_stride ? plane_stride : (int64_t)v.n1 * v.n2) * (int64_t)elem_bytes(dtype);
+    job.src.plane_bytes = (int64_t)v.n1 * v.n2 * (int64_t)elem_bytes(dtype);
     job.view = v;
     job.e0 = 0;
     job.e1 = (int32_t)v.n0;
     job.lo_inf = 1;
     job.hi_inf = 1;
     job.dtype = dtype;
-    job.invert = max_entry ? 1 : 0;
-    rc = launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
-    if (rc) return rc;
-    return launch_merge(ws->partial, tl.grid, m, vcec_out, false, false, nullptr, ws->status, nullptr,
-                        stream, max_entry);
+    job.invert = 1;
+    return launch_int_partial(job, tl, ws->partial, ws->status, nullptr, stream);
 }
 
 static bool is_device_ptr(const void *p) {
@@ -1396,6 +1390,32 @@ int ecc_autotune_load(const char *path) {
     return (int)rows.size();
 }
 
+// Waits for the scan of a dual curve, reports its status and copies the curve
+// to host memory if it belongs there.
+static int finish_dual(Workspace *ws, ecc_curve *curve, const int64_t *chi_dev, bool chi_direct, int64_t m,
+                       hipStream_t s) {
+    ECC_HIP(hipStreamSynchronize(s));
+    const uint32_t stv = *ws->host_status;
+    if (stv == 0xFFFFFFFFu) {
+        set_error("internal error: the scan did not report a status");
+        return ECC_E_HIP;
+    }
+    if (stv & kStatusRange) {
+        set_error("a 14-bit image holds a value >= 16384");
+        return ECC_E_RANGE;
+    }
+    if (stv != 0) {
+        set_error("internal error: device status 0x%08x", stv);
+        return ECC_E_HIP;
+    }
+    if (!chi_direct) {
+        ECC_HIP(hipMemcpyAsync(curve->chi, chi_dev, (size_t)m * sizeof(int64_t), hipMemcpyDefault, s));
+        ECC_HIP(hipStreamSynchronize(s));
+    }
+    curve->count = m;
+    return ECC_OK;
+}
+
 // Dual complex (voxels as vertices, lower-star filtration).  Its cells are
 // the cells of the voxel complex away from the box's outer boundary, with
 // dimension d - dim and value the maximum over their voxels, so by
@@ -1448,29 +1468,91 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
     }
     int nf = 1;
     for (int k = 0; k < d; ++k) nf *= 3;
+    const int gsign = (d & 1) ? -1 : 1;
     int64_t st[4] = {1, 1, 1, 1};  // element strides of the kept axes
     for (int k = d - 2; k >= 0; --k) st[k] = st[k + 1] * n[k + 1];
     int64_t face_max = 1;  // the largest face of codimension >= 1
     for (int k = 0; k < d; ++k)
         if (total / n[k] > face_max) face_max = total / n[k];
-    // dual_buf: [nf][m] per-face changes vectors, [m] the changes of the
-    // faces of at most one dimension (all of them, signed), [m] the signed
-    // sum, the table of faces of at most one dimension
-    const size_t curves_bytes = (size_t)(nf + 2) * m * sizeof(int64_t);
-    const size_t low_off = (curves_bytes + 255) & ~(size_t)255;
-    rc = ensure_bytes(&ws->dual_buf, &ws->dual_buf_bytes, low_off + ((nf * sizeof(LowFace) + 255) & ~(size_t)255));
+    // dual_buf: up to three dimensions [m] the signed sum's changes, [m] the
+    // curve; for a 4-D image [nf][m] changes vectors of the full box and its
+    // faces of three dimensions, [m] the changes of its faces of at most two
+    // (all of them, signed), [m] the signed sum, [m] the curve
+    const int nvec = d == 4 ? nf + 2 : 1;
+    rc = ensure_bytes(&ws->dual_buf, &ws->dual_buf_bytes, (size_t)(nvec + 1) * m * sizeof(int64_t));
     if (rc) return rc;
     int64_t *curves = (int64_t *)ws->dual_buf;
+    const bool chi_direct = is_device_ptr(curve->chi);
+    int64_t *chi_dev = chi_direct ? curve->chi : curves + (size_t)nvec * m;
+    struct Face {
+        int nfree, codim;
+        int64_t base, n[4], stride[4];
+    };
+    auto face = [&](int f) {  // axis k of face f: free, or fixed at its first or last index
+        Face F{0, 0, 0, {1, 1, 1, 1}, {0, 0, 0, 0}};
+        for (int k = 0, r = f; k < d; ++k, r /= 3) {
+            if (r % 3 == 0) {
+                F.n[F.nfree] = n[k];
+                F.stride[F.nfree] = st[k];
+                ++F.nfree;
+            } else {
+                F.base += (r % 3 == 1 ? 0 : n[k] - 1) * st[k];
+                ++F.codim;
+            }
+        }
+        return F;
+    };
+    std::vector<BoxFace> low;
+    for (int f = 0; f < nf; ++f) {
+        const Face F = face(f);
+        if (F.codim == 0 || F.nfree > 2) continue;
+        BoxFace B{};
+        B.base = F.base;
+        B.na = F.nfree == 2 ? F.n[0] : 0;
+        B.sa = F.nfree == 2 ? F.stride[0] : 0;
+        B.nb = F.nfree ? F.n[F.nfree - 1] : 0;
+        B.sb = F.nfree ? F.stride[F.nfree - 1] : 0;
+        B.sign = (F.codim & 1) ? -1 : 1;
+        low.push_back(B);
+    }
+    const int cus = device_cu_count();
+    const int low_rows = box_face_rows(low.data(), (int)low.size(), cus);
+    *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
+    if (d < 4) {
+        // One merge over the count rows of the box and of its faces, all on
+        // s: the faces' launch is short (16 us for 400 x 413 x 390, of 115 per
+        // curve); beside the volume on a side stream, with a fork, a join and a
+        // signed sum, the curve took 168.
+        ecc_dims bd{};
+        bd.ndim = d > 0 ? d : 1;
+        for (int k = 0; k < 4; ++k) bd.n[k] = k < d ? n[k] : 1;
+        IntView v{};
+        int unsup = 0, rows = 0;
+        if (!normalize_int_view(&bd, &v, &unsup)) {
+            set_error("ecc_compute_dual: shape not supported");
+            return ECC_E_UNSUPPORTED;
+        }
+        rc = enqueue_max_entry_rows(img_dev, v, dtype, low_rows, &rows, s, ws);
+        if (!rc)
+            rc = launch_box_faces(img_dev, (int)eb, low.data(), (int)low.size(), cus, ws->partial + (size_t)rows * m, s);
+        if (!rc)
+            rc = launch_merge(ws->partial, rows + low_rows, (int)m, curves, false, true, chi_dev, ws->status,
+                              ws->host_status_dev, s, true, gsign < 0);
+        if (rc) {
+            (void)hipStreamSynchronize(s);
+            return rc;
+        }
+        return finish_dual(ws, curve, chi_dev, chi_direct, m, s);
+    }
     int64_t *lowv = curves + (size_t)nf * m;
     int64_t *result = lowv + m;
-    LowFace *low_dev = (LowFace *)((uint8_t *)ws->dual_buf + low_off);
-    // Faces of two or more dimensions below the full box go round-robin to
-    // the side streams, each with its own workspace (and gather buffer in
-    // its img_tmp); the full box runs on s.
+    // The full box runs on s; its faces of three dimensions (of a 4-D image)
+    // go round-robin to the side streams, each with its own workspace (and
+    // gather buffer in its img_tmp), those of at most two in one launch.
     SideStreams *side = nullptr;
     rc = get_side_streams(s, &side);
     if (rc) return rc;
-    Workspace *sws[SideStreams::kCount];
+    Workspace *sws[SideStreams::kCount] = {};
     for (int k = 0; k < SideStreams::kCount; ++k) {
         rc = get_workspace(side->s[k], &sws[k]);
         if (rc) return rc;
@@ -1484,39 +1566,38 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
             if (used[k]) (void)hipStreamSynchronize(side->s[k]);
     };
     ECC_HIP(hipEventRecord(side->fork, s));  // the image (and its copy, if any) is ready here
-    const int gsign = (d & 1) ? -1 : 1;
+    auto fork_to = [&](int k) -> int {
+        if (used[k]) return ECC_OK;
+        const hipError_t e = hipStreamWaitEvent(side->s[k], side->fork, 0);
+        if (e != hipSuccess) return hip_fail(e, "ecc_compute_dual: fork");
+        used[k] = true;
+        return ECC_OK;
+    };
     uint64_t neg[2] = {0, 0}, skip[2] = {0, 0};  // bit f of the pair: face f
     auto set_bit = [](uint64_t *mask, int f) { mask[f >> 6] |= 1ull << (f & 63); };
-    // Box edges and corners (faces of at most one dimension, below the full
-    // box) have a closed-form changes vector; they are added by one launch
-    // after the signed sum instead of a gather, a kernel and a merge each.
-    std::vector<LowFace> low;
-    for (int f = 0; f < nf; ++f) {
-        int code[4] = {0, 0, 0, 0};
-        for (int k = 0, r = f; k < d; ++k, r /= 3) code[k] = r % 3;
-        int codim = 0, nfree = 0;
-        int64_t base = 0, fs[4] = {1, 1, 1, 1}, fst[4] = {0, 0, 0, 0};
-        for (int k = 0; k < d; ++k) {
-            if (code[k] == 0) {
-                fs[nfree] = n[k];
-                fst[nfree] = st[k];
-                ++nfree;
-            } else {
-                base += (code[k] == 1 ? 0 : n[k] - 1) * st[k];
-                ++codim;
-            }
+    // The faces of at most two dimensions on a side stream, summed as one more
+    // face (slot nf, which carries their signs already).
+    {
+        const int k = next_side++ % SideStreams::kCount;
+        Workspace *lws = sws[k];
+        rc = fork_to(k);
+        if (!rc) rc = ensure_bytes((void **)&lws->partial, &lws->partial_bytes, (size_t)low_rows * m * sizeof(int32_t));
+        if (!rc) rc = launch_box_faces(img_dev, (int)eb, low.data(), (int)low.size(), cus, lws->partial, side->s[k]);
+        if (!rc)
+            rc = launch_merge(lws->partial, low_rows, (int)m, lowv, false, false, nullptr, lws->status, nullptr,
+                              side->s[k], true);
+        if (rc) {
+            sync_sides();
+            return rc;
         }
-        if (codim > 0 && nfree <= 1) {
-            LowFace L{};
-            L.base = base;
-            L.stride = nfree ? fst[0] : 0;
-            L.len = nfree ? fs[0] : 0;
-            L.sign = (codim & 1) ? -gsign : gsign;
-            low.push_back(L);
+    }
+    for (int f = 0; f < nf; ++f) {
+        const Face F = face(f);
+        if (F.nfree <= 2) {
             set_bit(skip, f);
             continue;
         }
-        if (nfree == 4) {  // the whole 4-D box
+        if (F.nfree == 4) {  // the whole 4-D box
             ecc_dims bd{};
             bd.ndim = 4;
             for (int k = 0; k < 4; ++k) bd.n[k] = n[k];
@@ -1529,86 +1610,34 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
             }
             continue;
         }
-        // the full box on s, a face on the next side stream
-        const int k = codim > 0 ? (next_side++ % SideStreams::kCount) : -1;
-        hipStream_t fs_stream = k < 0 ? s : side->s[k];
-        Workspace *fws = k < 0 ? ws : sws[k];
-        if (k >= 0 && !used[k]) {
-            hipError_t e = hipStreamWaitEvent(fs_stream, side->fork, 0);
-            if (e != hipSuccess) {
-                sync_sides();
-                return hip_fail(e, "ecc_compute_dual: fork");
-            }
-            used[k] = true;
-        }
-        const void *src = img_dev;
-        int64_t pstride = 0;
-        if (codim > 0 && nfree == 2 && fst[1] == 1 && fst[0] * (int64_t)eb <= INT32_MAX) {
-            // a 2-D face whose rows are contiguous in the image: walked in
-            // place, one row per plane, fst[0] elements apart
-            src = (const uint8_t *)img_dev + base * (int64_t)eb;
-            pstride = fst[0];
-        } else if (codim > 0) {
-            // free axes as the trailing axes of an n0 x n1 x n2 gather, into
-            // the side stream's buffer (its faces run in stream order)
-            int64_t g[3] = {1, 1, 1}, gs[3] = {0, 0, 0};
-            for (int i = 0; i < nfree; ++i) {
-                g[3 - nfree + i] = fs[i];
-                gs[3 - nfree + i] = fst[i];
-            }
-            rc = ensure_bytes(&fws->img_tmp, &fws->img_tmp_bytes, (size_t)face_max * eb);
-            if (!rc) rc = launch_gather(img_dev, (int)eb, base, gs[0], gs[1], gs[2], g[0], g[1], g[2], fws->img_tmp, fs_stream);
-            if (rc) {
-                sync_sides();
-                return rc;
-            }
-            src = fws->img_tmp;
-        }
-        ecc_dims fd{};
-        fd.ndim = nfree > 0 ? nfree : 1;
-        for (int i = 0; i < 4; ++i) fd.n[i] = 1;
-        for (int i = 0; i < nfree; ++i) fd.n[i] = fs[i];
+        // a face of three dimensions, gathered into the next side stream's
+        // buffer (its faces run in stream order)
+        const int k = next_side++ % SideStreams::kCount;
+        Workspace *fws = sws[k];
+        rc = fork_to(k);
+        if (!rc) rc = ensure_bytes(&fws->img_tmp, &fws->img_tmp_bytes, (size_t)face_max * eb);
+        if (!rc)
+            rc = launch_gather(img_dev, (int)eb, F.base, F.stride[0], F.stride[1], F.stride[2], F.n[0], F.n[1], F.n[2],
+                               fws->img_tmp, side->s[k]);
         IntView v{};
-        int unsup = 0;
-        if (!normalize_int_view(&fd, &v, &unsup)) {
-            sync_sides();
+        ecc_dims fd{};
+        fd.ndim = 3;
+        fd.n[3] = 1;
+        for (int i = 0; i < 3; ++i) fd.n[i] = F.n[i];
+        int unsup = 0, rows = 0;
+        if (!rc && !normalize_int_view(&fd, &v, &unsup)) {
             set_error("ecc_compute_dual: face shape not supported");
-            return ECC_E_UNSUPPORTED;
+            rc = ECC_E_UNSUPPORTED;
         }
-        rc = enqueue_int_changes(src, v, dtype, curves + (size_t)f * m, fs_stream, fws, true, pstride);
+        if (!rc) rc = enqueue_max_entry_rows(fws->img_tmp, v, dtype, 0, &rows, side->s[k], fws);
+        if (!rc)
+            rc = launch_merge(fws->partial, rows, (int)m, curves + (size_t)f * m, false, false, nullptr, fws->status,
+                              nullptr, side->s[k], true);
         if (rc) {
             sync_sides();
             return rc;
         }
-        if (codim & 1) set_bit(neg, f);
-    }
-    // Box edges and corners: their table, a cleared vector and the
-    // closed-form changes on the next side stream, summed as one more face
-    // (slot nf, whose entries carry their signs already: the global sign
-    // is cancelled by the slot's own).  The host table must outlive the
-    // copy: every return below this point waits for the side streams (the
-    // join and the final synchronisation of s, or sync_sides).
-    if (!low.empty()) {
-        const int k = next_side % SideStreams::kCount;
-        hipStream_t ls = side->s[k];
-        hipError_t e = hipSuccess;
-        if (!used[k]) e = hipStreamWaitEvent(ls, side->fork, 0);
-        used[k] = true;
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(low_dev, low.data(), low.size() * sizeof(LowFace), hipMemcpyHostToDevice, ls);
-        if (e != hipSuccess) {
-            sync_sides();
-            return hip_fail(e, "ecc_compute_dual: edge and corner table");
-        }
-        rc = launch_zero(lowv, (size_t)m * sizeof(int64_t), ls);
-        if (!rc) rc = launch_low_faces(img_dev, (int)eb, low_dev, (int)low.size(), (int)m, lowv, ls);
-        if (rc) {
-            sync_sides();
-            return rc;
-        }
-        if (gsign < 0) set_bit(neg, nf);
-    } else {
-        set_bit(skip, nf);
+        if (F.codim & 1) set_bit(neg, f);
     }
     // join: s waits for every side stream that took work
     for (int k = 0; k < SideStreams::kCount; ++k) {
@@ -1625,33 +1654,16 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
         (void)hipStreamSynchronize(s);
         return rc;
     }
-    // scan into slot 0 (its changes are summed already); the status of every
-    // face launch (all read the image's values) is reported and cleared here
-    int64_t *chi_dev = curves;
-    *ws->host_status = 0xFFFFFFFFu;  // overwritten by the scan
+    // the scan (its changes are summed already), into the caller's buffer if
+    // it is device memory; the status of every launch on the volume or a face
+    // of three dimensions (the volume's reads all values) is reported and
+    // cleared here, and nothing is written unless it is clear
     rc = launch_merge(nullptr, 0, (int)m, result, true, true, chi_dev, ws->status, ws->host_status_dev, s);
     if (rc) {
         (void)hipStreamSynchronize(s);
         return rc;
     }
-    ECC_HIP(hipStreamSynchronize(s));
-    const uint32_t stv = *ws->host_status;
-    if (stv == 0xFFFFFFFFu) {
-        set_error("internal error: the scan did not report a status");
-        return ECC_E_HIP;
-    }
-    if (stv & kStatusRange) {
-        set_error("a 14-bit image holds a value >= 16384");
-        return ECC_E_RANGE;
-    }
-    if (stv != 0) {
-        set_error("internal error: device status 0x%08x", stv);
-        return ECC_E_HIP;
-    }
-    ECC_HIP(hipMemcpyAsync(curve->chi, chi_dev, (size_t)m * sizeof(int64_t), hipMemcpyDefault, s));
-    ECC_HIP(hipStreamSynchronize(s));
-    curve->count = m;
-    return ECC_OK;
+    return finish_dual(ws, curve, chi_dev, chi_direct, m, s);
 }
 
 }  // extern "C"

@@ -116,7 +116,7 @@ struct Workspace {
     size_t frec_bytes = 0;
     void *fbits = nullptr;       // float path: the bits of the distinct values
     size_t fbits_bytes = 0;
-    void *dual_buf = nullptr;    // dual complex: gathered faces of the box, per-face curves
+    void *dual_buf = nullptr;    // dual complex: per-face changes vectors
     size_t dual_buf_bytes = 0;
     int64_t *vcec16 = nullptr;   // [65536] changes vector of a 16-bit image (window passes)
     size_t vcec16_bytes = 0;
@@ -174,7 +174,8 @@ int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, u
 // prefix sum of vcec into chi (ecc_scan.hip).  The scan copies the status
 // word to status_out (when not null) and clears it.
 int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
-                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse = false);
+                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse = false,
+                 bool negate = false);
 // The same in parts for 16-bit images in 32768-bin passes: the column sums of
 // a pass over the lower (0) or upper (1) half of 0..65535 into that half of
 // vcec16 (clear, lower half only: the upper half is zeroed), then the scan.
@@ -192,14 +193,18 @@ int launch_minmax_u16(const uint16_t *img, int64_t n, uint32_t *out, hipStream_t
 // (faces f < 128: bit f of the pair {mask[0], mask[1]})
 int launch_signed_sum(const int64_t *curves, int nf, const uint64_t neg_mask[2], const uint64_t skip_mask[2],
                       int sign, int m, int64_t *out, hipStream_t stream);
-// A face of the box of at most one dimension: elements base + i * stride,
-// i < len (len = 0: a corner, the single element at base), added with sign.
-struct LowFace {
-    int64_t base, stride, len;
-    int64_t sign;
+// A face of the box of at most two dimensions: elements base + i * sa + j *
+// sb, i < na, j < nb (na or nb 0: no such axis), added with sign (+-1).
+struct BoxFace {
+    int64_t base, sa, sb, na, nb;
+    int32_t sign;
 };
-// Largest-value changes vectors of such faces, added into out (ecc_scan.hip).
-int launch_low_faces(const void *img, int elem, const LowFace *faces_dev, int nfaces, int m, int64_t *out,
+constexpr int kFacesPerLaunch = 32;  // (passed by value)
+// Largest-value changes of such faces of a u8 (elem 1, m = 256) or u14 (elem 2,
+// m = 16384) image as box_face_rows() count rows (max_rows: at most that many
+// per launch), entries at m-1-v (ecc_scan.hip).
+int box_face_rows(const BoxFace *faces, int nfaces, int max_rows);
+int launch_box_faces(const void *img, int elem, const BoxFace *faces, int nfaces, int max_rows, int32_t *rows,
                      hipStream_t stream);
 
 bool normalize_int_view(const ecc_dims *dims, IntView *v, int *err_ndim_dropped);

@@ -40,13 +40,13 @@ int launch_zero(void *p, size_t bytes, hipStream_t stream) {
 // at least (117 rows of 16384 columns: 10.8 -> 8.5 us, a 97 x 130 x 75 call
 // 39.7 -> 38.3 us; 1024 rows: 12.8 + 6.2 + 5.6 -> 13.9 + 5.3 us).
 // With `reverse`, column c of the rows lands at m-1-c (the largest-value
-// convention: the kernel counted at m-1-value).  vcec is overwritten, or added
-// to with `accumulate`.
+// convention: the kernel counted at m-1-value); with `negate` the sums change
+// sign.  vcec is overwritten, or added to with `accumulate`.
 // clear (may be null): m further entries to set to zero, with their totals.
 constexpr int kColBlock = 64;
 template <int RG>
 __global__ void __launch_bounds__(16 * RG) colsum_kernel(const int32_t *__restrict__ partial, int rows, int m,
-                                                         int64_t *__restrict__ vcec, int accumulate, int reverse,
+                                                         int64_t *__restrict__ vcec, int accumulate, int reverse, int negate,
                                                          int64_t *__restrict__ totals, int64_t *__restrict__ clear,
                                                          int hand, uint32_t *status) {
     constexpr int kWaves = RG / 4;
@@ -93,6 +93,7 @@ __global__ void __launch_bounds__(16 * RG) colsum_kernel(const int32_t *__restri
     for (int w = 0; w < kWaves; ++w) s += part[w][tid];
     const int c = blockIdx.x * kColBlock + tid;
     const int at = reverse ? m - 1 - c : c;
+    if (negate) s = -s;
     if (accumulate) s += vcec[at];
     vcec[at] = s;
     if (clear != nullptr) {
@@ -356,45 +357,131 @@ int launch_signed_sum(const int64_t *curves, int nf, const uint64_t neg_mask[2],
     return ECC_OK;
 }
 
-// Faces of at most one dimension (box edges and corners), largest-value
-// convention, added with their signs straight into a changes vector.  A
-// line of n voxels is the 1-D complex of n intervals (value: the voxel's)
-// and n + 1 vertices (value: the larger of the voxels they touch); its
-// changes vector adds +1 at each vertex's value and -1 at each interval's.
-// A corner is one vertex.  Values >= m are skipped (the volume's own launch
-// reports them as range errors).  One workgroup of 1024 threads per face
-// (an edge of up to 1023 voxels in one round of loads).
-template <typename T>
-__global__ void __launch_bounds__(1024) low_faces_kernel(const T *__restrict__ img, const LowFace *__restrict__ faces,
-                                                        int m, int64_t *__restrict__ out) {
-    const LowFace F = faces[blockIdx.x];
-    auto val = [&](int64_t i) -> uint32_t { return (uint32_t)img[F.base + i * F.stride]; };
-    auto add = [&](uint32_t v, int64_t c) {
-        if (v < (uint32_t)m) atomicAdd((unsigned long long *)&out[v], (unsigned long long)c);
+// Faces of the box of at most two dimensions, largest-value convention, with
+// their signs: all of them in one launch, into count rows that are merged with
+// the volume's (each face had a gather, a kernel and two merge launches of its
+// own before: 400 x 413 x 390 takes 115 us per dual curve, from
+// 187; a 2000 x 3000 image 46, from 91).
+// A face of na x nb voxels has the cells (interval or vertex) x (interval or
+// vertex); position (i, j), 0 <= i <= na and 0 <= j <= nb, stands for vertex i
+// by vertex j, and for interval i by vertex j where i < na, and so on; a
+// cell's value is the largest of the voxels around it.  An axis that the face
+// does not have (n = 0) has one vertex with one voxel.  Values >= m are
+// skipped (the volume's own launch reports them as range errors).
+// A wave's unit is 64 columns of up to kFaceRows consecutive rows of one face:
+// it walks them four rows of loads at a time, the row before and the columns
+// to the left already in its registers.  The loads' latency bounds it, so the
+// units are short and spread over up to one workgroup per CU; a workgroup's
+// waves count in one LDS histogram and write it out as a row, at m-1-v as the
+// volume's kernel does (most bins are touched, so adding them to one vector by
+// global atomics costs more than the rows).  The six 2-D faces of 400 x 413 x
+// 390: 16 us with 8 rows a unit and 128 workgroups that write rows; 51 us with
+// 32 rows, 35 workgroups and atomics, beside the volume.
+constexpr int kFaceRows = 8;
+struct FaceTable {
+    BoxFace f[kFacesPerLaunch];
+    int32_t first[kFacesPerLaunch + 1];  // units before face k
+    int32_t strips[kFacesPerLaunch];     // 64-column strips of face k
+    int32_t n;
+};
+
+template <typename T, int M>
+__global__ void __launch_bounds__(1024) box_faces_kernel(const T *__restrict__ img, FaceTable t,
+                                                         int32_t *__restrict__ out) {
+    __shared__ __align__(16) int32_t hist[M];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < M; i += 1024) hist[i] = 0;
+    __syncthreads();
+    auto add = [&](bool ok, uint32_t v, int s) {
+        if (ok && v < (uint32_t)M) atomicAdd(&hist[M - 1 - v], s);
     };
-    const int64_t s = F.sign;
-    for (int64_t i = threadIdx.x; i <= F.len; i += blockDim.x) {
-        if (F.len == 0) {  // a corner: one vertex
-            if (i == 0) add(val(0), s);
-            continue;
+    int k = 0;
+    for (int unit = (int)blockIdx.x * 16 + __builtin_amdgcn_readfirstlane(wave); unit < t.first[t.n];
+         unit += (int)gridDim.x * 16) {
+        while (k + 1 < t.n && t.first[k + 1] <= unit) ++k;
+        const BoxFace F = t.f[k];
+        const int u = unit - t.first[k];
+        const int64_t r0 = (int64_t)(u / t.strips[k]) * kFaceRows;
+        const int64_t r1 = r0 + kFaceRows < F.na + 1 ? r0 + kFaceRows : F.na + 1;
+        const int64_t j = (int64_t)(u % t.strips[k]) * 64 + lane;
+        const bool pos = j <= F.nb, mid = j < F.nb || F.nb == 0, edge = lane == 0 && j > 0;
+        const int s = F.sign;
+        // the value at (i, j), and at (i, j - 1); 0 where there is none
+        auto load = [&](int64_t i, uint32_t &v, uint32_t &left) {
+            const bool here = i >= 0 && (i < F.na || (F.na == 0 && i == 0));
+            const T *p = img + F.base + i * F.sa + j * F.sb;
+            v = here && mid ? p[0] : 0u;
+            left = here && edge ? p[-F.sb] : 0u;
+        };
+        auto with_left = [&](uint32_t v, uint32_t left) {  // lane 0 keeps its own load
+            return (uint32_t)__builtin_amdgcn_update_dpp((int)left, (int)v, 0x138, 0xF, 0xF, false);
+        };
+        uint32_t v01, v00;
+        load(r0 - 1, v01, v00);
+        v00 = with_left(v01, v00);
+        for (int64_t i = r0; i < r1; i += 4) {
+            uint32_t v[4], left[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) load(i + q < r1 ? i + q : -1, v[q], left[q]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t v11 = v[q], v10 = with_left(v11, left[q]);
+                const uint32_t a = max(v10, v11), b = max(v01, v11);
+                const bool row = pos && i + q < r1, ia = row && i + q < F.na, ib = row && j < F.nb;
+                add(row, max(max(a, b), v00), s);
+                add(ia, a, -s);
+                add(ib, b, -s);
+                add(ia && ib, v11, s);
+                v01 = v11;
+                v00 = v10;
+            }
         }
-        // vertex i: between voxels i-1 and i (one voxel at either end)
-        const uint32_t a = i > 0 ? val(i - 1) : 0u, b = i < F.len ? val(i) : 0u;
-        add(i == 0 ? b : i == F.len ? a : (a > b ? a : b), s);
-        if (i < F.len) add(b, -s);  // interval i
     }
+    __syncthreads();
+    int32_t *row = out + (size_t)blockIdx.x * M;
+    for (int i = tid * 4; i < M; i += 4096) *(int4 *)&row[i] = *(const int4 *)&hist[i];
 }
 
-int launch_low_faces(const void *img, int elem, const LowFace *faces_dev, int nfaces, int m, int64_t *out,
+static int64_t face_units(const BoxFace &F) { return (F.nb / 64 + 1) * (F.na / kFaceRows + 1); }
+
+int box_face_rows(const BoxFace *faces, int nfaces, int max_rows) {
+    int rows = 0;
+    for (int f0 = 0; f0 < nfaces; f0 += kFacesPerLaunch) {
+        int64_t units = 0;
+        for (int k = f0; k < nfaces && k < f0 + kFacesPerLaunch; ++k) units += face_units(faces[k]);
+        const int64_t wgs = (units + 15) / 16;
+        rows += (int)(wgs < max_rows ? wgs : max_rows);
+    }
+    return rows;
+}
+
+int launch_box_faces(const void *img, int elem, const BoxFace *faces, int nfaces, int max_rows, int32_t *rows,
                      hipStream_t stream) {
-    if (nfaces <= 0) return ECC_OK;
-    if (elem == 1)
-        hipLaunchKernelGGL(low_faces_kernel<uint8_t>, dim3(nfaces), dim3(1024), 0, stream, (const uint8_t *)img,
-                           faces_dev, m, out);
-    else
-        hipLaunchKernelGGL(low_faces_kernel<uint16_t>, dim3(nfaces), dim3(1024), 0, stream, (const uint16_t *)img,
-                           faces_dev, m, out);
-    ECC_HIP(hipGetLastError());
+    for (int f0 = 0; f0 < nfaces; f0 += kFacesPerLaunch) {
+        FaceTable t{};
+        t.n = nfaces - f0 < kFacesPerLaunch ? nfaces - f0 : kFacesPerLaunch;
+        for (int k = 0; k < t.n; ++k) {
+            const BoxFace &F = faces[f0 + k];
+            t.f[k] = F;
+            const int64_t units = face_units(F);
+            // (a thread's next unit stays below 2^31; an image of that size does not fit the card)
+            if (t.first[k] + units > INT32_MAX / 2) {
+                set_error("ecc_compute_dual: face too large");
+                return ECC_E_UNSUPPORTED;
+            }
+            t.strips[k] = (int32_t)(F.nb / 64 + 1);
+            t.first[k + 1] = t.first[k] + (int32_t)units;
+        }
+        const int grid = box_face_rows(faces + f0, t.n, max_rows);
+        if (elem == 1)
+            hipLaunchKernelGGL((box_faces_kernel<uint8_t, 256>), dim3(grid), dim3(1024), 0, stream, (const uint8_t *)img, t,
+                               rows);
+        else
+            hipLaunchKernelGGL((box_faces_kernel<uint16_t, 16384>), dim3(grid), dim3(1024), 0, stream,
+                               (const uint16_t *)img, t, rows);
+        ECC_HIP(hipGetLastError());
+        rows += (size_t)grid * (elem == 1 ? 256 : 16384);
+    }
     return ECC_OK;
 }
 
@@ -471,7 +558,7 @@ int launch_minmax_u16(const uint16_t *img, int64_t n, uint32_t *out, hipStream_t
 constexpr int kSmallMergeRows = 256;
 __global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *__restrict__ partial, int rows, int m,
                                                                 int64_t *__restrict__ vcec, int accumulate, int reverse,
-                                                                int64_t *__restrict__ chi, uint32_t *status,
+                                                                int negate, int64_t *__restrict__ chi, uint32_t *status,
                                                                 uint32_t *status_out) {
     __shared__ unsigned long long col[1024];
     __shared__ int64_t sh[16];
@@ -515,7 +602,7 @@ __global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *_
     int64_t v = 0;
     if (own) {
         if (rows == 0 || accumulate) v = vcec[tid];
-        v += (int64_t)col[tid];
+        v += negate ? -(int64_t)col[tid] : (int64_t)col[tid];
         if (rows > 0) vcec[tid] = v;
     }
     int64_t x = v;
@@ -538,33 +625,33 @@ __global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *_
 static int64_t *merge_totals(uint32_t *status) { return reinterpret_cast<int64_t *>(status) + kStatusTotalsOffset / 8; }
 
 static int launch_colsum(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, int64_t *totals,
-                         int64_t *clear, bool hand, uint32_t *status, hipStream_t stream, bool reverse) {
+                         int64_t *clear, bool hand, uint32_t *status, hipStream_t stream, bool reverse, bool negate) {
     if (rows <= 64)
         hipLaunchKernelGGL(colsum_kernel<16>, dim3(m / kColBlock), dim3(256), 0, stream, partial, rows, m, vcec,
-                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, clear, hand ? 1 : 0, status);
+                           accumulate ? 1 : 0, reverse ? 1 : 0, negate ? 1 : 0, totals, clear, hand ? 1 : 0, status);
     else
         hipLaunchKernelGGL(colsum_kernel<64>, dim3(m / kColBlock), dim3(1024), 0, stream, partial, rows, m, vcec,
-                           accumulate ? 1 : 0, reverse ? 1 : 0, totals, clear, hand ? 1 : 0, status);
+                           accumulate ? 1 : 0, reverse ? 1 : 0, negate ? 1 : 0, totals, clear, hand ? 1 : 0, status);
     ECC_HIP(hipGetLastError());
     return ECC_OK;
 }
 
 int launch_merge(const int32_t *partial, int rows, int m, int64_t *vcec, bool accumulate, bool do_scan, int64_t *chi,
-                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse) {
+                 uint32_t *status, uint32_t *status_out, hipStream_t stream, bool reverse, bool negate) {
     if (m % 256 != 0 || m > 65536 || (m < 1024 && 1024 % m != 0)) {
         set_error("launch_merge: m = %d not supported", m);
         return ECC_E_ARG;
     }
     if (do_scan && m <= 1024 && rows <= kSmallMergeRows) {
         hipLaunchKernelGGL(merge_scan_small_kernel, dim3(1), dim3(1024), 0, stream, partial, rows, m, vcec,
-                           accumulate ? 1 : 0, reverse ? 1 : 0, chi, status, status_out);
+                           accumulate ? 1 : 0, reverse ? 1 : 0, negate ? 1 : 0, chi, status, status_out);
         ECC_HIP(hipGetLastError());
         return ECC_OK;
     }
     int64_t *totals = merge_totals(status);
     if (rows > 0) {
         int rc = launch_colsum(partial, rows, m, vcec, accumulate, do_scan ? totals : nullptr, nullptr, do_scan, status,
-                               stream, reverse);
+                               stream, reverse, negate);
         if (rc) return rc;
     }
     if (do_scan) {
@@ -582,7 +669,7 @@ int launch_merge_half(const int32_t *partial, int rows, int64_t *vcec16, int hal
                       hipStream_t stream) {
     constexpr int m = 32768;
     return launch_colsum(partial, rows, m, vcec16 + half * m, false, merge_totals(status) + half * (m / kColBlock),
-                         clear ? vcec16 + m : nullptr, false, status, stream, false);
+                         clear ? vcec16 + m : nullptr, false, status, stream, false, false);
 }
 
 int launch_scan_halves(const int64_t *vcec16, int64_t *chi, uint32_t *status, uint32_t *status_out, hipStream_t stream) {
