@@ -250,8 +250,8 @@ int launch_batch_merge(const void *table_dev, int colsum_grid, int scan_grid, hi
 // Order-preserving 32-bit key of a float's bits: -0 is folded into +0; sign
 // bit set: all bits flipped, else the sign bit set.
 __device__ __forceinline__ uint32_t f32_key(uint32_t u) {
-    if ((u & 0x7FFFFFFFu) == 0u) u = 0u;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+    u = __float_as_uint(__uint_as_float(u) + 0.0f);  // -0 + 0 = +0; other values stay (denormals too)
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
 // Change kernel (ecc_change.hip): planes [e0, e1) of axis 0 of an image with
