@@ -85,6 +85,85 @@ hipError_t dev_malloc(void **p, size_t bytes) {
     return hipMalloc(p, bytes);
 }
 
+// Device blocks of finished ecc_stream objects, kept for the next ones (a
+// block is given to one object at a time, and comes back when the work that
+// used it is done).  At most kCacheBytes are kept, none above kCacheBlock;
+// ecc_release_workspaces frees them.
+constexpr size_t kCacheBytes = (size_t)256 << 20, kCacheBlock = (size_t)64 << 20;
+struct CachedBlock {
+    int dev;
+    void *p;
+    size_t bytes;
+};
+static std::mutex g_cache_mu;
+static std::vector<CachedBlock> g_cache;
+static size_t g_cache_held = 0;
+
+hipError_t cache_release(int dev) {
+    std::vector<CachedBlock> mine;
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        for (size_t i = 0; i < g_cache.size();) {
+            if (g_cache[i].dev != dev) {
+                ++i;
+                continue;
+            }
+            g_cache_held -= g_cache[i].bytes;
+            mine.push_back(g_cache[i]);
+            g_cache[i] = g_cache.back();
+            g_cache.pop_back();
+        }
+    }
+    hipError_t first = hipSuccess;
+    for (const CachedBlock &c : mine) {
+        const hipError_t e = hipFree(c.p);
+        if (e != hipSuccess && first == hipSuccess) first = e;
+    }
+    return first;
+}
+
+hipError_t cache_malloc(int dev, void **p, size_t bytes, size_t *got) {
+    if (injected_failure()) return hipErrorOutOfMemory;
+    bytes = (bytes + 4095) & ~(size_t)4095;
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        size_t best = g_cache.size();  // the smallest that fits and is at most a quarter larger
+        for (size_t i = 0; i < g_cache.size(); ++i)
+            if (g_cache[i].dev == dev && g_cache[i].bytes >= bytes && g_cache[i].bytes <= bytes + bytes / 4 &&
+                (best == g_cache.size() || g_cache[i].bytes < g_cache[best].bytes))
+                best = i;
+        if (best < g_cache.size()) {
+            *p = g_cache[best].p;
+            *got = g_cache[best].bytes;
+            g_cache_held -= *got;
+            g_cache[best] = g_cache.back();
+            g_cache.pop_back();
+            return hipSuccess;
+        }
+    }
+    *got = bytes;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        (void)cache_release(dev);
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+
+void cache_free(int dev, void *p, size_t bytes) {
+    if (!p) return;
+    if (bytes <= kCacheBlock) {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        if (g_cache_held + bytes <= kCacheBytes) {
+            g_cache.push_back({dev, p, bytes});
+            g_cache_held += bytes;
+            return;
+        }
+    }
+    (void)hipFree(p);
+}
+
 hipError_t host_malloc(void **p, size_t bytes, unsigned flags) {
     if (injected_failure()) return hipErrorOutOfMemory;
     return hipHostMalloc(p, bytes, flags);
@@ -1264,7 +1343,8 @@ void ecc_autotune_reset(void) {
     g_tuned.clear();
 }
 
-// The growable scratch of every workspace of the current device is freed
+// The growable scratch of every workspace of the current device is freed, as
+// are the blocks kept for its ecc_stream objects
 // (the small status block and host word stay, so the workspaces remain
 // valid); the next call on a stream grows its buffers again.  Work still in
 // flight on the device may use them: it is waited for first.
@@ -1272,8 +1352,8 @@ int ecc_release_workspaces(void) {
     int dev = 0;
     ECC_HIP(hipGetDevice(&dev));
     ECC_HIP(hipDeviceSynchronize());
+    hipError_t first = cache_release(dev);
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    hipError_t first = hipSuccess;
     auto drop = [&](void *p, size_t *cap) {
         if (p) {
             const hipError_t e = hipFree(p);

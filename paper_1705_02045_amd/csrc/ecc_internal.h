@@ -131,6 +131,13 @@ struct Workspace {
 // hipMalloc / hipHostMalloc through the allocation-failure injection hook
 // (ECC_FAIL_ALLOC, ecc_api.cpp); every allocation of the library uses them.
 hipError_t dev_malloc(void **p, size_t bytes);
+// Device memory of device dev (the current one) from the blocks that finished
+// ecc_stream objects left, or new: *got bytes, which cache_free() is given
+// back with once no work uses them.  A request counts as an allocation
+// whether or not a block was kept.
+hipError_t cache_malloc(int dev, void **p, size_t bytes, size_t *got);
+void cache_free(int dev, void *p, size_t bytes);
+hipError_t cache_release(int dev);
 hipError_t host_malloc(void **p, size_t bytes, unsigned flags);
 
 int get_workspace(void *stream, Workspace **out);

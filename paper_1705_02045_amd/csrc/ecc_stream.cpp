@@ -27,7 +27,7 @@ struct ecc_stream {
     ecc_dims dims{};  // as given to ecc_stream_begin
     int device = -1;
     hipStream_t compute = nullptr;  // caller's stream
-    hipStream_t copy = nullptr;     // owned
+    hipStream_t copy = nullptr;     // owned, made with the events at the first host chunk
     ecc::IntView view{};
     int dtype = 0;
     int m = 0;
@@ -37,11 +37,12 @@ struct ecc_stream {
     // carry buffers of two planes: [0, ncarry) hold image planes
     // [pushed - ncarry, pushed)
     uint8_t *carry_buf[2] = {nullptr, nullptr};
+    size_t carry_bytes[2] = {0, 0};
     int cur = 0;
     int ncarry = 0;
     // staging for host chunks
     uint8_t *stage[2] = {nullptr, nullptr};
-    size_t stage_cap = 0;
+    size_t stage_bytes[2] = {0, 0};
     hipEvent_t ready[2] = {nullptr, nullptr};
     hipEvent_t released[2] = {nullptr, nullptr};
     bool released_recorded[2] = {false, false};
@@ -50,7 +51,9 @@ struct ecc_stream {
     int32_t *partial = nullptr;
     size_t partial_bytes = 0;
     int64_t *vcec = nullptr;
+    size_t vcec_bytes = 0;
     uint32_t *status = nullptr;
+    size_t status_bytes = 0;
     // 4-D images: extents
     bool four_d = false;
     int64_t n4[4] = {0, 0, 0, 0};
@@ -65,20 +68,52 @@ void destroy(ecc_stream *st) {
     int prev = -1;
     (void)hipGetDevice(&prev);
     if (st->device >= 0) (void)hipSetDevice(st->device);
-    if (st->compute) (void)hipStreamSynchronize(st->compute);
-    if (st->copy) (void)hipStreamSynchronize(st->copy);
+    // (the blocks may go to another object: the work on them ends first)
+    if (hipStreamSynchronize(st->compute) != hipSuccess) (void)hipDeviceSynchronize();
+    if (st->copy && hipStreamSynchronize(st->copy) != hipSuccess) (void)hipDeviceSynchronize();
     for (int i = 0; i < 2; ++i) {
-        if (st->carry_buf[i]) (void)hipFree(st->carry_buf[i]);
-        if (st->stage[i]) (void)hipFree(st->stage[i]);
+        cache_free(st->device, st->carry_buf[i], st->carry_bytes[i]);
+        cache_free(st->device, st->stage[i], st->stage_bytes[i]);
         if (st->ready[i]) (void)hipEventDestroy(st->ready[i]);
         if (st->released[i]) (void)hipEventDestroy(st->released[i]);
     }
-    if (st->partial) (void)hipFree(st->partial);
-    if (st->vcec) (void)hipFree(st->vcec);
-    if (st->status) (void)hipFree(st->status);
+    cache_free(st->device, st->partial, st->partial_bytes);
+    cache_free(st->device, st->vcec, st->vcec_bytes);
+    cache_free(st->device, st->status, st->status_bytes);
     if (st->copy) (void)hipStreamDestroy(st->copy);
     if (prev >= 0) (void)hipSetDevice(prev);
     delete st;
+}
+
+// A buffer of at least need bytes, its contents lost if it grows.
+template <typename T>
+int take(ecc_stream *st, T **p, size_t *cap, size_t need) {
+    if (*p && *cap >= need) return ECC_OK;
+    if (*p) {
+        // (its block may go to another object: the work on it ends first)
+        ECC_HIP(hipStreamSynchronize(st->compute));
+        if (st->copy) ECC_HIP(hipStreamSynchronize(st->copy));
+        cache_free(st->device, *p, *cap);
+        *p = nullptr;
+        *cap = 0;
+    }
+    void *q = nullptr;
+    size_t got = 0;
+    const hipError_t e = cache_malloc(st->device, &q, need, &got);
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc(stream)");
+    *p = (T *)q;
+    *cap = got;
+    return ECC_OK;
+}
+
+// The copy stream and its events, at the first host chunk.
+int make_copy_stream(ecc_stream *st) {
+    for (int i = 0; i < 2; ++i) {
+        if (!st->ready[i]) ECC_HIP(hipEventCreateWithFlags(&st->ready[i], hipEventDisableTiming));
+        if (!st->released[i]) ECC_HIP(hipEventCreateWithFlags(&st->released[i], hipEventDisableTiming));
+    }
+    if (!st->copy) ECC_HIP(hipStreamCreateWithFlags(&st->copy, hipStreamNonBlocking));
+    return ECC_OK;
 }
 
 bool is_device_ptr(const void *p) {
@@ -112,7 +147,7 @@ int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int
     int rows = 0;
     int rc = change_count_rows(j, &rows);
     if (rc) return rc;
-    rc = ensure_bytes((void **)&st->partial, &st->partial_bytes, (size_t)rows * st->m * sizeof(int32_t));
+    rc = take(st, &st->partial, &st->partial_bytes, (size_t)rows * st->m * sizeof(int32_t));
     if (rc) return rc;
     rc = launch_change_counts(j, st->partial, nullptr, st->status, st->compute);
     if (rc) return rc;
@@ -148,7 +183,7 @@ int run_chunk(ecc_stream *st, const uint8_t *chunk, int64_t f, int64_t n, int64_
         const bool u16 = st->dtype == ECC_U16;
         const IntTiling tl = u16 ? range_pass_tiling(st->view, hi - lo) : choose_int_tiling(st->view, st->dtype, hi - lo);
         const int mloc = u16 ? 32768 : st->m;  // bins of one launch
-        int rc = ensure_bytes((void **)&st->partial, &st->partial_bytes, (size_t)tl.grid * mloc * sizeof(int32_t));
+        int rc = take(st, &st->partial, &st->partial_bytes, (size_t)tl.grid * mloc * sizeof(int32_t));
         if (rc) return rc;
         if (u16) {
             // two 32768-bin passes, each adding the values of its half of
@@ -276,19 +311,10 @@ int ecc_stream_begin(const ecc_dims *full_dims, ecc_dtype dtype, void *stream, e
         return code;
     };
     if (hipGetDevice(&st->device) != hipSuccess) return fail(hip_fail(hipErrorInvalidDevice, "hipGetDevice"));
-    hipError_t e = hipStreamCreateWithFlags(&st->copy, hipStreamNonBlocking);
-    if (e != hipSuccess) return fail(hip_fail(e, "hipStreamCreate"));
-    for (int i = 0; i < 2; ++i) {
-        if ((e = dev_malloc((void **)&st->carry_buf[i], (size_t)st->plane_bytes * 2)) != hipSuccess)
-            return fail(hip_fail(e, "hipMalloc(carry)"));
-        if ((e = hipEventCreateWithFlags(&st->ready[i], hipEventDisableTiming)) != hipSuccess)
-            return fail(hip_fail(e, "hipEventCreate"));
-        if ((e = hipEventCreateWithFlags(&st->released[i], hipEventDisableTiming)) != hipSuccess)
-            return fail(hip_fail(e, "hipEventCreate"));
-    }
-    if ((e = dev_malloc((void **)&st->vcec, (size_t)st->m * sizeof(int64_t))) != hipSuccess)
-        return fail(hip_fail(e, "hipMalloc(vcec)"));
-    if ((e = dev_malloc((void **)&st->status, kStatusBytes)) != hipSuccess) return fail(hip_fail(e, "hipMalloc(status)"));
+    for (int i = 0; i < 2; ++i)
+        if ((rc = take(st, &st->carry_buf[i], &st->carry_bytes[i], (size_t)st->plane_bytes * 2))) return fail(rc);
+    if ((rc = take(st, &st->vcec, &st->vcec_bytes, (size_t)st->m * sizeof(int64_t)))) return fail(rc);
+    if ((rc = take(st, &st->status, &st->status_bytes, kStatusBytes))) return fail(rc);
     if ((rc = launch_zero(st->vcec, (size_t)st->m * sizeof(int64_t), st->compute))) return fail(rc);
     if ((rc = launch_zero(st->status, kStatusBytes, st->compute))) return fail(rc);
     *out = st;
@@ -319,17 +345,14 @@ int ecc_stream_push_chunk(ecc_stream *st, const void *planes, int64_t n_planes) 
         // Host chunk: copy into staging buffer k % 2 on the copy stream, after
         // the kernels that last read that buffer are done.
         const int k = st->nstaged & 1;
-        if (bytes > st->stage_cap) {
-            ECC_HIP(hipStreamSynchronize(st->compute));
-            ECC_HIP(hipStreamSynchronize(st->copy));
-            for (int i = 0; i < 2; ++i) {
-                if (st->stage[i]) ECC_HIP(hipFree(st->stage[i]));
-                st->stage[i] = nullptr;
-                st->released_recorded[i] = false;
-            }
-            st->stage_cap = 0;
-            for (int i = 0; i < 2; ++i) ECC_HIP(dev_malloc((void **)&st->stage[i], bytes));
-            st->stage_cap = bytes;
+        rc = make_copy_stream(st);
+        for (int i = 0; i < 2 && !rc; ++i) {
+            if (st->stage_bytes[i] < bytes) st->released_recorded[i] = false;  // (take waits for its readers)
+            rc = take(st, &st->stage[i], &st->stage_bytes[i], bytes);
+        }
+        if (rc) {
+            if (prev != st->device) (void)hipSetDevice(prev);
+            return rc;
         }
         if (st->released_recorded[k]) ECC_HIP(hipStreamWaitEvent(st->copy, st->released[k], 0));
         ECC_HIP(hipMemcpyAsync(st->stage[k], planes, bytes, hipMemcpyHostToDevice, st->copy));
@@ -389,11 +412,9 @@ int ecc_stream_finish(ecc_stream *st, ecc_curve *curve) {
             break;
         }
         int64_t *tmp = nullptr;
-        hipError_t e = dev_malloc((void **)&tmp, (size_t)st->m * sizeof(int64_t));
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "hipMalloc(curve)");
-            break;
-        }
+        size_t tmp_bytes = 0;
+        if ((rc = take(st, &tmp, &tmp_bytes, (size_t)st->m * sizeof(int64_t)))) break;
+        hipError_t e = hipSuccess;
         rc = launch_merge(nullptr, 0, st->m, st->vcec, true, true, tmp, st->status, st->status + 2,
                           st->compute);
         uint32_t stv = 0;
@@ -415,7 +436,8 @@ int ecc_stream_finish(ecc_stream *st, ecc_curve *curve) {
             if (e != hipSuccess) rc = hip_fail(e, "curve copy");
             else curve->count = st->m;
         }
-        (void)hipFree(tmp);
+        if (rc) (void)hipStreamSynchronize(st->compute);
+        cache_free(st->device, tmp, tmp_bytes);
     } while (0);
     destroy(st);
     if (prev >= 0) (void)hipSetDevice(prev);
@@ -457,7 +479,7 @@ int ecc_stream_snapshot(ecc_stream *st, void *host_buf, int64_t capacity) {
     h.plane_bytes = st->plane_bytes;
     h.ncarry = st->ncarry;
     uint8_t *out = (uint8_t *)host_buf;
-    hipError_t e = hipStreamSynchronize(st->copy);
+    hipError_t e = st->copy ? hipStreamSynchronize(st->copy) : hipSuccess;
     if (e == hipSuccess) e = hipMemcpyAsync(out + sizeof h, st->vcec, (size_t)st->m * 8, hipMemcpyDeviceToHost, st->compute);
     if (e == hipSuccess && st->ncarry > 0)
         e = hipMemcpyAsync(out + sizeof h + (size_t)st->m * 8, st->carry_buf[st->cur],
