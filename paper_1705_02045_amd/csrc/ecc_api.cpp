@@ -915,8 +915,9 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
         img_dev = (const float *)ws->img_tmp;
     }
     // carve the float scratch: two key buffers (sort), the record regions
-    // (after the records are compacted, the change-point output's chi), the region counts and offsets, the digit table and its
-    // scan sums, the curve's tile sums, the counts
+    // (after the records are compacted, the change-point output's chi), the
+    // region counts and offsets, the split's first slots and head, the digit
+    // table and its scan sums, the curve's tile sums, the counts
     ChangeJob job{};
     rc = float_job(img_dev, dims, &job);
     if (rc) return rc;
@@ -927,11 +928,13 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     const int64_t slots = std::max(regions * region_slots, steps_only ? n : 0);
     const int64_t digit_entries = std::max(radix_count_entries(n, 4), radix_count_entries(n, 8));
     const int64_t ft = float_tiles(n);
-    enum { kKey0, kKey1, kNz, kNzCnt, kNzOff, kCounts, kSums, kTileA, kTileB, kBound, kCnt, kSteps, kNbuf };
+    enum { kKey0, kKey1, kNz, kNzCnt, kNzOff, kStarts, kHead, kCounts, kSums, kTileA, kTileB, kBound, kCnt, kSteps, kNbuf };
     size_t off[kNbuf], total = 0;
     const int64_t scan_entries = std::max(std::max(digit_entries, regions + 1), steps_only ? n : 0);
     const size_t sz[kNbuf] = {(size_t)n * 4, (size_t)n * 4, (size_t)slots * 8, (size_t)regions * 4,
-                              (size_t)(regions + 1) * 4, (size_t)digit_entries * 4,
+                              (size_t)(regions + 1) * 4,
+                              (size_t)((n + kSplitTile - 1) / kSplitTile * kSplitBuckets) * 2, split_head_bytes(n),
+                              (size_t)digit_entries * 4,
                               (size_t)radix_scan_tiles(scan_entries) * 4, (size_t)ft * 8, (size_t)ft * 8,
                               (size_t)(ft + 1) * 8, 64,
                               steps_only ? (size_t)n * 4 : 0};
@@ -959,13 +962,14 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     int64_t *bound = (int64_t *)(b + off[kBound]);
     int64_t *count_dev = (int64_t *)(b + off[kCnt] + 8);
     int64_t *count2_dev = (int64_t *)(b + off[kCnt] + 16);
-    uint32_t *mask_dev = (uint32_t *)(b + off[kCnt] + 32);  // the key sort's top-byte mask (8 words)
+    uint16_t *starts = (uint16_t *)(b + off[kStarts]);
+    uint32_t *head = (uint32_t *)(b + off[kHead]);
     float *out_keys = direct ? curve->keys : (float *)(b + out_k);
     int64_t *out_chi = direct ? curve->chi : (int64_t *)(b + out_c);
     // the host reads which top bytes occur while the change kernel runs
     hipEvent_t ev = nullptr;
     ECC_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    rc = radix_key_counts(img_dev, n, counts, sums, mask_dev, ws->host_status_dev + 4, ws->status, ev, s);
+    rc = launch_split(img_dev, n, key[0], starts, head, ws->host_status_dev + 4, ws->status, ev, s);
     if (!rc) rc = launch_change_records(job, nz, nz_cnt, s);
     hipError_t e = hipEventSynchronize(ev);
     int present = 0;
@@ -974,8 +978,8 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
         (void)hipEventDestroy(ev);
         rc = ensure_bytes(&ws->fbits, &ws->fbits_bytes, distinct_scratch_bytes(present, n));
         if (rc) return rc;
-        rc = launch_distinct_curve(img_dev, n, present, counts, mask_dev, key[0], ws->fbits, nz, nz_cnt, regions,
-                                   region_slots, out_keys, out_chi, count_dev, s);
+        rc = launch_distinct_curve(n, present, key[0], starts, head, ws->fbits, nz, nz_cnt, regions, region_slots,
+                                   out_keys, out_chi, count_dev, s);
         if (rc) return rc;
     } else {
         // the record count, read on the host while the keys are sorted: a
@@ -986,7 +990,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
             rc = launch_nz_total(nz_cnt, nz_off, regions, sums, (int64_t *)(ws->host_status_dev + 2), s);
             if (!rc) e = hipEventRecord(ev, s);
             if (!rc && e == hipSuccess) {
-                rc = radix_sort_keys(img_dev, key, n, counts, sums, s);
+                rc = radix_sort_keys(key, n, counts, sums, s);
                 e = hipEventSynchronize(ev);
             }
         }

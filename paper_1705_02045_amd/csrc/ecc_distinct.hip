@@ -7,13 +7,15 @@
 //
 // A bit per position in memory, set by every voxel, would be bound by atomics
 // (27 G/s at random places on MI355X: 10 ms for 2^28 voxels).  So the keys
-// are first split by their lowest 9 bits, which are spread evenly in any
-// image of many values, into 512 buckets (one pass: digit counts, their scan,
-// a scatter that need not keep an order), and a bucket's bits, one per
-// remaining value (P * 2^15), are set in LDS:
-//  1. bucket_scatter_kernel: the keys by bucket, as idx = p >> 9;
+// are first put in order of their lowest 9 bits, which are spread evenly in
+// any image of many values, within tiles of 16384; the keys of one of the 512
+// buckets are then a run in each tile, and a bucket's bits, one per remaining
+// value (P * 2^15), are set in LDS:
+//  1. split_kernel: the tiles' keys by bucket, the buckets' first slots in
+//     each tile and their totals; also which top bytes occur;
 //  2. bucket_bits_kernel: a workgroup per bucket (large ones are shared) sets
-//     the bucket's bits in LDS, P * 4 KiB, and adds them to bits[bucket][idx];
+//     the bits of its runs in LDS, P * 4 KiB, and adds them to
+//     bits[bucket][p >> 9];
 //  3. order_bits_kernel: bits[bucket][idx] to the order of p (idx first, then
 //     the bucket), with the count of set bits before each block of 256;
 //  4. expand_kernel: the k-th set bit is the k-th distinct value; its chi is
@@ -47,101 +49,164 @@ __device__ __forceinline__ void rank_table(const uint32_t *__restrict__ mask, ui
     __syncthreads();
 }
 
-// ---- 1. A workgroup takes two of the digit counts' tiles (the order within a
-// bucket is free), so that a bucket's run in it, 32 keys on average, fills a
-// line of memory: 2^28 keys take 530 us, 596 with one tile.
+// ---- 1. Bound by memory (a read and a write of every key, both in whole
+// lines): 2^28 keys take 440 us.  (Scattering the keys to the buckets instead
+// took 530 us, and counting them per tile and digit before it 320.)  The next
+// tile is not loaded ahead: two workgroups per CU overlap.
 constexpr int kThreads = 1024;
 constexpr int kItems = 16;
 constexpr int kTile = kThreads * kItems;
-constexpr int kCountTiles = kTile / kKeyTile;
+static_assert(kTile == kSplitTile && kBuckets == kSplitBuckets, "the tiles that the caller makes room for");
 
-__global__ void __launch_bounds__(kThreads) bucket_scatter_kernel(const float *__restrict__ img, int64_t n, int64_t tiles,
-                                                                  const uint32_t *__restrict__ offsets,
-                                                                  const uint32_t *__restrict__ mask,
-                                                                  uint32_t *__restrict__ out) {
-    __shared__ uint32_t buf[kTile];       // the tile's keys by bucket
-    __shared__ uint32_t cnt[kBuckets];    // keys per bucket, then the bucket's first slot
-    __shared__ uint32_t dest[kBuckets];   // output position minus slot
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8)))
+split_kernel(const float *__restrict__ img, int64_t n, int64_t tiles, uint32_t *__restrict__ out,
+             uint16_t *__restrict__ starts, uint32_t *__restrict__ rows, uint32_t *__restrict__ mask,
+             uint32_t *status) {
+    __shared__ __align__(16) uint32_t buf[kTile];  // the tile's keys by bucket
+    __shared__ uint32_t cnt[kBuckets];             // keys per bucket, then the bucket's first slot
     __shared__ uint32_t ws[kBuckets / 64];
-    __shared__ uint8_t rank[256];
+    __shared__ uint8_t present[256];  // top bytes seen
     const int tid = threadIdx.x, lane = tid & 63;
-    const uint32_t tile = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t t0 = (int64_t)tile * kTile;
-    const int valid = (int)std::min<int64_t>(kTile, n - t0);
-    const uint32_t gpos = tid < kBuckets ? offsets[(int64_t)tid * tiles + (int64_t)tile * kCountTiles] : 0u;
     if (tid < kBuckets) cnt[tid] = 0;
-    rank_table(mask, rank);
-    uint32_t key[kItems], at[kItems];
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(img) + t0;
-    const bool vec = valid == kTile && (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
-    if (vec) {
+    if (tid < 256) present[tid] = 0;
+    __syncthreads();
+    uint32_t mine = 0;     // this thread's bucket's keys
+    uint32_t last = 256u;  // the top byte this thread noted last (neighbouring voxels share theirs)
+    bool nan = false;
+    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int64_t t0 = tile * kTile;
+        const int valid = (int)std::min<int64_t>(kTile, n - t0);
+        uint32_t key[kItems], at[kItems / 2];  // at: places in the buckets, two per word
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(img) + t0;
+        const bool vec = valid == kTile && (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
+        if (vec) {
 #pragma unroll
-        for (int q = 0; q < kItems / 4; ++q) {
-            const uint4 w = reinterpret_cast<const uint4 *>(src)[q * kThreads + tid];
-            key[4 * q] = w.x;
-            key[4 * q + 1] = w.y;
-            key[4 * q + 2] = w.z;
-            key[4 * q + 3] = w.w;
+            for (int q = 0; q < kItems / 4; ++q) {
+                const uint4 w = reinterpret_cast<const uint4 *>(src)[q * kThreads + tid];
+                key[4 * q] = w.x;
+                key[4 * q + 1] = w.y;
+                key[4 * q + 2] = w.z;
+                key[4 * q + 3] = w.w;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < kItems; ++j) key[j] = j * kThreads + tid < valid ? src[j * kThreads + tid] : 0u;
         }
-    } else {
 #pragma unroll
-        for (int j = 0; j < kItems; ++j) key[j] = j * kThreads + tid < valid ? src[j * kThreads + tid] : 0u;
-    }
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        key[j] = f32_key(key[j]);
-        if (vec || j * kThreads + tid < valid) at[j] = atomicAdd(&cnt[key[j] & (kBuckets - 1)], 1u);
-    }
-    __syncthreads();
-    // first slot of each bucket
-    uint32_t c = 0, x = 0;
-    if (tid < kBuckets) {
-        c = x = cnt[tid];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
+        for (int j = 0; j < kItems; ++j) {
+            nan |= (key[j] & 0x7FFFFFFFu) > 0x7F800000u;
+            key[j] = f32_key(key[j]);
+            uint32_t a = 0;
+            if (vec || j * kThreads + tid < valid) {
+                const uint32_t top = key[j] >> 24;
+                if (top != last) {
+                    present[top] = 1;
+                    last = top;
+                }
+                a = atomicAdd(&cnt[key[j] & (kBuckets - 1)], 1u);
+            }
+            if (j & 1) at[j / 2] |= a << 16;
+            else at[j / 2] = a;
         }
-        if (lane == 63) ws[tid >> 6] = x;
-    }
-    __syncthreads();
-    if (tid < kBuckets) {
-        uint32_t s = x - c;
-        for (int w = 0; w < (tid >> 6); ++w) s += ws[w];
-        cnt[tid] = s;
-        dest[tid] = gpos - s;  // (mod 2^32: positions are below 2^30)
-    }
-    __syncthreads();
+        __syncthreads();
+        // first slot of each bucket
+        uint32_t c = 0, x = 0;
+        if (tid < kBuckets) {
+            c = x = cnt[tid];
 #pragma unroll
-    for (int j = 0; j < kItems; ++j)
-        if (vec || j * kThreads + tid < valid) buf[cnt[key[j] & (kBuckets - 1)] + at[j]] = key[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-        const int s = j * kThreads + tid;
-        if (s < valid) {
-            const uint32_t k = buf[s];
-            out[dest[k & (kBuckets - 1)] + (uint32_t)s] = ((uint32_t)rank[k >> 24] << (24 - kBucketBits)) | ((k & 0xFFFFFFu) >> kBucketBits);
+            for (int off = 1; off < 64; off <<= 1) {
+                const uint32_t u = __shfl_up(x, off, 64);
+                if (lane >= off) x += u;
+            }
+            if (lane == 63) ws[tid >> 6] = x;
         }
+        __syncthreads();
+        if (tid < kBuckets) {
+            uint32_t s = x - c;
+            for (int w = 0; w < (tid >> 6); ++w) s += ws[w];
+            cnt[tid] = s;
+            starts[tile * kBuckets + tid] = (uint16_t)s;
+            mine += c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kItems; ++j)
+            if (vec || j * kThreads + tid < valid) buf[cnt[key[j] & (kBuckets - 1)] + (j & 1 ? at[j / 2] >> 16 : at[j / 2] & 0xFFFFu)] = key[j];
+        __syncthreads();
+        if (tid < kBuckets) cnt[tid] = 0;
+        if (valid == kTile) {
+#pragma unroll
+            for (int q = 0; q < kItems / 4; ++q) {
+                const int i = q * kThreads + tid;
+                reinterpret_cast<uint4 *>(out + t0)[i] = reinterpret_cast<const uint4 *>(buf)[i];
+            }
+        } else {
+            for (int i = tid; i < valid; i += kThreads) out[t0 + i] = buf[i];
+        }
+        __syncthreads();  // cnt is zero, buf is read
+    }
+    // (a row per workgroup: added to one by atomics, all on 512 words, they
+    // made the launch 5 us longer)
+    if (tid < kBuckets) rows[(size_t)blockIdx.x * kBuckets + tid] = mine;
+    if (__builtin_amdgcn_ballot_w64(nan) != 0 && lane == 0) atomicOr(status, kStatusNaN);
+    if (tid < 256) {  // wave w: bytes 64 w .. 64 w + 63, mask words 2 w and 2 w + 1
+        const uint64_t b = __builtin_amdgcn_ballot_w64(present[tid] != 0);
+        if (lane == 0 && (uint32_t)b != 0u) atomicOr(&mask[2 * (tid >> 6)], (uint32_t)b);
+        if (lane == 0 && (uint32_t)(b >> 32) != 0u) atomicOr(&mask[2 * (tid >> 6) + 1], (uint32_t)(b >> 32));
     }
 }
 
-// ---- 2. Buckets are cut into shares of at most `share` keys; a workgroup
-// takes one share (at most kBuckets + n / share of them).  A bucket of one
-// share is stored, the others are OR-ed (bits is zero before the launch).
-__global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *__restrict__ idx, int64_t n, int64_t tiles,
-                                                               const uint32_t *__restrict__ offsets, uint32_t share,
+// The buckets' totals, 64 per workgroup; the first also copies the presence
+// mask to host-mapped memory (read by the host after an event, to choose
+// between the bits of the values and the sort).
+__global__ void __launch_bounds__(1024) bucket_totals_kernel(const uint32_t *__restrict__ rows, int nrows,
+                                                             uint32_t *__restrict__ totals,
+                                                             const uint32_t *__restrict__ mask, uint32_t *host) {
+    __shared__ uint32_t part[16][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (blockIdx.x == 0 && tid < 8) host[tid] = mask[tid];
+    const int c = blockIdx.x * 64 + lane;
+    uint32_t s = 0;
+#pragma unroll 8
+    for (int r = wave; r < nrows; r += 16) s += rows[(size_t)r * kBuckets + c];
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < 16; ++w) s += part[w][lane];
+    totals[c] = s;
+}
+
+// ---- 2. A bucket of more than `share` keys is cut into shares of at most
+// that many on average, each taking every ns-th tile; a workgroup takes one
+// share (at most kBuckets + n / share of them).  A bucket of one share is
+// stored, the others are OR-ed (bits is zero before the launch).
+// A wave takes the runs of up to 46 tiles as one sequence of keys, 64 per load
+// and 12 loads in flight (a run is 32 keys on average): which run a lane's key
+// is in is the count of run ends before it.  Neighbouring buckets run on one XCD at the same pace, so the
+// lines that hold the ends of their runs and their first slots are fetched
+// once.  2^28 keys take 371 us (430 with a half-wave per run, whose lanes
+// past the run idle).
+__global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *__restrict__ keys, int64_t n, int tiles,
+                                                               const uint16_t *__restrict__ starts,
+                                                               const uint32_t *__restrict__ totals,
+                                                               const uint32_t *__restrict__ mask, uint32_t share,
                                                                int words, uint32_t *__restrict__ bits) {
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t ws[kBuckets / 64];
-    __shared__ uint32_t my[4];  // bucket, its first key, keys of this share, shares of the bucket
+    __shared__ uint32_t my[3];  // bucket, share, shares of the bucket
+    constexpr int kWaves = kThreads / 64;
+    constexpr uint32_t kMaxKeys = 2304;  // of a group: three rounds of loads, 1.56 the mean
+    __shared__ uint32_t marks[kWaves][kMaxKeys / 32];
+    __shared__ uint8_t rank[256];
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (of evenly filled buckets the first kBuckets workgroups have work)
+    const uint32_t block = blockIdx.x < kBuckets ? xcd_block(blockIdx.x, kBuckets) : blockIdx.x;
     if (tid == 0) my[2] = 0;
-    uint32_t beg = 0, len = 0, ns = 0, x = 0;
+    uint32_t ns = 0, x = 0;
     if (tid < kBuckets) {
-        beg = offsets[(int64_t)tid * tiles];
-        len = (tid + 1 < kBuckets ? offsets[(int64_t)(tid + 1) * tiles] : (uint32_t)n) - beg;
-        ns = x = (len + share - 1) / share;
+        ns = x = (totals[tid] + share - 1) / share;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const uint32_t u = __shfl_up(x, off, 64);
@@ -149,53 +214,105 @@ __global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *_
         }
         if (lane == 63) ws[tid >> 6] = x;
     }
-    for (int i = tid; i < words; i += kThreads) lds[i] = 0;
-    __syncthreads();
+    rank_table(mask, rank);
     if (tid < kBuckets) {
         uint32_t s = x - ns;  // this bucket's first workgroup
         for (int w = 0; w < (tid >> 6); ++w) s += ws[w];
-        if (blockIdx.x >= s && blockIdx.x < s + ns) {
-            const uint32_t b = (blockIdx.x - s) * share;
+        if (block >= s && block < s + ns) {
             my[0] = (uint32_t)tid;
-            my[1] = beg + b;
-            my[2] = len - b < share ? len - b : share;
-            my[3] = ns;
+            my[1] = block - s;
+            my[2] = ns;
         }
     }
     __syncthreads();
-    const uint32_t m = my[2];
-    if (m == 0) return;  // (uniform) past the last share
-    const uint32_t *src = idx + my[1];
-    auto set = [&](uint32_t v) { atomicOr(&lds[v >> 5], 1u << (v & 31u)); };
-    uint32_t head = (uint32_t)((16u - (uint32_t)(reinterpret_cast<uintptr_t>(src) & 15u)) & 15u) / 4u;
-    if (head > m) head = m;
-    if ((uint32_t)tid < head) set(src[tid]);
-    const uint32_t quads = (m - head) / 4u;
-    const uint4 *q4 = reinterpret_cast<const uint4 *>(src + head);
-    uint32_t i = tid;
-    for (; i + 3 * kThreads < quads; i += 4 * kThreads) {
-        uint4 w[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = q4[i + u * kThreads];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            set(w[u].x);
-            set(w[u].y);
-            set(w[u].z);
-            set(w[u].w);
-        }
-    }
-    for (; i < quads; i += kThreads) {
-        const uint4 w = q4[i];
-        set(w.x);
-        set(w.y);
-        set(w.z);
-        set(w.w);
-    }
-    for (uint32_t t = head + 4u * quads + tid; t < m; t += kThreads) set(src[t]);
+    const int b = __builtin_amdgcn_readfirstlane((int)my[0]), first = __builtin_amdgcn_readfirstlane((int)my[1]);
+    const int step = __builtin_amdgcn_readfirstlane((int)my[2]);
+    if (step == 0) return;  // (uniform) past the last share
+    for (int i = tid; i < words; i += kThreads) lds[i] = 0;
     __syncthreads();
-    uint32_t *dst = bits + (size_t)my[0] * words;
-    const bool whole = my[3] == 1;
+    auto set = [&](uint32_t k) {
+        atomicOr(&lds[((uint32_t)rank[k >> 24] << 10) | ((k >> 14) & 0x3FFu)], 1u << ((k >> 9) & 31u));
+    };
+    // this share's tiles: first + step * i, i < count
+    const int count = first < tiles ? (tiles - first + step - 1) / step : 0;
+    constexpr int kGroup = 46, kSteps = 12;
+    const int group = std::min(kGroup, (count + kWaves - 1) / kWaves);
+    // lane: the run of tile i0 + lane (loaded a group ahead)
+    auto fetch = [&](int i0, uint32_t &beg, uint32_t &end) {
+        beg = end = 0;
+        if (lane < group && i0 + lane < count) {
+            const int64_t t = first + (int64_t)step * (i0 + lane);
+            const uint16_t *s = starts + t * kBuckets + b;
+            beg = s[0];
+            end = b + 1 < kBuckets ? (uint32_t)s[1] : (uint32_t)std::min<int64_t>(kTile, n - t * kTile);
+        }
+    };
+    uint32_t beg1, end1;
+    fetch(wave * group, beg1, end1);
+    for (int i0 = wave * group; i0 < count; i0 += kWaves * group) {
+        const uint32_t pos = ((uint32_t)first + (uint32_t)step * (uint32_t)(i0 + lane)) * kTile + beg1, len = end1 - beg1;
+        fetch(i0 + kWaves * group, beg1, end1);
+        uint32_t x = len;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t u = __shfl_up(x, off, 64);
+            if (lane >= off) x += u;
+        }
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63), before = x - len;
+        if (total > kMaxKeys) {  // (uniform) a crowded bucket: long runs
+            for (int r = 0; r < group; ++r) {
+                const uint32_t p = (uint32_t)__builtin_amdgcn_readlane((int)pos, r);
+                const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)len, r);
+                uint32_t j = lane;
+                for (; j + 192u < l; j += 256u) {
+                    uint32_t k[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) k[q] = keys[p + j + 64u * (uint32_t)q];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) set(k[q]);
+                }
+                for (; j < l; j += 64u) set(keys[p + j]);
+            }
+            continue;
+        }
+        // the runs that are not empty to the first lanes: where key g of the
+        // group lies, less g
+        const uint64_t some = __builtin_amdgcn_ballot_w64(len != 0);
+        const uint32_t slot = __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
+        const uint32_t dst = len != 0 ? slot : (uint32_t)__builtin_popcountll(some) + (uint32_t)lane - slot;
+        const uint32_t base = (uint32_t)__builtin_amdgcn_ds_permute((int)(dst * 4u), (int)(pos - before));
+        // a bit per key: the last key of a run with another behind it
+        marks[wave][lane] = 0;
+        if (lane < (int)kMaxKeys / 32 - 64) marks[wave][64 + lane] = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (len != 0 && before != 0) atomicOr(&marks[wave][(before - 1) >> 5], 1u << ((before - 1) & 31u));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t ended = 0;  // runs that end before the step
+        for (uint32_t g0 = 0; g0 < total; g0 += 64u * kSteps) {
+            uint32_t k[kSteps];
+#pragma unroll
+            for (uint32_t q = 0; q < kSteps; ++q) {
+                const uint32_t lo = marks[wave][(g0 >> 5) + 2 * q], hi = marks[wave][(g0 >> 5) + 2 * q + 1];
+                const uint32_t r = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, ended));
+                ended += (uint32_t)__builtin_popcount(lo) + (uint32_t)__builtin_popcount(hi);
+                const uint32_t at = (uint32_t)__shfl((int)base, (int)r, 64) + g0 + 64u * q + (uint32_t)lane;
+                // (a lane past the last key reads a word in range, unused)
+                k[q] = *(const uint32_t *)((const char *)keys + std::min(at, (uint32_t)n - 1u) * 4u);
+            }
+            if (g0 + 64u * kSteps <= total) {
+#pragma unroll
+                for (uint32_t q = 0; q < kSteps; ++q) set(k[q]);
+            } else {
+#pragma unroll
+                for (uint32_t q = 0; q < kSteps; ++q)
+                    if (g0 + 64u * q + (uint32_t)lane < total) set(k[q]);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+    uint32_t *dst = bits + (size_t)b * words;
+    const bool whole = step == 1;
     for (int w = tid; w < words; w += kThreads) {
         const uint32_t v = lds[w];
         if (v == 0) continue;
@@ -393,18 +510,35 @@ __global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_
     }
 }
 
-// ---- 5. A wave per region of records.
-__global__ void __launch_bounds__(256) add_records_kernel(const uint64_t *__restrict__ nz,
-                                                          const uint32_t *__restrict__ nz_cnt, int64_t regions,
-                                                          int64_t region_slots, const uint32_t *__restrict__ ord,
-                                                          const uint32_t *__restrict__ blk,
-                                                          const uint32_t *__restrict__ base,
-                                                          const uint32_t *__restrict__ mask,
-                                                          int64_t *__restrict__ chi) {
+// ---- 5. A wave per region of records.  Up to kFewValues values (images of
+// whole numbers, say) are added in LDS first: a workgroup's int32 sums (at
+// most 2^26: a record's change is at most 16), then one global add per value
+// and workgroup.  (All of a card's adds on 4096 values, without LDS: 2.5 ms
+// for 2^26 voxels, 0.47 with it.)  More values take a global add per record,
+// which is bound by the adds where neighbouring records lie apart (2^26 voxels
+// of white noise: 2.2 ms) and by the records' reads where they don't (2^28 of
+// smooth noise: 0.35 ms).
+constexpr int kFewValues = 16384;
+constexpr uint32_t kFewGroups = 512;
+
+__global__ void __launch_bounds__(1024) add_records_kernel(const uint64_t *__restrict__ nz,
+                                                           const uint32_t *__restrict__ nz_cnt, int64_t regions,
+                                                           int64_t region_slots, const uint32_t *__restrict__ ord,
+                                                           const uint32_t *__restrict__ blk,
+                                                           const uint32_t *__restrict__ base, int tiles,
+                                                           const uint32_t *__restrict__ mask,
+                                                           int64_t *__restrict__ chi) {
+    __shared__ int32_t acc[kFewValues];
     __shared__ uint8_t rank[256];
+    const uint32_t K = base[tiles];
+    const bool few = K <= (uint32_t)kFewValues;
+    const uint32_t groups = few ? std::min(gridDim.x, kFewGroups) : gridDim.x;
+    if (blockIdx.x >= groups) return;
+    if (few)
+        for (uint32_t i = threadIdx.x; i < K; i += 1024) acc[i] = 0;
     rank_table(mask, rank);
     const int lane = threadIdx.x & 63;
-    for (int64_t reg = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); reg < regions; reg += (int64_t)gridDim.x * 4) {
+    for (int64_t reg = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 6); reg < regions; reg += (int64_t)groups * 16) {
         const uint32_t c = nz_cnt[reg];
         const uint64_t *src = nz + reg * region_slots;
         auto add = [&](uint64_t r) {
@@ -419,7 +553,8 @@ __global__ void __launch_bounds__(256) add_records_kernel(const uint64_t *__rest
 #pragma unroll
             for (uint32_t j = 0; j < 8; ++j)
                 at += (uint32_t)__builtin_popcount(w[j] & (j < wi ? 0xFFFFFFFFu : j == wi ? below : 0u));
-            atomicAdd((unsigned long long *)&chi[at], (unsigned long long)(int64_t)(int32_t)(uint32_t)r);
+            if (few) atomicAdd(&acc[at], (int32_t)(uint32_t)r);
+            else atomicAdd((unsigned long long *)&chi[at], (unsigned long long)(int64_t)(int32_t)(uint32_t)r);
         };
         uint32_t i = lane;
         for (; i + 192 < c; i += 256) {  // four records of loads in flight
@@ -430,6 +565,12 @@ __global__ void __launch_bounds__(256) add_records_kernel(const uint64_t *__rest
             for (int q = 0; q < 4; ++q) add(r[q]);
         }
         for (; i < c; i += 64) add(src[i]);
+    }
+    if (!few) return;
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < K; i += 1024) {
+        const int32_t v = acc[i];
+        if (v != 0) atomicAdd((unsigned long long *)&chi[i], (unsigned long long)(int64_t)v);
     }
 }
 
@@ -570,30 +711,53 @@ Layout layout(int present, int64_t n) {
 
 size_t distinct_scratch_bytes(int present, int64_t n) { return layout(present, n).bytes; }
 
-int launch_distinct_curve(const float *img, int64_t n, int present, const uint32_t *offsets, const uint32_t *mask,
-                          uint32_t *idx, void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
+static int split_grid(int64_t n) {
+    return (int)std::min<int64_t>((n + kTile - 1) / kTile, 2 * device_cu_count());
+}
+size_t split_head_bytes(int64_t n) { return (8 + (size_t)(1 + split_grid(n)) * kBuckets) * 4; }
+
+int launch_split(const float *img, int64_t n, uint32_t *keys, uint16_t *starts, uint32_t *head, uint32_t *mask_host_dev,
+                 uint32_t *status, hipEvent_t noted, hipStream_t stream) {
+    if (n < 1 || n >= ((int64_t)1 << 30)) {
+        set_error("internal error: split of %lld values", (long long)n);
+        return ECC_E_ARG;
+    }
+    int rc = launch_zero(head, 8 * 4, stream);
+    if (rc) return rc;
+    const int64_t tiles = (n + kTile - 1) / kTile;
+    const int grid = split_grid(n);
+    uint32_t *totals = head + 8, *rows = totals + kBuckets;
+    hipLaunchKernelGGL(split_kernel, dim3((unsigned)grid), dim3(kThreads), 0, stream, img, n, tiles, keys, starts, rows,
+                       head, status);
+    ECC_HIP(hipGetLastError());
+    hipLaunchKernelGGL(bucket_totals_kernel, dim3(kBuckets / 64), dim3(1024), 0, stream, (const uint32_t *)rows, grid,
+                       totals, (const uint32_t *)head, mask_host_dev);
+    ECC_HIP(hipGetLastError());
+    ECC_HIP(hipEventRecord(noted, stream));
+    return ECC_OK;
+}
+
+int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const uint16_t *starts, const uint32_t *head,
+                          void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
                           int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream) {
-    static_assert(kTile % kKeyTile == 0 && kBuckets == kKeyDigits, "the tiles and digits of the counts");
     if (present < 1 || present > kMaxDistinctBytes || n < 1 || n >= ((int64_t)1 << 30)) {
         set_error("internal error: %d top bytes, %lld values", present, (long long)n);
         return ECC_E_ARG;
     }
+    const uint32_t *mask = head, *totals = head + 8;
     const Layout L = layout(present, n);
     uint8_t *b = (uint8_t *)scratch;
     uint32_t *bits = (uint32_t *)(b + L.bits), *ord = (uint32_t *)(b + L.ord), *blk = (uint32_t *)(b + L.blk);
     uint32_t *total = (uint32_t *)(b + L.total), *base = (uint32_t *)(b + L.base);
     int64_t *sums = (int64_t *)(b + L.sums);
-    const int64_t tiles = (n + kKeyTile - 1) / kKeyTile;
-    hipLaunchKernelGGL(bucket_scatter_kernel, dim3((unsigned)((n + kTile - 1) / kTile)), dim3(kThreads), 0, stream, img, n, tiles, offsets,
-                       mask, idx);
-    ECC_HIP(hipGetLastError());
+    const int64_t tiles = (n + kTile - 1) / kTile;
     int rc = launch_zero(bits, (size_t)L.words * kBuckets * 4, stream);
     if (rc) return rc;
     // evenly filled buckets are one share each (a fifth above the mean)
     const int64_t share = std::max<int64_t>(4096, n / kBuckets + n / kBuckets / 5);
     const int64_t grid = kBuckets + n / share;
-    hipLaunchKernelGGL(bucket_bits_kernel, dim3((unsigned)grid), dim3(kThreads), (size_t)L.words * 4, stream,
-                       (const uint32_t *)idx, n, tiles, offsets, (uint32_t)share, L.words, bits);
+    hipLaunchKernelGGL(bucket_bits_kernel, dim3((unsigned)grid), dim3(kThreads), (size_t)L.words * 4, stream, keys, n,
+                       (int)tiles, starts, totals, mask, (uint32_t)share, L.words, bits);
     ECC_HIP(hipGetLastError());
     hipLaunchKernelGGL(order_bits_kernel, dim3((unsigned)L.tiles), dim3(256), 0, stream, (const uint32_t *)bits, L.words,
                        ord, blk, total);
@@ -607,9 +771,9 @@ int launch_distinct_curve(const float *img, int64_t n, int present, const uint32
                        (const uint32_t *)ord, (const uint32_t *)blk, (const uint32_t *)base, mask, parts, out_keys,
                        out_chi);
     ECC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(add_records_kernel, dim3((unsigned)std::min<int64_t>((regions + 3) / 4, 8192)), dim3(256), 0, stream,
-                       nz, nz_cnt, regions, region_slots, (const uint32_t *)ord, (const uint32_t *)blk,
-                       (const uint32_t *)base, mask, out_chi);
+    hipLaunchKernelGGL(add_records_kernel, dim3((unsigned)std::min<int64_t>((regions + 15) / 16, 2048)),
+                       dim3(1024), 0, stream, nz, nz_cnt, regions, region_slots, (const uint32_t *)ord,
+                       (const uint32_t *)blk, (const uint32_t *)base, L.tiles, mask, out_chi);
     ECC_HIP(hipGetLastError());
     // (K is at most n)
     const unsigned cg = (unsigned)std::min<int64_t>((n + kChiTile - 1) / kChiTile, 4096);

@@ -301,25 +301,27 @@ int64_t radix_scan_tiles(int64_t entries);
 // Digit-table entries of a sort of n words of elem bytes (digits of up to
 // 9 bits for keys, 8 for records); sums: radix_scan_tiles of that.
 int64_t radix_count_entries(int64_t n, int elem);
-// The first pass over the keys of the n floats of img: their digit counts
-// (bits 0-8) per tile of kKeyTile, scanned to output positions in counts
-// (digit-major), and the mask of the top bytes that occur: mask_dev (8 device
-// words) and, complete at the event `noted`, mask_host_dev (the device's view
-// of 8 words of host memory).  A NaN sets kStatusNaN.
-constexpr int64_t kKeyTile = 8192;
-constexpr int kKeyDigits = 512;
-int radix_key_counts(const float *img, int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
-                     uint32_t *mask_host_dev, uint32_t *status, hipEvent_t noted, hipStream_t stream);
-// The rest of the sort into key[0], after radix_key_counts.
-int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
+// Sorts key[0] in place (four passes).
+int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
+// The keys (f32_key) of the n floats of img in tiles of kSplitTile, each in
+// order of its keys' lowest 9 bits; starts: the first slot of each of the
+// kSplitBuckets values of these bits, per tile; head: the mask of the top
+// bytes that occur (8 words), the buckets' totals, then scratch.  The mask is also,
+// complete at the event `noted`, at mask_host_dev (the device's view of 8
+// words of host memory).  A NaN sets kStatusNaN.
+constexpr int64_t kSplitTile = 16384;
+constexpr int kSplitBuckets = 512;
+size_t split_head_bytes(int64_t n);
+int launch_split(const float *img, int64_t n, uint32_t *keys, uint16_t *starts, uint32_t *head, uint32_t *mask_host_dev,
+                 uint32_t *status, hipEvent_t noted, hipStream_t stream);
 // The distinct values and the curve at them (ecc_distinct.hip), for images
-// whose keys hold at most kMaxDistinctBytes top bytes; offsets and mask from
-// radix_key_counts, idx: n words, scratch: distinct_scratch_bytes.  Their
-// number goes to *count (device memory).
+// whose keys hold at most kMaxDistinctBytes top bytes; keys, starts and head
+// from launch_split, scratch: distinct_scratch_bytes.  Their number goes to
+// *count (device memory).
 constexpr int kMaxDistinctBytes = 32;
 size_t distinct_scratch_bytes(int present, int64_t n);
-int launch_distinct_curve(const float *img, int64_t n, int present, const uint32_t *offsets, const uint32_t *mask,
-                          uint32_t *idx, void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
+int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const uint16_t *starts, const uint32_t *head,
+                          void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
                           int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream);
 // Sorts rec[0] in place (an even number of passes).
 int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);

@@ -5,9 +5,8 @@
 //
 // The records take four passes of 8-bit digits, the keys two of 9 bits and
 // two of 7.  The keys are only sorted when they hold more than
-// kMaxDistinctBytes top bytes (sign and high exponent bits): the first count
-// pass notes which occur, and with fewer the distinct values are found from
-// its counts without sorting (ecc_distinct.hip).
+// kMaxDistinctBytes top bytes (sign and high exponent bits); with fewer the
+// distinct values are found without sorting (ecc_distinct.hip).
 //
 // A workgroup owns a tile of kTile consecutive keys.  A pass:
 //  1. radix_count_kernel: digit counts per (digit, tile), digit-major;
@@ -47,28 +46,19 @@ __device__ __forceinline__ uint32_t digit_of(T r, int shift) {
 // small sorts take fewer tiles per workgroup to keep the chip busy.
 constexpr int kCountTiles = 16;
 
-// MASK (the first pass over 32-bit keys): the words are the image's floats,
-// mapped to keys as they are loaded; also ORs the presence of each key's top
-// byte into mask (8 words, zero before the launch) and reports a NaN.
-template <typename T, int BITS, bool AGG, bool MASK>
+template <typename T, int BITS, bool AGG>
 __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__restrict__ rec, int64_t n,
                                                                    int shift, int64_t tiles, int tpw,
-                                                                   uint32_t *__restrict__ counts,
-                                                                   uint32_t *__restrict__ mask, uint32_t *status) {
+                                                                   uint32_t *__restrict__ counts) {
     constexpr int kItems = SortTile<T>::kItems;
     constexpr int64_t kTile = SortTile<T>::kTile;
     constexpr int kDig = 1 << BITS;
-    static_assert(!MASK || sizeof(T) == 4, "top bytes of 32-bit keys");
     __shared__ uint32_t cnt[kCountTiles][kDig + 1];  // (padded: the final transpose reads a column)
-    __shared__ uint8_t present[MASK ? 256 : 1];  // MASK: top bytes seen
     const int tid = threadIdx.x;
     for (int i = tid; i < kCountTiles * (kDig + 1); i += kSortThreads) (&cnt[0][0])[i] = 0;
-    if (MASK && tid < 256) present[tid] = 0;
     __syncthreads();
     const int lane = tid & (kWave - 1);
     const int64_t tb = (int64_t)blockIdx.x * tpw;
-    uint32_t last = 256u;  // MASK: the top byte this thread noted last
-    bool nan = false;
     for (int k = 0; k < tpw && tb + k < tiles; ++k) {
         const int64_t t0 = (tb + k) * kTile;
         T r[kItems];
@@ -76,30 +66,17 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = t0 + (int64_t)j * kSortThreads + tid;
             r[j] = i < n ? rec[i] : T(0);
-            if constexpr (MASK) {
-                nan |= (r[j] & 0x7FFFFFFFu) > 0x7F800000u;
-                r[j] = f32_key(r[j]);
-            }
         }
         // AGG (a top digit: sign and exponent, a handful of values): same-digit
         // lanes would serialize on one LDS address, so up to four rounds take the
         // digit of the lowest lane not yet counted and add all its lanes through
         // that lane; what is left (many distinct digits) adds per lane.  On the
-        // low digits per-lane adds are cheaper.  MASK: a thread stores a
-        // presence byte only when its key's top byte differs from the last one
-        // it noted (neighbouring voxels share their top bytes).
+        // low digits per-lane adds are cheaper.
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = t0 + (int64_t)j * kSortThreads + tid;
             const bool ok = i < n;
             const uint32_t d = digit_of<T, BITS>(r[j], shift);
-            if constexpr (MASK) {
-                const uint32_t top = (uint32_t)r[j] >> 24;
-                if (ok && top != last) {
-                    present[top] = 1;
-                    last = top;
-                }
-            }
             if constexpr (!AGG) {
                 if (ok) atomicAdd(&cnt[k][d], 1u);
                 continue;
@@ -115,27 +92,14 @@ __global__ void __launch_bounds__(kSortThreads) radix_count_kernel(const T *__re
             if ((rem >> lane) & 1ull) atomicAdd(&cnt[k][d], 1u);
         }
     }
-    if (MASK && __builtin_amdgcn_ballot_w64(nan) != 0 && lane == 0) atomicOr(status, kStatusNaN);
     __syncthreads();
-    if (MASK && tid < 256) {  // wave w: bytes 64 w .. 64 w + 63, mask words 2 w and 2 w + 1
-        const uint64_t b = __builtin_amdgcn_ballot_w64(present[tid] != 0);
-        if (lane == 0 && (uint32_t)b != 0u) atomicOr(&mask[2 * (tid >> 6)], (uint32_t)b);
-        if (lane == 0 && (uint32_t)(b >> 32) != 0u) atomicOr(&mask[2 * (tid >> 6) + 1], (uint32_t)(b >> 32));
-    }
     for (int i = tid; i < tpw * kDig; i += kSortThreads) {
         const int k = i % tpw, d = i / tpw;
         if (tb + k < tiles) counts[(int64_t)d * tiles + tb + k] = cnt[k][d];
     }
 }
 
-// The presence mask, copied to host-mapped memory (read by the host after an
-// event, to choose between the bits of the values and the sort).
-__global__ void mask_publish_kernel(const uint32_t *__restrict__ mask, uint32_t *host) {
-    if (threadIdx.x < 8) host[threadIdx.x] = mask[threadIdx.x];
-}
-
-// FIRST: the words are the image's floats, mapped to keys as they are loaded.
-template <typename T, int BITS, bool FIRST = false>
+template <typename T, int BITS>
 __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(8))) radix_scatter_kernel(const T *__restrict__ in, int64_t n,
                                                                      int shift, int64_t tiles,
                                                                      const uint32_t *__restrict__ offsets,
@@ -177,14 +141,12 @@ __global__ void __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
             r[j] = in[wb + j * kWave + lane];
-            if constexpr (FIRST) r[j] = f32_key(r[j]);
         }
     } else {
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
             const int64_t i = wb + (int64_t)j * kWave + lane;
             r[j] = i < n ? in[i] : ~T(0);
-            if constexpr (FIRST) r[j] = i < n ? f32_key(r[j]) : ~T(0);
         }
     }
     auto digit = [&](int j) -> uint32_t { return digit_of<T, BITS>(r[j], shift); };
@@ -413,7 +375,7 @@ int64_t radix_tiles(int64_t n, int elem) {
     return (n + t - 1) / t;
 }
 int64_t radix_scan_tiles(int64_t entries) { return (entries + kScanTile - 1) / kScanTile; }
-int64_t radix_count_entries(int64_t n, int elem) { return (elem == 4 ? kKeyDigits : 256) * radix_tiles(n, elem); }
+int64_t radix_count_entries(int64_t n, int elem) { return (elem == 4 ? 512 : 256) * radix_tiles(n, elem); }
 
 static int count_tiles_per_wg(int64_t tiles) {
     return (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
@@ -425,8 +387,8 @@ static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts,
     const int64_t tiles = radix_tiles(n, (int)sizeof(T));
     const int tpw = count_tiles_per_wg(tiles);
     const unsigned cgrid = (unsigned)((tiles + tpw - 1) / tpw);
-    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG, false>), dim3(cgrid), dim3(kSortThreads), 0, stream,
-                       (const T *)v[*cur], n, shift, tiles, tpw, counts, (uint32_t *)nullptr, (uint32_t *)nullptr);
+    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG>), dim3(cgrid), dim3(kSortThreads), 0, stream,
+                       (const T *)v[*cur], n, shift, tiles, tpw, counts);
     ECC_HIP(hipGetLastError());
     int rc = exclusive_scan_u32(counts, ((int64_t)1 << BITS) * tiles, sums, stream);
     if (rc) return rc;
@@ -445,31 +407,11 @@ static int check_count(int64_t n) {
     return ECC_OK;
 }
 
-int radix_key_counts(const float *img, int64_t n, uint32_t *counts, uint32_t *sums, uint32_t *mask_dev,
-                     uint32_t *mask_host_dev, uint32_t *status, hipEvent_t noted, hipStream_t stream) {
-    static_assert(SortTile<uint32_t>::kTile == kKeyTile && kKeyDigits == 512, "9-bit digits of the keys' tiles");
+int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
     int rc = check_count(n);
-    if (rc) return rc;
-    rc = launch_zero(mask_dev, 32, stream);
-    if (rc) return rc;
-    const int64_t tiles = radix_tiles(n, 4);
-    const int tpw = count_tiles_per_wg(tiles);
-    hipLaunchKernelGGL((radix_count_kernel<uint32_t, 9, false, true>), dim3((unsigned)((tiles + tpw - 1) / tpw)),
-                       dim3(kSortThreads), 0, stream, (const uint32_t *)img, n, 0, tiles, tpw, counts, mask_dev, status);
-    ECC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(mask_publish_kernel, dim3(1), dim3(64), 0, stream, (const uint32_t *)mask_dev, mask_host_dev);
-    ECC_HIP(hipGetLastError());
-    ECC_HIP(hipEventRecord(noted, stream));
-    return exclusive_scan_u32(counts, (int64_t)kKeyDigits * tiles, sums, stream);
-}
-
-int radix_sort_keys(const float *img, uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
-    const int64_t tiles = radix_tiles(n, 4);
-    hipLaunchKernelGGL((radix_scatter_kernel<uint32_t, 9, true>), dim3((unsigned)tiles), dim3(kSortThreads), 0, stream,
-                       (const uint32_t *)img, n, 0, tiles, (const uint32_t *)counts, key[1]);
-    ECC_HIP(hipGetLastError());
-    int cur = 1;
-    int rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 9, counts, sums, stream);
+    int cur = 0;
+    if (!rc) rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 0, counts, sums, stream);
+    if (!rc) rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 9, counts, sums, stream);
     if (!rc) rc = radix_pass<uint32_t, 7, false>(key, &cur, n, 18, counts, sums, stream);
     // (bits 25-31: sign and high exponent bits, a handful of values)
     if (!rc) rc = radix_pass<uint32_t, 7, true>(key, &cur, n, 25, counts, sums, stream);
