@@ -974,12 +974,14 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     hipError_t e = hipEventSynchronize(ev);
     int present = 0;
     for (int w = 0; w < 8; ++w) present += __builtin_popcount((ws->host_status + 4)[w]);
-    if (!rc && e == hipSuccess && present <= kMaxDistinctBytes) {
+    const bool by_bits = !rc && e == hipSuccess && present <= kMaxDistinctBytes;
+    if (by_bits) {
         (void)hipEventDestroy(ev);
         rc = ensure_bytes(&ws->fbits, &ws->fbits_bytes, distinct_scratch_bytes(present, n));
         if (rc) return rc;
         rc = launch_distinct_curve(n, present, key[0], starts, head, ws->fbits, nz, nz_cnt, regions, region_slots,
-                                   out_keys, out_chi, count_dev, s);
+                                   out_keys, out_chi, count_dev, (int64_t *)(ws->host_status_dev + 12), ws->status,
+                                   ws->host_status_dev + 14, s);
         if (rc) return rc;
     } else {
         // the record count, read on the host while the keys are sorted: a
@@ -1020,9 +1022,15 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     }
     uint32_t st = 0;
     int64_t kcount = 0;
-    ECC_HIP(hipMemcpyAsync(&st, ws->status, 4, hipMemcpyDeviceToHost, s));
-    ECC_HIP(hipMemcpyAsync(&kcount, count_dev, 8, hipMemcpyDeviceToHost, s));
-    ECC_HIP(hipStreamSynchronize(s));
+    if (by_bits) {
+        ECC_HIP(hipStreamSynchronize(s));
+        st = ws->host_status[14];
+        kcount = *(volatile int64_t *)(ws->host_status + 12);
+    } else {
+        ECC_HIP(hipMemcpyAsync(&st, ws->status, 4, hipMemcpyDeviceToHost, s));
+        ECC_HIP(hipMemcpyAsync(&kcount, count_dev, 8, hipMemcpyDeviceToHost, s));
+        ECC_HIP(hipStreamSynchronize(s));
+    }
     if (st != 0) {
         rc = launch_zero(ws->status, 4, s);
         if (rc) return rc;

@@ -421,12 +421,16 @@ __global__ void __launch_bounds__(256) order_bits_kernel(const uint32_t *__restr
 }
 
 // The exclusive scan of the tiles' totals (base[tiles] = their sum, also to
-// *count): one workgroup.
+// *count) and the list of the tiles that are not empty (list[0]: how many):
+// one workgroup.  The count and the status word also go to host-mapped memory,
+// where the host finds them after its wait for the curve.
 __global__ void __launch_bounds__(1024) tile_base_kernel(const uint32_t *__restrict__ total, int tiles,
-                                                         uint32_t *__restrict__ base, int64_t *count) {
-    __shared__ uint32_t ws[16];
+                                                         uint32_t *__restrict__ base, uint32_t *__restrict__ list,
+                                                         int64_t *count, int64_t *count_host, const uint32_t *status,
+                                                         uint32_t *status_host) {
+    __shared__ uint32_t ws[16], wf[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t carry = 0;
+    uint32_t carry = 0, full = 0;
     for (int c0 = 0; c0 < tiles; c0 += 1024) {
         const int i = c0 + tid;
         const uint32_t v = i < tiles ? total[i] : 0u;
@@ -437,37 +441,49 @@ __global__ void __launch_bounds__(1024) tile_base_kernel(const uint32_t *__restr
             if (lane >= off) x += u;
         }
         if (lane == 63) ws[wave] = x;
+        const uint64_t some = __builtin_amdgcn_ballot_w64(v != 0);
+        if (lane == 0) wf[wave] = (uint32_t)__builtin_popcountll(some);
         __syncthreads();
-        uint32_t p = carry;
+        uint32_t p = carry, f = full;
         for (int w = 0; w < 16; ++w) {
-            if (w < wave) p += ws[w];
+            if (w < wave) p += ws[w], f += wf[w];
             carry += ws[w];
+            full += wf[w];
         }
         if (i < tiles) base[i] = p + x - v;
+        if (v != 0)
+            list[1 + f + __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u))] = (uint32_t)i;
         __syncthreads();
     }
     if (tid == 0) {
         base[tiles] = carry;
+        list[0] = full;
         *count = (int64_t)carry;
+        *count_host = (int64_t)carry;
+        *status_host = *status;
     }
 }
 
 // ---- 4. A wave takes 64 words (eight blocks) at a time: each lane's set
-// bits are put, in order, into LDS, and leave as one run.
+// bits are put, in order, into LDS, and leave as one run.  The workgroups
+// share the parts of the tiles that are not empty (a workgroup per part of
+// every tile: 27 us for 190 x 211 x 170 noise, much of it the launch of
+// workgroups without work; now 21).
 constexpr int kExpandWaves = 4;
+constexpr int kExpandParts = 32;  // of a tile: a chunk per wave
 constexpr int kExpandWords = 64;
 
 __global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_t *__restrict__ ord,
                                                                    const uint32_t *__restrict__ blk,
                                                                    const uint32_t *__restrict__ base,
-                                                                   const uint32_t *__restrict__ mask, int parts,
+                                                                   const uint32_t *__restrict__ list,
+                                                                   const uint32_t *__restrict__ mask,
                                                                    float *__restrict__ out_keys,
                                                                    int64_t *__restrict__ out_chi) {
     __shared__ uint32_t st[kExpandWaves][kExpandWords * 33];
     __shared__ uint8_t byte_of[256];  // top byte of a rank
+    static_assert(kOrdWords == kExpandWords * kExpandWaves * kExpandParts, "a chunk per wave and part");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tile = blockIdx.x / parts, part = blockIdx.x % parts;
-    if (base[tile] == base[tile + 1]) return;  // (uniform) an empty tile
     {
         uint32_t c = 0;
         for (int w = 0; w < (tid >> 5); ++w) c += (uint32_t)__builtin_popcount(mask[w]);
@@ -476,9 +492,10 @@ __global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_
         if ((m >> (tid & 31)) & 1u) byte_of[c] = (uint8_t)tid;
     }
     __syncthreads();
-    const int chunks = kOrdWords / kExpandWords / parts;  // chunks of this workgroup
-    for (int ch = wave; ch < chunks; ch += kExpandWaves) {
-        const uint32_t w0 = (uint32_t)tile * kOrdWords + (uint32_t)(part * chunks + ch) * kExpandWords;
+    const uint32_t items = list[0] * kExpandParts;
+    for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
+        const uint32_t tile = list[1 + item / kExpandParts], part = item % kExpandParts;
+        const uint32_t w0 = tile * kOrdWords + (part * kExpandWaves + (uint32_t)wave) * kExpandWords;
         uint32_t v = ord[w0 + lane];
         const uint32_t first = base[tile] + blk[w0 / kBlockWords];
         const uint32_t c = (uint32_t)__builtin_popcount(v);
@@ -689,7 +706,7 @@ size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // scratch of P top bytes and up to n values
 struct Layout {
-    size_t bits, ord, blk, total, base, sums, bytes;
+    size_t bits, ord, blk, total, base, list, sums, bytes;
     int words, tiles;
 };
 Layout layout(int present, int64_t n) {
@@ -702,7 +719,8 @@ Layout layout(int present, int64_t n) {
     L.blk = 2 * all;
     L.total = L.blk + up256((size_t)L.tiles * kTileBlocks * 4);
     L.base = L.total + up256((size_t)L.tiles * 4);
-    L.sums = L.base + up256((size_t)(L.tiles + 1) * 4);
+    L.list = L.base + up256((size_t)(L.tiles + 1) * 4);
+    L.sums = L.list + up256((size_t)(L.tiles + 1) * 4);
     L.bytes = L.sums + up256((size_t)((n + kChiTile - 1) / kChiTile) * 8);
     return L;
 }
@@ -739,7 +757,8 @@ int launch_split(const float *img, int64_t n, uint32_t *keys, uint16_t *starts, 
 
 int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const uint16_t *starts, const uint32_t *head,
                           void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
-                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream) {
+                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, int64_t *count_host,
+                          const uint32_t *status, uint32_t *status_host, hipStream_t stream) {
     if (present < 1 || present > kMaxDistinctBytes || n < 1 || n >= ((int64_t)1 << 30)) {
         set_error("internal error: %d top bytes, %lld values", present, (long long)n);
         return ECC_E_ARG;
@@ -748,7 +767,7 @@ int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const ui
     const Layout L = layout(present, n);
     uint8_t *b = (uint8_t *)scratch;
     uint32_t *bits = (uint32_t *)(b + L.bits), *ord = (uint32_t *)(b + L.ord), *blk = (uint32_t *)(b + L.blk);
-    uint32_t *total = (uint32_t *)(b + L.total), *base = (uint32_t *)(b + L.base);
+    uint32_t *total = (uint32_t *)(b + L.total), *base = (uint32_t *)(b + L.base), *list = (uint32_t *)(b + L.list);
     int64_t *sums = (int64_t *)(b + L.sums);
     const int64_t tiles = (n + kTile - 1) / kTile;
     int rc = launch_zero(bits, (size_t)L.words * kBuckets * 4, stream);
@@ -762,14 +781,12 @@ int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const ui
     hipLaunchKernelGGL(order_bits_kernel, dim3((unsigned)L.tiles), dim3(256), 0, stream, (const uint32_t *)bits, L.words,
                        ord, blk, total);
     ECC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(tile_base_kernel, dim3(1), dim3(1024), 0, stream, (const uint32_t *)total, L.tiles, base, count);
+    hipLaunchKernelGGL(tile_base_kernel, dim3(1), dim3(1024), 0, stream, (const uint32_t *)total, L.tiles, base,
+                       list, count, count_host, status, status_host);
     ECC_HIP(hipGetLastError());
-    // two chunks per wave: few tiles hold most of the values (190 x 211 x 170
-    // noise: 27 us, 36 with eight chunks per wave)
-    constexpr int parts = 16;
-    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)(L.tiles * parts)), dim3(64 * kExpandWaves), 0, stream,
-                       (const uint32_t *)ord, (const uint32_t *)blk, (const uint32_t *)base, mask, parts, out_keys,
-                       out_chi);
+    hipLaunchKernelGGL(expand_kernel, dim3((unsigned)std::min(L.tiles * kExpandParts, 16 * device_cu_count())),
+                       dim3(64 * kExpandWaves), 0, stream, (const uint32_t *)ord, (const uint32_t *)blk,
+                       (const uint32_t *)base, (const uint32_t *)list, mask, out_keys, out_chi);
     ECC_HIP(hipGetLastError());
     hipLaunchKernelGGL(add_records_kernel, dim3((unsigned)std::min<int64_t>((regions + 15) / 16, 2048)),
                        dim3(1024), 0, stream, nz, nz_cnt, regions, region_slots, (const uint32_t *)ord,

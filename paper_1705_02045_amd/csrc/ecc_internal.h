@@ -317,12 +317,13 @@ int launch_split(const float *img, int64_t n, uint32_t *keys, uint16_t *starts, 
 // The distinct values and the curve at them (ecc_distinct.hip), for images
 // whose keys hold at most kMaxDistinctBytes top bytes; keys, starts and head
 // from launch_split, scratch: distinct_scratch_bytes.  Their number goes to
-// *count (device memory).
+// *count (device memory) and, with the status word, to host-mapped memory.
 constexpr int kMaxDistinctBytes = 32;
 size_t distinct_scratch_bytes(int present, int64_t n);
 int launch_distinct_curve(int64_t n, int present, const uint32_t *keys, const uint16_t *starts, const uint32_t *head,
                           void *scratch, const uint64_t *nz, const uint32_t *nz_cnt, int64_t regions,
-                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, hipStream_t stream);
+                          int64_t region_slots, float *out_keys, int64_t *out_chi, int64_t *count, int64_t *count_host,
+                          const uint32_t *status, uint32_t *status_host, hipStream_t stream);
 // Sorts rec[0] in place (an even number of passes).
 int radix_sort_records(uint64_t *rec[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
 int64_t float_tiles(int64_t n);
