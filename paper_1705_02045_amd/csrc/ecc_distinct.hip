@@ -113,11 +113,7 @@ split_kernel(const float *__restrict__ img, int64_t n, int64_t tiles, uint32_t *
         uint32_t c = 0, x = 0;
         if (tid < kBuckets) {
             c = x = cnt[tid];
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const uint32_t u = __shfl_up(x, off, 64);
-                if (lane >= off) x += u;
-            }
+            x = wave_prefix(x);
             if (lane == 63) ws[tid >> 6] = x;
         }
         __syncthreads();
@@ -207,11 +203,7 @@ __global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *_
     uint32_t ns = 0, x = 0;
     if (tid < kBuckets) {
         ns = x = (totals[tid] + share - 1) / share;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         if (lane == 63) ws[tid >> 6] = x;
     }
     rank_table(mask, rank);
@@ -253,11 +245,7 @@ __global__ void __launch_bounds__(kThreads) bucket_bits_kernel(const uint32_t *_
         const uint32_t pos = ((uint32_t)first + (uint32_t)step * (uint32_t)(i0 + lane)) * kTile + beg1, len = end1 - beg1;
         fetch(i0 + kWaves * group, beg1, end1);
         uint32_t x = len;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63), before = x - len;
         if (total > kMaxKeys) {  // (uniform) a crowded bucket: long runs
             for (int r = 0; r < group; ++r) {
@@ -403,11 +391,7 @@ __global__ void __launch_bounds__(256) order_bits_kernel(const uint32_t *__restr
     }
     const uint32_t s = c[0] + c[1] + c[2] + c[3];
     uint32_t x = s;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t u = __shfl_up(x, off, 64);
-        if (lane >= off) x += u;
-    }
+    x = wave_prefix(x);
     if (lane == 63) ws[wave] = x;
     __syncthreads();
     uint32_t p = x - s;
@@ -435,11 +419,7 @@ __global__ void __launch_bounds__(1024) tile_base_kernel(const uint32_t *__restr
         const int i = c0 + tid;
         const uint32_t v = i < tiles ? total[i] : 0u;
         uint32_t x = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         if (lane == 63) ws[wave] = x;
         const uint64_t some = __builtin_amdgcn_ballot_w64(v != 0);
         if (lane == 0) wf[wave] = (uint32_t)__builtin_popcountll(some);
@@ -500,11 +480,7 @@ __global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_
         const uint32_t first = base[tile] + blk[w0 / kBlockWords];
         const uint32_t c = (uint32_t)__builtin_popcount(v);
         uint32_t x = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
         if (cnt == 0) continue;
         const uint32_t p0 = (w0 + lane) * 32u;
@@ -633,11 +609,7 @@ __global__ void __launch_bounds__(1024) chi_scan_kernel(const int64_t *__restric
             s += v[j];
         }
         int64_t x = s;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         if (lane == 63) ws[wave] = x;
         __syncthreads();
         int64_t p = carry + x - s;
@@ -678,11 +650,7 @@ __global__ void __launch_bounds__(kChiThreads) chi_prefix_kernel(int64_t *__rest
             s += v[j];
         }
         int64_t x = s;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t u = __shfl_up(x, off, 64);
-            if (lane >= off) x += u;
-        }
+        x = wave_prefix(x);
         if (lane == 63) ws[wave] = x;
         __syncthreads();
         int64_t p = sums[t] + x - s;

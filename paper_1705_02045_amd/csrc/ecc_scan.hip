@@ -147,11 +147,7 @@ __global__ void __launch_bounds__(1024) scan_kernel(const int64_t *__restrict__ 
     }
     before = block_sum_1024(before, sh);
     int64_t x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t u = __shfl_up(x, off, 64);
-        if (lane >= off) x += u;
-    }
+    x = wave_prefix(x);
     if (lane == 63) sh[wave] = x;
     __syncthreads();
     for (int w = 0; w < wave; ++w) before += sh[w];
@@ -250,13 +246,7 @@ __global__ void __launch_bounds__(1024) batch_scan_kernel(const uint8_t *__restr
                     v[k] = i < J.m ? J.vcec[i] : 0;
                 }
 #pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const int64_t u = __shfl_up(v[k], off, 64);
-                        if (lane >= off) v[k] += u;
-                    }
-                }
+                for (int k = 0; k < 16; ++k) v[k] = wave_prefix(v[k]);
                 if (lane == 63) {
 #pragma unroll
                     for (int k = 0; k < 16; ++k) ws[k][wave] = v[k];
@@ -606,11 +596,7 @@ __global__ void __launch_bounds__(1024) merge_scan_small_kernel(const int32_t *_
         if (rows > 0) vcec[tid] = v;
     }
     int64_t x = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t u = __shfl_up(x, off, 64);
-        if (lane >= off) x += u;
-    }
+    x = wave_prefix(x);
     if (lane == 63) sh[wave] = x;
     __syncthreads();
     for (int w = 0; w < wave; ++w) x += sh[w];
