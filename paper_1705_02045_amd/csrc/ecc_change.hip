@@ -103,12 +103,43 @@ __device__ __forceinline__ uint32_t bits_of(float v) { return __float_as_uint(v)
 __device__ __forceinline__ void from_bits(uint32_t b, uint32_t &v) { v = b; }
 __device__ __forceinline__ void from_bits(uint32_t b, float &v) { v = __uint_as_float(b); }
 
-// m = 2 m + (lane bit of the comparison)
-__device__ __forceinline__ void push(uint32_t &m, bool c) {
-    const uint64_t mask = __builtin_amdgcn_ballot_w64(c);
-    uint64_t co;
-    asm("v_addc_co_u32_e64 %0, %1, %0, %0, %2" : "+v"(m), "=&s"(co) : "s"(mask));
+// The comparisons x < y of two or four pairs as the low bits of a word, the
+// first pair's highest.  A vector instruction may read a mask only two wait
+// states after the comparison that wrote it, and the compiler does not add
+// them around inline assembly: each block holds its comparisons and what reads
+// their masks, the ones of the other pairs in between.
+#define ECC_CMP(type, mask, x, y) "v_cmp_lt_" type "_e64 " mask ", " x ", " y "\n\t"
+#define ECC_PUSH(mask) "v_addc_co_u32_e64 %0, %1, %0, %0, " mask "\n\t"  // m = 2 m + (lane bit)
+#define ECC_LT2(type)                                                                                       \
+    uint32_t m;                                                                                             \
+    uint64_t k1, k0;                                                                                        \
+    asm(ECC_CMP(type, "%1", "%3", "%4") ECC_CMP(type, "%2", "%5", "%6") "s_nop 0\n\t"                       \
+        "v_cndmask_b32_e64 %0, 0, 1, %1\n\t" ECC_PUSH("%2")                                                 \
+        : "=&v"(m), "=&s"(k1), "=&s"(k0)                                                                    \
+        : "v"(x1), "v"(y1), "v"(x0), "v"(y0));                                                              \
+    return m;
+#define ECC_LT4(type)                                                                                       \
+    uint32_t m;                                                                                             \
+    uint64_t k3, k2, k1, k0;                                                                                \
+    asm(ECC_CMP(type, "%1", "%5", "%6") ECC_CMP(type, "%2", "%7", "%8") ECC_CMP(type, "%3", "%9", "%10")      \
+        ECC_CMP(type, "%4", "%11", "%12") "v_cndmask_b32_e64 %0, 0, 1, %1\n\t" ECC_PUSH("%2") ECC_PUSH("%3") \
+        ECC_PUSH("%4")                                                                                      \
+        : "=&v"(m), "=&s"(k3), "=&s"(k2), "=&s"(k1), "=&s"(k0)                                              \
+        : "v"(x3), "v"(y3), "v"(x2), "v"(y2), "v"(x1), "v"(y1), "v"(x0), "v"(y0));                          \
+    return m;
+__device__ __forceinline__ uint32_t lt2(float x1, float y1, float x0, float y0) { ECC_LT2("f32") }
+__device__ __forceinline__ uint32_t lt2(uint32_t x1, uint32_t y1, uint32_t x0, uint32_t y0) { ECC_LT2("u32") }
+__device__ __forceinline__ uint32_t lt4(float x3, float y3, float x2, float y2, float x1, float y1, float x0, float y0) {
+    ECC_LT4("f32")
 }
+__device__ __forceinline__ uint32_t lt4(uint32_t x3, uint32_t y3, uint32_t x2, uint32_t y2, uint32_t x1, uint32_t y1,
+                                        uint32_t x0, uint32_t y0) {
+    ECC_LT4("u32")
+}
+#undef ECC_LT4
+#undef ECC_LT2
+#undef ECC_PUSH
+#undef ECC_CMP
 
 // Cell types of a position: bit 0: y is a vertex axis, bit 1: z is one; type
 // t's byte of a word is byte t.  At row position a == A (the row past the
@@ -255,25 +286,24 @@ __global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
                     }
             }
         };
-        // c of plane i from the fields of planes i and i+1: words without x
-        // and with x
-        // bits of the types at a position, spread to their bytes
-        auto gather = [&](int a, int b, auto &&bit) -> uint32_t {
-            uint32_t m = 0;
-            bool first = true;
+        // x(t) < y(t) for the types t at a position, spread to their bytes
+        auto gather = [&](int a, int b, auto &&x, auto &&y) -> uint32_t {
+            int ty[4], n = 0;
 #pragma unroll
             for (int t = 3; t >= 0; --t)
-                if (Ty::has(a, b, t)) {
-                    if (first) m = bit(t) ? 1u : 0u;
-                    else push(m, bit(t));
-                    first = false;
-                }
+                if (Ty::has(a, b, t)) ty[n++] = t;
+            uint32_t m;
+            if (n == 4) m = lt4(x(ty[0]), y(ty[0]), x(ty[1]), y(ty[1]), x(ty[2]), y(ty[2]), x(ty[3]), y(ty[3]));
+            else if (n == 2) m = lt2(x(ty[0]), y(ty[0]), x(ty[1]), y(ty[1]));
+            else m = x(ty[0]) < y(ty[0]) ? 1u : 0u;  // (no position has three types)
             return Ty::spread(m, a, b);
         };
+        // c of plane i from the fields of planes i and i+1: words without x
+        // and with x
         auto compare = [&](const V (&gn)[PA][PB][4][2], const V (&gc)[PA][PB][4][2], int a, int b, uint32_t valid,
                            uint32_t &ca, uint32_t &cb) {
-            ca = gather(a, b, [&](int t) { return gn[a][b][t][0] < gc[a][b][t][0]; }) & myx[a] & valid;
-            cb = gather(a, b, [&](int t) { return gn[a][b][t][1] < gc[a][b][t][1]; }) & my[a] & valid;
+            ca = gather(a, b, [&](int t) { return gn[a][b][t][0]; }, [&](int t) { return gc[a][b][t][0]; }) & myx[a] & valid;
+            cb = gather(a, b, [&](int t) { return gn[a][b][t][1]; }, [&](int t) { return gc[a][b][t][1]; }) & my[a] & valid;
         };
         const bool lo_real = !(zs == P.e0 && P.lo_inf);
         const bool hi_real = !(ze == P.e1 && P.hi_inf);
@@ -336,7 +366,8 @@ __global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
                     uint32_t ca, cb;
                     compare(gn, gc, a, b, on[b], ca, cb);
                     // types whose left value is strictly smaller
-                    const uint32_t m = gather(a, b, [&](int t) { return gc[a][b][t][1] < gc[a][b][t][0]; });
+                    const uint32_t m =
+                        gather(a, b, [&](int t) { return gc[a][b][t][1]; }, [&](int t) { return gc[a][b][t][0]; });
                     const uint32_t xn = ca - cb;
                     // (what goes to the left, negated, and the rest kept
                     // opaque: the shifted value is then only ever added.  A
