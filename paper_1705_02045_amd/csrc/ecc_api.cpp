@@ -895,6 +895,20 @@ static int compute_int(const void *image, const ecc_dims *dims, int64_t total, e
     return ECC_OK;
 }
 
+// A call that gives up after its kernels were launched: the status word that
+// they may have set (a NaN) is cleared, so that the next call on the stream does
+// not report it, and they are waited for, since the caller may free the image.
+struct StatusCleanup {
+    Workspace *ws;
+    hipStream_t s;
+    bool armed = false;
+    ~StatusCleanup() {
+        if (!armed) return;
+        (void)launch_zero(ws->status, 4, s);
+        (void)hipStreamSynchronize(s);
+    }
+};
+
 // steps_only: the output keeps the keys where chi changes (chi = 0 before
 // the first key), compacted after the full curve is built.
 static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc_curve *curve, hipStream_t s,
@@ -969,6 +983,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     // the host reads which top bytes occur while the change kernel runs
     hipEvent_t ev = nullptr;
     ECC_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    StatusCleanup cleanup{ws, s, true};
     rc = launch_split(img_dev, n, key[0], starts, head, ws->host_status_dev + 4, ws->status, ev, s);
     if (!rc) rc = launch_change_records(job, nz, nz_cnt, s);
     hipError_t e = hipEventSynchronize(ev);
@@ -1032,9 +1047,6 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
         ECC_HIP(hipStreamSynchronize(s));
     }
     if (st != 0) {
-        rc = launch_zero(ws->status, 4, s);
-        if (rc) return rc;
-        ECC_HIP(hipStreamSynchronize(s));
         if (st & kStatusNaN) {
             set_error("a float image holds a NaN");
             return ECC_E_NAN;
@@ -1042,6 +1054,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
         set_error("internal error: device status 0x%08x", st);
         return ECC_E_HIP;
     }
+    cleanup.armed = false;  // (the status word is clear, the image is read)
     if (steps_only) {  // compact into buffers free after the curve: the second key buffer, the regions
         float *step_keys = (float *)key[1];
         int64_t *step_chi = (int64_t *)nz;

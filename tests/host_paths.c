@@ -1,0 +1,216 @@
+/*
+ * Host paths of libecc without a GPU: this program defines the HIP runtime
+ * calls that the library makes (its own definitions come before the runtime's
+ * for the libraries that it loads), with device memory as addresses that are
+ * only counted, and kernels that are only noted.  What a few kernels report to
+ * the host is filled in.  argv[1] names the scenario; it prints "key value"
+ * lines for the test.
+ */
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <hip/hip_runtime_api.h>
+
+#include "ecc.h"
+
+/* ------------------------------------------------------------ the runtime */
+
+#define DEVICE_LO 0x010000000000ull
+#define DEVICE_HI 0x200000000000ull
+static uint64_t next_address = DEVICE_LO;
+static struct {
+    uint64_t p;
+    size_t bytes;
+} blocks[4096];
+static int nblocks;
+static size_t used, peak, limit_bytes = (size_t)-1;
+static hipError_t last_error;
+
+static struct {
+    const void *host;
+    const char *name;
+} kernels[4096];
+static int nkernels;
+static long launches;
+static int syncs;
+
+static uint32_t status_word;  /* the status word of the one stream that a scenario uses */
+static int nan_image;         /* the float image holds a NaN */
+static int top_bytes = 3;     /* top bytes of the float image's keys */
+static long change_launches;  /* of the change kernel */
+
+static int is_device(const void *p) { return (uint64_t)p >= DEVICE_LO && (uint64_t)p < DEVICE_HI; }
+static hipError_t result(hipError_t e) {
+    if (e != hipSuccess) last_error = e;
+    return e;
+}
+
+hipError_t hipMalloc(void **p, size_t n) {
+    if (n > limit_bytes - used) return result(hipErrorOutOfMemory);
+    blocks[nblocks].p = next_address;
+    blocks[nblocks++].bytes = n;
+    *p = (void *)next_address;
+    next_address += (n + 0x200000) & ~(uint64_t)0xFFFFF;
+    used += n;
+    if (used > peak) peak = used;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p) {
+    if (!p) return hipSuccess;
+    for (int i = 0; i < nblocks; ++i)
+        if (blocks[i].p == (uint64_t)p) {
+            used -= blocks[i].bytes;
+            blocks[i] = blocks[--nblocks];
+            return hipSuccess;
+        }
+    printf("bad_free 1\n");
+    return result(hipErrorInvalidValue);
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) { return (*p = calloc(1, n)) ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned flags) { *d = h; return hipSuccess; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p) {
+    if (!is_device(p)) return result(hipErrorInvalidValue);
+    a->type = hipMemoryTypeDevice;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) {
+    hipError_t e = last_error;
+    last_error = hipSuccess;
+    return e;
+}
+const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipSetDevice(int d) { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int d) { *v = 256; return hipSuccess; }
+hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { ++syncs; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned f) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned f) { *s = (hipStream_t)malloc(8); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(8); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned f) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t e) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b) { *ms = 1.0f; return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {
+    if (is_device(d)) return hipSuccess;
+    if (!is_device(s)) memcpy(d, s, n);
+    else if (n == 4) memcpy(d, &status_word, 4);
+    else memset(d, 0, n);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind k) { return hipMemcpyAsync(d, s, n, k, 0); }
+
+void **__hipRegisterFatBinary(const void *data) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **h) {}
+void __hipRegisterVar(void **m, void *v, char *hv, char *dv, int e, size_t n, int c, int g) {}
+void __hipRegisterFunction(void **m, const void *f, char *df, const char *name, unsigned n, void *t, void *b, void *bd,
+                           void *gd, int *w) {
+    kernels[nkernels].host = f;
+    kernels[nkernels++].name = name;
+}
+static dim3 pushed_grid, pushed_block;
+static size_t pushed_shared;
+static hipStream_t pushed_stream;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t shared, hipStream_t s) {
+    pushed_grid = g;
+    pushed_block = b;
+    pushed_shared = shared;
+    pushed_stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *shared, hipStream_t *s) {
+    *g = pushed_grid;
+    *b = pushed_block;
+    *shared = pushed_shared;
+    *s = pushed_stream;
+    return hipSuccess;
+}
+/* argument k of a launch, a pointer to host memory, or NULL */
+static uint32_t *host_argument(void **args, int k) {
+    void *p = *(void **)args[k];
+    return p && !is_device(p) ? (uint32_t *)p : NULL;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t shared, hipStream_t s) {
+    const char *name = "";
+    for (int i = 0; i < nkernels; ++i)
+        if (kernels[i].host == f) name = kernels[i].name;
+    ++launches;
+    uint32_t *out;
+    if (strstr(name, "zero_kernel")) {
+        const size_t words = *(size_t *)args[1];
+        if (words <= 2 || words == (128 + 1024 * 8 + 128) / 4) status_word = 0;  /* the word, or a new status block */
+    } else if (strstr(name, "split_kernel")) {
+        if (nan_image) status_word |= 2u;
+    } else if (strstr(name, "bucket_totals_kernel")) {
+        out = host_argument(args, 4);
+        for (int w = 0; w < 8; ++w) out[w] = 0;
+        for (int k = 0; k < top_bytes; ++k) out[k / 32] |= 1u << (k % 32);
+    } else if (strstr(name, "nz_total_kernel")) {
+        memset(host_argument(args, 2), 0, 8);
+    } else if (strstr(name, "tile_base_kernel")) {
+        *(int64_t *)host_argument(args, 5) = 1;
+        *host_argument(args, 7) = status_word;
+    } else if (strstr(name, "merge_scan_small_kernel")) {
+        if ((out = host_argument(args, 9))) *out = status_word;
+        status_word = 0;
+    } else if (strstr(name, "11scan_kernel")) {
+        if ((out = host_argument(args, 6))) *out = status_word;
+        status_word = 0;
+    } else if (strstr(name, "change_kernel")) {
+        ++change_launches;
+    }
+    return hipSuccess;
+}
+
+/* -------------------------------------------------------------- scenarios */
+
+static ecc_dims dims_of(int nd, int64_t a, int64_t b, int64_t c, int64_t d) {
+    ecc_dims r = {nd, {a, b, c, d}};
+    return r;
+}
+/* device memory that is an input or output of a call */
+static void *device_bytes(size_t n) {
+    void *p = (void *)next_address;
+    next_address += (n + 0x200000) & ~(uint64_t)0xFFFFF;
+    return p;
+}
+
+/* A float image with a NaN whose call fails for want of memory at each of its
+ * allocations in turn, and a valid 14-bit image on the same stream after it. */
+static int float_exits(void) {
+    ecc_dims d = dims_of(3, 20, 30, 40, 1);
+    void *img = device_bytes(24000 * 4);
+    static float keys[24000];
+    static int64_t chi[24000];
+    for (int k = 0; k < 6; ++k) {
+        for (top_bytes = 3; top_bytes <= 40; top_bytes += 37) {
+            char num[8];
+            void *stream = malloc(8);
+            ecc_curve c = {24000, 0, chi, keys};
+            nan_image = 0;
+            snprintf(num, sizeof num, "%d", k + 1);
+            setenv("ECC_FAIL_ALLOC", num, 1);
+            const int before = syncs;
+            nan_image = 1;
+            const int rc = ecc_compute(img, &d, ECC_F32, &c, stream);
+            printf("float rc %d waits %d status %u\n", rc, syncs - before, status_word);
+            unsetenv("ECC_FAIL_ALLOC");
+            ecc_curve v = {16384, 0, chi, NULL};
+            printf("next rc %d\n", ecc_compute(img, &d, ECC_U14, &v, stream));
+        }
+    }
+    return 0;
+}
+
+int main(int argc, char **argv) {
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "float_exits")) return float_exits();
+    fprintf(stderr, "no scenario %s\n", what);
+    return 2;
+}

@@ -1,0 +1,47 @@
+"""The library's host side without a GPU: what it allocates, launches, gives
+back and reports, seen by the HIP runtime calls that host_paths.c defines."""
+import os
+import pathlib
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = pathlib.Path(__file__).resolve().parents[1]
+LIB = pathlib.Path(os.environ.get("ECC_LIB_DIR", ROOT / "paper_1705_02045_amd"))
+ROCM = pathlib.Path(shutil.which("hipcc") or "/opt/rocm/bin/hipcc").resolve().parents[1]
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if not (ROCM / "include" / "hip" / "hip_runtime_api.h").exists():
+        ROCM_INC = pathlib.Path("/opt/rocm/include")
+    else:
+        ROCM_INC = ROCM / "include"
+    out = tmp_path_factory.mktemp("host") / "host_paths"
+    subprocess.run(["gcc", "-O1", "-std=gnu11", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I", str(ROCM_INC),
+                    "-I", str(ROOT / "include"), str(ROOT / "tests" / "host_paths.c"), str(LIB / "libecc.so"),
+                    f"-Wl,-rpath,{LIB}", "-Wl,--allow-shlib-undefined", "-o", str(out)], check=True)
+    return out
+
+
+def run(program, *args):
+    r = subprocess.run([str(program), *args], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return [line.split() for line in r.stdout.splitlines()]
+
+
+ECC_OK, ECC_E_NAN, ECC_E_NOMEM = 0, -3, -6
+
+
+def test_float_call_leaves_no_status_behind(program):
+    """A float call that fails after its kernels were launched clears the
+    status word that they set and waits for them: the next call on the stream
+    is not disturbed."""
+    lines = run(program, "float_exits")
+    calls = [dict(zip(line[1::2], map(int, line[2::2]))) for line in lines]
+    failed = [c for c, line in zip(calls, lines) if line[0] == "float"]
+    assert {c["rc"] for c in failed} <= {ECC_E_NOMEM, ECC_E_NAN}
+    assert sum(c["rc"] == ECC_E_NOMEM for c in failed) >= 6
+    assert all(c["status"] == 0 for c in failed), failed
+    assert all(c["rc"] == ECC_OK for c, line in zip(calls, lines) if line[0] == "next"), calls
