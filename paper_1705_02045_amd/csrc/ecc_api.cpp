@@ -1633,16 +1633,15 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
             set_error("ecc_compute_dual: shape not supported");
             return ECC_E_UNSUPPORTED;
         }
+        StatusCleanup cleanup{ws, s, true};
         rc = enqueue_max_entry_rows(img_dev, v, dtype, low_rows, &rows, s, ws);
         if (!rc)
             rc = launch_box_faces(img_dev, (int)eb, low.data(), (int)low.size(), cus, ws->partial + (size_t)rows * m, s);
         if (!rc)
             rc = launch_merge(ws->partial, rows + low_rows, (int)m, curves, false, true, chi_dev, ws->status,
                               ws->host_status_dev, s, true, gsign < 0);
-        if (rc) {
-            (void)hipStreamSynchronize(s);
-            return rc;
-        }
+        if (rc) return rc;
+        cleanup.armed = false;  // (the scan clears the status word)
         return finish_dual(ws, curve, chi_dev, chi_direct, m, s);
     }
     int64_t *lowv = curves + (size_t)nf * m;
@@ -1666,6 +1665,7 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
         for (int k = 0; k < SideStreams::kCount; ++k)
             if (used[k]) (void)hipStreamSynchronize(side->s[k]);
     };
+    StatusCleanup cleanup{ws, s, true};
     ECC_HIP(hipEventRecord(side->fork, s));  // the image (and its copy, if any) is ready here
     auto fork_to = [&](int k) -> int {
         if (used[k]) return ECC_OK;
@@ -1751,19 +1751,14 @@ int ecc_compute_dual(const void *image, const ecc_dims *dims, ecc_dtype dtype, e
         }
     }
     rc = launch_signed_sum(curves, nf + 1, neg, skip, gsign, (int)m, result, s);
-    if (rc) {
-        (void)hipStreamSynchronize(s);
-        return rc;
-    }
+    if (rc) return rc;
     // the scan (its changes are summed already), into the caller's buffer if
     // it is device memory; the status of every launch on the volume or a face
     // of three dimensions (the volume's reads all values) is reported and
     // cleared here, and nothing is written unless it is clear
     rc = launch_merge(nullptr, 0, (int)m, result, true, true, chi_dev, ws->status, ws->host_status_dev, s);
-    if (rc) {
-        (void)hipStreamSynchronize(s);
-        return rc;
-    }
+    if (rc) return rc;
+    cleanup.armed = false;  // (the scan clears the status word)
     return finish_dual(ws, curve, chi_dev, chi_direct, m, s);
 }
 

@@ -38,6 +38,9 @@ static int syncs;
 
 static uint32_t status_word;  /* the status word of the one stream that a scenario uses */
 static int nan_image;         /* the float image holds a NaN */
+static int range_image;       /* the 14-bit image holds a value >= 16384 */
+static int stream_waits;      /* for the stream that the scenario gave */
+static hipStream_t its_stream;
 static int top_bytes = 3;     /* top bytes of the float image's keys */
 static long change_launches;  /* of the change kernel */
 
@@ -86,7 +89,11 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int d) { return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int d) { *v = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t s) { ++syncs; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    ++syncs;
+    if (s == its_stream) ++stream_waits;
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned f) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned f) { *s = (hipStream_t)malloc(8); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
@@ -164,6 +171,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
         status_word = 0;
     } else if (strstr(name, "change_kernel")) {
         ++change_launches;
+        if (range_image) status_word |= 1u;
     }
     return hipSuccess;
 }
@@ -208,9 +216,33 @@ static int float_exits(void) {
     return 0;
 }
 
+/* The dual curve of a 4-D image with a value out of range whose call fails at
+ * each of its allocations in turn, and a valid image on the same stream. */
+static int dual_exits(void) {
+    ecc_dims d = dims_of(4, 6, 7, 8, 9), v = dims_of(2, 20, 30, 1, 1);
+    void *img = device_bytes(6 * 7 * 8 * 9 * 2);
+    static int64_t chi[16384];
+    for (int k = 1; k <= 40; ++k) {
+        char num[8];
+        its_stream = (hipStream_t)malloc(8);
+        ecc_curve c = {16384, 0, chi, NULL};
+        snprintf(num, sizeof num, "%d", k);
+        setenv("ECC_FAIL_ALLOC", num, 1);
+        range_image = 1;
+        change_launches = stream_waits = 0;
+        const int rc = ecc_compute_dual(img, &d, ECC_U14, &c, its_stream);
+        printf("dual rc %d launched %ld waits %d status %u\n", rc, change_launches, stream_waits, status_word);
+        range_image = 0;
+        unsetenv("ECC_FAIL_ALLOC");
+        printf("next rc %d\n", ecc_compute(img, &v, ECC_U14, &c, its_stream));
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
+    if (!strcmp(what, "dual_exits")) return dual_exits();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

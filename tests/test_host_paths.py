@@ -31,7 +31,12 @@ def run(program, *args):
     return [line.split() for line in r.stdout.splitlines()]
 
 
-ECC_OK, ECC_E_NAN, ECC_E_NOMEM = 0, -3, -6
+def records(lines, key):
+    """The "key value" pairs of the lines that start with key."""
+    return [dict(zip(line[1::2], map(int, line[2::2]))) for line in lines if line[0] == key]
+
+
+ECC_OK, ECC_E_RANGE, ECC_E_NAN, ECC_E_NOMEM = 0, -2, -3, -6
 
 
 def test_float_call_leaves_no_status_behind(program):
@@ -39,9 +44,20 @@ def test_float_call_leaves_no_status_behind(program):
     status word that they set and waits for them: the next call on the stream
     is not disturbed."""
     lines = run(program, "float_exits")
-    calls = [dict(zip(line[1::2], map(int, line[2::2]))) for line in lines]
-    failed = [c for c, line in zip(calls, lines) if line[0] == "float"]
+    failed = records(lines, "float")
     assert {c["rc"] for c in failed} <= {ECC_E_NOMEM, ECC_E_NAN}
     assert sum(c["rc"] == ECC_E_NOMEM for c in failed) >= 6
     assert all(c["status"] == 0 for c in failed), failed
-    assert all(c["rc"] == ECC_OK for c, line in zip(calls, lines) if line[0] == "next"), calls
+    assert all(c["rc"] == ECC_OK for c in records(lines, "next")), lines
+
+
+def test_dual_call_leaves_no_status_behind(program):
+    """The dual curve of a 4-D image that fails after its volume was launched:
+    the status word is clear and the caller's stream has been waited for."""
+    lines = run(program, "dual_exits")
+    failed = records(lines, "dual")
+    assert {c["rc"] for c in failed} == {ECC_E_NOMEM, ECC_E_RANGE}
+    assert any(c["rc"] == ECC_E_NOMEM and c["launched"] for c in failed)
+    assert all(c["status"] == 0 for c in failed), failed
+    assert all(c["waits"] for c in failed if c["launched"]), failed
+    assert all(c["rc"] == ECC_OK for c in records(lines, "next")), lines
