@@ -230,9 +230,14 @@ int ecc_autotune_load(const char *path);
 /* Memory of long-running processes (no passage of the paper: library
  * housekeeping).  The calls above keep, per stream, the device scratch they
  * grew (sized by the largest image computed on that stream) for the next
- * call.  ecc_release_workspaces frees that scratch for the current device;
- * the next call on a stream grows what it needs again.  It first waits for
- * all work on the device.  It must not overlap another call of the library
+ * call.  A float image's call keeps about 4 MiB more per group of its values
+ * (sign and 7 high bits of the exponent; at most 32 groups), whatever its size.
+ * The device blocks of finished streams (ecc_stream_finish, _abort; at most 256
+ * MiB, blocks of up to 64 MiB) are kept for the next streams, and given back as
+ * soon as an allocation of the library finds no memory.
+ * ecc_release_workspaces frees the scratch and these blocks for the current
+ * device; the next call on a stream grows what it needs again.  It first waits
+ * for all work on the device.  It must not overlap another call of the library
  * on the same device, whose buffers it would free.  Stream, batch and serve
  * handles own their buffers and keep them; so does the fixed scratch of
  * ecc_compute_async_noalloc; tuned tilings are kept.

@@ -80,46 +80,67 @@ static bool injected_failure() {
     return k > 0 && ++g_fail_count >= k;
 }
 
-hipError_t dev_malloc(void **p, size_t bytes) {
-    if (injected_failure()) return hipErrorOutOfMemory;
-    return hipMalloc(p, bytes);
-}
-
 // Device blocks of finished ecc_stream objects, kept for the next ones (a
 // block is given to one object at a time, and comes back when the work that
-// used it is done).  At most kCacheBytes are kept, none above kCacheBlock;
-// ecc_release_workspaces frees them.
+// used it is done).  At most kCacheBlocks blocks and kCacheBytes are kept, the
+// oldest making room, none above kCacheBlock; ecc_release_workspaces frees them,
+// and so does any allocation that finds no memory.
 constexpr size_t kCacheBytes = (size_t)256 << 20, kCacheBlock = (size_t)64 << 20;
+constexpr int kCacheBlocks = 64;
 struct CachedBlock {
     int dev;
     void *p;
     size_t bytes;
 };
 static std::mutex g_cache_mu;
-static std::vector<CachedBlock> g_cache;
+static CachedBlock g_cache[kCacheBlocks];  // oldest first
+static int g_cache_n = 0;
 static size_t g_cache_held = 0;
 
+// Takes block i out (g_cache_mu held).
+static CachedBlock cache_take(int i) {
+    const CachedBlock c = g_cache[i];
+    g_cache_held -= c.bytes;
+    for (--g_cache_n; i < g_cache_n; ++i) g_cache[i] = g_cache[i + 1];
+    return c;
+}
+
 hipError_t cache_release(int dev) {
-    std::vector<CachedBlock> mine;
+    CachedBlock mine[kCacheBlocks];
+    int n = 0;
     {
         std::lock_guard<std::mutex> lk(g_cache_mu);
-        for (size_t i = 0; i < g_cache.size();) {
-            if (g_cache[i].dev != dev) {
-                ++i;
-                continue;
-            }
-            g_cache_held -= g_cache[i].bytes;
-            mine.push_back(g_cache[i]);
-            g_cache[i] = g_cache.back();
-            g_cache.pop_back();
+        for (int i = 0; i < g_cache_n;) {
+            if (g_cache[i].dev == dev) mine[n++] = cache_take(i);
+            else ++i;
         }
     }
     hipError_t first = hipSuccess;
-    for (const CachedBlock &c : mine) {
-        const hipError_t e = hipFree(c.p);
+    for (int i = 0; i < n; ++i) {
+        const hipError_t e = hipFree(mine[i].p);
         if (e != hipSuccess && first == hipSuccess) first = e;
     }
     return first;
+}
+
+// hipMalloc on dev, the current device; where there is no memory, again
+// without the kept blocks.  (The runtime's own record of the failure is
+// cleared: the caller reports it, and no later launch does.)
+static hipError_t malloc_without_cache(int dev, void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipErrorOutOfMemory) return e;
+    (void)hipGetLastError();
+    (void)cache_release(dev);
+    e = hipMalloc(p, bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
+hipError_t dev_malloc(void **p, size_t bytes) {
+    if (injected_failure()) return hipErrorOutOfMemory;
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    return e == hipSuccess ? malloc_without_cache(dev, p, bytes) : e;
 }
 
 hipError_t cache_malloc(int dev, void **p, size_t bytes, size_t *got) {
@@ -127,41 +148,37 @@ hipError_t cache_malloc(int dev, void **p, size_t bytes, size_t *got) {
     bytes = (bytes + 4095) & ~(size_t)4095;
     {
         std::lock_guard<std::mutex> lk(g_cache_mu);
-        size_t best = g_cache.size();  // the smallest that fits and is at most a quarter larger
-        for (size_t i = 0; i < g_cache.size(); ++i)
+        int best = -1;  // the smallest that fits and is at most a quarter larger
+        for (int i = 0; i < g_cache_n; ++i)
             if (g_cache[i].dev == dev && g_cache[i].bytes >= bytes && g_cache[i].bytes <= bytes + bytes / 4 &&
-                (best == g_cache.size() || g_cache[i].bytes < g_cache[best].bytes))
+                (best < 0 || g_cache[i].bytes < g_cache[best].bytes))
                 best = i;
-        if (best < g_cache.size()) {
-            *p = g_cache[best].p;
-            *got = g_cache[best].bytes;
-            g_cache_held -= *got;
-            g_cache[best] = g_cache.back();
-            g_cache.pop_back();
+        if (best >= 0) {
+            const CachedBlock c = cache_take(best);
+            *p = c.p;
+            *got = c.bytes;
             return hipSuccess;
         }
     }
     *got = bytes;
-    hipError_t e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        (void)cache_release(dev);
-        e = hipMalloc(p, bytes);
-    }
-    return e;
+    return malloc_without_cache(dev, p, bytes);
 }
 
 void cache_free(int dev, void *p, size_t bytes) {
     if (!p) return;
-    if (bytes <= kCacheBlock) {
-        std::lock_guard<std::mutex> lk(g_cache_mu);
-        if (g_cache_held + bytes <= kCacheBytes) {
-            g_cache.push_back({dev, p, bytes});
-            g_cache_held += bytes;
-            return;
-        }
+    if (bytes > kCacheBlock) {
+        (void)hipFree(p);
+        return;
     }
-    (void)hipFree(p);
+    CachedBlock out[kCacheBlocks];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_cache_mu);
+        while (g_cache_n == kCacheBlocks || g_cache_held + bytes > kCacheBytes) out[n++] = cache_take(0);
+        g_cache[g_cache_n++] = {dev, p, bytes};
+        g_cache_held += bytes;
+    }
+    for (int i = 0; i < n; ++i) (void)hipFree(out[i].p);
 }
 
 hipError_t host_malloc(void **p, size_t bytes, unsigned flags) {

@@ -239,10 +239,36 @@ static int dual_exits(void) {
     return 0;
 }
 
+/* Memory enough for a call only without the blocks that a finished stream left. */
+static int kept_blocks(void) {
+    ecc_dims d = dims_of(3, 64, 2048, 2048, 1), v = dims_of(3, 200, 300, 300, 1);
+    void *img = device_bytes(1 << 26);
+    static int64_t chi[16384];
+    ecc_curve c = {16384, 0, chi, NULL};
+    for (int k = 0; k < 100; ++k) {  /* more blocks than are kept, of many sizes */
+        ecc_dims small = dims_of(2, 100, 100 + 7000 * k, 1, 1);
+        ecc_stream *st[2];
+        for (int i = 0; i < 2; ++i) ecc_stream_begin(&small, ECC_U8, NULL, &st[i]);
+        for (int i = 0; i < 2; ++i) ecc_stream_abort(st[i]);
+    }
+    printf("small kept %zu\n", used);
+    ecc_stream *st = NULL;
+    printf("begin rc %d\n", ecc_stream_begin(&d, ECC_U14, NULL, &st));
+    ecc_stream_abort(st);
+    printf("large kept %zu\n", used);
+    limit_bytes = used + (1 << 20);
+    printf("call rc %d\n", ecc_compute(img, &v, ECC_U14, &c, NULL));
+    printf("after used %zu\n", used);
+    limit_bytes = used;
+    printf("none rc %d error %d\n", ecc_compute(img, &d, ECC_U14, &c, NULL), (int)hipGetLastError());
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
     if (!strcmp(what, "dual_exits")) return dual_exits();
+    if (!strcmp(what, "kept_blocks")) return kept_blocks();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

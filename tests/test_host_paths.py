@@ -61,3 +61,15 @@ def test_dual_call_leaves_no_status_behind(program):
     assert all(c["status"] == 0 for c in failed), failed
     assert all(c["waits"] for c in failed if c["launched"]), failed
     assert all(c["rc"] == ECC_OK for c in records(lines, "next")), lines
+
+
+def test_kept_blocks_give_way(program):
+    """The device blocks that finished streams left are bounded, and given
+    back when another call finds no memory; a call that fails all the same
+    leaves no error of the runtime behind."""
+    lines = run(program, "kept_blocks")
+    assert records(lines, "begin") == [{"rc": ECC_OK}]
+    kept = [int(line[2]) for line in lines if line[1] == "kept"]
+    assert 0 < kept[0] <= 256 << 20 and 32 << 20 <= kept[1] <= 256 << 20
+    assert records(lines, "call") == [{"rc": ECC_OK}]
+    assert records(lines, "none") == [{"rc": ECC_E_NOMEM, "error": 0}]
