@@ -1006,11 +1006,20 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
     hipError_t e = hipEventSynchronize(ev);
     int present = 0;
     for (int w = 0; w < 8; ++w) present += __builtin_popcount((ws->host_status + 4)[w]);
-    const bool by_bits = !rc && e == hipSuccess && present <= kMaxDistinctBytes;
+    bool by_bits = !rc && e == hipSuccess && present <= kMaxDistinctBytes;
+    if (by_bits) {
+        rc = ensure_bytes(&ws->fbits, &ws->fbits_bytes, distinct_scratch_bytes(present, n));
+        if (rc == ECC_E_NOMEM) {  // the sort's buffers are there, and its records' are as small as the image
+            g_err_clear();
+            rc = ECC_OK;
+            by_bits = false;
+        } else if (rc) {
+            (void)hipEventDestroy(ev);
+            return rc;
+        }
+    }
     if (by_bits) {
         (void)hipEventDestroy(ev);
-        rc = ensure_bytes(&ws->fbits, &ws->fbits_bytes, distinct_scratch_bytes(present, n));
-        if (rc) return rc;
         rc = launch_distinct_curve(n, present, key[0], starts, head, ws->fbits, nz, nz_cnt, regions, region_slots,
                                    out_keys, out_chi, count_dev, (int64_t *)(ws->host_status_dev + 12), ws->status,
                                    ws->host_status_dev + 14, s);

@@ -264,11 +264,24 @@ static int kept_blocks(void) {
     return 0;
 }
 
+/* A float image of a few thousand voxels on a nearly full card. */
+static int float_nearly_full(void) {
+    ecc_dims d = dims_of(3, 10, 20, 30, 1);
+    void *img = device_bytes(6000 * 4);
+    static float keys[6000];
+    static int64_t chi[6000];
+    ecc_curve c = {6000, 0, chi, keys};
+    limit_bytes = 1 << 20;
+    printf("float rc %d\n", ecc_compute(img, &d, ECC_F32, &c, NULL));
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
     if (!strcmp(what, "dual_exits")) return dual_exits();
     if (!strcmp(what, "kept_blocks")) return kept_blocks();
+    if (!strcmp(what, "float_nearly_full")) return float_nearly_full();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

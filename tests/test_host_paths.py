@@ -73,3 +73,9 @@ def test_kept_blocks_give_way(program):
     assert 0 < kept[0] <= 256 << 20 and 32 << 20 <= kept[1] <= 256 << 20
     assert records(lines, "call") == [{"rc": ECC_OK}]
     assert records(lines, "none") == [{"rc": ECC_E_NOMEM, "error": 0}]
+
+
+def test_small_float_image_on_a_nearly_full_card(program):
+    """The bits of the distinct values take some MiB however small the image;
+    where they find no memory the keys are sorted instead."""
+    assert records(run(program, "float_nearly_full"), "float") == [{"rc": ECC_OK}]
