@@ -72,7 +72,8 @@ using namespace ecc;
 // tiles of max(min_planes, planes / split) planes (or the whole image), so
 // that small images take one workgroup and large ones a few hundred.  The
 // defaults (64, 4) are the footprint's; runs take what ecc_batch_autotune
-// picked, or their own plan (below).
+// picked, or their own plan (below), whose count rows are no larger in all
+// than the footprints'.
 constexpr int kBatchMinPlanes = 64, kBatchSplit = 4;
 
 IntTiling batch_tiling(const IntView &v, int min_planes = kBatchMinPlanes, int split = kBatchSplit) {
@@ -111,7 +112,12 @@ IntTiling batch_tiling(const IntView &v, int min_planes = kBatchMinPlanes, int s
 // longest tile's walk for the last tiles to end.  Fitted to nine batches of 8
 // to 128 images at ten depths (7 % off on average); with tiles of 64 planes or
 // a quarter of the image, the 2-D images' long tiles ended last (96 images of
-// the serving mix: 287 us, planned 228; 16 images 170 and 97).
+// the serving mix: 287 us, planned 228; 16 images 170 and 97).  Depths whose
+// count rows take more memory than the footprints count for the run's images
+// are passed over (admission adds up the footprints): the mix's depth of 128
+// takes 0.6 of it; runs of fewer than about 16 images would take depths of 48
+// with 1.2 to 1.3 times the rows.  The footprint's own tiles are one of the
+// choices, and the only one for images of a few columns and millions of rows.
 constexpr double kTilePlanes14 = 22.0, kTilePlanes8 = 11.0;
 int64_t planned_walk(int64_t n0, int64_t depth) {
     const int64_t k = (n0 + depth - 1) / depth;
@@ -129,6 +135,7 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 struct Prepared {
     IntView view;
     IntTiling tl;
+    int64_t tiles_xy;  // tiles of one depth
     int group;  // (dtype == U14) * 2 + (nin == 2)
     int m;
     int64_t voxels;
@@ -730,7 +737,8 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
             wide.push_back(j);
             continue;
         }
-        P.tl = b->planned ? batch_tiling(P.view, INT32_MAX, 1) : batch_tiling(P.view, b->min_planes, b->split);
+        P.tl = b->planned ? batch_tiling(P.view) : batch_tiling(P.view, b->min_planes, b->split);
+        P.tiles_xy = P.tl.grid / ((P.view.n0 + P.tl.zc - 1) / P.tl.zc);
         P.group = (J.dtype == ECC_U14 ? 2 : 0) + (P.view.nin == 2 ? 1 : 0);
         P.m = (int)threshold_count(J.dtype);
         P.voxels = total;
@@ -738,28 +746,30 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
         vcec_words += P.m;
     }
     if (b->planned) {
-        static constexpr int64_t kDepths[] = {16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 1024};
-        int64_t depth = kDepths[0];
+        static constexpr int64_t kDepths[] = {0, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 1024};
+        int64_t depth = 0, limit = 0;  // 0: the footprints' tiles, with `limit` entries of count rows
         double best = 0;
         for (const int64_t d : kDepths) {
             double planes = 0;
-            int64_t longest = 0;
+            int64_t longest = 0, entries = 0;
             for (const Prepared &P : prep) {
                 if (P.m == 0) continue;  // (a 16-bit job)
-                const int64_t zc = planned_walk(P.view.n0, d), tiles = P.tl.grid * ((P.view.n0 + zc - 1) / zc);
+                const int64_t zc = d ? planned_walk(P.view.n0, d) : P.tl.zc, tiles = P.tiles_xy * ((P.view.n0 + zc - 1) / zc);
                 planes += (double)tiles * ((double)zc * (P.tl.wx * P.tl.wy) / 16.0 + (P.m > 256 ? kTilePlanes14 : kTilePlanes8));
                 longest = std::max(longest, zc);
+                entries += tiles * P.m;
             }
             const double cost = planes / b->tile_grid + 0.25 * (double)longest;
-            if (best == 0 || cost < best) {
+            if (d == 0) limit = entries;
+            if (d == 0 || (entries <= limit && cost < best)) {
                 best = cost;
                 depth = d;
             }
         }
         for (Prepared &P : prep) {
-            if (P.m == 0) continue;
+            if (P.m == 0 || depth == 0) continue;
             P.tl.zc = (int)planned_walk(P.view.n0, depth);
-            P.tl.grid *= (int)((P.view.n0 + P.tl.zc - 1) / P.tl.zc);
+            P.tl.grid = (int)(P.tiles_xy * ((P.view.n0 + P.tl.zc - 1) / P.tl.zc));
         }
     }
     for (const Prepared &P : prep) {

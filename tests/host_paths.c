@@ -276,12 +276,57 @@ static int float_nearly_full(void) {
     return 0;
 }
 
+/* What a run allocates, against its jobs' footprints less images and curves. */
+static void batch_of(const char *name, int n, const ecc_dims *dims, const int *dtypes) {
+    ecc_batch *b = NULL;
+    ecc_job jobs[64];
+    int64_t bound = (64 << 10) + 4 * n + 1024;  /* the table and the status words */
+    for (int i = 0; i < n; ++i) {
+        ecc_job j = {device_bytes(16), dims[i], dtypes[i], (int64_t *)device_bytes(65536 * 8)};
+        int64_t foot = 0, bytes = dtypes[i] == ECC_U8 ? 1 : 2;
+        ecc_job_footprint(&j, &foot);
+        for (int k = 0; k < dims[i].ndim; ++k) bytes *= dims[i].n[k];
+        bound += foot - bytes - 8 * (dtypes[i] == ECC_U8 ? 256 : 16384);
+        jobs[i] = j;
+    }
+    ecc_batch_create(NULL, &b);
+    const size_t before = used;
+    const int rc = ecc_batch_run(b, n, jobs, NULL);
+    printf("%s rc %d bytes %zu bound %lld\n", name, rc, used - before, (long long)bound);
+    ecc_batch_destroy(b);
+}
+static int batch_rows(void) {
+    setenv("ECC_BATCH_GRAPH", "0", 1);
+    const int u14[1] = {ECC_U14}, u8[1] = {ECC_U8};
+    ecc_dims d = dims_of(3, 128, 128, 128, 1);
+    batch_of("cube", 1, &d, u14);
+    d = dims_of(2, 1 << 30, 2, 1, 1);
+    batch_of("columns", 1, &d, u14);
+    d = dims_of(2, 2000, 64, 1, 1);
+    batch_of("picture", 1, &d, u8);
+    unsigned seed = 1;
+    for (int n = 2; n <= 64; n *= 2) {
+        ecc_dims dims[64];
+        int types[64];
+        for (int i = 0; i < n; ++i) {
+            int64_t r[3];
+            for (int k = 0; k < 3; ++k) r[k] = (seed = seed * 1664525u + 1013904223u) >> 8;
+            types[i] = r[0] & 1 ? ECC_U8 : ECC_U14;
+            if (types[i] == ECC_U8) dims[i] = dims_of(2, 32 + r[1] % 2000, 32 + r[2] % 2000, 1, 1);
+            else dims[i] = dims_of(3, 16 + r[0] / 2 % 241, 16 + r[1] % 241, 16 + r[2] % 241, 1);
+        }
+        batch_of("mix", n, dims, types);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
     if (!strcmp(what, "dual_exits")) return dual_exits();
     if (!strcmp(what, "kept_blocks")) return kept_blocks();
     if (!strcmp(what, "float_nearly_full")) return float_nearly_full();
+    if (!strcmp(what, "batch_rows")) return batch_rows();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

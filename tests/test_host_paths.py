@@ -79,3 +79,13 @@ def test_small_float_image_on_a_nearly_full_card(program):
     """The bits of the distinct values take some MiB however small the image;
     where they find no memory the keys are sorted instead."""
     assert records(run(program, "float_nearly_full"), "float") == [{"rc": ECC_OK}]
+
+
+def test_batch_memory_is_within_the_footprints(program):
+    """What a run's planned tiles make it allocate is at most what
+    ecc_job_footprint counts for its images (admission adds those up)."""
+    lines = run(program, "batch_rows")
+    assert len(lines) == 9
+    for line in lines:
+        r = dict(zip(line[1::2], map(int, line[2::2])))
+        assert r["rc"] == ECC_OK and r["bytes"] <= r["bound"], line
