@@ -334,11 +334,10 @@ void ecc_batch_destroy(ecc_batch *b);
 
 /* Tile depth of a batch context.  By default each run plans it from its
  * images.  Times ecc_batch_run on the given jobs (their chi buffers are
- * written) as planned and with an image of n0 planes cut into tiles of
- * max(min_planes, n0 / split) planes, for min_planes in {16, 32, 64, 128} x
- * split in {2, 4, 8}, and keeps the fastest for the context's later runs; the
- * outputs (optional) receive the fastest min_planes and split and the time of
- * what is kept.
+ * written) with an image of n0 planes cut into tiles of max(min_planes,
+ * n0 / split) planes, for min_planes in {16, 32, 64, 128} x split in {2, 4, 8},
+ * and keeps the fastest for the context's later runs, which then plan no
+ * more; the outputs (optional) receive it and its time.
  * Synchronizes the context's stream.  Errors as ecc_batch_run. */
 int ecc_batch_autotune(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, int32_t *min_planes, int32_t *split,
                        float *ms);

@@ -52,7 +52,7 @@ struct ecc_batch {
     int tile_grid = 0, colsum_grid = 0, scan_grid = 0;
     // batch tile depth (ecc_batch_autotune)
     int min_planes = 64, split = 4;
-    bool planned = true;  // until ecc_batch_autotune: each run plans its own depth
+    bool planned = true;  // until ecc_batch_autotune picks one: each run plans its own depth
     // scratch shared by consecutive runs (ordered by the stream)
     int32_t *partial8 = nullptr;
     size_t partial8_bytes = 0;
@@ -946,14 +946,13 @@ int ecc_batch_autotune(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, int32_
     int rc = e == hipSuccess ? ECC_OK : hip_fail(e, "ecc_batch_autotune: events");
     const int mp_c[4] = {16, 32, 64, 128}, sp_c[3] = {2, 4, 8};
     int best_mp = b->min_planes, best_sp = b->split;
-    float best = 1e30f, plan = 1e30f;
-    for (int i = -1; i < 4 && !rc; ++i)  // i = -1: the planned depth
-        for (int k = 0; k < (i < 0 ? 1 : 3) && !rc; ++k) {
-            b->planned = i < 0;
-            if (i >= 0) {
-                b->min_planes = mp_c[i];
-                b->split = sp_c[k];
-            }
+    float best = 1e30f;
+    const bool was_planned = b->planned;
+    b->planned = false;
+    for (int i = 0; i < 4 && !rc; ++i)
+        for (int k = 0; k < 3 && !rc; ++k) {
+            b->min_planes = mp_c[i];
+            b->split = sp_c[k];
             float tmin = 1e30f;
             for (int rep = 0; rep < 4 && !rc; ++rep) {  // one warm-up, three timed
                 if ((e = hipEventRecord(ev[0], b->stream)) != hipSuccess) rc = hip_fail(e, "ecc_batch_autotune");
@@ -965,9 +964,7 @@ int ecc_batch_autotune(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, int32_
                     rc = hip_fail(e, "ecc_batch_autotune");
                 if (!rc && rep > 0 && t < tmin) tmin = t;
             }
-            if (!rc && i < 0) {
-                plan = tmin;
-            } else if (!rc && tmin < best) {
+            if (!rc && tmin < best) {
                 best = tmin;
                 best_mp = mp_c[i];
                 best_sp = sp_c[k];
@@ -977,11 +974,11 @@ int ecc_batch_autotune(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, int32_
     if (ev[1]) (void)hipEventDestroy(ev[1]);
     b->min_planes = best_mp;
     b->split = best_sp;
-    b->planned = rc || plan <= best;
+    if (rc) b->planned = was_planned;
     if (!rc) {
         if (min_planes) *min_planes = best_mp;
         if (split) *split = best_sp;
-        if (ms) *ms = std::min(plan, best);
+        if (ms) *ms = best;
     }
     if (prev != b->device) (void)hipSetDevice(prev);
     return rc;

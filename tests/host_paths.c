@@ -104,8 +104,12 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t e) { return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t e) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b) { *ms = 1.0f; return hipSuccess; }
+static int32_t copied[2];  /* the first words of the last copy to the device */
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {
-    if (is_device(d)) return hipSuccess;
+    if (is_device(d)) {
+        if (!is_device(s) && n >= sizeof copied) memcpy(copied, s, sizeof copied);
+        return hipSuccess;
+    }
     if (!is_device(s)) memcpy(d, s, n);
     else if (n == 4) memcpy(d, &status_word, 4);
     else memset(d, 0, n);
@@ -320,6 +324,24 @@ static int batch_rows(void) {
     return 0;
 }
 
+/* The tiles of a run (word 1 of its table) after the tuner, every candidate as fast. */
+static int batch_tuned(void) {
+    setenv("ECC_BATCH_GRAPH", "0", 1);
+    const int n0[3] = {256, 2000, 150};
+    for (int i = 0; i < 3; ++i) {
+        ecc_batch *b = NULL;
+        ecc_job j = {device_bytes(16), dims_of(3, n0[i], 32, 64, 1), ECC_U14, (int64_t *)device_bytes(65536 * 8)};
+        int32_t min_planes = 0, split = 0;
+        float ms = 0;
+        ecc_batch_create(NULL, &b);
+        const int rc = ecc_batch_autotune(b, 1, &j, &min_planes, &split, &ms);
+        ecc_batch_run(b, 1, &j, NULL);
+        printf("tuned rc %d n0 %d min_planes %d split %d tiles %d\n", rc, n0[i], min_planes, split, copied[1]);
+        ecc_batch_destroy(b);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -327,6 +349,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "kept_blocks")) return kept_blocks();
     if (!strcmp(what, "float_nearly_full")) return float_nearly_full();
     if (!strcmp(what, "batch_rows")) return batch_rows();
+    if (!strcmp(what, "batch_tuned")) return batch_tuned();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

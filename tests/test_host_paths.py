@@ -89,3 +89,13 @@ def test_batch_memory_is_within_the_footprints(program):
     for line in lines:
         r = dict(zip(line[1::2], map(int, line[2::2])))
         assert r["rc"] == ECC_OK and r["bytes"] <= r["bound"], line
+
+
+def test_batch_tuner_reports_the_depth_in_use(program):
+    """After ecc_batch_autotune a run cuts an image into tiles of
+    max(min_planes, n0 / split) planes, with the values that it returned."""
+    tuned = records(run(program, "batch_tuned"), "tuned")
+    assert len(tuned) == 3
+    for t in tuned:
+        depth = max(t["min_planes"], -(-t["n0"] // t["split"]))
+        assert t["rc"] == ECC_OK and t["tiles"] == -(-t["n0"] // depth), t
