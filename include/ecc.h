@@ -184,16 +184,18 @@ int ecc_compute_async_noalloc(const void *image_dev, const ecc_dims *dims, ecc_d
  * Tile shapes.  The integer kernel's tiling of a launch has three
  * parameters: rows per wave (2 or 4), waves along x (up to 16 of a
  * workgroup's 16) and workgroups per CU (the image is split along axis 0
- * into at most about that many tiles per CU, as many as fill whole rounds of
- * the CUs best; planes with more tiles give a workgroup several).  By default a rule of the launch's size picks them
- * (measured on MI355X); ecc_autotune times the candidates on an image and
- * keeps the fastest for its shape in a process-wide table consulted by every
- * later launch of that shape (dtype, plane shape and number of planes; the
- * planes of a streamed chunk are its own shape).  Results do not depend on
- * the tiling. */
+ * until there are about that many tiles per CU; planes with more tiles give a
+ * workgroup several).  By default a rule of the launch's size picks them
+ * (measured on MI355X) and, for launches of less than 2^30 voxels (8-bit: 2^27),
+ * takes fewer workgroups where those fill whole rounds of the CUs better.
+ * ecc_autotune times the rule's tiling and the other candidates, those exactly
+ * as their parameters say, on an image and keeps the fastest for its shape in a
+ * process-wide table consulted by every later launch of that shape (dtype,
+ * plane shape and number of planes; the planes of a streamed chunk are its own
+ * shape).  Results do not depend on the tiling. */
 typedef struct {
     int32_t rows;          /* rows per wave: 2 or 4 */
-    int32_t tiles_per_cu;  /* workgroups per CU: 4, 8 or 16 */
+    int32_t tiles_per_cu;  /* workgroups per CU: 4, 8 or 16 (the rule's: at most) */
     int32_t waves_x;       /* waves along x per workgroup: 8 or 16 */
     float ms;              /* ecc_autotune: the fastest candidate's time (kernel + column sums) */
 } ecc_tiling;

@@ -517,15 +517,20 @@ static ecc_tiling tiling_params(const IntView &v, int dtype, int64_t planes) {
     return c;
 }
 
-// Whether a launch's workgroups are planned (make_int_tiling): 14-bit
-// launches below 2^30 voxels, 8-bit ones below 2^27.  Above that, finer splits
-// than the plan's were as fast or faster (1024^3 at 14 bits: 649 us in 1024
-// workgroups, 658 in 512; 128 x 1024^2 at 8 bits: 102 us against 104).
-static bool planned_tiling(const IntView &v, int dtype, int64_t planes) {
-    return planes * (int64_t)v.n1 * v.n2 < (int64_t)1 << (dtype == ECC_U8 ? 27 : 30) && env_int("ECC_INT_PLAN", 1) != 0;
+// Whether a launch's workgroups are planned (make_int_tiling): by the rule's
+// parameters, 14-bit launches below 2^30 voxels, 8-bit ones below 2^27.  Above
+// that, finer splits than the plan's were as fast or faster (1024^3 at 14 bits:
+// 649 us in 1024 workgroups, 658 in 512; 128 x 1024^2 at 8 bits: 102 us against
+// 104).  Other parameters (a tuned or loaded tiling, ECC_INT_*) are taken as
+// they are: they were timed so.
+static bool planned_tiling(const IntView &v, int dtype, int64_t planes, const ecc_tiling &c) {
+    if (planes * (int64_t)v.n1 * v.n2 >= (int64_t)1 << (dtype == ECC_U8 ? 27 : 30) || env_int("ECC_INT_PLAN", 1) == 0)
+        return false;
+    const ecc_tiling r = rule_tiling(v, dtype, planes);
+    return c.rows == r.rows && c.tiles_per_cu == r.tiles_per_cu && c.waves_x == r.waves_x;
 }
 static IntTiling tiling_from(const IntView &v, int dtype, int64_t planes, const ecc_tiling &c, int max_grid) {
-    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned_tiling(v, dtype, planes),
+    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned_tiling(v, dtype, planes, c),
                            dtype == ECC_U8 ? 0.0075 : 0.045);
 }
 

@@ -43,6 +43,7 @@ static int stream_waits;      /* for the stream that the scenario gave */
 static hipStream_t its_stream;
 static int top_bytes = 3;     /* top bytes of the float image's keys */
 static long change_launches;  /* of the change kernel */
+static unsigned int_grid;     /* workgroups of the last launch of the integer kernel */
 
 static int is_device(const void *p) { return (uint64_t)p >= DEVICE_LO && (uint64_t)p < DEVICE_HI; }
 static hipError_t result(hipError_t e) {
@@ -173,6 +174,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
     } else if (strstr(name, "11scan_kernel")) {
         if ((out = host_argument(args, 6))) *out = status_word;
         status_word = 0;
+    } else if (strstr(name, "int_vcec_kernel")) {
+        int_grid = g.x;
     } else if (strstr(name, "change_kernel")) {
         ++change_launches;
         if (range_image) status_word |= 1u;
@@ -342,6 +345,25 @@ static int batch_tuned(void) {
     return 0;
 }
 
+/* The workgroups of a launch by the rule and with tilings loaded from argv[2]. */
+static int tilings(const char *path) {
+    ecc_dims d = dims_of(3, 200, 300, 300, 1);
+    void *img = device_bytes(1 << 26);
+    int64_t *chi = device_bytes(16384 * 8);
+    ecc_compute_async(img, &d, ECC_U14, chi, NULL, NULL);
+    printf("rule grid %u\n", int_grid);
+    const char *params[4] = {"2 4 16", "2 16 16", "2 8 8", "4 4 8"};
+    for (int i = 0; i < 4; ++i) {
+        FILE *f = fopen(path, "w");
+        fprintf(f, "ecc-tiling-v1 2 2 300 300 200 %s 0.1\n", params[i]);
+        fclose(f);
+        const int rc = ecc_autotune_load(path);
+        ecc_compute_async(img, &d, ECC_U14, chi, NULL, NULL);
+        printf("loaded rc %d grid %u\n", rc, int_grid);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -350,6 +372,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "float_nearly_full")) return float_nearly_full();
     if (!strcmp(what, "batch_rows")) return batch_rows();
     if (!strcmp(what, "batch_tuned")) return batch_tuned();
+    if (!strcmp(what, "tilings")) return tilings(argv[2]);
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

@@ -99,3 +99,23 @@ def test_batch_tuner_reports_the_depth_in_use(program):
     for t in tuned:
         depth = max(t["min_planes"], -(-t["n0"] // t["split"]))
         assert t["rc"] == ECC_OK and t["tiles"] == -(-t["n0"] // depth), t
+
+
+def test_loaded_tilings_are_taken_as_they_are(program, tmp_path):
+    """A stored tiling's workgroups follow from its parameters (200 planes of
+    300 x 300 in at least tiles_per_cu * 256 tiles, walks of 8 planes or more);
+    only the rule's own parameters are planned."""
+    lines = run(program, "tilings", str(tmp_path / "tiling.txt"))
+    rule = records(lines, "rule")[0]["grid"]
+    want = []
+    for rows, per_cu, wx in ((2, 16, 16), (2, 8, 8), (4, 4, 8)):
+        w = min(wx, 5)  # 300 columns are 5 segments of 64
+        tiles = -(-5 // w) * -(-(-(-300 // rows)) // (16 // w))
+        walk = max(8, -(-200 // min(200, -(-256 * per_cu // tiles))))
+        all_tiles = tiles * -(-200 // walk)
+        per = -(-all_tiles // (256 * per_cu)) if all_tiles > 256 * per_cu else 1
+        want.append(-(-all_tiles // per))
+    loaded = records(lines, "loaded")
+    assert all(x["rc"] == 1 for x in loaded)
+    assert [x["grid"] for x in loaded] == [rule, *want], (rule, want)
+    assert rule not in want
