@@ -548,7 +548,10 @@ int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hi
 // 16384-bin histogram (64 KiB of LDS), one workgroup per CU (two waves per
 // SIMD at the kernel's registers); the 256-bin form has four per workgroup.
 // The workgroups take items in turn, so there is one count row per workgroup
-// of a grid of at most one (16384 bins) or four (256 bins) per CU.
+// of a grid of at most one (16384 bins) or four (256 bins) per CU.  Bins and
+// rows are int32: a launch has less than 2^30 values (of a resident image, and
+// of a stream's launches), its items go round all workgroups of a full grid, so
+// that one counts at most some 2^23 voxels, and a voxel's change is at most 16.
 static int int_geometry(const ChangeJob &job, ChangeParams *p, int *waves, int64_t *grid) {
     if (job.nl != 2) {
         set_error("internal error: integer change kernel on %d line axes", job.nl);

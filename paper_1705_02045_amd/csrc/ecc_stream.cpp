@@ -130,29 +130,52 @@ bool is_device_ptr(const void *p) {
 int64_t min64(int64_t a, int64_t b) { return a < b ? a : b; }
 
 // 4-D images: the changes of image planes [lo, hi) of a push whose chunk
-// holds image planes from f on, the carry holding the planes before it.
+// holds image planes from f on, the carry holding the planes before it, in
+// launches of less than 2^30 values (the bound of the change kernel's counts).
 int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int64_t hi) {
-    ChangeJob j{};
-    j.dtype = st->dtype;
-    j.nl = 2;
-    j.nx = (int32_t)st->n4[3];
-    j.ny = (int32_t)st->n4[2];
-    j.nz = (int32_t)st->n4[1];
-    j.src = src;
-    j.e0 = (int32_t)(lo - f);
-    j.e1 = (int32_t)(hi - f);
-    j.lo_inf = lo == 0;
-    j.hi_inf = hi == st->view.n0;
-    if (st->dtype == ECC_U16) return launch_change_counts(j, nullptr, st->vcec, st->status, st->compute);
-    int rows = 0;
-    int rc = change_count_rows(j, &rows);
+    const int64_t step = (((int64_t)1 << 30) - 1) / (st->n4[1] * st->n4[2] * st->n4[3]);  // (>= 3: planes of at most 2^28)
+    auto launch = [&](int64_t b0) {
+        ChangeJob j{};
+        j.dtype = st->dtype;
+        j.nl = 2;
+        j.nx = (int32_t)st->n4[3];
+        j.ny = (int32_t)st->n4[2];
+        j.nz = (int32_t)st->n4[1];
+        j.src = src;
+        const int64_t b1 = min64(b0 + step, hi);
+        j.e0 = (int32_t)(b0 - f);
+        j.e1 = (int32_t)(b1 - f);
+        j.lo_inf = b0 == 0;
+        j.hi_inf = b1 == st->view.n0;
+        return j;
+    };
+    if (st->dtype == ECC_U16) {
+        for (int64_t b = lo; b < hi; b += step) {
+            int rc = launch_change_counts(launch(b), nullptr, st->vcec, st->status, st->compute);
+            if (rc) return rc;
+        }
+        return ECC_OK;
+    }
+    // the rows at their largest number first: a push that fails to allocate
+    // has added nothing, so it can be pushed again
+    int most = 0;
+    for (int64_t b = lo; b < hi; b += step) {
+        int rows = 0;
+        int rc = change_count_rows(launch(b), &rows);
+        if (rc) return rc;
+        if (rows > most) most = rows;
+    }
+    int rc = take(st, &st->partial, &st->partial_bytes, (size_t)most * st->m * sizeof(int32_t));
     if (rc) return rc;
-    rc = take(st, &st->partial, &st->partial_bytes, (size_t)rows * st->m * sizeof(int32_t));
-    if (rc) return rc;
-    rc = launch_change_counts(j, st->partial, nullptr, st->status, st->compute);
-    if (rc) return rc;
-    return launch_merge(st->partial, rows, st->m, st->vcec, true, false, nullptr, st->status, nullptr,
-                        st->compute);
+    for (int64_t b = lo; b < hi; b += step) {
+        int rows = 0;
+        rc = change_count_rows(launch(b), &rows);
+        if (!rc) rc = launch_change_counts(launch(b), st->partial, nullptr, st->status, st->compute);
+        if (!rc)
+            rc = launch_merge(st->partial, rows, st->m, st->vcec, true, false, nullptr, st->status, nullptr, st->compute);
+        if (rc) return rc;
+    }
+    return ECC_OK;
 }
 
 // Adds the changes of image planes [emitted, hi) of a push whose chunk holds

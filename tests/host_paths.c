@@ -364,6 +364,24 @@ static int tilings(const char *path) {
     return 0;
 }
 
+/* The launches of 4-D chunks of more than 2^30 values. */
+static int stream_4d(void) {
+    const int types[3] = {ECC_U8, ECC_U14, ECC_U16};
+    for (int i = 0; i < 3; ++i) {
+        ecc_dims d = dims_of(4, 10000, 64, 64, 64);
+        ecc_stream *st = NULL;
+        ecc_stream_begin(&d, types[i], NULL, &st);
+        change_launches = 0;
+        const int rc = ecc_stream_push_chunk(st, device_bytes((size_t)5000 << 19), 5000);
+        printf("push rc %d values %ld launches %ld\n", rc, 4999L << 18, change_launches);
+        change_launches = 0;
+        const int rc2 = ecc_stream_push_chunk(st, device_bytes((size_t)5000 << 19), 5000);
+        printf("push rc %d values %ld launches %ld\n", rc2, 5001L << 18, change_launches);
+        ecc_stream_abort(st);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -373,6 +391,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "batch_rows")) return batch_rows();
     if (!strcmp(what, "batch_tuned")) return batch_tuned();
     if (!strcmp(what, "tilings")) return tilings(argv[2]);
+    if (!strcmp(what, "stream_4d")) return stream_4d();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

@@ -119,3 +119,11 @@ def test_loaded_tilings_are_taken_as_they_are(program, tmp_path):
     assert all(x["rc"] == 1 for x in loaded)
     assert [x["grid"] for x in loaded] == [rule, *want], (rule, want)
     assert rule not in want
+
+
+def test_4d_chunks_are_cut_below_2_30_values(program):
+    """The change kernel counts in int32: a launch has less than 2^30 values."""
+    pushes = records(run(program, "stream_4d"), "push")
+    assert len(pushes) == 6
+    for p in pushes:
+        assert p["rc"] == ECC_OK and p["launches"] * ((1 << 30) - 1) >= p["values"], p
