@@ -434,11 +434,32 @@ __global__ void __launch_bounds__(1024) box_faces_kernel(const T *__restrict__ i
 
 static int64_t face_units(const BoxFace &F) { return (F.nb / 64 + 1) * (F.na / kFaceRows + 1); }
 
+// The faces of the launch that starts with face f0: as many as its table holds,
+// with up to 2^30 units in all, so that a thread's next unit stays below 2^31
+// (2^31 - 5 x 2 x 2 voxels take two launches), and up to 2^37 positions, so that
+// a workgroup's int32 bins hold its share (a position changes a bin by at most
+// 2).  One face alone is within both: one that is not is a face of a volume
+// beyond the card's memory.
+static int faces_of_launch(const BoxFace *faces, int nfaces, int f0, int64_t *units) {
+    int n = 0;
+    int64_t positions = 0;
+    *units = 0;
+    while (n < kFacesPerLaunch && f0 + n < nfaces) {
+        const BoxFace &F = faces[f0 + n];
+        const int64_t u = face_units(F), p = (F.na + 1) * (F.nb + 1);
+        if (n > 0 && (*units + u > INT32_MAX / 2 || positions + p > (int64_t)1 << 37)) break;
+        *units += u;
+        positions += p;
+        ++n;
+    }
+    return n;
+}
+
 int box_face_rows(const BoxFace *faces, int nfaces, int max_rows) {
     int rows = 0;
-    for (int f0 = 0; f0 < nfaces; f0 += kFacesPerLaunch) {
+    for (int f0 = 0; f0 < nfaces;) {
         int64_t units = 0;
-        for (int k = f0; k < nfaces && k < f0 + kFacesPerLaunch; ++k) units += face_units(faces[k]);
+        f0 += faces_of_launch(faces, nfaces, f0, &units);
         const int64_t wgs = (units + 15) / 16;
         rows += (int)(wgs < max_rows ? wgs : max_rows);
     }
@@ -447,20 +468,18 @@ int box_face_rows(const BoxFace *faces, int nfaces, int max_rows) {
 
 int launch_box_faces(const void *img, int elem, const BoxFace *faces, int nfaces, int max_rows, int32_t *rows,
                      hipStream_t stream) {
-    for (int f0 = 0; f0 < nfaces; f0 += kFacesPerLaunch) {
+    for (int f0 = 0; f0 < nfaces;) {
+        int64_t units = 0;
         FaceTable t{};
-        t.n = nfaces - f0 < kFacesPerLaunch ? nfaces - f0 : kFacesPerLaunch;
+        t.n = faces_of_launch(faces, nfaces, f0, &units);
+        if (units > INT32_MAX / 2) {
+            set_error("ecc_compute_dual: face too large");
+            return ECC_E_UNSUPPORTED;
+        }
         for (int k = 0; k < t.n; ++k) {
-            const BoxFace &F = faces[f0 + k];
-            t.f[k] = F;
-            const int64_t units = face_units(F);
-            // (a thread's next unit stays below 2^31; an image of that size does not fit the card)
-            if (t.first[k] + units > INT32_MAX / 2) {
-                set_error("ecc_compute_dual: face too large");
-                return ECC_E_UNSUPPORTED;
-            }
-            t.strips[k] = (int32_t)(F.nb / 64 + 1);
-            t.first[k + 1] = t.first[k] + (int32_t)units;
+            t.f[k] = faces[f0 + k];
+            t.strips[k] = (int32_t)(t.f[k].nb / 64 + 1);
+            t.first[k + 1] = t.first[k] + (int32_t)face_units(t.f[k]);
         }
         const int grid = box_face_rows(faces + f0, t.n, max_rows);
         if (elem == 1)
@@ -471,6 +490,7 @@ int launch_box_faces(const void *img, int elem, const BoxFace *faces, int nfaces
                                (const uint16_t *)img, t, rows);
         ECC_HIP(hipGetLastError());
         rows += (size_t)grid * (elem == 1 ? 256 : 16384);
+        f0 += t.n;
     }
     return ECC_OK;
 }

@@ -43,6 +43,7 @@ static int stream_waits;      /* for the stream that the scenario gave */
 static hipStream_t its_stream;
 static int top_bytes = 3;     /* top bytes of the float image's keys */
 static long change_launches;  /* of the change kernel */
+static long face_launches;    /* of the box faces' kernel */
 static unsigned int_grid;     /* workgroups of the last launch of the integer kernel */
 
 static int is_device(const void *p) { return (uint64_t)p >= DEVICE_LO && (uint64_t)p < DEVICE_HI; }
@@ -174,6 +175,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
     } else if (strstr(name, "11scan_kernel")) {
         if ((out = host_argument(args, 6))) *out = status_word;
         status_word = 0;
+    } else if (strstr(name, "box_faces_kernel")) {
+        ++face_launches;
     } else if (strstr(name, "int_vcec_kernel")) {
         int_grid = g.x;
     } else if (strstr(name, "change_kernel")) {
@@ -382,6 +385,20 @@ static int stream_4d(void) {
     return 0;
 }
 
+/* The dual curve of volumes with faces of many short rows. */
+static int dual_long(void) {
+    const int64_t n[5][3] = {{0x7FFFFFFFll - 4, 2, 2}, {1500000000, 60, 2}, {2000000000, 2, 2}, {1000, 900, 800}, {2, 2, 2}};
+    for (int i = 0; i < 5; ++i) {
+        ecc_dims d = dims_of(3, n[i][0], n[i][1], n[i][2], 1);
+        static int64_t chi[16384];
+        ecc_curve c = {16384, 0, chi, NULL};
+        face_launches = 0;
+        const int rc = ecc_compute_dual(device_bytes((size_t)n[i][0] * n[i][1] * n[i][2]), &d, ECC_U8, &c, NULL);
+        printf("dual rc %d launches %ld\n", rc, face_launches);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -392,6 +409,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "batch_tuned")) return batch_tuned();
     if (!strcmp(what, "tilings")) return tilings(argv[2]);
     if (!strcmp(what, "stream_4d")) return stream_4d();
+    if (!strcmp(what, "dual_long")) return dual_long();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

@@ -127,3 +127,10 @@ def test_4d_chunks_are_cut_below_2_30_values(program):
     assert len(pushes) == 6
     for p in pushes:
         assert p["rc"] == ECC_OK and p["launches"] * ((1 << 30) - 1) >= p["values"], p
+
+
+def test_dual_of_volumes_with_very_long_faces(program):
+    """Faces of more rows than one launch's units can number go to several."""
+    duals = records(run(program, "dual_long"), "dual")
+    assert [d["rc"] for d in duals] == [ECC_OK] * 5
+    assert [d["launches"] > 1 for d in duals] == [True, True, True, False, False]
