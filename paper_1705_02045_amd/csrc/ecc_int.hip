@@ -469,7 +469,10 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
     // planes zs-1 and ze are +inf outside the image
     const bool lo_real = !(zs == P.e0 && P.lo_inf);
     const bool hi_real = !(ze == P.e1 && P.hi_inf);
-    auto real = [&](int p) { return p < ze || (p == ze && hi_real); };  // for p >= zs
+    // planes from the current one on (a plane's index may be close to 2^31, so
+    // that only differences are compared); plane j of them is read
+    int left = ze - zs;
+    auto real = [&](int j) { return j < left || (j == left && hi_real); };
 
     auto load_at = [&](const uint8_t *pp, uint32_t (&a)[NR], uint32_t (&b)[NR]) {
         __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)pp, (short)0, pbytes, kBufferWord3);
@@ -583,15 +586,14 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
     for (int i = 0; i < NI; ++i) cp[i] = cmp(g[0][i], g[1][i], i);
 #pragma unroll
     for (int j = 1; j <= PD; ++j)
-        if (real(zs + j)) load_plane(zs + j, ra[j], rb[j]);
+        if (real(j)) load_plane(zs + j, ra[j], rb[j]);
 
     // Phase u of a block handles plane z+u: start the load of plane z+u+1+PD
     // into the buffer that held plane z+u, turn plane z+u+1 into fields and
     // compare.  `nxt` points at the next plane to load.  Steady state: every
     // plane touched lies inside the tile.
     const uint8_t *nxt = plane_ptr(zs + 1 + PD);  // zs >= -1, so this plane is in `base`
-    int z = zs;
-    for (; z + U + PD < ze; z += U) {
+    for (; left > U + PD; left -= U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             load_at(nxt, ra[u % NB], rb[u % NB]);
@@ -602,23 +604,22 @@ __device__ __forceinline__ void walk(const KParams &P, int zs, int ze, const uin
         }
     }
     // Last planes, with boundary tests.
-    while (z < ze) {
+    while (left > 0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int zz = z + u;
-            if (zz < ze) {
-                if (real(zz + 1 + PD)) load_at(nxt, ra[u % NB], rb[u % NB]);
+            if (u < left) {
+                if (real(u + 1 + PD)) load_at(nxt, ra[u % NB], rb[u % NB]);
                 nxt += pb;
-                if (real(zz + 1)) {
+                if (real(u + 1)) {
                     fields(ra[(u + 1) % NB], rb[(u + 1) % NB], g[(u + 1) & 1]);
-                    if (zz + 1 < ze) range_acc(ra[(u + 1) % NB]);
+                    if (u + 1 < left) range_acc(ra[(u + 1) % NB]);
                 } else {
                     W::set_inf(g[(u + 1) & 1], kSent);
                 }
                 step(g[u & 1], g[(u + 1) & 1], cp);
             }
         }
-        z += U;
+        left -= U;
     }
 }
 
@@ -689,7 +690,7 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     const int ty = (t / P.tiles_x) % P.tiles_y;
     const int tz = t / (P.tiles_x * P.tiles_y);
     const int zs = P.e0 + tz * P.zc;
-    const int ze = min(zs + P.zc, P.e1);
+    const int ze = P.e1 - zs > P.zc ? zs + P.zc : P.e1;
 
     // Per loaded row: byte offsets of x and of x-1 (clamped into the row) and
     // the row's byte offset within a plane.  NIN == 1: row r is the 64-wide
@@ -977,7 +978,7 @@ static KParams make_params(const IntJob &job, const IntTiling &tl, int32_t *part
     const int64_t xw = (int64_t)kWave * tl.wx * (nin == 1 ? tl.rows : 1);
     p.tiles_x = (int32_t)((job.view.n2 + xw - 1) / xw);
     p.tiles_y = nin == 1 ? 1 : (int32_t)((job.view.n1 + (int64_t)tl.rows * tl.wy - 1) / ((int64_t)tl.rows * tl.wy));
-    p.tiles_z = (job.e1 - job.e0 + tl.zc - 1) / tl.zc;
+    p.tiles_z = (int32_t)(((int64_t)job.e1 - job.e0 + tl.zc - 1) / tl.zc);
     p.per_wg = tl.per_wg > 0 ? tl.per_wg : 1;
     p.tile_stride = tl.tile_stride;
     p.win_shift = job.win_shift;
