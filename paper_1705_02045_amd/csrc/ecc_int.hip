@@ -921,18 +921,19 @@ static int launch_rows(const KParams &p, const IntTiling &tl, hipStream_t stream
 // depend on the image, a single histogram's does: 512^3 99 us against 107 on
 // smooth noise and 148 on white, 240 x 1024^2 175 against 184 and 264, 256 x
 // 1024^2 202 against 197 and 281, 512 x 1024^2 443 against 372 and 548.
-static bool lane_copies(const IntTiling &tl, int64_t voxels) {
+// (Planes of look-ahead as make_int_tiling gives them: two with four rows, one
+// with two rows and one in-plane axis; other forms are not built.)
+static bool lane_copies(int nin, const IntTiling &tl, int64_t voxels) {
+    if (tl.rows == 4 ? tl.pd != 2 : tl.rows != 2 || (tl.pd != 1 && nin == 1)) return false;
     return tl.mode == 0 && tl.wx * tl.wy > 12 && (int64_t)tl.zc * tl.per_wg >= 16 && voxels < (int64_t)1 << 28;
 }
 template <int NIN, int XF>
 static int launch_u8_copies(const KParams &p, const IntTiling &tl, hipStream_t stream) {
-    const bool pd2 = tl.pd == 2;
-    if (tl.rows == 2)
-        return pd2 ? launch_one<uint8_t, 256, NIN, 2, 0, 2, XF, 6>(p, tl, stream) : launch_one<uint8_t, 256, NIN, 2, 0, 1, XF, 6>(p, tl, stream);
-    if (tl.rows == 4)
-        return pd2 ? launch_one<uint8_t, 256, NIN, 4, 0, 2, XF, 6>(p, tl, stream) : launch_one<uint8_t, 256, NIN, 4, 0, 1, XF, 6>(p, tl, stream);
-    set_error("integer kernel: %d rows per wave not built", tl.rows);
-    return ECC_E_UNSUPPORTED;
+    if (tl.rows == 4) return launch_one<uint8_t, 256, NIN, 4, 0, 2, XF, 6>(p, tl, stream);
+    if constexpr (NIN == 2) {
+        if (tl.pd == 2) return launch_one<uint8_t, 256, NIN, 2, 0, 2, XF, 6>(p, tl, stream);
+    }
+    return launch_one<uint8_t, 256, NIN, 2, 0, 1, XF, 6>(p, tl, stream);
 }
 
 // Transformed values (largest-value convention, 16-bit windows): walking
@@ -1002,7 +1003,7 @@ int launch_int_partial(const IntJob &job, const IntTiling &tl, int32_t *partial,
     if (job.dtype == ECC_U16)  // one window of 16382 values per launch
         return nin == 1 ? launch_transformed<uint16_t, 16384, 1, kXfWindow>(p, tl, stream)
                         : launch_transformed<uint16_t, 16384, 2, kXfWindow>(p, tl, stream);
-    if (job.dtype == ECC_U8 && lane_copies(tl, (int64_t)(job.e1 - job.e0) * job.view.n1 * job.view.n2)) {
+    if (job.dtype == ECC_U8 && lane_copies(nin, tl, (int64_t)(job.e1 - job.e0) * job.view.n1 * job.view.n2)) {
         if (job.invert)
             return nin == 1 ? launch_u8_copies<1, kXfInvert>(p, tl, stream) : launch_u8_copies<2, kXfInvert>(p, tl, stream);
         return nin == 1 ? launch_u8_copies<1, kXfNone>(p, tl, stream) : launch_u8_copies<2, kXfNone>(p, tl, stream);

@@ -45,6 +45,7 @@ static int top_bytes = 3;     /* top bytes of the float image's keys */
 static long change_launches;  /* of the change kernel */
 static long face_launches;    /* of the box faces' kernel */
 static unsigned int_grid;     /* workgroups of the last launch of the integer kernel */
+static const char *int_kernel = "";
 
 static int is_device(const void *p) { return (uint64_t)p >= DEVICE_LO && (uint64_t)p < DEVICE_HI; }
 static hipError_t result(hipError_t e) {
@@ -179,6 +180,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
         ++face_launches;
     } else if (strstr(name, "int_vcec_kernel")) {
         int_grid = g.x;
+        int_kernel = name;
     } else if (strstr(name, "change_kernel")) {
         ++change_launches;
         if (range_image) status_word |= 1u;
@@ -399,6 +401,24 @@ static int dual_long(void) {
     return 0;
 }
 
+/* The integer kernel that images take: argv[2] tilings to load ("-": none),
+ * argv[3] "min" or "max", then per image its extents as n0xn1xn2 (8 bits). */
+static int kernel_of(int argc, char **argv) {
+    if (strcmp(argv[2], "-")) printf("loaded rc %d\n", ecc_autotune_load(argv[2]));
+    static int64_t chi[256];
+    for (int i = 4; i < argc; ++i) {
+        ecc_dims d = dims_of(1, 1, 1, 1, 1);
+        char *p = argv[i];
+        for (d.ndim = 0; *p; ++d.ndim, p += *p == 'x') d.n[d.ndim] = strtoll(p, &p, 10);
+        ecc_curve c = {256, 0, chi, NULL};
+        int (*call)(const void *, const ecc_dims *, ecc_dtype, ecc_curve *, void *) =
+            strcmp(argv[3], "max") ? ecc_compute : ecc_compute_max_entry;
+        const int rc = call(device_bytes(1 << 20), &d, ECC_U8, &c, NULL);
+        printf("%s rc %d grid %u kernel %s\n", argv[i], rc, int_grid, int_kernel);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -410,6 +430,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "tilings")) return tilings(argv[2]);
     if (!strcmp(what, "stream_4d")) return stream_4d();
     if (!strcmp(what, "dual_long")) return dual_long();
+    if (!strcmp(what, "kernel_of")) return kernel_of(argc, argv);
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }
