@@ -335,7 +335,8 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
 void ecc_batch_destroy(ecc_batch *b);
 
 /* Tile depth of a batch context.  By default each run plans it from its
- * images.  Times ecc_batch_run on the given jobs (their chi buffers are
+ * images, with count rows of at most 32 MiB more in all than ecc_job_footprint
+ * counts for them (none more where memory is short).  Times ecc_batch_run on the given jobs (their chi buffers are
  * written) with an image of n0 planes cut into tiles of max(min_planes,
  * n0 / split) planes, for min_planes in {16, 32, 64, 128} x split in {2, 4, 8},
  * and keeps the fastest for the context's later runs, which then plan no

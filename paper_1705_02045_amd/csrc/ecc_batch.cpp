@@ -72,8 +72,7 @@ using namespace ecc;
 // tiles of max(min_planes, planes / split) planes (or the whole image), so
 // that small images take one workgroup and large ones a few hundred.  The
 // defaults (64, 4) are the footprint's; runs take what ecc_batch_autotune
-// picked, or their own plan (below), whose count rows are no larger in all
-// than the footprints'.
+// picked, or their own plan (below).
 constexpr int kBatchMinPlanes = 64, kBatchSplit = 4;
 
 IntTiling batch_tiling(const IntView &v, int min_planes = kBatchMinPlanes, int split = kBatchSplit) {
@@ -112,12 +111,14 @@ IntTiling batch_tiling(const IntView &v, int min_planes = kBatchMinPlanes, int s
 // longest tile's walk for the last tiles to end.  Fitted to nine batches of 8
 // to 128 images at ten depths (7 % off on average); with tiles of 64 planes or
 // a quarter of the image, the 2-D images' long tiles ended last (96 images of
-// the serving mix: 287 us, planned 228; 16 images 170 and 97).  Depths whose
-// count rows take more memory than the footprints count for the run's images
-// are passed over (admission adds up the footprints): the mix's depth of 128
-// takes 0.6 of it; runs of fewer than about 16 images would take depths of 48
-// with 1.2 to 1.3 times the rows.  The footprint's own tiles are one of the
-// choices, and the only one for images of a few columns and millions of rows.
+// the serving mix: 287 us, planned 228; 16 images 170 and 97).
+// Depths whose count rows take over kPlanExtra more memory than the footprints
+// count for the run's images are passed over (admission adds up the
+// footprints): the mix's depth of 128 takes 0.6 of it, runs of fewer than about
+// 16 images depths of 48 with 1.2 to 1.3 times the rows, and images of a few
+// columns and millions of rows are held back.  The footprint's own tiles are
+// one of the choices, and what a run falls back on where memory is short.
+constexpr int64_t kPlanExtra = (int64_t)32 << 20;
 constexpr double kTilePlanes14 = 22.0, kTilePlanes8 = 11.0;
 int64_t planned_walk(int64_t n0, int64_t depth) {
     const int64_t k = (n0 + depth - 1) / depth;
@@ -136,6 +137,7 @@ struct Prepared {
     IntView view;
     IntTiling tl;
     int64_t tiles_xy;  // tiles of one depth
+    int default_zc;    // the depth of tl as prepared
     int group;  // (dtype == U14) * 2 + (nin == 2)
     int m;
     int64_t voxels;
@@ -739,44 +741,48 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
         }
         P.tl = b->planned ? batch_tiling(P.view) : batch_tiling(P.view, b->min_planes, b->split);
         P.tiles_xy = P.tl.grid / ((P.view.n0 + P.tl.zc - 1) / P.tl.zc);
+        P.default_zc = P.tl.zc;
         P.group = (J.dtype == ECC_U14 ? 2 : 0) + (P.view.nin == 2 ? 1 : 0);
         P.m = (int)threshold_count(J.dtype);
         P.voxels = total;
         nitems += (P.m + 1023) / 1024;
         vcec_words += P.m;
     }
+    int64_t depth = 0;  // 0: tiles as prepared
     if (b->planned) {
         static constexpr int64_t kDepths[] = {0, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 1024};
-        int64_t depth = 0, limit = 0;  // 0: the footprints' tiles, with `limit` entries of count rows
+        int64_t limit = 0;  // bytes of count rows
         double best = 0;
         for (const int64_t d : kDepths) {
             double planes = 0;
-            int64_t longest = 0, entries = 0;
+            int64_t longest = 0, bytes = 0;
             for (const Prepared &P : prep) {
                 if (P.m == 0) continue;  // (a 16-bit job)
                 const int64_t zc = d ? planned_walk(P.view.n0, d) : P.tl.zc, tiles = P.tiles_xy * ((P.view.n0 + zc - 1) / zc);
                 planes += (double)tiles * ((double)zc * (P.tl.wx * P.tl.wy) / 16.0 + (P.m > 256 ? kTilePlanes14 : kTilePlanes8));
                 longest = std::max(longest, zc);
-                entries += tiles * P.m;
+                bytes += tiles * P.m * (int64_t)sizeof(int32_t);
             }
             const double cost = planes / b->tile_grid + 0.25 * (double)longest;
-            if (d == 0) limit = entries;
-            if (d == 0 || (entries <= limit && cost < best)) {
+            if (d == 0) limit = bytes + kPlanExtra;
+            if (d == 0 || (bytes <= limit && cost < best)) {
                 best = cost;
                 depth = d;
             }
         }
+    }
+    // the tiles at a depth, and their numbers
+    auto cut = [&](int64_t d) {
+        rows8 = rows14 = ntiles = 0;
         for (Prepared &P : prep) {
-            if (P.m == 0 || depth == 0) continue;
-            P.tl.zc = (int)planned_walk(P.view.n0, depth);
+            if (P.m == 0) continue;
+            P.tl.zc = d ? (int)planned_walk(P.view.n0, d) : P.default_zc;
             P.tl.grid = (int)(P.tiles_xy * ((P.view.n0 + P.tl.zc - 1) / P.tl.zc));
+            (P.m == 256 ? rows8 : rows14) += P.tl.grid;
+            ntiles += P.tl.grid;
         }
-    }
-    for (const Prepared &P : prep) {
-        if (P.m == 0) continue;
-        (P.m == 256 ? rows8 : rows14) += P.tl.grid;
-        ntiles += P.tl.grid;
-    }
+    };
+    cut(depth);
     if (ntiles > INT32_MAX) {
         set_error("ecc_batch_run: too many tiles in one batch");
         return ECC_E_UNSUPPORTED;
@@ -795,8 +801,6 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
     do {
         if (nb == 0) break;
         // device scratch
-        if ((rc = grow(b, (void **)&b->partial8, &b->partial8_bytes, (size_t)rows8 * 256 * 4))) break;
-        if ((rc = grow(b, (void **)&b->partial14, &b->partial14_bytes, (size_t)rows14 * 16384 * 4))) break;
         if ((rc = grow(b, (void **)&b->vcec, &b->vcec_bytes, (size_t)vcec_words * 8))) break;
         if (b->status_bytes < (size_t)n_jobs * 4 || !b->status) {
             if ((rc = grow(b, (void **)&b->status, &b->status_bytes, (size_t)n_jobs * 4))) break;
@@ -822,7 +826,6 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
             break;
         }
         hd.njobs = nb;
-        hd.ntiles = (int32_t)ntiles;
         hd.nitems = (int32_t)nitems;
         hd.next_tile = 0;
         // a free slot (its previous run's table copy has been consumed)
@@ -850,6 +853,25 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
             }
             b->cap[s] = want;
         }
+        // the count rows last: planned tiles give way where memory is short
+        auto grow_rows = [&]() -> int {
+            int e = grow(b, (void **)&b->partial8, &b->partial8_bytes, (size_t)rows8 * 256 * 4);
+            return e ? e : grow(b, (void **)&b->partial14, &b->partial14_bytes, (size_t)rows14 * 16384 * 4);
+        };
+        rc = grow_rows();
+        if (rc == ECC_E_NOMEM && depth != 0) {
+            cut(0);
+            (void)hipStreamSynchronize(b->stream);  // in-flight runs may still use the rows
+            for (auto part : {std::make_pair(&b->partial8, &b->partial8_bytes), std::make_pair(&b->partial14, &b->partial14_bytes)}) {
+                if (*part.first) (void)hipFree(*part.first);
+                *part.first = nullptr;
+                *part.second = 0;
+            }
+            rc = grow_rows();
+            if (!rc) g_err_clear();
+        }
+        if (rc) break;
+        hd.ntiles = (int32_t)ntiles;
         uint8_t *h = (uint8_t *)b->host[s];
         uint8_t *d = (uint8_t *)b->dev[s];
         memcpy(h, &hd, sizeof hd);

@@ -292,6 +292,7 @@ static int float_nearly_full(void) {
 static void batch_of(const char *name, int n, const ecc_dims *dims, const int *dtypes) {
     ecc_batch *b = NULL;
     ecc_job jobs[64];
+    const int64_t extra = 32 << 20;
     int64_t bound = (64 << 10) + 4 * n + 1024;  /* the table and the status words */
     for (int i = 0; i < n; ++i) {
         ecc_job j = {device_bytes(16), dims[i], dtypes[i], (int64_t *)device_bytes(65536 * 8)};
@@ -304,8 +305,14 @@ static void batch_of(const char *name, int n, const ecc_dims *dims, const int *d
     ecc_batch_create(NULL, &b);
     const size_t before = used;
     const int rc = ecc_batch_run(b, n, jobs, NULL);
-    printf("%s rc %d bytes %zu bound %lld\n", name, rc, used - before, (long long)bound);
+    printf("%s rc %d bytes %zu bound %lld\n", name, rc, used - before, (long long)(bound + extra));
     ecc_batch_destroy(b);
+    limit_bytes = used + bound;  /* no more memory than the footprints' */
+    ecc_batch_create(NULL, &b);
+    const int rc2 = ecc_batch_run(b, n, jobs, NULL);
+    printf("short rc %d bytes %zu bound %lld\n", rc2, used - before, (long long)bound);
+    ecc_batch_destroy(b);
+    limit_bytes = (size_t)-1;
 }
 static int batch_rows(void) {
     setenv("ECC_BATCH_GRAPH", "0", 1);
