@@ -530,8 +530,18 @@ static bool planned_tiling(const IntView &v, int dtype, int64_t planes, const ec
     return c.rows == r.rows && c.tiles_per_cu == r.tiles_per_cu && c.waves_x == r.waves_x;
 }
 static IntTiling tiling_from(const IntView &v, int dtype, int64_t planes, const ecc_tiling &c, int max_grid) {
-    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned_tiling(v, dtype, planes, c),
-                           dtype == ECC_U8 ? 0.0075 : 0.045);
+    const bool planned = planned_tiling(v, dtype, planes, c);
+    IntTiling t = make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned,
+                                  dtype == ECC_U8 ? 0.0075 : 0.045);
+    // The plan counts a workgroup as its CU's work.  8-bit workgroups of up to
+    // four waves (planes of a few hundred voxels) run many to a CU, their 1 KiB
+    // histograms beside each other, each bound by its walk's latency, so they
+    // are split as finely as the rule says (300000 x 64: 50 us, planned 74;
+    // 100000 x 4 x 4: 38 and 56; from seven waves on the plan is as fast).  At
+    // 14 bits the 64 KiB histograms admit two to a CU however small.
+    if (planned && dtype == ECC_U8 && t.wx * t.wy <= 4)
+        t = make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid);
+    return t;
 }
 
 IntTiling choose_int_tiling(const IntView &v, int dtype, int64_t planes, int max_grid) {

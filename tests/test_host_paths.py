@@ -135,3 +135,14 @@ def test_dual_of_volumes_with_very_long_faces(program):
     duals = records(run(program, "dual_long"), "dual")
     assert [d["rc"] for d in duals] == [ECC_OK] * 5
     assert [d["launches"] > 1 for d in duals] == [True, True, True, False, False]
+
+
+def test_narrow_8_bit_launches_are_split_finely(program):
+    """8-bit workgroups of up to four waves: about four tiles per CU, walks of
+    at least 8 planes."""
+    shapes = [(1000000, 8), (100000, 130), (2000000, 2), (200000, 2, 2), (100000, 4, 4), (20000, 4, 64), (5000, 64)]
+    lines = run(program, "kernel_of", "-", "min", *["x".join(map(str, s)) for s in shapes])
+    for shape, line in zip(shapes, lines):
+        r = dict(zip(line[1:5:2], map(int, line[2:5:2])))
+        walk = max(8, -(-shape[0] // 1024))
+        assert r["rc"] == ECC_OK and r["grid"] == -(-shape[0] // walk), line
