@@ -917,20 +917,24 @@ static int launch_rows(const KParams &p, const IntTiling &tl, hipStream_t stream
 // 8-bit launches with a histogram copy per lane: workgroups that fill a CU in
 // pairs anyway (more than 12 waves: the 64 KiB then cost no occupancy) and
 // walk at least 16 planes (clearing the copies and summing them takes as
-// long as about one plane); below 2^28 voxels.  The copies' time does not
-// depend on the image, a single histogram's does: 512^3 99 us against 107 on
-// smooth noise and 148 on white, 240 x 1024^2 175 against 184 and 264, 256 x
-// 1024^2 202 against 197 and 281, 512 x 1024^2 443 against 372 and 548.
-// (Planes of look-ahead as make_int_tiling gives them: two with four rows, one
-// with two rows and one in-plane axis; other forms are not built.)
+// long as about one plane); below 2^28 voxels, with one in-plane axis 2^25.  The
+// copies' time does not depend on the image, a single histogram's does: 512^3
+// 99 us against 107 on smooth noise and 148 on white, 240 x 1024^2 175 against
+// 184 and 264, 256 x 1024^2 202 against 197 and 281, 512 x 1024^2 443 against
+// 372 and 548; 4096^2 21 against 23 and 23, 6000^2 32 against 31 and 35,
+// 8192^2 45 against 39 and 49, 16384 x 16000 151 against 100 and 150.
+// (Planes of look-ahead as make_int_tiling gives them: two with four rows, which
+// no tiling of one in-plane axis below 2^25 voxels brings here, and one with two
+// rows and one in-plane axis; other forms are not built.)
 static bool lane_copies(int nin, const IntTiling &tl, int64_t voxels) {
-    if (tl.rows == 4 ? tl.pd != 2 : tl.rows != 2 || (tl.pd != 1 && nin == 1)) return false;
-    return tl.mode == 0 && tl.wx * tl.wy > 12 && (int64_t)tl.zc * tl.per_wg >= 16 && voxels < (int64_t)1 << 28;
+    const bool built = nin == 1 ? tl.rows == 2 && tl.pd == 1 : tl.rows == 2 || (tl.rows == 4 && tl.pd == 2);
+    return built && tl.mode == 0 && tl.wx * tl.wy > 12 && (int64_t)tl.zc * tl.per_wg >= 16 &&
+           voxels < (int64_t)1 << (nin == 1 ? 25 : 28);
 }
 template <int NIN, int XF>
 static int launch_u8_copies(const KParams &p, const IntTiling &tl, hipStream_t stream) {
-    if (tl.rows == 4) return launch_one<uint8_t, 256, NIN, 4, 0, 2, XF, 6>(p, tl, stream);
     if constexpr (NIN == 2) {
+        if (tl.rows == 4) return launch_one<uint8_t, 256, NIN, 4, 0, 2, XF, 6>(p, tl, stream);
         if (tl.pd == 2) return launch_one<uint8_t, 256, NIN, 2, 0, 2, XF, 6>(p, tl, stream);
     }
     return launch_one<uint8_t, 256, NIN, 2, 0, 1, XF, 6>(p, tl, stream);

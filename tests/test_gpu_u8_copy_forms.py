@@ -12,9 +12,8 @@ from test_host_paths import program, run  # noqa: F401 (a fixture)
 torch = pytest.importorskip("torch")
 
 # shape, stored tiling ("": the rule's), in-plane axes, rows, look-ahead
-FORMS = [((16500, 2051), "", 1, 2, 1), ((16500, 3300), "4 4 16", 1, 4, 2), ((16390, 4097), "4 4 16", 1, 4, 2),
-         ((97, 1100, 129), "", 2, 2, 1), ((600, 700, 300), "", 2, 2, 2), ((300, 1000, 203), "4 4 16", 2, 4, 2),
-         ((301, 1003, 129), "4 4 16", 2, 4, 2)]
+FORMS = [((16200, 2051), "", 1, 2, 1), ((12000, 1793), "", 1, 2, 1), ((97, 1100, 129), "", 2, 2, 1),
+         ((600, 700, 300), "", 2, 2, 2), ((300, 1000, 203), "4 4 16", 2, 4, 2), ((301, 1003, 129), "4 4 16", 2, 4, 2)]
 
 
 def tiling_file(path, shape, params):
@@ -30,6 +29,12 @@ def test_form_taken(program, tmp_path, convention, shape, params, axes, rows, ah
     line = run(program, "kernel_of", tilings, convention, "x".join(map(str, shape)))[-1]
     transform = 0 if convention == "min" else 1
     assert f"kernelIhLi256ELi{axes}ELi{rows}ELi0ELi{ahead}ELi{transform}ELi6E" in line[-1], line
+
+
+def test_one_copy_for_large_pictures(program):  # noqa: F811
+    """With one in-plane axis and 2^25 voxels or more a single histogram counts."""
+    lines = run(program, "kernel_of", "-", "min", "16384x2047", "16384x2048", "8192x8192", "16384x16000")
+    assert ["Li6E" in line[-1] for line in lines] == [True, False, False, False], lines
 
 
 @pytest.mark.gpu
