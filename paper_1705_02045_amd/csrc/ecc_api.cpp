@@ -789,15 +789,6 @@ static int four_d_job(const void *img_dev, const ecc_dims *dims, int64_t total, 
 static int enqueue_four_d(const ChangeJob &job, bool max_entry, int64_t *chi_dev, int64_t *changes_out,
                           uint32_t *status_out, hipStream_t s, Workspace *ws) {
     const int m = (int)threshold_count(job.dtype);
-    if (job.dtype == ECC_U16) {
-        int rc = ensure_bytes((void **)&ws->vcec16, &ws->vcec16_bytes, (size_t)m * sizeof(int64_t));
-        if (rc) return rc;
-        rc = launch_zero(ws->vcec16, (size_t)m * sizeof(int64_t), s);
-        if (rc) return rc;
-        rc = launch_change_counts(job, nullptr, ws->vcec16, ws->status, s);
-        if (rc) return rc;
-        return launch_merge(nullptr, 0, m, ws->vcec16, true, true, chi_dev, ws->status, status_out, s);
-    }
     int rows = 0;
     int rc = change_count_rows(job, &rows);
     if (rc) return rc;
@@ -805,7 +796,7 @@ static int enqueue_four_d(const ChangeJob &job, bool max_entry, int64_t *chi_dev
     if (rc) return rc;
     rc = ensure_bytes((void **)&ws->vcec, &ws->vcec_bytes, (size_t)m * sizeof(int64_t));
     if (rc) return rc;
-    rc = launch_change_counts(job, ws->partial, nullptr, ws->status, s);
+    rc = launch_change_counts(job, ws->partial, ws->status, s);
     if (rc) return rc;
     if (changes_out)
         return launch_merge(ws->partial, rows, m, changes_out, false, false, nullptr, ws->status, nullptr, s,

@@ -73,9 +73,9 @@ struct ChangeParams {
     uint64_t *rec;
     uint32_t *cnt;
     uint32_t region;
-    // integers: count rows (one per workgroup) or the changes vector
+    // integers: count rows, one per workgroup or (kAtomic) `rows` shared ones
     int32_t *partial;
-    int64_t *vcec;
+    uint32_t rows;
     uint32_t *status;
     uint32_t limit;  // integers: values >= limit are an error
 };
@@ -170,7 +170,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 enum { kRecords = 0, kHistogram = 1, kAtomic = 2 };
 
 // EMIT: kRecords (float), kHistogram (integers, m = M bins in LDS, one count
-// row per workgroup), kAtomic (integers, int64 adds to the changes vector).
+// row per workgroup), kAtomic (integers, adds to the rows in memory, workgroup b
+// to row b modulo their number).
 template <typename T, int NL, int EMIT, int M, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
     using V = typename Val<T>::type;
@@ -190,6 +191,8 @@ __global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
         __syncthreads();
     }
     uint32_t orv = 0;
+    int32_t *shared_row = nullptr;
+    if constexpr (EMIT == kAtomic) shared_row = P.partial + (size_t)(blockIdx.x % P.rows) * 65536u;
     const uint32_t blk = xcd_block(blockIdx.x, gridDim.x);
     for (int64_t item = (int64_t)blk * WAVES + wave; item < P.items; item += (int64_t)gridDim.x * WAVES) {
         const int32_t k = (int32_t)(item % P.wu);
@@ -440,7 +443,7 @@ __global__ void __launch_bounds__(64 * WAVES) change_kernel(ChangeParams P) {
                             if constexpr (EMIT == kHistogram) {
                                 if (v < (uint32_t)M) atomicAdd(&hist[v], chg);
                             } else {
-                                if (v < P.limit) atomicAdd((unsigned long long *)&P.vcec[v], (unsigned long long)(int64_t)chg);
+                                if (v < P.limit) atomicAdd(&shared_row[v], chg);
                             }
                         }
                     }
@@ -567,24 +570,34 @@ static int int_geometry(const ChangeJob &job, ChangeParams *p, int *waves, int64
     return ECC_OK;
 }
 
+// 16-bit images (more bins than a workgroup's LDS holds) add to rows in memory.
+// Adds to one line wait for each other (0.2 G/s, 27 G/s on many lines), and an
+// image of few values makes all its adds on few lines: with one row, 60^4 voxels
+// of two values took 30 ms.  A row per 8192 voxels, up to 64, keeps that to the
+// rate of the adds; the rows' clearing and merging then take about as long as
+// the launch of a small image.
 int change_count_rows(const ChangeJob &job, int *rows) {
     ChangeParams p{};
     int waves = 0;
     int64_t grid = 0;
     int rc = int_geometry(job, &p, &waves, &grid);
     if (rc) return rc;
-    *rows = (int)grid;
+    const int64_t voxels = (int64_t)(job.e1 - job.e0) * job.nx * job.ny * job.nz;
+    // (a multiple of 8: the workgroups of a row are then on one XCD)
+    *rows = job.dtype == ECC_U16 ? (int)std::min<int64_t>(64, (voxels / 8192 + 8) / 8 * 8) : (int)grid;
     return ECC_OK;
 }
 
-int launch_change_counts(const ChangeJob &job, int32_t *partial, int64_t *vcec, uint32_t *status, hipStream_t stream) {
+int launch_change_counts(const ChangeJob &job, int32_t *partial, uint32_t *status, hipStream_t stream) {
     ChangeParams p{};
-    int waves = 0;
+    int waves = 0, rows = 0;
     int64_t grid = 0;
     int rc = int_geometry(job, &p, &waves, &grid);
+    if (!rc) rc = change_count_rows(job, &rows);
+    if (!rc && job.dtype == ECC_U16) rc = launch_zero(partial, (size_t)rows * 65536 * sizeof(int32_t), stream);
     if (rc) return rc;
     p.partial = partial;
-    p.vcec = vcec;
+    p.rows = (uint32_t)rows;
     p.status = status;
     void *tok = nullptr;
     rc = profile_begin(stream, &tok);

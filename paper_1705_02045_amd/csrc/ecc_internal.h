@@ -300,12 +300,10 @@ struct ChangeJob {
 // rec[i * region_slots] on.
 int change_regions(const ChangeJob &job, int64_t *regions, int64_t *region_slots);
 int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hipStream_t stream);
-// Integer images with four axes longer than 1.  u8 and u14: count rows, one
-// per workgroup (change_count_rows of them, m int32 each), merged as the
-// integer kernel's; u16 (m = 65536, more than a workgroup's histogram
-// holds): int64 adds straight into vcec.  A value >= m sets kStatusRange.
+// Integer images with four axes longer than 1: change_count_rows count rows of
+// m int32 each, merged as the integer kernel's.  A value >= m sets kStatusRange.
 int change_count_rows(const ChangeJob &job, int *rows);
-int launch_change_counts(const ChangeJob &job, int32_t *partial, int64_t *vcec, uint32_t *status, hipStream_t stream);
+int launch_change_counts(const ChangeJob &job, int32_t *partial, uint32_t *status, hipStream_t stream);
 
 // Float path (ecc_float.hip, ecc_sort.hip).
 // The change kernel's job for a float image.

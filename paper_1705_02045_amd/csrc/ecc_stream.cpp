@@ -149,13 +149,6 @@ int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int
         j.hi_inf = b1 == st->view.n0;
         return j;
     };
-    if (st->dtype == ECC_U16) {
-        for (int64_t b = lo; b < hi; b += step) {
-            int rc = launch_change_counts(launch(b), nullptr, st->vcec, st->status, st->compute);
-            if (rc) return rc;
-        }
-        return ECC_OK;
-    }
     // the rows at their largest number first: a push that fails to allocate
     // has added nothing, so it can be pushed again
     int most = 0;
@@ -170,7 +163,7 @@ int run_chunk_4d(ecc_stream *st, const PlaneSrc &src, int64_t f, int64_t lo, int
     for (int64_t b = lo; b < hi; b += step) {
         int rows = 0;
         rc = change_count_rows(launch(b), &rows);
-        if (!rc) rc = launch_change_counts(launch(b), st->partial, nullptr, st->status, st->compute);
+        if (!rc) rc = launch_change_counts(launch(b), st->partial, st->status, st->compute);
         if (!rc)
             rc = launch_merge(st->partial, rows, st->m, st->vcec, true, false, nullptr, st->status, nullptr, st->compute);
         if (rc) return rc;
