@@ -168,8 +168,8 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
     } else if (strstr(name, "nz_total_kernel")) {
         memset(host_argument(args, 2), 0, 8);
     } else if (strstr(name, "tile_base_kernel")) {
-        *(int64_t *)host_argument(args, 5) = 1;
-        *host_argument(args, 7) = status_word;
+        *(int64_t *)host_argument(args, 7) = 1;
+        *host_argument(args, 9) = status_word;
     } else if (strstr(name, "merge_scan_small_kernel")) {
         if ((out = host_argument(args, 9))) *out = status_word;
         status_word = 0;
