@@ -1039,7 +1039,7 @@ static int compute_float(const void *image, const ecc_dims *dims, int64_t n, ecc
             rc = launch_nz_total(nz_cnt, nz_off, regions, sums, (int64_t *)(ws->host_status_dev + 2), s);
             if (!rc) e = hipEventRecord(ev, s);
             if (!rc && e == hipSuccess) {
-                rc = radix_sort_keys(key, n, counts, sums, s);
+                rc = radix_sort_keys(key, n, starts, counts, sums, s);
                 e = hipEventSynchronize(ev);
             }
         }

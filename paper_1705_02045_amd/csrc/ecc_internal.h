@@ -322,8 +322,6 @@ int64_t radix_scan_tiles(int64_t entries);
 // Digit-table entries of a sort of n words of elem bytes (digits of up to
 // 9 bits for keys, 8 for records); sums: radix_scan_tiles of that.
 int64_t radix_count_entries(int64_t n, int elem);
-// Sorts key[0] in place (four passes).
-int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream);
 // The keys (f32_key) of the n floats of img in tiles of kSplitTile, each in
 // order of its keys' lowest 9 bits; starts: the first slot of each of the
 // kSplitBuckets values of these bits, per tile; head: the mask of the top
@@ -333,6 +331,9 @@ int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sum
 constexpr int64_t kSplitTile = 16384;
 constexpr int kSplitBuckets = 512;
 size_t split_head_bytes(int64_t n);
+// Sorts key[0] in place (four passes): the keys and starts of launch_split.
+int radix_sort_keys(uint32_t *key[2], int64_t n, const uint16_t *starts, uint32_t *counts, uint32_t *sums,
+                    hipStream_t stream);
 int launch_split(const float *img, int64_t n, uint32_t *keys, uint16_t *starts, uint32_t *head, uint32_t *mask_host_dev,
                  uint32_t *status, hipEvent_t noted, hipStream_t stream);
 // The distinct values and the curve at them (ecc_distinct.hip), for images

@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles_kernel(uint32_t *__re
     }
     if (lane == 63) ws[wave] = x;
     __syncthreads();
-    uint32_t p = sums[blockIdx.x] + x - s;
+    uint32_t p = (sums ? sums[blockIdx.x] : 0u) + x - s;
     for (int w = 0; w < wave; ++w) p += ws[w];
     uint32_t e[kScanItems];  // exclusive prefix of the run
 #pragma unroll
@@ -359,6 +359,11 @@ __global__ void __launch_bounds__(kScanThreads) scan_tiles_kernel(uint32_t *__re
 
 int exclusive_scan_u32(uint32_t *a, int64_t n, uint32_t *sums, hipStream_t stream) {
     const int64_t nt = (n + kScanTile - 1) / kScanTile;
+    if (nt == 1) {  // one tile has no tiles before it
+        hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kScanThreads), 0, stream, a, n, (const uint32_t *)nullptr);
+        ECC_HIP(hipGetLastError());
+        return ECC_OK;
+    }
     hipLaunchKernelGGL(scan_tile_sums_kernel, dim3((unsigned)nt), dim3(kScanThreads), 0, stream, (const uint32_t *)a, n,
                        sums);
     ECC_HIP(hipGetLastError());
@@ -381,15 +386,52 @@ static int count_tiles_per_wg(int64_t tiles) {
     return (int)std::min<int64_t>(kCountTiles, std::max<int64_t>(1, tiles / 2048));
 }
 
-// One pass: counts, their scan, the scatter from v[*cur] to the other buffer.
+// Digit counts of the first pass over split keys (bits 0-8): a split tile, two
+// sort tiles, holds its keys by this digit, so the counts follow from the
+// digits' first slots, without a read of the keys (whose equal neighbours would
+// also meet in the counting kernel's LDS adds).  A workgroup takes 16 split
+// tiles and writes runs of 32 counts per digit.
+constexpr int kSplitGroup = 16;
+static_assert(kSplitTile == 2 * SortTile<uint32_t>::kTile && kSplitBuckets == 512, "two sort tiles per split tile");
+__global__ void __launch_bounds__(kSplitBuckets) split_counts_kernel(const uint16_t *__restrict__ starts, int64_t n,
+                                                                     int64_t tiles, uint32_t *__restrict__ counts) {
+    constexpr int64_t kHalf = SortTile<uint32_t>::kTile;
+    __shared__ uint16_t cnt[2 * kSplitGroup][kSplitBuckets + 2];
+    const int tid = threadIdx.x;
+    const int64_t g0 = (int64_t)blockIdx.x * kSplitGroup, splits = (n + kSplitTile - 1) / kSplitTile;
+    for (int k = 0; k < kSplitGroup; ++k) {
+        const int64_t t = g0 + k;
+        int64_t lo = 0, hi = 0;  // the digit's keys in the split tile
+        if (t < splits) {
+            lo = starts[t * kSplitBuckets + tid];
+            hi = tid + 1 < kSplitBuckets ? (int64_t)starts[t * kSplitBuckets + tid + 1]
+                                         : std::min<int64_t>(kSplitTile, n - t * kSplitTile);
+        }
+        const int64_t low = std::min(hi, kHalf) - std::min(lo, kHalf);
+        cnt[2 * k][tid] = (uint16_t)low;
+        cnt[2 * k + 1][tid] = (uint16_t)(hi - lo - low);
+    }
+    __syncthreads();
+    for (int i = tid; i < 2 * kSplitGroup * kSplitBuckets; i += kSplitBuckets) {
+        const int k = i % (2 * kSplitGroup), d = i / (2 * kSplitGroup);
+        const int64_t t = 2 * g0 + k;
+        if (t < tiles) counts[(int64_t)d * tiles + t] = cnt[k][d];
+    }
+}
+
+// One pass: counts (already there with `counted`), their scan, the scatter from
+// v[*cur] to the other buffer.
 template <typename T, int BITS, bool AGG>
-static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
+static int radix_pass(T *v[2], int *cur, int64_t n, int shift, uint32_t *counts, uint32_t *sums, hipStream_t stream,
+                      bool counted = false) {
     const int64_t tiles = radix_tiles(n, (int)sizeof(T));
-    const int tpw = count_tiles_per_wg(tiles);
-    const unsigned cgrid = (unsigned)((tiles + tpw - 1) / tpw);
-    hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG>), dim3(cgrid), dim3(kSortThreads), 0, stream,
-                       (const T *)v[*cur], n, shift, tiles, tpw, counts);
-    ECC_HIP(hipGetLastError());
+    if (!counted) {
+        const int tpw = count_tiles_per_wg(tiles);
+        const unsigned cgrid = (unsigned)((tiles + tpw - 1) / tpw);
+        hipLaunchKernelGGL((radix_count_kernel<T, BITS, AGG>), dim3(cgrid), dim3(kSortThreads), 0, stream,
+                           (const T *)v[*cur], n, shift, tiles, tpw, counts);
+        ECC_HIP(hipGetLastError());
+    }
     int rc = exclusive_scan_u32(counts, ((int64_t)1 << BITS) * tiles, sums, stream);
     if (rc) return rc;
     hipLaunchKernelGGL((radix_scatter_kernel<T, BITS>), dim3((unsigned)tiles), dim3(kSortThreads), 0, stream,
@@ -407,10 +449,16 @@ static int check_count(int64_t n) {
     return ECC_OK;
 }
 
-int radix_sort_keys(uint32_t *key[2], int64_t n, uint32_t *counts, uint32_t *sums, hipStream_t stream) {
+int radix_sort_keys(uint32_t *key[2], int64_t n, const uint16_t *starts, uint32_t *counts, uint32_t *sums,
+                    hipStream_t stream) {
     int rc = check_count(n);
+    if (rc) return rc;
+    const int64_t splits = (n + kSplitTile - 1) / kSplitTile;
+    hipLaunchKernelGGL(split_counts_kernel, dim3((unsigned)((splits + kSplitGroup - 1) / kSplitGroup)),
+                       dim3(kSplitBuckets), 0, stream, starts, n, radix_tiles(n, 4), counts);
+    ECC_HIP(hipGetLastError());
     int cur = 0;
-    if (!rc) rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 0, counts, sums, stream);
+    rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 0, counts, sums, stream, true);
     if (!rc) rc = radix_pass<uint32_t, 9, false>(key, &cur, n, 9, counts, sums, stream);
     if (!rc) rc = radix_pass<uint32_t, 7, false>(key, &cur, n, 18, counts, sums, stream);
     // (bits 25-31: sign and high exponent bits, a handful of values)
