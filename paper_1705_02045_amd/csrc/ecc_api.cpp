@@ -13,6 +13,7 @@
 #include "ecc_internal.h"
 
 #include <algorithm>
+#include <atomic>
 
 namespace ecc {
 
@@ -52,10 +53,13 @@ size_t elem_bytes(int dtype) {
 }
 
 int device_cu_count() {
+    static std::atomic<int> known[16] = {};  // per device, 0: not asked yet
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (dev >= 0 && dev < 16 && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return 256;
+    if (dev >= 0 && dev < 16) known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 
@@ -385,7 +389,7 @@ static int choose_wx(int64_t xs, int cap, int max_waves) {
 // two per CU, takes 104 us where 1024 took 149; 400 x 413 x 390 82 us where
 // 1040 workgroups, most CUs idle in their last round, took 91.
 IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_per_cu, int wx_cap,
-                          int max_grid = 0, bool planned = false, double row_cost = 0) {
+                          int max_grid = 0, bool planned = false, double row_cost = 0, bool small_bins = false) {
     IntTiling t{};
     t.rows = rows;
     t.mode = env_int("ECC_INT_MODE", 0);
@@ -398,14 +402,26 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
         t.wy = 1;
         tiles_xy = (segs + t.wx - 1) / t.wx;
     } else {
-        const int64_t xs = (v.n2 + kWave - 1) / kWave;
-        if (planned) t.wx = choose_wx(xs, std::min(xs <= 16 ? 16 : 8, wx_cap), max_waves);
-        else t.wx = (int)(xs < wx_cap ? xs : wx_cap);
-        const int64_t ys = (v.n1 + t.rows - 1) / t.rows;
-        const int64_t wy = max_waves / t.wx;
-        t.wy = (int)(ys < wy ? ys : wy);
-        tiles_xy = ((xs + t.wx - 1) / t.wx) * ((ys + t.wy - 1) / t.wy);
+        const int64_t xs = (v.n2 + kWave - 1) / kWave, ys = (v.n1 + t.rows - 1) / t.rows;
+        auto shape = [&](int wx) {
+            const int64_t wy = max_waves / wx;
+            t.wx = wx;
+            t.wy = (int)(ys < wy ? ys : wy);
+            return ((xs + t.wx - 1) / t.wx) * ((ys + t.wy - 1) / t.wy);
+        };
+        tiles_xy = shape((int)(xs < wx_cap ? xs : wx_cap));
+        // (fewer tiles than CUs are not made fewer still: 19 x 10 x 598 at 8
+        // bits 17 us in 15 workgroups of ten waves, 20 in 12 of fifteen)
+        if (planned && tiles_xy * ((planes + 7) / 8) >= cus)
+            tiles_xy = shape(choose_wx(xs, std::min(xs <= 16 ? 16 : 8, wx_cap), max_waves));
     }
+    // The plan counts a workgroup as its CU's work.  8-bit workgroups of up to
+    // four waves (planes of a few hundred voxels) run many to a CU, their 1 KiB
+    // histograms beside each other, each bound by its walk's latency, so they
+    // are split as finely as the rule says (300000 x 64: 50 us, planned 74;
+    // 100000 x 4 x 4: 38 and 56; from seven waves on the plan is as fast).  At
+    // 14 bits the 64 KiB histograms admit two to a CU however small.
+    if (small_bins && t.wx * t.wy <= 4) planned = false;
     // split axis 0 until there are about tiles_per_cu tiles per CU; planes
     // with more tiles than that get several tiles per workgroup, so the
     // per-workgroup rows stay about tiles_per_cu per CU
@@ -531,17 +547,8 @@ static bool planned_tiling(const IntView &v, int dtype, int64_t planes, const ec
 }
 static IntTiling tiling_from(const IntView &v, int dtype, int64_t planes, const ecc_tiling &c, int max_grid) {
     const bool planned = planned_tiling(v, dtype, planes, c);
-    IntTiling t = make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned,
-                                  dtype == ECC_U8 ? 0.0075 : 0.045);
-    // The plan counts a workgroup as its CU's work.  8-bit workgroups of up to
-    // four waves (planes of a few hundred voxels) run many to a CU, their 1 KiB
-    // histograms beside each other, each bound by its walk's latency, so they
-    // are split as finely as the rule says (300000 x 64: 50 us, planned 74;
-    // 100000 x 4 x 4: 38 and 56; from seven waves on the plan is as fast).  At
-    // 14 bits the 64 KiB histograms admit two to a CU however small.
-    if (planned && dtype == ECC_U8 && t.wx * t.wy <= 4)
-        t = make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid);
-    return t;
+    return make_int_tiling(v, planes, c.rows, c.tiles_per_cu, c.waves_x, max_grid, planned,
+                           dtype == ECC_U8 ? 0.0075 : 0.045, dtype == ECC_U8);
 }
 
 IntTiling choose_int_tiling(const IntView &v, int dtype, int64_t planes, int max_grid) {
