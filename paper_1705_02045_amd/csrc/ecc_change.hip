@@ -516,13 +516,19 @@ static int change_params(const ChangeJob &job, int per_lane_a, int per_lane_b, C
 static int lane_rows(int nl) { return nl == 0 ? 1 : nl == 1 ? 4 : 2; }
 static int lane_planes(int nl) { return nl == 2 ? 2 : 1; }
 
+// Records of one walk at most: a voxel of each of the wave's lanes (planes of
+// fewer than 64 positions have fewer lanes that emit) per plane.
+static int64_t walk_records(const ChangeParams &p, int a, int b) {
+    return (int64_t)std::min(64, p.lanes) * a * b * p.zc;
+}
+
 int change_regions(const ChangeJob &job, int64_t *regions, int64_t *region_slots) {
     ChangeParams p{};
     const int a = lane_rows(job.nl), b = lane_planes(job.nl);
     int rc = change_params(job, a, b, &p);
     if (rc) return rc;
     *regions = p.items;
-    *region_slots = (int64_t)64 * a * b * p.zc;
+    *region_slots = walk_records(p, a, b);
     return ECC_OK;
 }
 
@@ -533,7 +539,7 @@ int launch_change_records(const ChangeJob &job, uint64_t *rec, uint32_t *cnt, hi
     if (rc) return rc;
     p.rec = rec;
     p.cnt = cnt;
-    p.region = (uint32_t)(64 * a * b * p.zc);
+    p.region = (uint32_t)walk_records(p, a, b);
     void *tok = nullptr;
     rc = profile_begin(stream, &tok);
     if (rc) return rc;

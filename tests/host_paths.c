@@ -426,6 +426,20 @@ static int kernel_of(int argc, char **argv) {
     return 0;
 }
 
+/* Device memory of float images of narrow planes. */
+static int float_memory(void) {
+    const int64_t n[4][4] = {{1 << 22, 2, 2, 1}, {1 << 23, 2, 1, 1}, {1 << 20, 2, 2, 2}, {256, 256, 256, 1}};
+    for (int i = 0; i < 4; ++i) {
+        ecc_dims d = dims_of(4, n[i][0], n[i][1], n[i][2], n[i][3]);
+        const int64_t voxels = n[i][0] * n[i][1] * n[i][2] * n[i][3];
+        ecc_curve c = {voxels, 0, device_bytes(voxels * 8), device_bytes(voxels * 4)};
+        const size_t before = used;
+        const int rc = ecc_compute(device_bytes(voxels * 4), &d, ECC_F32, &c, malloc(8));
+        printf("float rc %d bytes %zu voxels %lld\n", rc, used - before, (long long)voxels);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -438,6 +452,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "stream_4d")) return stream_4d();
     if (!strcmp(what, "dual_long")) return dual_long();
     if (!strcmp(what, "kernel_of")) return kernel_of(argc, argv);
+    if (!strcmp(what, "float_memory")) return float_memory();
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

@@ -146,3 +146,10 @@ def test_narrow_8_bit_launches_are_split_finely(program):
         r = dict(zip(line[1:5:2], map(int, line[2:5:2])))
         walk = max(8, -(-shape[0] // 1024))
         assert r["rc"] == ECC_OK and r["grid"] == -(-shape[0] // walk), line
+
+
+def test_float_images_of_narrow_planes_take_no_more_memory(program):
+    """Two key buffers, the records' slots (8 bytes, twice the voxels where rows
+    of two fill lanes of four), some per mille of tables, and the bits."""
+    for f in records(run(program, "float_memory"), "float"):
+        assert f["rc"] == ECC_OK and f["bytes"] <= 28 * f["voxels"] + (32 << 20), f
