@@ -1147,7 +1147,7 @@ int compute_async_ws(const void *image_dev, const ecc_dims *dims, ecc_dtype dtyp
         rc = get_workspace(stream, &ws);
         if (rc) return rc;
     }
-    if (dtype == ECC_U16)  // stream-ordered: windows over all values (no host read of the value range)
+    if (dtype == ECC_U16)  // stream-ordered: planned for all values (no host read of the value range)
         return enqueue_u16(image_dev, v, chi_dev, status_dev, stream, ws, 0, 65535);
     return enqueue_int(image_dev, v, dtype, chi_dev, status_dev, stream, ws);
 }

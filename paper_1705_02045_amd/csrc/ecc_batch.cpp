@@ -714,7 +714,7 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
     }
     if (n_jobs == 0) return ECC_OK;
     std::vector<Prepared> prep(n_jobs);
-    std::vector<int> wide;  // ECC_U16 jobs: windowed launches of their own, after the batch
+    std::vector<int> wide;  // ECC_U16 jobs: two passes of their own, after the batch
     int64_t rows8 = 0, rows14 = 0, ntiles = 0, nitems = 0, vcec_words = 0;
     for (int j = 0; j < n_jobs; ++j) {
         const ecc_job &J = jobs[j];
@@ -941,8 +941,8 @@ int ecc_batch_run(ecc_batch *b, int32_t n_jobs, const ecc_job *jobs, uint32_t *s
         }
         b->used[s] = true;
     } while (0);
-    // 16-bit images: one launch per window of 16384 values each (the
-    // persistent kernel's histograms hold 16384 bins), on the same stream
+    // 16-bit images: two 32768-bin passes each (the persistent kernel's
+    // histograms hold 16384 bins), on the same stream
     for (size_t w = 0; !rc && w < wide.size(); ++w) {
         const int j = wide[w];
         rc = u16_curve_async(jobs[j].image, prep[j].view, jobs[j].chi, status_dev ? status_dev + j : nullptr,

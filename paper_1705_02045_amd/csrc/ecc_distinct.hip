@@ -510,15 +510,15 @@ __global__ void __launch_bounds__(64 * kExpandWaves) expand_kernel(const uint32_
 // whole numbers, say) are added in LDS first: a workgroup's int32 sums (at
 // most 2^26: a record's change is at most 16), then one global add per value
 // and workgroup.  (All of a card's adds on 4096 values, without LDS: 2.5 ms
-// for 2^26 voxels, 0.47 with it.)  More values take a global add per record,
-// which is bound by the adds where neighbouring records lie apart (2^26 voxels
-// of white noise: 2.2 ms) and by the gathers before it where they don't (2^28
-// of smooth noise: 0.35 ms); but adds to one value wait for each other (0.2 G/s),
-// and images that are clipped, or mostly zero, have most of their records at one
-// or two values.  Such a value shows in its bucket's total: where one is an
-// eighth above the mean, the first values that a workgroup meets are summed in
-// LDS, in kHot slots found by a hash of the rank, two tries; a value that occurs
-// often is among them before they are full.  (2^24 voxels of noise clipped at
+// for 2^26 voxels, 0.47 with it.)  More values take a global add per record, and
+// the adds, which all go to memory, bound it: 7.3 million of 2^28 voxels of smooth
+// noise take 0.37 ms (20 G/s; the gathers before them and the records move 0.11
+// GB), those of 2^26 of white noise 2.2 ms (27 G/s).  Adds to one value wait
+// for each other (0.2 G/s), and images that are clipped, or mostly zero, have
+// most of their records at one or two values.  Such a value shows in its bucket's
+// total: where one is an eighth above the mean, the first values that a workgroup
+// meets are summed in LDS, in kHot slots found by a hash of the rank, two tries;
+// a value that occurs often is among them before they are full.  (2^24 voxels of noise clipped at
 // both ends: 43 ms without, 0.62 with them; where no bucket stands out the slots
 // would make 6.8 million voxels of smooth noise 3 % slower.)
 constexpr int kFewValues = 16384;

@@ -1,8 +1,11 @@
 // Float32 images (Sec. 3, "Other Ranges of Gray Values"): the values are not known
-// in advance, so every voxel's key is sorted to find the distinct values; the
-// voxels whose change is not zero (a few in a hundred) leave (key, change)
-// records (ecc_change.hip), and each change is added at its key's rank among
-// the distinct values; a prefix sum over the distinct values gives the curve.
+// in advance; the voxels whose change is not zero (a few in a hundred) leave
+// (key, change) records (ecc_change.hip), and each change is added at its key's
+// rank among the distinct values; a prefix sum over them gives the curve.  The
+// distinct values are found by bits (ecc_distinct.hip) or, where the keys hold
+// more than 32 top bytes (or the bits find no memory), by sorting every voxel's
+// key (ecc_sort.hip); here are the compaction of the sort's records, the curve
+// from the sorted keys and records, the change points and the quantisation.
 //
 // Keys: the canonical float (-0 folded into +0) mapped to an unsigned integer
 // with the same order (f32_key).

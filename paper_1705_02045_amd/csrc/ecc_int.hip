@@ -660,8 +660,10 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
     }
     // (loops with a uniform trip count: a thread-dependent one makes the
     // compiler treat later lane masks as divergent)
-    for (int i0 = 0; i0 < (M << REP); i0 += (int)blockDim.x)
-        if (i0 + tid < (M << REP)) hist[i0 + tid] = 0;
+    // (four words at a time: workgroups of one wave spend most of their time in
+    // this loop and the last one; 8 x 10 voxels at 14 bits 37 us with one, 16 with four)
+    for (int i0 = 0; i0 < (M << REP) / 4; i0 += (int)blockDim.x)
+        if (i0 + tid < (M << REP) / 4) reinterpret_cast<int4 *>(hist)[i0 + tid] = int4{0, 0, 0, 0};
     if (P.zero_vcec && b == 0)
         for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
             if (i0 + tid < M) P.zero_vcec[i0 + tid] = 0;
@@ -810,8 +812,8 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
             if (i < M * 4 && q == 0) dst[bin] = c;
         }
     } else {
-        for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
-            if (i0 + tid < M) dst[i0 + tid] = hist[i0 + tid];
+        for (int i0 = 0; i0 < M / 4; i0 += (int)blockDim.x)
+            if (i0 + tid < M / 4) reinterpret_cast<int4 *>(dst)[i0 + tid] = reinterpret_cast<const int4 *>(hist)[i0 + tid];
     }
 }
 
@@ -829,7 +831,7 @@ template <typename T, int M, int NIN, int R, int MODE, int PD, int XF = kXfNone,
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(M > 16384 ? 4 : kWavesPerEU<NIN, R, PD>())))
 int_vcec_kernel(KParams P) {
     static_assert(raw_fields(XF) == (M == 32768), "32768 bins: raw-value passes, and only those");
-    __shared__ int32_t hist[M << REP];
+    __shared__ __align__(16) int32_t hist[M << REP];
     tile_body<T, M, NIN, R, MODE, PD, XF, REP>(P, hist, blockIdx.x, gridDim.x);
 }
 
@@ -841,7 +843,7 @@ int_vcec_kernel(KParams P) {
 // histogram) until the tiles run out.
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(kWavesPerEU<2, 2, 1>())))
 int_vcec_persistent_kernel(uint8_t *__restrict__ table) {
-    __shared__ int32_t hist[16384];
+    __shared__ __align__(16) int32_t hist[16384];
     BatchHeader *H = (BatchHeader *)table;
     const int ntiles = H->ntiles, njobs = H->njobs;
     const KParams *jobs = (const KParams *)(table + H->off_kparams);

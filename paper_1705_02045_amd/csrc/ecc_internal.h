@@ -101,9 +101,10 @@ struct Workspace {
     uint32_t *status = nullptr;  // device status block (kStatusBytes)
     // A pinned, coherent host block of 16 words: word 0, the status that the
     // scan writes (read after the stream is synchronized, without a
-    // device-to-host copy); word 1, the 16-bit path's high-value flag; words
-    // 2-3, the float path's record count; words 4-11, the float key sort's
-    // top-byte mask.  With its device-side address.
+    // device-to-host copy); word 1, the 16-bit path's high-value flag; of the
+    // float path words 2-3, the sort's record count, 4-11, the mask of the keys'
+    // top bytes, 12-13, the number of distinct values found by bits, and 14, the
+    // status with them.  With its device-side address.
     volatile uint32_t *host_status = nullptr;
     uint32_t *host_status_dev = nullptr;
     int64_t *chi_tmp = nullptr;  // [m] curve staging for host outputs
@@ -173,8 +174,8 @@ struct U16Window {
 };
 constexpr int kU16MaxWindows = 5;  // 16383 + 3 * 16382 + 16383 >= 65536
 int plan_u16_windows(uint32_t vmin, uint32_t vmax, U16Window *w);
-// The whole curve of a device-resident 16-bit image on stream (windows over
-// the whole value range), the status copied to status_out (may be null).
+// The whole curve of a device-resident 16-bit image on stream (two 32768-bin
+// passes), the status copied to status_out (may be null).
 int u16_curve_async(const void *image_dev, const IntView &v, int64_t *chi_dev, uint32_t *status_out,
                     hipStream_t stream);
 // Column sums of the per-workgroup rows into vcec and, with do_scan, the

@@ -5,11 +5,13 @@
 //
 // The records take four passes of 8-bit digits, the keys two of 9 bits and
 // two of 7.  The keys are only sorted when they hold more than
-// kMaxDistinctBytes top bytes (sign and high exponent bits); with fewer the
-// distinct values are found without sorting (ecc_distinct.hip).
+// kMaxDistinctBytes top bytes (sign and high exponent bits), or the bits of the
+// distinct values find no memory; else those are found without sorting
+// (ecc_distinct.hip).
 //
 // A workgroup owns a tile of kTile consecutive keys.  A pass:
-//  1. radix_count_kernel: digit counts per (digit, tile), digit-major;
+//  1. radix_count_kernel: digit counts per (digit, tile), digit-major (of the
+//     keys' first pass split_counts_kernel, from the split's first slots);
 //  2. exclusive scan of that table: the output position of the first key
 //     of each digit of each tile;
 //  3. radix_scatter_kernel: the tile is ranked stably in LDS (each wave
