@@ -419,9 +419,10 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
     // four waves (planes of a few hundred voxels) run many to a CU, their 1 KiB
     // histograms beside each other, each bound by its walk's latency, so they
     // are split as finely as the rule says (300000 x 64: 50 us, planned 74;
-    // 100000 x 4 x 4: 38 and 56; from seven waves on the plan is as fast).  At
-    // 14 bits the 64 KiB histograms admit two to a CU however small.
-    if (small_bins && t.wx * t.wy <= 4) planned = false;
+    // 100000 x 4 x 4: 38 and 56; from seven waves on the plan is as fast), unless
+    // that leaves walks of fewer than 16 planes (8000 x 64: 13.5 us, planned
+    // 13.0).  At 14 bits the 64 KiB histograms admit two to a CU however small.
+    if (small_bins && t.wx * t.wy <= 4 && planes * tiles_xy >= (int64_t)16 * cus * tiles_per_cu) planned = false;
     // split axis 0 until there are about tiles_per_cu tiles per CU; planes
     // with more tiles than that get several tiles per workgroup, so the
     // per-workgroup rows stay about tiles_per_cu per CU
@@ -449,17 +450,25 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
     if (planned) {
         double best = 0;
         int64_t best_target = 0, best_tz = 0;
+        auto consider = [&](int64_t target, int64_t tz, double margin) {
+            const double c = fit(target, tz);
+            if (best_target == 0 || c * margin < best) {
+                best = c;
+                best_target = target;
+                best_tz = tz;
+            }
+        };
         for (int k = 1; k <= tiles_per_cu; ++k) {
             const int64_t target = (int64_t)cus * k;
-            for (int64_t tz = target / tiles_xy; tz <= target / tiles_xy + 1; ++tz) {
-                const double c = fit(target, tz);
-                if (best_target == 0 || c < best) {
-                    best = c;
-                    best_target = target;
-                    best_tz = tz;
-                }
-            }
+            for (int64_t tz = target / tiles_xy; tz <= target / tiles_xy + 1; ++tz) consider(target, tz, 1.0);
         }
+        // Several shorter tiles per workgroup, where the splits above leave many
+        // CUs idle: 264 tiles of a plane at one workgroup per CU make 132 of two
+        // (16-bit passes over 2000 x 700 x 700: 1685 us per call, 1431 with four
+        // workgroups per CU, 1003 in 235 of nine).
+        if (tiles_xy * 4 > cus)
+            for (int k = 1; k <= tiles_per_cu; ++k)
+                for (int64_t tz = 2; tz <= 32; tz *= 2) consider((int64_t)cus * k, tz, 1.1);
         (void)fit(best_target, best_tz);
     } else {
         const int64_t target = (int64_t)cus * tiles_per_cu;

@@ -811,9 +811,12 @@ __device__ __forceinline__ void tile_body(const KParams &P, int32_t *hist, const
             c += __shfl_xor(c, 2, 64);
             if (i < M * 4 && q == 0) dst[bin] = c;
         }
-    } else {
+    } else if constexpr (M > 1024) {
         for (int i0 = 0; i0 < M / 4; i0 += (int)blockDim.x)
             if (i0 + tid < M / 4) reinterpret_cast<int4 *>(dst)[i0 + tid] = reinterpret_cast<const int4 *>(hist)[i0 + tid];
+    } else {  // (256 bins by one wave alone: 500 x 1000 x 700 takes 345 us, by four 284)
+        for (int i0 = 0; i0 < M; i0 += (int)blockDim.x)
+            if (i0 + tid < M) dst[i0 + tid] = hist[i0 + tid];
     }
 }
 

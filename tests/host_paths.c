@@ -410,13 +410,16 @@ static int dual_long(void) {
 
 /* The integer kernel that images take: argv[2] tilings to load ("-": none),
  * argv[3] "min" or "max", then per image its extents as n0xn1xn2 (8 bits). */
+static ecc_dims parse_dims(char *p) {
+    ecc_dims d = dims_of(1, 1, 1, 1, 1);
+    for (d.ndim = 0; *p; ++d.ndim, p += *p == 'x') d.n[d.ndim] = strtoll(p, &p, 10);
+    return d;
+}
 static int kernel_of(int argc, char **argv) {
     if (strcmp(argv[2], "-")) printf("loaded rc %d\n", ecc_autotune_load(argv[2]));
     static int64_t chi[256];
     for (int i = 4; i < argc; ++i) {
-        ecc_dims d = dims_of(1, 1, 1, 1, 1);
-        char *p = argv[i];
-        for (d.ndim = 0; *p; ++d.ndim, p += *p == 'x') d.n[d.ndim] = strtoll(p, &p, 10);
+        ecc_dims d = parse_dims(argv[i]);
         ecc_curve c = {256, 0, chi, NULL};
         int (*call)(const void *, const ecc_dims *, ecc_dtype, ecc_curve *, void *) =
             strcmp(argv[3], "max") ? ecc_compute : ecc_compute_max_entry;
@@ -440,6 +443,16 @@ static int float_memory(void) {
     return 0;
 }
 
+/* The workgroups of a 16-bit image's passes, per image. */
+static int grids_u16(int argc, char **argv) {
+    for (int i = 2; i < argc; ++i) {
+        ecc_dims d = parse_dims(argv[i]);
+        const int rc = ecc_compute_async(device_bytes(1 << 20), &d, ECC_U16, device_bytes(65536 * 8), NULL, NULL);
+        printf("%s rc %d grid %u\n", argv[i], rc, int_grid);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "float_exits")) return float_exits();
@@ -453,6 +466,7 @@ int main(int argc, char **argv) {
     if (!strcmp(what, "dual_long")) return dual_long();
     if (!strcmp(what, "kernel_of")) return kernel_of(argc, argv);
     if (!strcmp(what, "float_memory")) return float_memory();
+    if (!strcmp(what, "grids_u16")) return grids_u16(argc, argv);
     fprintf(stderr, "no scenario %s\n", what);
     return 2;
 }

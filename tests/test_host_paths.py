@@ -138,13 +138,13 @@ def test_dual_of_volumes_with_very_long_faces(program):
 
 
 def test_narrow_8_bit_launches_are_split_finely(program):
-    """8-bit workgroups of up to four waves: about four tiles per CU, walks of
-    at least 8 planes."""
-    shapes = [(1000000, 8), (100000, 130), (2000000, 2), (200000, 2, 2), (100000, 4, 4), (20000, 4, 64), (5000, 64)]
+    """8-bit workgroups of up to four waves: about four tiles per CU where that
+    gives walks of 16 planes or more."""
+    shapes = [(1000000, 8), (100000, 130), (2000000, 2), (200000, 2, 2), (100000, 4, 4), (20000, 4, 64), (16384, 64)]
     lines = run(program, "kernel_of", "-", "min", *["x".join(map(str, s)) for s in shapes])
     for shape, line in zip(shapes, lines):
         r = dict(zip(line[1:5:2], map(int, line[2:5:2])))
-        walk = max(8, -(-shape[0] // 1024))
+        walk = -(-shape[0] // 1024)
         assert r["rc"] == ECC_OK and r["grid"] == -(-shape[0] // walk), line
 
 
@@ -153,3 +153,12 @@ def test_float_images_of_narrow_planes_take_no_more_memory(program):
     of two fill lanes of four), some per mille of tables, and the bits."""
     for f in records(run(program, "float_memory"), "float"):
         assert f["rc"] == ECC_OK and f["bytes"] <= 28 * f["voxels"] + (32 << 20), f
+
+
+def test_wide_16_bit_planes_fill_the_cus(program, tmp_path):
+    """Planes of somewhat more tiles than CUs are cut into several tiles per
+    workgroup, so that three in four CUs or more have work (16-bit passes: one
+    workgroup per CU)."""
+    lines = run(program, "grids_u16", "2000x700x700", "256x700x750", "500x1000x700", "1000x600x800", "1024x1024x1024")
+    grids = [int(line[4]) for line in lines]
+    assert all(192 <= g <= 256 for g in grids), lines
