@@ -360,20 +360,26 @@ static int env_int(const char *name, int dflt) {
 // ECC_U16_WINDOWS (1: 16-bit images in the window form),
 // ECC_INT_WAVES, ECC_INT_TILES_PER_CU, ECC_INT_TILE_STRIDE, ECC_INT_PAIR (0: no row pairs),
 // ECC_INT_PLAN (0: exactly the tiles per CU asked for).
-// Waves along x of a plane of xs 64-column segments, at most cap: the fewest
-// idle wave slots of 16 (whole tiles cover xs, whole waves fill a workgroup),
-// from 4 on (narrower tiles touch more pages per byte); the widest of equals.
-static int choose_wx(int64_t xs, int cap, int max_waves) {
-    int best = (int)std::min<int64_t>(xs, cap);
-    double best_use = 0;
-    for (int w = best; w >= std::min<int64_t>(xs, 4); --w) {
-        const int64_t tx = (xs + w - 1) / w;
-        const double use = (double)xs / (double)(tx * w) * (double)(max_waves / w * w) / max_waves;
-        if (use > best_use + 1e-9) {
-            best_use = use;
-            best = w;
-        }
-    }
+// Waves along x of a plane of xs 64-column segments and ys rows of waves, at
+// most cap: the fewest idle waves (whole tiles cover the plane) and wave slots
+// of 16 (whole rows of waves fill a workgroup), from 4 on (narrower tiles touch
+// more pages per byte); the widest of equals up to 8.  Wider than 8 where that
+// leaves a seventh fewer idle.  Planes of few rows leave rows of waves idle:
+// 10000 planes of 5 x 2048, three rows of waves, take 100 us at 8 bits and 118
+// at 14 in workgroups of 4 x 3 waves, 125 and 168 in 8 x 2; of 9 x 2048, five
+// rows of waves, 152 at 14 bits in 16 x 1, 158 in 8 x 2.
+static int choose_wx(int64_t xs, int64_t ys, int cap, int max_waves) {
+    const auto use = [&](int w) {
+        const int64_t wy = std::min<int64_t>(ys, max_waves / w);
+        const int64_t tx = (xs + w - 1) / w, ty = (ys + wy - 1) / wy;
+        return (double)(xs * ys) / (double)(tx * w * ty * wy) * (double)(max_waves / w * w) / max_waves;
+    };
+    const int narrowest = (int)std::min<int64_t>(xs, 4);
+    int best = (int)std::min<int64_t>(xs, std::min(xs <= 16 ? 16 : 8, cap));
+    for (int w = best - 1; w >= narrowest; --w)
+        if (use(w) > use(best) + 1e-9) best = w;
+    for (int w = (int)std::min<int64_t>(xs, cap); w > 8 && xs > 16; --w)
+        if (use(w) > use(best) * 1.15) best = w;
     return best;
 }
 
@@ -413,7 +419,7 @@ IntTiling make_int_tiling(const IntView &v, int64_t planes, int rows, int tiles_
         // (fewer tiles than CUs are not made fewer still: 19 x 10 x 598 at 8
         // bits 17 us in 15 workgroups of ten waves, 20 in 12 of fifteen)
         if (planned && tiles_xy * ((planes + 7) / 8) >= cus)
-            tiles_xy = shape(choose_wx(xs, std::min(xs <= 16 ? 16 : 8, wx_cap), max_waves));
+            tiles_xy = shape(choose_wx(xs, ys, wx_cap, max_waves));
     }
     // The plan counts a workgroup as its CU's work.  8-bit workgroups of up to
     // four waves (planes of a few hundred voxels) run many to a CU, their 1 KiB

@@ -45,6 +45,7 @@ static int top_bytes = 3;     /* top bytes of the float image's keys */
 static long change_launches;  /* of the change kernel */
 static long face_launches;    /* of the box faces' kernel */
 static unsigned int_grid;     /* workgroups of the last launch of the integer kernel */
+static unsigned int_waves;    /* and the waves of each */
 static const char *int_kernel = "";
 
 static int is_device(const void *p) { return (uint64_t)p >= DEVICE_LO && (uint64_t)p < DEVICE_HI; }
@@ -180,6 +181,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
         ++face_launches;
     } else if (strstr(name, "int_vcec_kernel")) {
         int_grid = g.x;
+        int_waves = b.x / 64;
         int_kernel = name;
     } else if (strstr(name, "change_kernel")) {
         ++change_launches;
@@ -424,7 +426,7 @@ static int kernel_of(int argc, char **argv) {
         int (*call)(const void *, const ecc_dims *, ecc_dtype, ecc_curve *, void *) =
             strcmp(argv[3], "max") ? ecc_compute : ecc_compute_max_entry;
         const int rc = call(device_bytes(1 << 20), &d, ECC_U8, &c, NULL);
-        printf("%s rc %d grid %u kernel %s\n", argv[i], rc, int_grid, int_kernel);
+        printf("%s rc %d grid %u waves %u kernel %s\n", argv[i], rc, int_grid, int_waves, int_kernel);
     }
     return 0;
 }

@@ -162,3 +162,11 @@ def test_wide_16_bit_planes_fill_the_cus(program, tmp_path):
     lines = run(program, "grids_u16", "2000x700x700", "256x700x750", "500x1000x700", "1000x600x800", "1024x1024x1024")
     grids = [int(line[4]) for line in lines]
     assert all(192 <= g <= 256 for g in grids), lines
+
+
+def test_planes_of_few_rows_leave_no_row_of_waves_idle(program):
+    """Three rows of waves: workgroups of 4 x 3 waves (8 x 2 left a quarter of
+    them idle); two rows and four fill 8 x 2."""
+    shapes = ["10000x5x2048", "2810x6x5418", "10000x4x2048", "10000x8x2048"]
+    lines = run(program, "kernel_of", "-", "min", *shapes)
+    assert [int(line[line.index("waves") + 1]) for line in lines] == [12, 12, 16, 16], lines
