@@ -43,8 +43,8 @@
 // bytes of one word: the comparison masks are pushed into the low bits
 // of a word, spread to bytes by one 24-bit product, and steps 1 and 2 work
 // on whole words.
-// Bound by vector instructions: a 128^4 float image takes 1.00 ms, of which
-// 124 instructions per voxel take 0.88 ms to issue (1.06 ms with the planes
+// Bound by vector instructions: a 128^4 float image takes 0.99 ms, of which
+// 132 instructions per voxel take 0.90 ms to issue (1.06 ms with the planes
 // after the last one made by moves and stores under branches).
 #include <algorithm>
 
